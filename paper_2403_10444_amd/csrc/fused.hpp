@@ -532,13 +532,11 @@ __device__ __forceinline__ bool decode_unit(const FusedParams &P, int wave, Unit
     return U.b < P.B;
 }
 
-// The logits a lane holds of one row, as loaded: raw 16-byte vectors on the aligned path.
-template <typename T, bool ALIGNED, int LANE> struct RawSlice;
-template <typename T, int LANE> struct RawSlice<T, true, LANE> {
+// The logits a lane holds of one row, as loaded: raw 16-byte vectors.
+template <typename T, bool ALIGNED, int LANE> struct RawSlice {
     static constexpr int kNV = LANE / ElemTraits<T>::kVec;
     uint4 v[kNV];
 };
-template <typename T, int LANE> struct RawSlice<T, false, LANE> { };      // the element-wise path loads when it unpacks
 
 // Vector v of a lane starts at element first + v * 64 * kVec of the row, so one load instruction of
 // the wave covers 1 KB of contiguous memory.
@@ -546,61 +544,52 @@ template <typename T, bool ALIGNED, int LANE>
 __device__ __forceinline__ void issue_loads(const T *row, int unit_first, int V, RawSlice<T, ALIGNED, LANE> &raw)
 {
     constexpr int kUnitLogits = kWave * LANE;
-    if constexpr (ALIGNED) {
-        constexpr int kVec = ElemTraits<T>::kVec;
+    constexpr int kVec = ElemTraits<T>::kVec;
+    const int first = unit_first + (int)(threadIdx.x & 63) * kVec;
+    if (unit_first + kUnitLogits <= V) {                   // wave-uniform: the whole unit lies inside the row
         const char *base = reinterpret_cast<const char *>(row);
-        const unsigned lane_off = (unsigned)(unit_first + (int)(threadIdx.x & 63) * kVec) * (unsigned)sizeof(T);
-        if (unit_first + kUnitLogits <= V) {                   // wave-uniform: the whole unit lies inside the row
+        const unsigned lane_off = (unsigned)first * (unsigned)sizeof(T);
 #pragma unroll
-            for (int v = 0; v < RawSlice<T, true, LANE>::kNV; ++v)
-                raw.v[v] = load_streamed(base + (lane_off + (unsigned)(v * kWave * 16)));
-        } else {
-#pragma unroll
-            for (int v = 0; v < RawSlice<T, true, LANE>::kNV; ++v) {
-                const unsigned off = lane_off + (unsigned)(v * kWave * 16);
-                // vectors beyond the row are recognised again when the slice is unpacked; load something valid
-                raw.v[v] = load_streamed(base + (off < (unsigned)V * (unsigned)sizeof(T) ? off : 0u));
-            }
-        }
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void unpack_vec(const uint4 &v, float *out)
-{
-    if constexpr (ElemTraits<T>::kVec == 4) {
-        out[0] = __uint_as_float(v.x); out[1] = __uint_as_float(v.y);
-        out[2] = __uint_as_float(v.z); out[3] = __uint_as_float(v.w);
+        for (int v = 0; v < RawSlice<T, ALIGNED, LANE>::kNV; ++v)
+            raw.v[v] = load_streamed<kRowAlign<T, ALIGNED>>(base + (lane_off + (unsigned)(v * kWave * 16)));
     } else {
-        out[0] = bf16_lo(v.x); out[1] = bf16_hi(v.x); out[2] = bf16_lo(v.y); out[3] = bf16_hi(v.y);
-        out[4] = bf16_lo(v.z); out[5] = bf16_hi(v.z); out[6] = bf16_lo(v.w); out[7] = bf16_hi(v.w);
+        // (vectors that reach beyond the row are recognised again when the slice is unpacked)
+        if (!ALIGNED && V < kVec) {
+            const uint4 all = load_short_row(row, V);
+#pragma unroll
+            for (int v = 0; v < RawSlice<T, ALIGNED, LANE>::kNV; ++v) raw.v[v] = all;
+            return;
+        }
+        const char *base = reinterpret_cast<const char *>(row);
+        // (byte offset of the last vector that ends inside the row)
+        const unsigned last = ALIGNED ? 0u : (unsigned)(V - kVec) * (unsigned)sizeof(T);
+        const unsigned lane_off = (unsigned)first * (unsigned)sizeof(T);
+#pragma unroll
+        for (int v = 0; v < RawSlice<T, ALIGNED, LANE>::kNV; ++v) {
+            const unsigned off = lane_off + (unsigned)(v * kWave * 16);
+            raw.v[v] = load_streamed<kRowAlign<T, ALIGNED>>(
+                base + (ALIGNED ? (off < (unsigned)V * (unsigned)sizeof(T) ? off : 0u) : (off < last ? off : last)));
+        }
     }
 }
 
 template <typename T, bool ALIGNED, int LANE>
-__device__ __forceinline__ void unpack_slice(const T *row, int unit_first, int V, const RawSlice<T, ALIGNED, LANE> &raw,
-                                             float (&x)[LANE])
+__device__ __forceinline__ void unpack_slice(int unit_first, int V, RawSlice<T, ALIGNED, LANE> &raw, float (&x)[LANE])
 {
     constexpr int kVec = ElemTraits<T>::kVec;
     constexpr int kNV = LANE / kVec;
-    constexpr int kUnitLogits = kWave * LANE;
     const int first = unit_first + (int)(threadIdx.x & 63) * kVec;
-    if constexpr (ALIGNED) {
+    // only a row's last units reach beyond the row (wave-uniform test): blank what lies beyond
+    const bool tail = unit_first + kWave * LANE > V;
+    if (!ALIGNED && tail) {
 #pragma unroll
-        for (int v = 0; v < kNV; ++v) unpack_vec<T>(raw.v[v], x + v * kVec);
-        // only a row's last units reach beyond the row (wave-uniform test): blank what lies beyond
-        if (unit_first + kUnitLogits > V) {
+        for (int v = 0; v < kNV; ++v) settle_raw<T, ALIGNED>(raw.v[v], V, first + v * kWave * kVec);
+    }
 #pragma unroll
-            for (int v = 0; v < kNV; ++v) {
-                const bool out = first + v * kWave * kVec >= V;
+    for (int v = 0; v < kNV; ++v) unpack_vec<T>(raw.v[v], x + v * kVec);
+    if (tail) {
 #pragma unroll
-                for (int e = 0; e < kVec; ++e)
-                    if (out) x[v * kVec + e] = -INFINITY;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int v = 0; v < kNV; ++v) load_vec<T, false>(row, V, first + v * kWave * kVec, x + v * kVec);
+        for (int v = 0; v < kNV; ++v) blank_beyond<T, ALIGNED>(V, first + v * kWave * kVec, x + v * kVec);
     }
 }
 
@@ -744,15 +733,13 @@ __device__ __forceinline__ int draw_from_row(const FusedParams &P, const Words &
     const T *prow = target + (base + row) * P.tstride;
     const T *qrow = draft + drow * P.dstride;
     const int first = slot * kUnitLogits + lane * kVec;
-    // (the sixteen-byte path asks for the whole chunk at once and keeps it as loaded until each vector's turn)
-    uint4 rp[ALIGNED ? kNV : 1], rq[ALIGNED ? kNV : 1];
-    if constexpr (ALIGNED) {
+    // (the whole chunk is asked for at once and kept as loaded until each vector's turn)
+    uint4 rp[kNV], rq[kNV];
 #pragma unroll
-        for (int v = 0; v < kNV; ++v) {
-            const int idx = first + v * kWave * kVec;
-            rp[v] = *reinterpret_cast<const uint4 *>(prow + (idx < V ? idx : 0));
-            if (mode == 0) rq[v] = *reinterpret_cast<const uint4 *>(qrow + (idx < V ? idx : 0));
-        }
+    for (int v = 0; v < kNV; ++v) {
+        const int idx = first + v * kWave * kVec;
+        rp[v] = load_raw<T, ALIGNED, false>(prow, V, idx);
+        if (mode == 0) rq[v] = load_raw<T, ALIGNED, false>(qrow, V, idx);
     }
     float shift = 0.f, scale = 1.f;
     if (mode != 0) {
@@ -765,17 +752,8 @@ __device__ __forceinline__ int draw_from_row(const FusedParams &P, const Words &
     for (int v = 0; v < kNV; ++v) {
         const int idx = first + v * kWave * kVec;
         float wgt[kVec], xpv[kVec], xqv[kVec];
-        if constexpr (ALIGNED) {
-            unpack_vec<T>(rp[v], xpv);
-            if (mode == 0) unpack_vec<T>(rq[v], xqv);
-            if (idx >= V) {
-#pragma unroll
-                for (int e = 0; e < kVec; ++e) { xpv[e] = -INFINITY; xqv[e] = -INFINITY; }
-            }
-        } else {
-            load_vec<T, false>(prow, V, idx, xpv);
-            if (mode == 0) load_vec<T, false>(qrow, V, idx, xqv);
-        }
+        unpack_raw<T, ALIGNED>(rp[v], V, idx, xpv);
+        if (mode == 0) unpack_raw<T, ALIGNED>(rq[v], V, idx, xqv);
         if (mode == 0) {
 #pragma unroll
             for (int e = 0; e < kVec; ++e) wgt[e] = fmaxf(residual_term(xpv[e], xqv[e], k, rc), 0.f);
@@ -838,7 +816,7 @@ __device__ __forceinline__ int draw_from_target_row(const FusedParams &P, const 
         RawSlice<T, ALIGNED, LANE> raw;
         float x[LANE], shift;
         issue_loads<T, ALIGNED, LANE>(prow, c * kUnitLogits, P.V, raw);
-        unpack_slice<T, ALIGNED, LANE>(prow, c * kUnitLogits, P.V, raw, x);
+        unpack_slice<T, ALIGNED, LANE>(c * kUnitLogits, P.V, raw, x);
         const u64 word = first_sweep_row(x, P.k, shift);
         if (lane == 0) st_u64(st + c, word);
     }
@@ -1141,7 +1119,7 @@ void fused_verify_kernel(const FusedParams P)
         }
         issue_loads<T, ALIGNED, LANE>(rowA, unit_first, V, rawA);
         float xa[LANE], shiftA;
-        unpack_slice<T, ALIGNED, LANE>(rowA, unit_first, V, rawA, xa);
+        unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawA, xa);
         const u64 stA = first_sweep_row(xa, k, shiftA);
         if (lane == 0) st_u64(W.plast + (size_t)U.b * nu + U.c, stA);
         if (!P.skip_last && clears) {
@@ -1182,12 +1160,12 @@ void fused_verify_kernel(const FusedParams P)
     // ---- first sweep: exponentials stay in xa / xb; the unit's words go out
     float xa[LANE], xb[LANE];
     float shiftA, shiftB;
-    unpack_slice<T, ALIGNED, LANE>(rowA, unit_first, V, rawA, xa);
+    unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawA, xa);
     const u64 stA = first_sweep_row(xa, k, shiftA);
     // (the draft row's logits are taken out of their load registers before anything else is sent to memory: the
     // hardware counts outstanding loads and stores in one counter, in order, and a wait for these loads placed after
     // a store would be a wait for that store's acknowledgement too)
-    unpack_slice<T, ALIGNED, LANE>(rowB, unit_first, V, rawB, xb);
+    unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawB, xb);
     // (smaller units: the target row's word of this wave, stA, goes to the workgroup's word only - per wave chunk nobody
     // needs it but a draw from the row itself, which forms it again where it happens: 36 864 stores less per call at
     // B = 64, gamma = 8, V = 128256, 52.2 -> 51.1 us)

@@ -227,7 +227,7 @@ void resident_verify_kernel(const FusedParams P)
             if (leader) res_first = ld_u64(W.rowres + seq_d + (lane < gb ? lane : 0));
         }
         float xa[LANE], shiftA;
-        unpack_slice<T, ALIGNED, LANE>(rowA, unit_first, V, rawA, xa);
+        unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawA, xa);
         const u64 stA = first_sweep_row(xa, k, shiftA);
         if (lane == 0) wave_words[0][wave] = stA;
         __syncthreads();
@@ -333,9 +333,9 @@ void resident_verify_kernel(const FusedParams P)
     // ---- first sweep (as in the large kernel): exponentials stay in xa / xb
     float xa[LANE], xb[LANE];
     float shiftA, shiftB;
-    unpack_slice<T, ALIGNED, LANE>(rowA, unit_first, V, rawA, xa);
+    unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawA, xa);
     const u64 stA = first_sweep_row(xa, k, shiftA);
-    unpack_slice<T, ALIGNED, LANE>(rowB, unit_first, V, rawB, xb);
+    unpack_slice<T, ALIGNED, LANE>(unit_first, V, rawB, xb);
     uint32_t ya_bits = 0, yb_bits = 0;
     if (leader) { ya_bits = logit_bits(rowA + tok); yb_bits = logit_bits(rowB + tok); }
     const u64 stB = first_sweep_row(xb, k, shiftB);
