@@ -1,76 +1,286 @@
 // The drafting step of the outer loop of speculative decoding (Alg. 3, "sample X_1 .. X_gamma from M_s")
 // for a model whose conditional distributions are handed over as rows of logits: one token per row
 // from softmax(logits / T), Y = min{x : C_x > u * C_total} with C the running sum in vocabulary order
-// (the same convention as the draw of the correction token).  Not a hot path: a drafter produces its
-// tokens as it runs; this exists so that the outer loop on toy models stays on the device.
+// (the same convention as the draw of the correction token).
+//
+// One read of the row.  A row is cut into units of 64 * 32 contiguous logits, a wave takes a stretch of neighbouring
+// units: it loads the next unit (sixteen-byte loads, 1 KB per instruction) while it turns the one before into
+// exponentials against an integer shift of the unit's own, and keeps each unit's (largest scaled logit, sum) in one of
+// its lanes.  The waves' totals meet in LDS once; every wave then knows which wave's stretch holds u * C_total, and that
+// wave finds the unit from its lanes, reads that one unit again and walks it.  Sums are formed in double throughout
+// (exponentials are float), recombined through exact powers of two.
+//
+// What bounds it: the bytes where there are rows for the whole device (2048 rows of 128256 bf16 logits: 91 us, 5.8 TB/s;
+// float32 161 us, 6.5 TB/s); with fewer rows the vector instructions of the one compute unit a row has (64 such rows: 13.6
+// us, about 8 of them in the sweep).  The kernel before this one gave each thread a contiguous stretch (uncoalesced) and
+// read the row three times: 255 us for the 64 rows, 7497 for the 2048.
 #pragma once
 
-#include "common.hpp"
+#include "fused.hpp"
 
 namespace sv {
 
-// One workgroup per row; thread t owns the contiguous range [t * len, (t + 1) * len) of the row, so that
-// per-thread sums, scanned over the threads, are the running sum in vocabulary order.
-template <typename T>
-__global__ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, int32_t *tokens)
+constexpr int kSampleUnit = kWave * kLaneSmall;          // logits per unit
+// Rows of at most this many logits go to one thread each (81920 rows of 2: 7.4 us, launch included, against 88 with a
+// wave per row), up to 512 to sixteen lanes (65536 rows of 100: 9.4 against 71), up to a unit to a wave (65536 rows of
+// 1000: 40 against 244).
+constexpr int kSampleSerial = 32;
+// Sixteen waves per row are a row's shortest time (64 rows of 128256 bf16 logits: 13.6 us against 15.4 with eight waves);
+// four let the draws of some rows run under the sweeps of others once every compute unit has several rows (512 rows 32.1 us with
+// sixteen, 31.8 with four; 4096 rows of 32000: 49 with four).  Rows of up to four units have no work for more than four.
+constexpr int kSampleManyRows = 512;
+
+// Rows of more than one unit: one workgroup of WPR waves per row.
+template <typename T, int WPR>
+__global__ __launch_bounds__(WPR * kWave)
+void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, int32_t *tokens)
 {
-    __shared__ double part[kThreads];
-    __shared__ float red[kThreads];
-    __shared__ int winner;
-    __shared__ double total_all;
-    const int nt = blockDim.x, t = threadIdx.x;
-    const T *row = logits + (size_t)blockIdx.x * V;
-    const int len = (V + nt - 1) / nt;
-    const int lo = t * len < V ? t * len : V, hi = lo + len < V ? lo + len : V;
+    constexpr int LANE = kLaneSmall, kVec = ElemTraits<T>::kVec, kNV = LANE / kVec;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t r = blockIdx.x;
+    const T *const row = logits + r * (size_t)V;
+    const float u = load_uniform(uniforms + r);
 
-    float m = -INFINITY;
-    for (int x = lo; x < hi; ++x) m = fmaxf(m, (float)logit_as_double(row + x));
-    red[t] = m;
-    __syncthreads();
-    for (int s = nt / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] = fmaxf(red[t], red[t + s]);
-        __syncthreads();
-    }
-    const float shift = red[0] * k;
+    // the wave's entries (at most one per lane): `span` units each, neighbours
+    const int units = (V - 1) / kSampleUnit + 1;
+    const int span = (units - 1) / (WPR * kWave) + 1;
+    const int entries = (units - 1) / span + 1;
+    const int per = (entries - 1) / WPR + 1;
+    const int first_unit = min((long long)w * per * span, (long long)units), end_unit = min((long long)(w + 1) * per * span, (long long)units);
 
-    double mine = 0.0;
-    for (int x = lo; x < hi; ++x) mine += (double)fast_exp2(__builtin_fmaf((float)logit_as_double(row + x), k, -shift));
-    part[t] = mine;
-    if (t == 0) winner = -1;
-    __syncthreads();
-    // running sum over the threads, in order (thread 0 walks the at most 256 partial sums)
-    if (t == 0) {
-        double c = 0.0;
-        for (int i = 0; i < nt; ++i) { const double s = part[i]; part[i] = c; c += s; }
-        total_all = c;
-    }
-    __syncthreads();
-    const double total = total_all;
-    const double target = (double)uniforms[blockIdx.x] * total;
-    const double below = part[t];
-    // the thread whose range holds the target walks it; the last such claim in thread order wins when
-    // rounding makes neighbours both claim (it cannot: ranges are disjoint half-open intervals)
-    if (mine > 0.0 && below <= target && target < below + mine) {
-        double c = below;
-        int y = -1, last_positive = -1;
-        for (int x = lo; x < hi; ++x) {
-            const float e = fast_exp2(__builtin_fmaf((float)logit_as_double(row + x), k, -shift));
-            c += (double)e;
-            if (e > 0.f) last_positive = x;
-            if (c > target) { y = x; break; }
+    float my_m = -INFINITY;                                  // lane j: the wave's entry j
+    double my_z = 0.0;
+    {
+        // (a unit is addressed from its own start: offsets stay small whatever V is)
+        auto issue = [&](int unit, RawSlice<T, false, LANE> &raw) {
+            const int at = unit * kSampleUnit;
+            issue_loads<T, false, LANE>(row + at, 0, V - at, raw);
+        };
+        RawSlice<T, false, LANE> raw, next;
+        if (first_unit < end_unit) issue(first_unit, raw);
+        int entry = 0, in_entry = 0;
+        for (int unit = first_unit; unit < end_unit; ++unit) {
+            if (unit + 1 < end_unit) issue(unit + 1, next);
+            const int left = V - unit * kSampleUnit;
+            float x[LANE];
+            unpack_slice<T, false, LANE>(0, left, raw, x);
+            float m = x[0];
+#pragma unroll
+            for (int j = 1; j < LANE; ++j) m = fmaxf(m, x[j]);
+            const float M = wave_max(m * k), shift = shift_of(M);
+            double acc[2] = {0.0, 0.0};
+#pragma unroll
+            for (int j = 0; j < LANE; ++j) acc[j & 1] += (double)fast_exp2(__builtin_fmaf(x[j], k, -shift));
+            double z0, z1;
+            halves_sum_f64(acc[0] + acc[1], z0, z1);
+            if (lane == entry && M > -INFINITY) {
+                const double z = z0 + z1;
+                const float top = fmaxf(my_m, M);
+                my_z = (my_m > -INFINITY ? ldexp(my_z, (int)(shift_of(my_m) - shift_of(top))) : 0.0) + ldexp(z, (int)(shift - shift_of(top)));
+                my_m = top;
+            }
+            if (++in_entry == span) { in_entry = 0; ++entry; }
+            raw = next;
         }
-        winner = y >= 0 ? y : last_positive;
     }
-    __syncthreads();
-    if (winner < 0 && t == 0) {
-        // rounding pushed the target to the total: the last token of positive weight
-        int y = 0;
-        for (int x = V - 1; x >= 0; --x)
-            if (fast_exp2(__builtin_fmaf((float)logit_as_double(row + x), k, -shift)) > 0.f) { y = x; break; }
-        winner = y;
+
+    // ---- the waves' totals, relative to the integer shift of the wave's largest
+    const float Mw = wave_max(my_m);
+    const double z_lane = my_m > -INFINITY ? ldexp(my_z, (int)(shift_of(my_m) - shift_of(Mw))) : 0.0;
+    const double inc_lane = wave_scan(z_lane);
+    const double z_wave = read_lane_double(inc_lane, kWave - 1);
+    double t;                                                // what is left of u * C_total where the wave's stretch begins
+    {
+        __shared__ float wave_m[WPR];
+        __shared__ double wave_z[WPR];
+        if (lane == 0) { wave_m[w] = Mw; wave_z[w] = z_wave; }
+        __syncthreads();
+        const float m = lane < WPR ? wave_m[lane] : -INFINITY;
+        const float M = wave_max(m);
+        const double z = m > -INFINITY ? ldexp(wave_z[lane & (WPR - 1)], (int)(shift_of(m) - shift_of(M))) : 0.0;
+        const double inc = wave_scan(z);
+        const double target = (double)u * read_lane_double(inc, kWave - 1);
+        // the first wave whose running sum exceeds the target (rounding may leave none: then the last with any weight)
+        const u64 hit = __ballot(inc > target), nz = __ballot(z > 0.0);
+        const int holder = hit ? __ffsll((long long)hit) - 1 : nz ? 63 - __clzll((long long)nz) : 0;
+        if (holder != w) return;
+        t = hit ? ldexp(target - read_lane_double(inc - z, holder), (int)(shift_of(M) - shift_of(Mw))) : (double)INFINITY;
+        if (!(Mw > -INFINITY)) t = INFINITY;
     }
-    __syncthreads();
-    if (t == 0) tokens[blockIdx.x] = winner;
+    // ---- the entry of the wave's stretch, the same way
+    const u64 hit = __ballot(inc_lane > t), nz = __ballot(z_lane > 0.0);
+    const int entry = hit ? __ffsll((long long)hit) - 1 : nz ? 63 - __clzll((long long)nz) : 0;
+    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_m), entry)));
+    t = hit ? ldexp(t - read_lane_double(inc_lane - z_lane, entry), (int)(shift_of(Mw) - shift)) : (double)INFINITY;
+
+    // ---- and the token: the entry's units again, in vocabulary order (vector, lane, element)
+    int y = -1, last_positive = -1;
+    const int from = first_unit + entry * span;
+    for (int unit = from; unit < from + span && unit < end_unit && y < 0; ++unit) {
+        const int at = unit * kSampleUnit, left = V - at;
+        RawSlice<T, false, LANE> raw;
+        issue_loads<T, false, LANE>(row + at, 0, left, raw);
+        float x[LANE];
+        unpack_slice<T, false, LANE>(0, left, raw, x);
+#pragma unroll
+        for (int v = 0; v < kNV; ++v) {
+            if (y >= 0) continue;
+            double mine = 0.0;
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) {
+                float &wgt = x[v * kVec + e];
+                wgt = fast_exp2(__builtin_fmaf(wgt, k, -shift));
+                mine += (double)wgt;
+                if (wgt > 0.f) last_positive = at + (v * kWave + lane) * kVec + e;
+            }
+            const double inc = wave_scan(mine);
+            const u64 here = __ballot(inc > t);
+            if (here) {
+                const int l = __ffsll((long long)here) - 1;
+                double run = inc - mine;
+                int e_hit = -1, e_last = 0;
+#pragma unroll
+                for (int e = 0; e < kVec; ++e) {
+                    const float wgt = x[v * kVec + e];
+                    run += (double)wgt;
+                    if (wgt > 0.f) e_last = e;
+                    if (e_hit < 0 && run > t) e_hit = e;
+                }
+                // (scan and walk may round differently: then the lane's last token with weight)
+                y = at + (v * kWave + l) * kVec + __builtin_amdgcn_readlane(e_hit < 0 ? e_last : e_hit, l);
+            }
+            t -= read_lane_double(inc, kWave - 1);
+        }
+    }
+    if (y < 0) {
+        // rounding pushed t to the end: the last token with weight (none in the row: token 0)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) last_positive = max(last_positive, __shfl_xor(last_positive, off, kWave));
+        y = last_positive < 0 ? 0 : last_positive;
+    }
+    if (lane == 0) tokens[r] = y;
+}
+
+// Reductions over the G lanes (16 or 64) that share a row, every lane getting the result, and the inclusive scan.
+template <int G> __device__ __forceinline__ float group_max(float v)
+{
+    if constexpr (G == kWave) return wave_max(v);
+    v = fmaxf(v, __int_as_float(dpp_shift<0xB1>(__float_as_int(v))));         // quad_perm:[1,0,3,2]
+    v = fmaxf(v, __int_as_float(dpp_shift<0x4E>(__float_as_int(v))));         // quad_perm:[2,3,0,1]
+    v = fmaxf(v, __int_as_float(dpp_shift<0x141>(__float_as_int(v))));        // row_half_mirror
+    return fmaxf(v, __int_as_float(dpp_shift<0x140>(__float_as_int(v))));     // row_mirror
+}
+template <int G> __device__ __forceinline__ double group_scan(double v)
+{
+    if constexpr (G == kWave) return wave_scan(v);
+    v += dpp_shift_double<0x111>(v);
+    v += dpp_shift_double<0x112>(v);
+    v += dpp_shift_double<0x114>(v);
+    v += dpp_shift_double<0x118>(v);
+    return v;
+}
+
+// Rows of at most G * 32 logits: G lanes per row, the whole row in their registers, nothing read twice.
+template <typename T, int G>
+__global__ __launch_bounds__(kThreads)
+void sample_small_rows_kernel(const T *logits, int rows, int V, float k, const float *uniforms, int32_t *tokens)
+{
+    constexpr int kVec = ElemTraits<T>::kVec, kNV = kLaneSmall / kVec;
+    const int lane = threadIdx.x & 63, l = lane & (G - 1);
+    const long long at = ((long long)blockIdx.x * kThreads + threadIdx.x) / G;
+    const bool mine = at < rows;                                              // (lanes beyond the last row work on it too and write nothing)
+    const size_t r = mine ? (size_t)at : (size_t)rows - 1;
+    const T *const row = logits + r * (size_t)V;
+    const int nv = (V - 1) / (G * kVec) + 1;                                  // vectors of a lane that reach into the row
+    uint4 raw[kNV];
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) raw[v] = load_raw<T, false, true>(row, V, (v * G + l) * kVec);
+    const float u = uniforms[r];
+    float x[kNV * kVec], m = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) {
+            unpack_raw<T, false>(raw[v], V, (v * G + l) * kVec, x + v * kVec);
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) m = fmaxf(m, x[v * kVec + e]);
+        }
+    const float shift = shift_of(group_max<G>(m * k));
+    // (in vocabulary order: vector, lane, element)
+    double before[kNV], mass[kNV], total = 0.0;                               // per vector: the weights before the lane's, and the lane's
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) {
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) {
+                float &wgt = x[v * kVec + e];
+                wgt = fast_exp2(__builtin_fmaf(wgt, k, -shift));
+                s += (double)wgt;
+            }
+            const double inc = group_scan<G>(s);
+            before[v] = total + (inc - s);
+            mass[v] = s;
+            total += G == kWave ? read_lane_double(inc, kWave - 1) : __shfl(inc, lane | (G - 1), kWave);
+        }
+    const double t = (double)u * total;
+    // the token lies with the first lane and vector whose running sum exceeds t
+    const u64 group_bits = G == kWave ? ~0ull : ((1ull << (G & 63)) - 1ull) << (lane & ~(G - 1));
+    bool found = false;
+    int last_positive = -1;
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) {
+            const int first = (v * G + l) * kVec;
+            const u64 hit = __ballot(before[v] + mass[v] > t) & group_bits;
+            if (!found && hit && lane == __ffsll((long long)hit) - 1) {
+                double run = before[v];
+                int y = -1, y_last = 0;
+#pragma unroll
+                for (int e = 0; e < kVec; ++e) {
+                    const float wgt = x[v * kVec + e];
+                    run += (double)wgt;
+                    if (wgt > 0.f) y_last = e;
+                    if (y < 0 && run > t) y = e;
+                }
+                if (mine) tokens[r] = first + (y < 0 ? y_last : y);
+            }
+            found = found || hit != 0;
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) if (x[v * kVec + e] > 0.f) last_positive = first + e;
+        }
+    // rounding pushed t to the end: the last token with weight (none in the row: token 0)
+    if (__any(!found)) {
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) last_positive = max(last_positive, __shfl_xor(last_positive, off, kWave));
+        if (!found && l == 0 && mine) tokens[r] = last_positive < 0 ? 0 : last_positive;
+    }
+}
+
+// Rows of a handful of logits (the toy models of Sec. 2): one thread per row; the row's three readings after the first
+// come from the cache.
+template <typename T>
+__global__ __launch_bounds__(kThreads)
+void sample_short_rows_kernel(const T *logits, int rows, int V, float k, const float *uniforms, int32_t *tokens)
+{
+    const long long r = (long long)blockIdx.x * kThreads + threadIdx.x;
+    if (r >= rows) return;
+    const T *row = logits + (size_t)r * (size_t)V;
+    float m = -INFINITY;
+    for (int x = 0; x < V; ++x) m = fmaxf(m, logit_as_float(row + x));
+    const float shift = shift_of(m * k);
+    double total = 0.0;
+    for (int x = 0; x < V; ++x) total += (double)fast_exp2(__builtin_fmaf(logit_as_float(row + x), k, -shift));
+    const double target = (double)uniforms[r] * total;
+    double c = 0.0;
+    int y = -1, last_positive = 0;
+    for (int x = 0; x < V && y < 0; ++x) {
+        const float e = fast_exp2(__builtin_fmaf(logit_as_float(row + x), k, -shift));
+        c += (double)e;
+        if (e > 0.f) last_positive = x;
+        if (c > target) y = x;
+    }
+    tokens[r] = y < 0 ? last_positive : y;
 }
 
 }  // namespace sv

@@ -283,6 +283,24 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
+// The drafting step: how many waves share a row.
+template <typename T>
+sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, hipStream_t stream)
+{
+    const T *logits = static_cast<const T *>(logits_v);
+    if (V <= kSampleSerial)
+        sample_short_rows_kernel<T><<<(unsigned)((rows - 1) / kThreads + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
+    else if (V <= 16 * kLaneSmall)
+        sample_small_rows_kernel<T, 16><<<(unsigned)((rows - 1) / (kThreads / 16) + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
+    else if (V <= kSampleUnit)
+        sample_small_rows_kernel<T, 64><<<(unsigned)((rows - 1) / kWaves + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
+    else if (V <= 4 * kSampleUnit || rows >= kSampleManyRows)
+        sample_rows_kernel<T, 4><<<(unsigned)rows, 4 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
+    else
+        sample_rows_kernel<T, 16><<<(unsigned)rows, 16 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
+    return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
+}
+
 sv_status_t verify_entry(int algo, bool probs, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
                          int64_t target_row_stride, int64_t draft_row_stride,
                          const float *uniforms, int32_t B, int32_t gamma, int32_t V, sv_dtype_t dtype,
@@ -494,13 +512,10 @@ sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_d
     if (dtype != SV_DTYPE_F32 && dtype != SV_DTYPE_BF16) return SV_ERR_INVALID_ARG;
     if (rows > 0x7fffffffll) return SV_ERR_UNSUPPORTED;
     const float k = (float)(1.4426950408889634074 / (double)temperature);
-    const unsigned threads = V > 8192 ? kThreads : kWave;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    if (dtype == SV_DTYPE_F32)
-        sample_rows_kernel<float><<<(unsigned)rows, threads, 0, stream>>>(static_cast<const float *>(logits), V, k, uniforms, tokens);
-    else
-        sample_rows_kernel<bf16_t><<<(unsigned)rows, threads, 0, stream>>>(static_cast<const bf16_t *>(logits), V, k, uniforms, tokens);
-    return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
+    return dtype == SV_DTYPE_F32
+        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, stream)
+        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, stream);
 }
 
 #ifdef SV_PROFILE

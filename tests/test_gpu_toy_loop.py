@@ -33,6 +33,31 @@ def test_sample_tokens_matches_the_oracle(rows, V, dtype):
         assert bad.mean() < 0.02
 
 
+# (the edges of the kernels' ranges: one thread, sixteen lanes, a wave, four and sixteen waves per row, rows whose waves keep
+# several units per lane; row counts that leave the last workgroup partly empty; rows at every alignment)
+@pytest.mark.parametrize("rows,V,dtype", [(257, 32, "bf16"), (1, 33, "f32"), (37, 100, "bf16"), (18, 511, "f32"), (5, 512, "bf16"), (7, 513, "f32"),
+                                          (6, 2047, "bf16"), (5, 2048, "f32"), (3, 2049, "bf16"), (4, 8191, "bf16"), (5, 8193, "f32"),
+                                          (513, 8197, "bf16"), (600, 10001, "f32"), (2, 32768, "f32"), (3, 32769, "bf16"), (2, 2097153, "bf16")])
+def test_sample_tokens_at_the_edges_of_its_kernels(rows, V, dtype):
+    g = torch.Generator(device="cpu").manual_seed(rows * 11 + V)
+    logits = torch.randn((rows, V), generator=g) * 4.0
+    logits[rows // 2, V // 3:] = float("-inf")               # one row masked down to its head
+    logits[0, : V // 2] = float("-inf")                      # one to its tail
+    logits = logits.to(torch.bfloat16 if dtype == "bf16" else torch.float32).to(DEV)
+    u = workloads.philox_uniforms(rows + V, (rows,))
+    u[-1], u[0] = 0.0, 1.0 - 2.0 ** -24
+    got = sv.spec_sample_tokens(logits, torch.as_tensor(u, device=DEV), 0.7).cpu().numpy()
+    want, margins = oracle.sample_rows(workloads.logits_to_numpy(logits), u, 0.7, dtype=oracle.BF16 if dtype == "bf16" else oracle.F32)
+    bad = got != want
+    assert not np.any(bad & (margins >= MARGIN)), (np.nonzero(bad)[0], got[bad], want[bad], margins[bad])
+
+
+def test_sample_tokens_of_rows_without_weight_is_token_0():
+    for V in (2, 300, 1500, 9000, 40000):
+        logits = torch.full((3, V), float("-inf"), device=DEV)
+        assert sv.spec_sample_tokens(logits, torch.tensor([0.0, 0.5, 0.99], device=DEV), 1.0).tolist() == [0, 0, 0]
+
+
 def test_sample_tokens_uniform_extremes():
     logits = torch.tensor([[0.0, -80.0, 1.0, -80.0]], device=DEV)
     assert int(sv.spec_sample_tokens(logits, torch.zeros(1, device=DEV), 1.0)[0]) == 0
