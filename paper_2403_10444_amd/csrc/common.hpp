@@ -131,18 +131,17 @@ __device__ __forceinline__ void unpack_vec(const uint4 &v, float *out)
 // logits, 67.9 against 30.7 for 48 drafts of up to 6 over 100277.)
 template <typename T, bool ALIGNED> constexpr int kRowAlign = ALIGNED ? 16 : (int)sizeof(T);
 
-// The sixteen bytes that end with a row of fewer than kVec logits, gathered one by one.
+// The sixteen bytes that end with a row of fewer than kVec logits, gathered one by one (what lies in front of them repeats
+// the first).
 template <typename T>
 __device__ __forceinline__ uint4 load_short_row(const T *row, int V)
 {
-    constexpr int kBits = 8 * (int)sizeof(T);
-    unsigned long long lo = 0, hi = 0;
-#pragma nounroll
-    for (int e = 0; e < V; ++e) {
-        lo = lo >> kBits | hi << (64 - kBits);
-        hi = hi >> kBits | (unsigned long long)logit_bits(row + e) << (64 - kBits);
-    }
-    return make_uint4((unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32));
+    constexpr int kVec = ElemTraits<T>::kVec;
+    uint32_t bits[kVec];
+#pragma unroll
+    for (int e = 0; e < kVec; ++e) bits[e] = logit_bits(row + (e > kVec - V ? e - (kVec - V) : 0));
+    if constexpr (kVec == 4) return make_uint4(bits[0], bits[1], bits[2], bits[3]);
+    else return make_uint4(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16, bits[4] | bits[5] << 16, bits[6] | bits[7] << 16);
 }
 
 // The vector of kVec logits at element `idx` (a multiple of kVec, possibly beyond the row), as unpack_raw takes it.

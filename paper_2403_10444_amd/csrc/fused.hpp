@@ -421,6 +421,104 @@ __device__ __forceinline__ void halves_sum_f64(double v, double &first, double &
     second = read_lane_double(v, 63);
 }
 
+// ------------------------------------------------------------------ groups of lanes
+// Several rows (or row pairs) in one wave, G = 4, 16 or 64 lanes each: reductions over a group that leave every lane with
+// the result, and the inclusive scan over it (fixed orders, DPP).
+template <int G> __device__ __forceinline__ float group_max(float v)
+{
+    if constexpr (G == kWave) return wave_max(v);
+    v = fmaxf(v, __int_as_float(dpp_shift<0xB1>(__float_as_int(v))));             // quad_perm:[1,0,3,2]
+    v = fmaxf(v, __int_as_float(dpp_shift<0x4E>(__float_as_int(v))));             // quad_perm:[2,3,0,1]
+    if constexpr (G == 16) {
+        v = fmaxf(v, __int_as_float(dpp_shift<0x141>(__float_as_int(v))));        // row_half_mirror
+        v = fmaxf(v, __int_as_float(dpp_shift<0x140>(__float_as_int(v))));        // row_mirror
+    }
+    return v;
+}
+template <int G> __device__ __forceinline__ double group_sum(double v)
+{
+    if constexpr (G == kWave) {
+        double first, second;
+        halves_sum_f64(v, first, second);
+        return first + second;
+    }
+    v += dpp_shift_double<0xB1>(v);
+    v += dpp_shift_double<0x4E>(v);
+    if constexpr (G == 16) {
+        v += dpp_shift_double<0x141>(v);
+        v += dpp_shift_double<0x140>(v);
+    }
+    return v;
+}
+template <int G> __device__ __forceinline__ double group_scan(double v)
+{
+    if constexpr (G == kWave) return wave_scan(v);
+    if constexpr (G == 4) {
+        const int l = threadIdx.x & 3;
+        const double one = dpp_shift_double<0x111>(v);                            // (row_shr moves across quads too)
+        v += l >= 1 ? one : 0.0;
+        const double two = dpp_shift_double<0x112>(v);
+        return v + (l >= 2 ? two : 0.0);
+    }
+    v += dpp_shift_double<0x111>(v);
+    v += dpp_shift_double<0x112>(v);
+    v += dpp_shift_double<0x114>(v);
+    v += dpp_shift_double<0x118>(v);
+    return v;
+}
+// The draw from weights that a group holds in registers: weight(j), j = v * KVEC + e, is the lane's weight of token
+// (v * G + lane in the group) * KVEC + e, v < nv.  The first token whose running sum (in double, in vocabulary order:
+// vector, lane, element) exceeds u * total; where rounding leaves none, the last with weight, and 0 if none has any.
+// Every lane of the group gets it.
+template <int G, int NV, int KVEC, typename F>
+__device__ __forceinline__ int draw_in_group(F weight, int nv, float u)
+{
+    const int lane = threadIdx.x & 63, l = lane & (G - 1);
+    double before[NV], mass[NV], total = 0.0;                // per vector: the weights in front of the lane's, and the lane's
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v < nv) {
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < KVEC; ++e) s += (double)weight(v * KVEC + e);
+            const double inc = group_scan<G>(s);
+            before[v] = total + (inc - s);
+            mass[v] = s;
+            total += G == kWave ? read_lane_double(inc, kWave - 1) : __shfl(inc, lane | (G - 1), kWave);
+        }
+    const double t = (double)u * total;
+    const u64 group_bits = G == kWave ? ~0ull : ((1ull << (G & 63)) - 1ull) << (lane & ~(G - 1));
+    int y = -1, owner = -1, last_positive = -1;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v < nv) {
+            const int first = (v * G + l) * KVEC;
+            const u64 hit = __ballot(before[v] + mass[v] > t) & group_bits;
+            const bool here = owner < 0 && hit;
+            if (here) owner = __ffsll((long long)hit) - 1;
+            if (here && lane == owner) {
+                double run = before[v];
+                int found = -1, last = 0;
+#pragma unroll
+                for (int e = 0; e < KVEC; ++e) {
+                    const float w = weight(v * KVEC + e);
+                    run += (double)w;
+                    if (w > 0.f) last = e;
+                    if (found < 0 && run > t) found = e;
+                }
+                y = first + (found < 0 ? last : found);
+            }
+#pragma unroll
+            for (int e = 0; e < KVEC; ++e) if (weight(v * KVEC + e) > 0.f) last_positive = first + e;
+        }
+    if (__any(owner < 0)) {
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) last_positive = max(last_positive, __shfl_xor(last_positive, off, kWave));
+        if (owner < 0) { y = last_positive < 0 ? 0 : last_positive; owner = lane; }
+    }
+    return __shfl(y, owner, kWave);
+}
+
 // Log2-normaliser of a row from the words of its n <= 64 NW units: every lane combines its entries
 // (in that fixed order), then the wave combines.  Returns L; M_out is the largest shift.
 template <int NW>

@@ -161,25 +161,6 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
     if (lane == 0) tokens[r] = y;
 }
 
-// Reductions over the G lanes (16 or 64) that share a row, every lane getting the result, and the inclusive scan.
-template <int G> __device__ __forceinline__ float group_max(float v)
-{
-    if constexpr (G == kWave) return wave_max(v);
-    v = fmaxf(v, __int_as_float(dpp_shift<0xB1>(__float_as_int(v))));         // quad_perm:[1,0,3,2]
-    v = fmaxf(v, __int_as_float(dpp_shift<0x4E>(__float_as_int(v))));         // quad_perm:[2,3,0,1]
-    v = fmaxf(v, __int_as_float(dpp_shift<0x141>(__float_as_int(v))));        // row_half_mirror
-    return fmaxf(v, __int_as_float(dpp_shift<0x140>(__float_as_int(v))));     // row_mirror
-}
-template <int G> __device__ __forceinline__ double group_scan(double v)
-{
-    if constexpr (G == kWave) return wave_scan(v);
-    v += dpp_shift_double<0x111>(v);
-    v += dpp_shift_double<0x112>(v);
-    v += dpp_shift_double<0x114>(v);
-    v += dpp_shift_double<0x118>(v);
-    return v;
-}
-
 // Rows of at most G * 32 logits: G lanes per row, the whole row in their registers, nothing read twice.
 template <typename T, int G>
 __global__ __launch_bounds__(kThreads)
@@ -201,60 +182,20 @@ void sample_small_rows_kernel(const T *logits, int rows, int V, float k, const f
 #pragma unroll
     for (int v = 0; v < kNV; ++v)
         if (v < nv) {
-            unpack_raw<T, false>(raw[v], V, (v * G + l) * kVec, x + v * kVec);
+            if (v + 1 < nv) unpack_vec<T>(raw[v], x + v * kVec);              // (only a row's last vectors reach beyond it)
+            else unpack_raw<T, false>(raw[v], V, (v * G + l) * kVec, x + v * kVec);
 #pragma unroll
             for (int e = 0; e < kVec; ++e) m = fmaxf(m, x[v * kVec + e]);
         }
     const float shift = shift_of(group_max<G>(m * k));
-    // (in vocabulary order: vector, lane, element)
-    double before[kNV], mass[kNV], total = 0.0;                               // per vector: the weights before the lane's, and the lane's
 #pragma unroll
     for (int v = 0; v < kNV; ++v)
         if (v < nv) {
-            double s = 0.0;
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) {
-                float &wgt = x[v * kVec + e];
-                wgt = fast_exp2(__builtin_fmaf(wgt, k, -shift));
-                s += (double)wgt;
-            }
-            const double inc = group_scan<G>(s);
-            before[v] = total + (inc - s);
-            mass[v] = s;
-            total += G == kWave ? read_lane_double(inc, kWave - 1) : __shfl(inc, lane | (G - 1), kWave);
+            for (int e = 0; e < kVec; ++e) x[v * kVec + e] = fast_exp2(__builtin_fmaf(x[v * kVec + e], k, -shift));
         }
-    const double t = (double)u * total;
-    // the token lies with the first lane and vector whose running sum exceeds t
-    const u64 group_bits = G == kWave ? ~0ull : ((1ull << (G & 63)) - 1ull) << (lane & ~(G - 1));
-    bool found = false;
-    int last_positive = -1;
-#pragma unroll
-    for (int v = 0; v < kNV; ++v)
-        if (v < nv) {
-            const int first = (v * G + l) * kVec;
-            const u64 hit = __ballot(before[v] + mass[v] > t) & group_bits;
-            if (!found && hit && lane == __ffsll((long long)hit) - 1) {
-                double run = before[v];
-                int y = -1, y_last = 0;
-#pragma unroll
-                for (int e = 0; e < kVec; ++e) {
-                    const float wgt = x[v * kVec + e];
-                    run += (double)wgt;
-                    if (wgt > 0.f) y_last = e;
-                    if (y < 0 && run > t) y = e;
-                }
-                if (mine) tokens[r] = first + (y < 0 ? y_last : y);
-            }
-            found = found || hit != 0;
-#pragma unroll
-            for (int e = 0; e < kVec; ++e) if (x[v * kVec + e] > 0.f) last_positive = first + e;
-        }
-    // rounding pushed t to the end: the last token with weight (none in the row: token 0)
-    if (__any(!found)) {
-#pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1) last_positive = max(last_positive, __shfl_xor(last_positive, off, kWave));
-        if (!found && l == 0 && mine) tokens[r] = last_positive < 0 ? 0 : last_positive;
-    }
+    const int y = draw_in_group<G, kNV, kVec>([&](int j) { return x[j]; }, nv, u);
+    if (l == 0 && mine) tokens[r] = y;
 }
 
 // Rows of a handful of logits (the toy models of Sec. 2): one thread per row; the row's three readings after the first

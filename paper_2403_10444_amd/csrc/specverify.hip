@@ -161,12 +161,48 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
 // Whether a sequence's 2 gamma + 1 rows fit the LDS of one workgroup.
 bool tiny_ok(int gamma, int V) { return (size_t)(2 * gamma + 1) * (size_t)V <= (size_t)kTinyMaxFloats; }
 
+// The kernel that keeps a sequence's rows in the registers of one workgroup, and its launch; none where the rows or their
+// groups are too many.  As few logits per lane as the row allows: fewer registers, shorter chains (8192 sequences of 4 over
+// 1000 bf16 logits: 58 us with sixteen per lane, 105 with 32).  Rows of 129 ... 512 logits have a wave each while a
+// workgroup's sixteen waves are enough (8192 sequences of 4 over 300: 42 us) and share one in four beyond (of 16 over 300, float32:
+// 131 us against 177 with a wave each).  Four sequences share a workgroup where a wave holds a whole one (8192 toy
+// sequences: 12.4 us against 13.1 with a workgroup each).
+struct SmallLaunch {
+    void (*kernel)(const FusedParams);
+    unsigned blocks, threads;
+};
+template <typename T, int G, int LANE>
+SmallLaunch small_launch_of(int B, int gamma)
+{
+    const int threads = ((gamma + 1) * G + kWave - 1) / kWave * kWave;           // a group per row pair and one for the last target row
+    if constexpr (G == 4) {
+        if (threads == kWave) return {small_verify_kernel<T, G, LANE, 4, false>, (unsigned)((B - 1) / 4 + 1), 4 * kWave};
+    } else {
+        if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, 1, true>, (unsigned)B, kTinyThreads};
+    }
+    if (threads > kTinyThreads) return {nullptr, 0, 0};
+    return {small_verify_kernel<T, G, LANE, 1, false>, (unsigned)B, (unsigned)threads};
+}
+template <typename T>
+SmallLaunch small_launch(int B, int gamma, int V)
+{
+    if (V <= 4 * 8) return small_launch_of<T, 4, 8>(B, gamma);
+    if (V <= 16 * 8) return small_launch_of<T, 16, 8>(B, gamma);
+    if (V <= 64 * 8 && gamma < kTinyWaves) return small_launch_of<T, 64, 8>(B, gamma);
+    if (V <= 16 * 32) return small_launch_of<T, 16, 32>(B, gamma);
+    if (V <= 64 * 16) return small_launch_of<T, 64, 16>(B, gamma);
+    if (V <= 64 * 32 && (tiny_ok(gamma, V) || B > kSmallMinWide)) return small_launch_of<T, 64, 32>(B, gamma);
+    return {nullptr, 0, 0};
+}
+
+// One workgroup per sequence (SV_ERR_UNSUPPORTED: the sequence does not fit one).
 template <typename T>
 sv_status_t launch_tiny(int algo, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
                         size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd,
                         char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
-    if (!tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
+    const SmallLaunch small = small_launch<T>(B, gamma, V);
+    if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     FusedParams P = {};
     P.target = target; P.draft = draft; P.tokens = tokens; P.draft_lens = draft_lens; P.uniforms = uniforms;
     P.B = B; P.gamma = gamma; P.V = V; P.tstride = tstride; P.dstride = dstride;
@@ -178,7 +214,8 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
 #ifdef SV_PROFILE
     P.prof = g_prof.load();
 #endif
-    tiny_verify_kernel<T><<<(unsigned)B, kTinyThreads, 0, stream>>>(P);
+    if (small.kernel) small.kernel<<<small.blocks, small.threads, 0, stream>>>(P);
+    else tiny_verify_kernel<T><<<(unsigned)B, kTinyThreads, 0, stream>>>(P);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
@@ -339,12 +376,14 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
     }
     const int path = g_path.load();
     if (path == 2 && !L.fused_ok) return SV_ERR_UNSUPPORTED;
-    // sequences small enough for one workgroup each need nothing between workgroups
-    if (path == 5 || (path == 0 && tiny_ok(gamma, V))) {
-        g_last_kernel.store(SV_KERNEL_TINY);
-        return dtype == SV_DTYPE_F32
+    // sequences small enough for one workgroup each need nothing between workgroups (the testing hook asks for those of
+    // them that fit LDS)
+    if (path == 5 && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
+    if (path == 5 || path == 0) {
+        const sv_status_t st = dtype == SV_DTYPE_F32
             ? launch_tiny<float>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, ws, accept_len, next_token, debug_out, stream)
             : launch_tiny<bf16_t>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, ws, accept_len, next_token, debug_out, stream);
+        if (st != SV_ERR_UNSUPPORTED) { g_last_kernel.store(SV_KERNEL_TINY); return st; }
     }
 
 #define SV_ARGS algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L, ws, \

@@ -278,4 +278,215 @@ void tiny_verify_kernel(const FusedParams P)
     SV_STAMP(8);
 }
 
+// ------------------------------------------------------------------ sequences whose rows fit a group of lanes
+// The same for rows of at most 2048 logits, in registers: a row pair belongs to G lanes with at most LANE logits of each
+// row per lane, a sequence's row pairs (and its last target row) to neighbouring groups of one workgroup.  The rows'
+// exponentials never leave the registers between the sweeps: a call is one trip to memory for the rows, with the drafted
+// tokens' logits coming in under the first sweep.  Everything that exists once per position - normalisers, ratios,
+// weights, row factors, tests, all in double - is the first wave's, one position per lane; the other waves only sweep.
+// What bounds it: for a few sequences that chain of steps, for many the vector instructions.  Against one workgroup of
+// sixteen waves and 61 KB of LDS per sequence (above): one sequence, gamma = 4, V = 1000, float32 8.4 -> 6.2 us, 8192 of
+// them 152 -> 66; 8192 toy sequences, gamma = 10, V = 2, 126 -> 12.6.  Against the fused kernel, whose wave chunks such rows
+// fill by half: 8192 sequences, gamma = 10, V = 1000, bf16 544 -> 123; 1024, V = 2000 74 -> 39.
+// Rows of 1025 ... 2048 logits that do not fit LDS: from more than how many sequences on (below, the kernel for calls of
+// few resident sets spreads a sequence over several compute units: gamma = 10, V = 2000, this kernel / that one: 1 sequence
+// of bf16 10.3 / 10.0 us, 64 of float32 14.5 / 13.4; 100 of bf16 11.6 here against 12.7 for 64 there)
+constexpr int kSmallMinWide = 64;
+
+// SEQS: sequences per workgroup, 1, or 4 where a sequence's groups fit one wave (then nothing crosses waves).
+// LATE: a workgroup's groups are as many as the draft's positions, there is none for the last target row; where every
+// token of a full draft is accepted the row is read when that is known.
+template <int SEQS> __device__ __forceinline__ void sequence_barrier()
+{
+    if constexpr (SEQS == 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+template <typename T, int G, int LANE, int SEQS, bool LATE>
+__global__ __launch_bounds__(SEQS == 1 ? kTinyThreads : SEQS * kWave)
+void small_verify_kernel(const FusedParams P)
+{
+    constexpr int kPositions = SEQS == 1 ? SV_MAX_GAMMA : kWave / G;
+    constexpr int kVec = ElemTraits<T>::kVec, kNV = LANE / kVec;
+    // per row pair, as its group leaves them: the sums of both rows' exponentials, their largest scaled logits, the drafted
+    // token's two logits; the second sweep's factor as the first wave forms it; the sum of the residual terms
+    __shared__ struct {
+        double sum_p[kPositions], sum_q[kPositions], mass[kPositions];
+        float max_p[kPositions], max_q[kPositions], tok_p[kPositions], tok_q[kPositions], factor[kPositions];
+        int tau, residual;                          // whether the draw is from the residual of row tau
+    } shared[SEQS];
+    const int in_block = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, l = lane & (G - 1);
+    const int wave = SEQS == 1 ? in_block : 0, tid = wave * kWave + lane;       // within the sequence
+    const int b = SEQS == 1 ? (int)blockIdx.x : (int)blockIdx.x * SEQS + in_block;
+    if (SEQS > 1 && b >= P.B) return;
+    auto &own = shared[SEQS == 1 ? 0 : in_block];
+    const int gamma = P.gamma, V = P.V, algo = P.algo;
+    const float k = P.k;
+    int gb = gamma;
+    if (P.draft_lens) { gb = load_uniform(P.draft_lens + b); gb = gb < 1 ? 1 : gb > gamma ? gamma : gb; }
+    const size_t seq_d = (size_t)b * gamma, seq_u = (size_t)b * (gamma + 1);
+    // the group's row: row pair i, the last target row (i == gb), or nothing (the groups beyond)
+    const int i = tid / G;
+    const bool has_a = i <= gb, pair = i < gb;
+    const T *const rowA = static_cast<const T *>(P.target) + (seq_u + (has_a ? i : gb)) * P.tstride;
+    const T *const rowB = static_cast<const T *>(P.draft) + (seq_d + (pair ? i : 0)) * P.dstride;
+    const int nv = (V - 1) / (G * kVec) + 1;                                  // vectors of a lane that reach into the row
+
+    // ---- everything that depends on the arguments only, asked for at once
+    const int tok = pair ? P.tokens[seq_d + i] : 0;
+    uint4 rawA[kNV], rawB[kNV];
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) {
+            rawA[v] = rawB[v] = make_uint4(0, 0, 0, 0);
+            if (has_a) rawA[v] = load_raw<T, false, true>(rowA, V, (v * G + l) * kVec);
+            if (pair) rawB[v] = load_raw<T, false, true>(rowB, V, (v * G + l) * kVec);
+        }
+    float eta = 0.f, eta_next = 0.f;                                          // first wave, lane j: eta_j, eta_{j+1}
+    if (wave == 0) {
+        eta = P.uniforms[seq_u + (lane < gb && lane > 0 ? lane - 1 : 0)];
+        eta_next = P.uniforms[seq_u + (lane < gb ? lane : 0)];
+    }
+    const float u = load_uniform(P.uniforms + seq_u + gb);
+    const int magic_word = load_uniform(P.header + kHdrMagic);
+    if (magic_word != P.magic) {
+        // the workspace was not initialised for this shape: this kernel needs none of it, but the contract is one
+        if (tid == 0) { P.accept_len[b] = -1; P.next_token[b] = -1; }
+        return;
+    }
+    const float ya = logit_as_float(rowA + tok), yb = logit_as_float(rowB + tok);
+
+    // ---- first sweep: exponentials against an integer shift per row, their sums in double
+    float xa[LANE], xb[LANE];
+    auto sweep = [&](uint4 (&raw)[kNV], bool there, float (&x)[LANE], float &M) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < kNV; ++v)
+            if (v < nv) {
+                // (only a row's last vectors reach beyond it)
+                if (v + 1 < nv) unpack_vec<T>(raw[v], x + v * kVec);
+                else unpack_raw<T, false>(raw[v], V, (v * G + l) * kVec, x + v * kVec);
+#pragma unroll
+                for (int e = 0; e < kVec; ++e) m = fmaxf(m, x[v * kVec + e]);
+            }
+        M = group_max<G>(m * k);
+        const float shift = shift_of(M);
+        double acc = 0.0;
+#pragma unroll
+        for (int v = 0; v < kNV; ++v)
+            if (v < nv) {
+#pragma unroll
+                for (int e = 0; e < kVec; ++e) {
+                    float &y = x[v * kVec + e];
+                    y = there ? fast_exp2(__builtin_fmaf(y, k, -shift)) : 0.f;
+                    acc += (double)y;
+                }
+            }
+        return group_sum<G>(acc);
+    };
+    {
+        float Mp, Mq;
+        const double zp = sweep(rawA, has_a, xa, Mp), zq = sweep(rawB, pair, xb, Mq);
+        if (pair && l == 0) {
+            own.sum_p[i] = zp; own.sum_q[i] = zq; own.max_p[i] = Mp; own.max_q[i] = Mq;
+            own.tok_p[i] = ya; own.tok_q[i] = yb;
+        }
+    }
+    sequence_barrier<SEQS>();
+
+    // ---- the first wave, lane j for position j: L_p, L_q, log2 r_{j+1}, log2 w_j, the second sweep's factor
+    const bool token_algo = algo == kToken;
+    u64 ratio_word = 0;
+    double lw = 0.0, lw_next = 0.0, scale = 0.0;             // log2 w_j, log2 w_{j+1}, the unit of the residual terms
+    if (wave == 0) {
+        const int j = lane < gb ? lane : 0;
+        const float Mp = own.max_p[j], Mq = own.max_q[j], sp = shift_of(Mp), sq = shift_of(Mq);
+        const double log2_zp = log2_precise(own.sum_p[j]), log2_zq = log2_precise(own.sum_q[j]);
+        // (see the large kernel for the correction by k_eps)
+        const double lp = (double)own.tok_p[j] * P.kd - ((double)sp + log2_zp + P.k_eps * (double)Mp);
+        const double lq = (double)own.tok_q[j] * P.kd - ((double)sq + log2_zq + P.k_eps * (double)Mq);
+        const double lr = fmax(lp - lq, kLog2RatioFloor);
+        ratio_word = pack_ratio(lr, token_algo && (double)eta_next < exp2_precise(fmin(lr, 0.0)));
+        lw_next = weights_from_ratios(algo, ratio_word, gb);
+        lw = __shfl_up(lw_next, 1, kWave);
+        // (the residual of token verification is p - q; Alg. 4: w stays finite)
+        if (lane == 0 || token_algo) lw = 0.0;
+        if (algo == kGreedy) { lw = fmin(lw, 100.0); lw_next = fmin(lw_next, 100.0); }
+        const TinyCoef c = tiny_coef(lw - log2_zp, -log2_zq);
+        scale = c.scale;
+        if (lane < gb) own.factor[lane] = c.q_units ? c.f : -c.f;
+    }
+    sequence_barrier<SEQS>();
+
+    // ---- S_i = sum_x max(w_i p_i(x) - q_i(x), 0), in units of the larger row factor
+    const float f = pair ? own.factor[i] : 0.f;
+    const bool q_units = !(f < 0.f);
+    auto term = [&](int n) {
+        return q_units ? __builtin_amdgcn_fmed3f(__builtin_fmaf(xa[n], f, -xb[n]), 0.f, 1.f)
+                       : __builtin_amdgcn_fmed3f(__builtin_fmaf(xb[n], f, xa[n]), 0.f, 1.f);
+    };
+    double acc = 0.0;
+#pragma unroll
+    for (int v = 0; v < kNV; ++v)
+        if (v < nv) {
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) acc += (double)term(v * kVec + e);
+        }
+    acc = group_sum<G>(acc);
+    if (pair && l == 0) own.mass[i] = acc;
+    sequence_barrier<SEQS>();
+
+    // ---- the first wave again: the accept tests, tau
+    if (wave == 0) {
+        const double S = (lane < gb ? own.mass[lane] : 0.0) * scale;
+        // Alg. 2 / 4, lane j judges position j >= 1: eta_j < h_j = S_j / (S_j + 1 - w_j), 1 where w_j >= 1 (see AcceptTest),
+        // without the division; the last position, by lane gb - 1: eta_gb < w_gb.  Alg. 1: the tests came with the ratios
+        const double one_minus_w = one_minus_exp2(fmin(lw, 0.0));
+        u64 tests = __ballot(token_algo ? lane < gb && ratio_passes(ratio_word)
+                                        : lane > 0 && lane < gb && (lw >= 0.0 || (double)eta * (S + one_minus_w) < S));
+        int tau;
+        if (token_algo) {
+            tau = __ffsll((long long)~tests) - 1;                                    // leading run of passes
+            if (tau < 0 || tau > gb) tau = gb;
+        } else {
+            const bool last = lane == gb - 1 && (lw_next >= 0.0 || (double)eta_next < exp2_precise(lw_next));
+            tau = __any(last) ? gb : tests ? 63 - __clzll((long long)tests) : 0;     // last passing sub-block
+        }
+        if (P.debug_out && lane < gb) {
+            const double next_h = exp2_precise(fmin(token_algo ? unpack_ratio(ratio_word) : lw_next, 0.0));
+            const double h = lane == 0 || lw >= 0.0 ? 1.0 : S / (S + one_minus_w);
+            float *d = P.debug_out + (seq_u + lane) * 3;
+            d[0] = (float)exp2_precise(lw); d[1] = (float)S;
+            if (!token_algo || lane == 0) d[2] = (float)h;
+            // (Alg. 1 has no w; its h_i = min(r_i, 1).  S_gamma = w_gamma: q_gamma == 0)
+            if (token_algo) d[5] = (float)next_h;
+            if (lane == gb - 1) {
+                d[3] = d[4] = token_algo ? 1.f : (float)exp2_precise(lw_next);
+                d[5] = (float)next_h;
+            }
+        }
+        if (lane == 0) own.tau = tau;
+        if (lane == (tau < gb ? tau : 0)) own.residual = tau < gb && S > 0.0;          // (a residual without mass: Y comes from p_tau)
+    }
+    sequence_barrier<SEQS>();
+    // ---- Y, by the wave that holds row tau
+    const int tau = __builtin_amdgcn_readfirstlane(own.tau);
+    const bool late = LATE && tau == (int)blockDim.x / G;
+    if ((late ? 0 : tau / (kWave / G)) != wave) return;
+    if (late) {
+#pragma unroll
+        for (int v = 0; v < kNV; ++v)
+            if (v < nv) rawA[v] = load_raw<T, false, true>(static_cast<const T *>(P.target) + (seq_u + gb) * P.tstride, V, (v * G + l) * kVec);
+        float M;
+        sweep(rawA, true, xa, M);
+    }
+    const bool residual = own.residual != 0;
+    const int y = draw_in_group<G, kNV, kVec>([&](int n) { return residual ? term(n) : xa[n]; }, nv, u);
+    if ((late ? tid == 0 : i == tau && l == 0)) { P.accept_len[b] = tau; P.next_token[b] = y; }
+}
+
 }  // namespace sv

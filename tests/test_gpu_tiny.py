@@ -192,3 +192,33 @@ def test_workspace_must_be_initialised_for_the_shape():
                                   workspace=ws)
     torch.cuda.synchronize()
     assert bool((tau == -1).all()) and bool((y == -1).all())
+
+
+# ---- rows in the registers of groups of lanes: every group size and register count at its edges, drafts that fill a wave or
+# the workgroup (the last target row then has no group of its own), sequences that leave a shared workgroup partly empty,
+# draft lengths, padded and unaligned rows.  (The library's own choice: path 0.)
+EDGES = [
+    # B, gamma, V, dtype
+    (5, 10, 2, "f32"), (6, 15, 32, "bf16"), (7, 16, 32, "f32"), (3, 64, 3, "bf16"),
+    (5, 3, 33, "f32"), (9, 8, 128, "bf16"), (2, 63, 100, "f32"), (2, 64, 128, "bf16"),
+    (5, 15, 129, "bf16"), (4, 16, 300, "f32"), (3, 4, 512, "f32"), (2, 64, 512, "f32"),
+    (6, 4, 513, "bf16"), (5, 15, 1000, "f32"), (4, 16, 1024, "bf16"), (3, 16, 1023, "f32"),
+    (5, 3, 2048, "f32"), (70, 8, 1025, "bf16"), (66, 15, 2047, "f32"), (65, 16, 2048, "bf16"), (66, 16, 2041, "f32"),
+]
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", EDGES)
+def test_groups_of_lanes_at_their_edges(B, gamma, V, dtype, algo):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"groups_B{B}_g{gamma}_V{V}_{dtype}", B, gamma, V, dtype, 2.0, 0.5, 0.9, False, 1)
+    for n, (lens, pad_t, pad_d) in enumerate([(False, 0, 0), (True, 3, 8)]):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, False)
+        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_TINY
+    # the same distributions: everything is accepted, the token comes from the last target row
+    sv.spec_verify_debug_config(0, -1)
+    inp = workloads.generate(cfg, seed=V + gamma, device=DEV)
+    inp["draft_logits"] = inp["target_logits"][:, :gamma].contiguous()
+    got = parity.run_gpu(algo, inp, 0.9)
+    assert np.all(got["accept_len"] == gamma)
+    parity.compare(got, parity.run_oracle(algo, inp, 0.9), label=f"{cfg.name}/{algo}/identical", greedy=algo == "greedy")
