@@ -468,10 +468,10 @@ template <int G> __device__ __forceinline__ double group_scan(double v)
 }
 // The draw from weights that a group holds in registers: weight(j), j = v * KVEC + e, is the lane's weight of token
 // (v * G + lane in the group) * KVEC + e, v < nv.  The first token whose running sum (in double, in vocabulary order:
-// vector, lane, element) exceeds u * total; where rounding leaves none, the last with weight, and 0 if none has any.
-// Every lane of the group gets it.
-template <int G, int NV, int KVEC, typename F>
-__device__ __forceinline__ int draw_in_group(F weight, int nv, float u)
+// vector, lane, element) exceeds `threshold` (of the weights' total); where rounding leaves none, the last with weight, and
+// 0 if none has any.  Every lane of the group gets it.
+template <int G, int NV, int KVEC, typename F, typename Threshold>
+__device__ __forceinline__ int draw_in_group(F weight, int nv, Threshold threshold)
 {
     const int lane = threadIdx.x & 63, l = lane & (G - 1);
     double before[NV], mass[NV], total = 0.0;                // per vector: the weights in front of the lane's, and the lane's
@@ -486,7 +486,7 @@ __device__ __forceinline__ int draw_in_group(F weight, int nv, float u)
             mass[v] = s;
             total += G == kWave ? read_lane_double(inc, kWave - 1) : __shfl(inc, lane | (G - 1), kWave);
         }
-    const double t = (double)u * total;
+    const double t = threshold(total);
     const u64 group_bits = G == kWave ? ~0ull : ((1ull << (G & 63)) - 1ull) << (lane & ~(G - 1));
     int y = -1, owner = -1, last_positive = -1;
 #pragma unroll

@@ -3,22 +3,27 @@
 // w_i of Alg. 2 needs only the two gathered probabilities of each earlier drafted token, so every
 // element is read from HBM exactly once and no workgroup waits for another:
 //
-//   1. probs_weights_kernel   one wave per sequence: the ratios r_i of the drafted tokens and the
-//                             recursion w_i = min(w_{i-1} r_i, 1) (in double, in the log domain)
-//   2. probs_residual_kernel  one workgroup per (sequence, position, chunk of kChunk tokens): the
+//   1. probs_residual_kernel  one workgroup per (sequence, position, chunk of kChunk tokens): the position's weight from
+//                             the ratios r_1 .. r_i of the drafted tokens and the recursion w_i = min(w_{i-1} r_i, 1) (in
+//                             double, in the log domain), by its first wave under the workgroup's loads; then the
 //                             chunk's share of S_i = sum_x max(w_i p_i(x) - q_i(x), 0)
 //                             (numerator of the block acceptance formula; for greedy block verification,
 //                             Alg. 4, also the rejected mass sum_x max(q_i - w_i p_i, 0)); at the
 //                             sequence's last position the chunk's share of sum_x p(x)
-//   3. probs_finalize_kernel  one workgroup per sequence: S_i, h_i, the accept tests of Alg. 1 / 2 / 4,
+//   2. probs_finalize_kernel  one workgroup per sequence: S_i, h_i, the accept tests of Alg. 1 / 2 / 4,
 //                             then the inverse-CDF draw of Y (pick the chunk from the partial sums,
 //                             re-read that one chunk)
+// (In some calls the weights come from a kernel in front, probs_weights_kernel, one wave per sequence.)
+// What bounds it: the bytes, then the second launch.  B = 64, gamma = 8, V = 128256, bf16: 42.2 us (6.6 TB/s) for the first
+// kernel, 7.0 for the second, which took 10.7 while its threads read the chunk in stretches of 64 bytes each (uncoalesced)
+// and scanned all of it; now each wave reads a quarter, and the one that holds the token draws from its registers.
 #pragma once
 
 #include "fused.hpp"
 
 namespace sv {
 
+constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: up to how many each workgroup forms its position's weight
 constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the finishing kernel keeps in LDS (32 KB)
 
 struct ProbWeight {
@@ -29,11 +34,11 @@ struct ProbWeight {
     int needed;          // whether the sums over rows i can matter (see probs_weights_kernel); where not, none are formed
 };
 
-// kVec consecutive probabilities of a row; elements at or beyond V count as 0
+// kVec consecutive probabilities of a row from the vector as loaded (load_raw); elements at or beyond V count as 0
 template <typename T, bool ALIGNED>
-__device__ __forceinline__ void load_probs(const T *row, int V, int idx, float *out)
+__device__ __forceinline__ void unpack_probs(const uint4 &raw, int V, int idx, float *out)
 {
-    load_vec<T, ALIGNED>(row, V, idx, out);
+    unpack_raw<T, ALIGNED>(raw, V, idx, out);
 #pragma unroll
     for (int e = 0; e < ElemTraits<T>::kVec; ++e) out[e] = fmaxf(out[e], 0.f);
 }
@@ -52,43 +57,32 @@ __device__ __forceinline__ int clamped_draft_len(const int32_t *draft_lens, int 
     return g < 1 ? 1 : g > gamma ? gamma : g;
 }
 
-// w_0 = 1, w_i = min(w_{i-1} r_i, 1) (Alg. 2; Alg. 4 omits the min), r_i = p_{i-1}(X_i) / q_{i-1}(X_i).
-// One wave per sequence: lane j gathers the two probabilities of drafted token j + 1, every lane runs
-// the recursion up to the position it carries in log2 (products of ratios neither overflow nor lose 1 - w_i
-// next to 1), lane i writes the constants of position i.
+constexpr ProbWeight kFirstWeight = {1.0, 0.0, 1.0, 1.f, 0.f, 1};      // position 0: w_0 = 1; tau = 0 draws from the residual of rows 0
+
+// w_0 = 1, w_i = min(w_{i-1} r_i, 1) (Alg. 2; Alg. 4 omits the min), r_i = p_{i-1}(X_i) / q_{i-1}(X_i), for positions
+// 1 .. n of a sequence of draft length gb, by one wave: lane j comes with drafted token j + 1 (and its uniform), gathers its
+// two probabilities, runs the recursion up to position j + 1 in log2 (products of ratios neither overflow nor lose
+// 1 - w_i next to 1), and gets that position's constants.
 template <typename T>
-__global__ __launch_bounds__(64) void probs_weights_kernel(
-    const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
-    const int32_t *__restrict__ tokens, const int32_t *__restrict__ draft_lens, int gamma, int algo,
-    ProbWeight *__restrict__ weights, const float *__restrict__ uniforms, int every_sum)
+__device__ __forceinline__ ProbWeight form_weights(const T *target_seq, const T *draft_seq, size_t tstride, size_t dstride, int tok, float eta,
+                                                   int n, int gb, int algo, bool every_sum)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int gb = clamped_draft_len(draft_lens, b, gamma);
+    const int lane = threadIdx.x & 63, i = lane + 1;
     double mine = 0.0;
-    if (lane < gb) {
-        const int tok = tokens[(size_t)b * gamma + lane];
-        const double lp = log2(logit_as_double(target + ((size_t)b * (gamma + 1) + lane) * tstride + tok));
-        const double lq = log2(logit_as_double(draft + ((size_t)b * gamma + lane) * dstride + tok));
+    if (lane < n) {
+        const double lp = log2(logit_as_double(target_seq + (size_t)lane * tstride + tok));
+        const double lq = log2(logit_as_double(draft_seq + (size_t)lane * dstride + tok));
         mine = fmax(lp - lq, kLog2RatioFloor);     // a drafted token outside the target's support: r = 0, kept finite
     }
-    // lane l carries position l + 1 (positions 1 .. gb <= SV_MAX_GAMMA = 64); position 0 is w_0 = 1
     double log2w = 0.0, log2r = 0.0;
-    for (int j = 0; j < gb; ++j) {
-        const double r = __shfl(mine, j, 64);
+    for (int j = 0; j < n; ++j) {
+        const double r = read_lane_double(mine, j);
         if (j <= lane) {
             log2r = r;
             log2w += r;
             if (algo != kGreedy && log2w > 0.0) log2w = 0.0;
         }
     }
-    ProbWeight *wb = weights + (size_t)b * (gamma + 1);
-    if (lane == 0) {
-        ProbWeight first;
-        first.w = 1.0; first.one_minus_w = 0.0; first.h_token = 1.0; first.w_hi = 1.f; first.w_lo = 0.f;
-        first.needed = 1;                                  // tau = 0 draws from the residual of rows 0
-        wb[0] = first;
-    }
-    const int i = lane + 1;
     const double w_block = exp2(log2w);
     if (algo == kToken) log2w = 0.0;
     ProbWeight pw;
@@ -101,88 +95,137 @@ __global__ __launch_bounds__(64) void probs_weights_kernel(
     // position that every earlier test let through can become tau; the last target row is summed (and drawn
     // from) only if tau = gamma: every test passed (Alg. 1), or the last one did (Alg. 2 / 4: eta < w_gamma).
     // The tests are evaluated with the expressions the finishing kernel uses, on the same stored values.
-    const float eta_i = i <= gb ? uniforms[(size_t)b * (gamma + 1) + i - 1] : 1.f;
-    const unsigned long long failed = __ballot(i <= gb && !((double)eta_i < pw.h_token));
+    const unsigned long long failed = __ballot(i <= n && !((double)eta < pw.h_token));
     const bool prefix_pass = (failed & ((2ull << lane) - 1ull)) == 0;     // tests 1 .. i
-    if (i > gb) return;
     if (every_sum) pw.needed = 1;
     else if (algo == kToken) pw.needed = prefix_pass ? 1 : 0;
-    else pw.needed = (i < gb || (double)eta_i < fmin(w_block, 1.0)) ? 1 : 0;
-    wb[i] = pw;
+    else pw.needed = (i < gb || (double)eta < fmin(w_block, 1.0)) ? 1 : 0;
+    return pw;
 }
 
-template <typename T, bool ALIGNED, bool GREEDY>
+// One wave per sequence: the constants of all its positions.
+template <typename T>
+__global__ __launch_bounds__(64) void probs_weights_kernel(
+    const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
+    const int32_t *__restrict__ tokens, const int32_t *__restrict__ draft_lens, int gamma, int algo,
+    ProbWeight *__restrict__ weights, const float *__restrict__ uniforms, int every_sum)
+{
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int gb = clamped_draft_len(draft_lens, b, gamma);
+    const int tok = lane < gb ? tokens[(size_t)b * gamma + lane] : 0;
+    const float eta = lane < gb ? uniforms[(size_t)b * (gamma + 1) + lane] : 1.f;
+    const ProbWeight pw = form_weights(target + (size_t)b * (gamma + 1) * tstride, draft + (size_t)b * gamma * dstride, tstride, dstride,
+                                       tok, eta, gb, gb, algo, every_sum != 0);
+    ProbWeight *wb = weights + (size_t)b * (gamma + 1);
+    if (lane == 0) wb[0] = kFirstWeight;
+    if (lane < gb) wb[lane + 1] = pw;
+}
+
+// FORM: the workgroup forms its position's weight itself, under its loads; a sequence's chunk-0 workgroups leave them for
+// the finishing kernel.  (Without: they come from probs_weights_kernel.)
+template <typename T, bool ALIGNED, bool GREEDY, bool FORM>
 __global__ __launch_bounds__(kThreads) void probs_residual_kernel(
     const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
-    const int32_t *__restrict__ draft_lens,
-    int gamma, int V, int nchunks, float2 *__restrict__ part, const ProbWeight *__restrict__ weights)
+    const int32_t *__restrict__ tokens, const int32_t *__restrict__ draft_lens, const float *__restrict__ uniforms,
+    int gamma, int V, int nchunks, int algo, int every_sum, float2 *__restrict__ part, ProbWeight *__restrict__ weights)
 {
     constexpr int kVec = ElemTraits<T>::kVec;
     constexpr int kU = kChunk / (kThreads * kVec);
     __shared__ float lds[kWaves];
+    __shared__ ProbWeight formed;
     const int pr = blockIdx.x / nchunks, c = blockIdx.x - pr * nchunks, tid = threadIdx.x;
     const int b = pr / (gamma + 1), i = pr - b * (gamma + 1);
     const int gb = clamped_draft_len(draft_lens, b, gamma);
     if (i > gb) return;                                          // a position this sequence does not use
-    if (!weights[pr].needed) return;                             // sums that cannot matter (whole workgroup)
+    if (!FORM && !weights[pr].needed) return;                    // sums that cannot matter (whole workgroup)
     const T *target_seq = target + (size_t)b * (gamma + 1) * tstride;
     const T *draft_seq = draft + (size_t)b * gamma * dstride;
     const T *prow = target_seq + (size_t)i * tstride;
     const bool last = i == gb;                                   // no draft row: q == 0
     const T *qrow = draft_seq + (size_t)(last ? 0 : i) * dstride;
-    const float w_hi = weights[pr].w_hi, w_lo = weights[pr].w_lo;
 
-    float xp[kU][kVec], xq[kU][kVec];
+    uint4 rp[kU], rq[kU];
+    const int in_row = V - c * kChunk;                           // (short rows: vectors beyond the row are left out, for the whole workgroup)
+    auto load = [&]() {
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const int idx = c * kChunk + (u * kThreads + tid) * kVec;
-        load_probs<T, ALIGNED>(prow, V, idx, xp[u]);
-        if (!last) load_probs<T, ALIGNED>(qrow, V, idx, xq[u]);
+        for (int u = 0; u < kU; ++u) {
+            if (u * kThreads * kVec >= in_row) continue;
+            const int idx = c * kChunk + (u * kThreads + tid) * kVec;
+            rp[u] = load_raw<T, ALIGNED, true>(prow, V, idx);
+            if (!last) rq[u] = load_raw<T, ALIGNED, true>(qrow, V, idx);
+        }
+    };
+    if constexpr (FORM) {
+        // (the drafted tokens are asked for in front of the rows, so that their probabilities follow under the rows' loads;
+        // a last target row, which is needed only where the last test passes, waits for its weight)
+        const bool at_once = !last || every_sum;
+        const bool forms = tid < kWave && i > 0;
+        int tok = 0;
+        float eta = 1.f;
+        if (forms && tid < i) { tok = tokens[(size_t)b * gamma + tid]; eta = uniforms[(size_t)b * (gamma + 1) + tid]; }
+        if (at_once) load();
+        if (forms) {
+            const ProbWeight pw = form_weights(target_seq, draft_seq, tstride, dstride, tok, eta, i, gb, algo, every_sum != 0);
+            if (tid == i - 1) { formed = pw; if (c == 0) weights[pr] = pw; }
+        } else if (tid == 0) {
+            formed = kFirstWeight;
+            if (c == 0) weights[pr] = kFirstWeight;
+        }
+        __syncthreads();
+        if (!formed.needed) return;
+        if (!at_once) load();
+    } else {
+        load();
     }
+    const float w_hi = FORM ? formed.w_hi : weights[pr].w_hi, w_lo = FORM ? formed.w_lo : weights[pr].w_lo;
 
     float acc = 0.f, rej = 0.f;
-    if (last) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
+    for (int u = 0; u < kU; ++u) {
+        if (u * kThreads * kVec >= in_row) continue;
+        const int idx = c * kChunk + (u * kThreads + tid) * kVec;
+        float xp[kVec], xq[kVec];
+        unpack_probs<T, ALIGNED>(rp[u], V, idx, xp);
+        if (last) {
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) acc += xp[u][e];
-    } else {
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
+            for (int e = 0; e < kVec; ++e) acc += xp[e];
+        } else {
+            unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
 #pragma unroll
             for (int e = 0; e < kVec; ++e) {
-                const float d = prob_residual(xp[u][e], xq[u][e], w_hi, w_lo);
+                const float d = prob_residual(xp[e], xq[e], w_hi, w_lo);
                 acc += fmaxf(d, 0.f);
                 if constexpr (GREEDY) rej += fmaxf(-d, 0.f);
             }
+        }
     }
     acc = block_sum(acc, lds);
     if constexpr (GREEDY) rej = block_sum(rej, lds);
     if (tid == 0) part[(size_t)pr * nchunks + c] = make_float2(acc, rej);
 }
 
-// The workgroup's sum of the weights of chunk c of a row pair, thread t owning the kPerThread
-// consecutive tokens from c * kChunk + t * kPerThread; every thread receives its own sum.
+// The weights of a wave's kWaveChunk consecutive tokens of a row pair from `start` on, in its registers: element
+// v * kVec + e of a lane is token start + (v * 64 + lane) * kVec + e (every load instruction covers 1 KB).
 template <typename T, bool ALIGNED>
-__device__ __forceinline__ float prob_thread_weights(const T *prow, const T *qrow, int V, int c, bool residual,
-                                                     float w_hi, float w_lo, float *wgt)
+__device__ __forceinline__ void prob_wave_weights(const T *prow, const T *qrow, int V, int start, bool residual,
+                                                  float w_hi, float w_lo, float (&wgt)[kPerThread])
 {
-    constexpr int kVec = ElemTraits<T>::kVec;
-    const int start = c * kChunk + (int)threadIdx.x * kPerThread;
-    float mine = 0.f;
+    constexpr int kVec = ElemTraits<T>::kVec, kNV = kPerThread / kVec;
+    const int first = start + (int)(threadIdx.x & 63) * kVec;
+    uint4 rp[kNV], rq[kNV];
 #pragma unroll
-    for (int v = 0; v < kPerThread / kVec; ++v) {
-        float xp[kVec], xq[kVec];
-        load_probs<T, ALIGNED>(prow, V, start + v * kVec, xp);
-        if (residual) load_probs<T, ALIGNED>(qrow, V, start + v * kVec, xq);
-#pragma unroll
-        for (int e = 0; e < kVec; ++e) {
-            const float g = residual ? fmaxf(prob_residual(xp[e], xq[e], w_hi, w_lo), 0.f) : xp[e];
-            wgt[v * kVec + e] = g;
-            mine += g;
-        }
+    for (int v = 0; v < kNV; ++v) {
+        rp[v] = load_raw<T, ALIGNED, false>(prow, V, first + v * kWave * kVec);
+        if (residual) rq[v] = load_raw<T, ALIGNED, false>(qrow, V, first + v * kWave * kVec);
     }
-    return mine;
+#pragma unroll
+    for (int v = 0; v < kNV; ++v) {
+        float xp[kVec], xq[kVec];
+        unpack_probs<T, ALIGNED>(rp[v], V, first + v * kWave * kVec, xp);
+        if (residual) unpack_probs<T, ALIGNED>(rq[v], V, first + v * kWave * kVec, xq);
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) wgt[v * kVec + e] = residual ? fmaxf(prob_residual(xp[e], xq[e], w_hi, w_lo), 0.f) : xp[e];
+    }
 }
 
 // Sums and inclusive sums over the lanes of a wave in double, through DPP (fixed orders).
@@ -203,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
 {
     extern __shared__ double smd[];                     // [gamma+1] S_i, [gamma+1] rejected mass, then the kept partial sums
     __shared__ double wave_tot[kWaves];
-    __shared__ int s_tau, s_chunk, s_mode, s_winner, wave_cand[kWaves];
+    __shared__ int s_tau, s_chunk, s_mode;
     __shared__ double s_t, s_total;
     double *S = smd, *R = smd + (gamma + 1);
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -300,29 +343,30 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
     if (residual) { w_hi = wb[tau].w_hi; w_lo = wb[tau].w_lo; }
     float wgt[kPerThread];
 
-    // the workgroup's chunk c: every thread's own sum, the sum of the threads before it, the chunk's total
-    auto scan_chunk = [&](int c, bool res, float &mine, double &below, double &total) {
-        mine = prob_thread_weights<T, ALIGNED>(prow, qrow, V, c, res, w_hi, w_lo, wgt);
-        const double inc = wave_inclusive_scan_double((double)mine);
-        __syncthreads();
-        if (lane == 63) wave_tot[wave] = inc;
-        __syncthreads();
-        double base = 0.0, tot = 0.0;
+    // the workgroup's chunk c, a quarter per wave: the sum of the waves before the thread's own, the chunk's
+    auto sum_chunk = [&](int c, double &before, double &total) {
+        prob_wave_weights<T, ALIGNED>(prow, qrow, V, c * kChunk + wave * kWaveChunk, residual, w_hi, w_lo, wgt);
+        double sum = 0.0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) { if (w < wave) base += wave_tot[w]; tot += wave_tot[w]; }
-        below = base + inc - (double)mine;
-        total = tot;
+        for (int e = 0; e < kPerThread; ++e) sum += (double)wgt[e];
+        sum = wave_total_double(sum);
+        __syncthreads();
+        if (lane == 0) wave_tot[wave] = sum;
+        __syncthreads();
+        before = total = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) { if (w < wave) before += wave_tot[w]; total += wave_tot[w]; }
     };
 
     if (mode == 2) {
         // chunk sums of p_tau were never formed for this row: form the row total here (rare: rounding ate a residual)
         double row_total = 0.0;
         for (int c = 0; c < nchunks; ++c) {
-            float mine; double below, total;
-            scan_chunk(c, false, mine, below, total);
+            double before, total;
+            sum_chunk(c, before, total);
             row_total += total;
         }
-        if (tid == 0) { s_total = (double)u * row_total; s_winner = -1; }
+        if (tid == 0) s_total = (double)u * row_total;
     } else if (wave == 0) {
         // pick the chunk of row tau that holds t = u * (total weight): 64 chunk sums at a time, scanned in order
         const double total = mode == 1 ? S[gb] : S[tau];
@@ -346,57 +390,45 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         if (lane == 0) {
             s_chunk = chunk < 0 ? last_nonzero : chunk;      // rounding pushed t past the end: the last chunk with weight
             s_t = t_in;
-            s_winner = -1;
         }
     }
     __syncthreads();
 
     // walk: the chosen chunk, or (mode 2) every chunk in turn until the one whose running sum passes t.
-    // Inside that chunk the token lies with the last thread whose preceding sum does not exceed t (one
-    // thread exactly, whatever the rounding of the scan); if rounding left t at or beyond the chunk's own
-    // total, that thread is the last one with weight and the token its last one with weight.
+    // Inside that chunk the token lies with the first wave whose running sum exceeds t, which then draws it from its
+    // registers; where rounding left t at or beyond the chunk's own total, with the last wave that has weight, and
+    // there it is the last token with weight (token 0 of the chunk if nothing has any).
     int c = mode == 2 ? 0 : s_chunk;
     double t_in = mode == 2 ? s_total : s_t;
-    int last_positive = -1;
-    for (;;) {
-        float mine; double below, total;
-        scan_chunk(c, residual, mine, below, total);
-        const int start = c * kChunk + tid * kPerThread;
-#pragma unroll
-        for (int e = 0; e < kPerThread; ++e)
-            if (wgt[e] > 0.f) last_positive = start + e;
-        if (mode != 2 || t_in < total || c + 1 >= nchunks) {
-            // the last thread with weight whose preceding sum does not exceed t: per wave by a ballot, then the last
-            // wave that has one (hundreds of atomic operations on one LDS word took microseconds here)
-            const unsigned long long cands = __ballot(mine > 0.f && below <= t_in);
-            if (lane == 0) wave_cand[wave] = cands ? wave * kWave + 63 - __clzll((long long)cands) : -1;
-            __syncthreads();
-            int cand = -1;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) cand = wave_cand[w] > cand ? wave_cand[w] : cand;
-            if (tid == cand) {
-                double run = below;
-                int y = -1, lastpos = 0;
-#pragma unroll
-                for (int e = 0; e < kPerThread; ++e) {
-                    run += (double)wgt[e];
-                    if (wgt[e] > 0.f) lastpos = e;
-                    if (y < 0 && run > t_in) y = e;
-                }
-                s_winner = start + (y < 0 ? lastpos : y);
-            }
+    double before, total;
+    for (int last_c = -1;;) {
+        sum_chunk(c, before, total);
+        if (mode != 2 || t_in < total) break;
+        if (total > 0.0) last_c = c;
+        if (c + 1 >= nchunks) {
+            // rounding left t beyond the row's total: the last token with weight
+            if (last_c >= 0 && last_c != c) { c = last_c; sum_chunk(c, before, total); }
+            t_in = INFINITY;
             break;
         }
         t_in -= total;
         ++c;
     }
-    __syncthreads();
-    if (s_winner < 0) {
-        // no weight at all in the chunk the walk ended in: the last token of positive weight seen before it
-        atomicMax(&s_winner, last_positive);
-        __syncthreads();
+    int holder = -1, last_weight = 0;
+    {
+        double running = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (wave_tot[w] > 0.0) last_weight = w;
+            running += wave_tot[w];
+            if (holder < 0 && running > t_in) holder = w;
+        }
     }
-    if (tid == 0) next_token[b] = s_winner < 0 ? 0 : s_winner;
+    if (wave != (holder < 0 ? last_weight : holder)) return;
+    const double t = holder < 0 ? INFINITY : t_in - before;
+    const int offset = draw_in_group<kWave, kPerThread / ElemTraits<T>::kVec, ElemTraits<T>::kVec>(
+        [&](int j) { return wgt[j]; }, kPerThread / ElemTraits<T>::kVec, [&](double) { return t; });
+    if (lane == 0) next_token[b] = c * kChunk + wave * kWaveChunk + offset;
 }
 
 }  // namespace sv

@@ -194,7 +194,7 @@ void sample_small_rows_kernel(const T *logits, int rows, int V, float k, const f
 #pragma unroll
             for (int e = 0; e < kVec; ++e) x[v * kVec + e] = fast_exp2(__builtin_fmaf(x[v * kVec + e], k, -shift));
         }
-    const int y = draw_in_group<G, kNV, kVec>([&](int j) { return x[j]; }, nv, u);
+    const int y = draw_in_group<G, kNV, kVec>([&](int j) { return x[j]; }, nv, [&](double total) { return (double)u * total; });
     if (l == 0 && mine) tokens[r] = y;
 }
 

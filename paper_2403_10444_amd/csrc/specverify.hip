@@ -130,7 +130,7 @@ sv_status_t launch_staged(int algo, const void *target_v, const void *draft_v, c
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
-// Probabilities as inputs: three launches, every element read once.  Scratch: the staged path's areas
+// Probabilities as inputs: two or three launches, every element read once.  Scratch: the staged path's areas
 // (chunk partial sums where its row statistics go, the weights where its row constants go).
 template <typename T, bool ALIGNED>
 sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, const int32_t *tokens, const int32_t *draft_lens,
@@ -143,13 +143,20 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     float2 *part = reinterpret_cast<float2 *>(ws + L.off_stats);
     ProbWeight *weights = reinterpret_cast<ProbWeight *>(ws + L.off_coef);
     const unsigned blocks = (unsigned)((size_t)B * (gamma + 1) * L.nchunks);
-    probs_weights_kernel<T><<<B, 64, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, gamma, algo, weights, uniforms, debug_out ? 1 : 0);
-    if (algo == kGreedy)
-        probs_residual_kernel<T, ALIGNED, true><<<blocks, kThreads, 0, stream>>>(
-            target, draft, tstride, dstride, draft_lens, gamma, V, L.nchunks, part, weights);
-    else
-        probs_residual_kernel<T, ALIGNED, false><<<blocks, kThreads, 0, stream>>>(
-            target, draft, tstride, dstride, draft_lens, gamma, V, L.nchunks, part, weights);
+    // A position's weight: formed by each of its workgroups under its loads (B = 64, gamma = 8, V = 128256, bf16: 58 -> 51 us,
+    // 1 sequence 18 -> 14), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
+    // (Alg. 1 unless every sum is reported: 26 us against 30 there) and where there are many of them with less to read
+    // than the weight takes to form (4096 sequences of 8 over 500 tokens: 150 us against 185, and 89 since short rows leave
+    // out the vectors beyond them).
+    const int every_sum = debug_out ? 1 : 0;
+    const bool many_short = V <= kChunk / 2 && (long long)B * (gamma + 1) > kProbsFormMax;
+    const bool in_front = (algo == kToken && !every_sum) || many_short;
+    if (in_front)
+        probs_weights_kernel<T><<<B, 64, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, gamma, algo, weights, uniforms, every_sum);
+    void (*const residual)(const T *, const T *, size_t, size_t, const int32_t *, const int32_t *, const float *, int, int, int, int, int, float2 *, ProbWeight *) =
+        algo == kGreedy ? (in_front ? probs_residual_kernel<T, ALIGNED, true, false> : probs_residual_kernel<T, ALIGNED, true, true>)
+        : in_front ? probs_residual_kernel<T, ALIGNED, false, false> : probs_residual_kernel<T, ALIGNED, false, true>;
+    residual<<<blocks, kThreads, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, uniforms, gamma, V, L.nchunks, algo, every_sum, part, weights);
     const size_t kept_floats = (size_t)(gamma + 1) * L.nchunks * (algo == kGreedy ? 2 : 1);      // chunk sums (Alg. 4: and rejected masses)
     const size_t keep = kept_floats <= (size_t)kProbsKeepMax ? kept_floats * sizeof(float) : 0;
     probs_finalize_kernel<T, ALIGNED><<<B, kThreads, 2 * (gamma + 1) * sizeof(double) + keep, stream>>>(

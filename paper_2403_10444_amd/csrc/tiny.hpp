@@ -485,7 +485,7 @@ void small_verify_kernel(const FusedParams P)
         sweep(rawA, true, xa, M);
     }
     const bool residual = own.residual != 0;
-    const int y = draw_in_group<G, kNV, kVec>([&](int n) { return residual ? term(n) : xa[n]; }, nv, u);
+    const int y = draw_in_group<G, kNV, kVec>([&](int n) { return residual ? term(n) : xa[n]; }, nv, [&](double total) { return (double)u * total; });
     if ((late ? tid == 0 : i == tau && l == 0)) { P.accept_len[b] = tau; P.next_token[b] = y; }
 }
 

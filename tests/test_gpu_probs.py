@@ -127,3 +127,24 @@ def test_probs_unnormalised_rows_are_used_as_given():
             a, b = sv.spec_verify_probs(algo, p, q, tok, uni)
             torch.cuda.synchronize()
             assert (int(a[0]), int(b[0])) == (tau, y), (algo, eta, u)
+
+
+# (where the weights are formed - by every workgroup, or by a kernel in front - and how the finishing kernel walks: the last
+# positions of long drafts, rows at the edges of a wave's quarter of a chunk, thousands of short rows on both sides of the rule)
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", [(3, 64, 2049, "f32"), (4, 5, 2048, "bf16"), (5, 3, 4097, "bf16"), (3, 2, 8193, "f32"), (4, 1, 16383, "bf16"),
+                                             (499, 3, 40, "f32"), (501, 3, 40, "bf16"), (501, 3, 4100, "bf16")])
+def test_weights_and_walk_at_their_edges(algo, B, gamma, V, dtype):
+    import paper_2403_10444_amd as sv
+    cfg = _custom(B, gamma, V, dtype, sigma_t=2.0, sigma_d=0.4, T=1.0)
+    P, Q, inp = _probs_inputs(cfg, seed=B + V)
+    inp["uniforms"][0, :] = 0.0                                       # the first tokens with weight
+    inp["uniforms"][1, gamma] = 1.0 - 2.0 ** -24                      # the last one, or next to it
+    ref = _run_oracle(algo, P, Q, inp)
+    safe = ref["margins"].min(axis=1) >= parity.MARGIN
+    assert safe[2:].all() or safe[2:].mean() > 0.99
+    got = _run_gpu(sv, algo, P, Q, inp)
+    tau, y = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"])        # (sums that cannot matter left out)
+    for key, plain in (("accept_len", tau), ("next_token", y)):
+        assert np.array_equal(got[key][safe], ref[key][safe]), key
+        assert np.array_equal(got[key], plain.cpu().numpy()), key
