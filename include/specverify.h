@@ -93,11 +93,12 @@ sv_status_t spec_verify_workspace_init(void *workspace, size_t workspace_bytes,
 sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_t gamma, int32_t V,
                                         void *stream);
 
-/* Testing hook, process-wide: `path` 0 = the library's choice by the shape of the call: sequences whose
- * 2 gamma + 1 rows fit into LDS together, (2 gamma + 1) V <= 14336: the kernel of one workgroup per
- * sequence; else, calls of at most three times the workgroups that the device keeps resident and rows
- * of at most 32 * 8192 logits: the kernel for calls of few resident sets; else the fused kernel where it
- * takes the shape, else the staged kernels.  5 = the one-workgroup-per-sequence kernel, 7 = the
+/* Testing hook, process-wide: `path` 0 = the library's choice by the shape of the call: sequences of rows of at
+ * most 2048 logits, or whose 2 gamma + 1 rows fit into LDS together, (2 gamma + 1) V <= 14336: one workgroup
+ * (or wave) per sequence; else, calls of at most a few times the workgroups that the device keeps resident
+ * (about 1 + gamma / 4 times) and rows of at most 32 * 8192 logits: the kernel for calls of few resident sets;
+ * else the fused kernel where it takes the shape, else the staged kernels.  5 = the kernels of one workgroup
+ * per sequence, as far as the sequence fits LDS; 7 = the
  * kernel for calls of few resident sets (calls beyond their limits are then refused), 1 = the
  * four-launch staged kernels, 2 = the
  * single-launch fused kernel (takes V <= 128 * 8192 and a device that keeps four rows'

@@ -24,6 +24,7 @@
 namespace sv {
 
 constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: up to how many each workgroup forms its position's weight
+constexpr unsigned kProbsAtOnce = 1280;   // workgroups that run at once, or nearly
 constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the finishing kernel keeps in LDS (32 KB)
 
 struct ProbWeight {

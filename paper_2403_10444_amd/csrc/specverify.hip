@@ -145,12 +145,13 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     const unsigned blocks = (unsigned)((size_t)B * (gamma + 1) * L.nchunks);
     // A position's weight: formed by each of its workgroups under its loads (B = 64, gamma = 8, V = 128256, bf16: 58 -> 51 us,
     // 1 sequence 18 -> 14), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
-    // (Alg. 1 unless every sum is reported: 26 us against 30 there) and where there are many of them with less to read
+    // (Alg. 1 unless every sum is reported: 25 us against 48 there, unless the call runs at once anyway: 8 sequences of
+    // V = 32000 16.8 against 12.7) and where there are many of them with less to read
     // than the weight takes to form (4096 sequences of 8 over 500 tokens: 150 us against 185, and 89 since short rows leave
     // out the vectors beyond them).
     const int every_sum = debug_out ? 1 : 0;
     const bool many_short = V <= kChunk / 2 && (long long)B * (gamma + 1) > kProbsFormMax;
-    const bool in_front = (algo == kToken && !every_sum) || many_short;
+    const bool in_front = (algo == kToken && !every_sum && blocks > kProbsAtOnce) || many_short;
     if (in_front)
         probs_weights_kernel<T><<<B, 64, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, gamma, algo, weights, uniforms, every_sum);
     void (*const residual)(const T *, const T *, size_t, size_t, const int32_t *, const int32_t *, const float *, int, int, int, int, int, float2 *, ProbWeight *) =
@@ -258,7 +259,7 @@ FusedParams word_params(int algo, const void *target, const void *draft, const i
 }
 
 // The kernel for calls of few resident sets; SV_ERR_UNSUPPORTED for the calls it does not take (more workgroups than
-// kResidentSets times what the device keeps resident, rows of more than kResidentMaxGroups workgroups).
+// resident_sets() times what the device keeps resident, rows of more than kResidentMaxGroups workgroups).
 template <typename T, bool ALIGNED>
 sv_status_t launch_resident(int algo, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
                             size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd, const Layout &L,
@@ -270,7 +271,8 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     void (*kernel)(const FusedParams) = resident_verify_kernel<T, ALIGNED>;
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
-    if ((long long)nwg * B * (gamma + 1) > (long long)kResidentSets * capacity) return SV_ERR_UNSUPPORTED;
+    const double sets = g_path.load() == 7 ? kResidentSetsForced : resident_sets(gamma, nwg, draft_lens != nullptr);
+    if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,
                                       ws, accept_len, next_token, debug_out);
     kernel<<<dim3((unsigned)nwg, (unsigned)B, (unsigned)(gamma + 1)), kThreads, 0, stream>>>(P);
