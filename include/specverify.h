@@ -96,7 +96,7 @@ sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_
 /* Testing hook, process-wide: `path` 0 = the library's choice by the shape of the call: sequences of rows of at
  * most 2048 logits, or whose 2 gamma + 1 rows fit into LDS together, (2 gamma + 1) V <= 14336: one workgroup
  * (or wave) per sequence; else, calls of at most a few times the workgroups that the device keeps resident
- * (about 1 + gamma / 4 times) and rows of at most 32 * 8192 logits: the kernel for calls of few resident sets;
+ * (two or three times) and rows of at most 32 * 8192 logits: the kernel for calls of few resident sets;
  * else the fused kernel where it takes the shape, else the staged kernels.  5 = the kernels of one workgroup
  * per sequence, as far as the sequence fits LDS; 7 = the
  * kernel for calls of few resident sets (calls beyond their limits are then refused), 1 = the
@@ -108,7 +108,8 @@ sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_
  * ones; both also switch on, whatever the size of the call, what the library otherwise
  * does only in calls larger than one resident set of workgroups: residual masses that cannot
  * matter are left out, the last target row is read only where every token can be accepted, and
- * w_i travels from position to position as one published word); `spin_limit` bounds every wait
+ * w_i travels from position to position as one published word); 6 = 3, but every position forms w_i
+ * from the ratios of the earlier ones; `spin_limit` bounds every wait
  * inside the kernels that wait for each other's words, in polls (negative: default).        */
 void spec_verify_debug_config(int32_t path, int32_t spin_limit);
 

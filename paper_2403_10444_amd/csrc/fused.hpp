@@ -121,6 +121,7 @@ struct FusedParams {
     unsigned inv_slots, inv_wpr;   // floor(2^32 / d) + 1 for d = gamma + 1 and d = workgroups per row: n / d = mulhi(n, .) for the n that occur
     int prune;            // leave out what cannot matter (residual_needed, the last target row); off for calls so small
                           // that all positions run at once, where asking for the ratios first only lengthens the chain
+    int chain;            // w_i comes as one word from the leader of the position before (else everybody scans the ratios)
     int skip_last;        // the last target row is read only where every token can be accepted (its workgroups ask first)
     int spin_limit;
     int magic;            // workspace_magic(B, gamma, V)
@@ -972,7 +973,7 @@ __device__ __forceinline__ FusedParams reread_params()
 #define SV_ARG(f) Q.f = *reinterpret_cast<__attribute__((address_space(4))) const decltype(Q.f) *>(kp + offsetof(FusedParams, f))
     SV_ARG(target); SV_ARG(draft); SV_ARG(tokens); SV_ARG(draft_lens); SV_ARG(uniforms); SV_ARG(B); SV_ARG(gamma); SV_ARG(V);
     SV_ARG(tstride); SV_ARG(dstride); SV_ARG(k); SV_ARG(kd); SV_ARG(k_eps); SV_ARG(algo); SV_ARG(nu); SV_ARG(group_seqs);
-    SV_ARG(inv_slots); SV_ARG(inv_wpr); SV_ARG(prune); SV_ARG(skip_last); SV_ARG(spin_limit);
+    SV_ARG(inv_slots); SV_ARG(inv_wpr); SV_ARG(prune); SV_ARG(chain); SV_ARG(skip_last); SV_ARG(spin_limit);
     SV_ARG(magic); SV_ARG(header); SV_ARG(gen); SV_ARG(copy_bytes); SV_ARG(accept_len); SV_ARG(next_token); SV_ARG(debug_out);
     SV_ARG(words.ratio); SV_ARG(words.lw); SV_ARG(words.rowres); SV_ARG(words.pstat); SV_ARG(words.plast);
     SV_ARG(words.pgrp); SV_ARG(words.qgrp); SV_ARG(words.spart); SV_ARG(words.lseen);
@@ -1166,13 +1167,12 @@ void fused_verify_kernel(const FusedParams P)
     __shared__ unsigned wave_shares[kWaves];
     bool gave_up = false;
 
-    // Two ways to w_i.  Calls larger than one resident set ("chain"): the leader of row pair i - 1 publishes log2 w_i
-    // itself, one word that the workgroups of position i read at their start - position i starts up to a resident set
-    // after position i - 1 (where a position is less than that, the word is often not there yet, and a second look goes
-    // out with the workgroup's own words).  Smaller calls, where all positions run at once: the first wave of a
-    // workgroup reads the ratios of all earlier positions (lane j: the word of log2 r_{j+1}) and forms w_i from them.
+    // Two ways to w_i.  "Chain" (calls whose positions take longer than a trip through memory): the leader of row pair i - 1
+    // publishes log2 w_i itself, one word that the workgroups of position i read.  Else the first wave of a workgroup reads
+    // the ratios of all earlier positions (lane j: the word of log2 r_{j+1}), which their leaders publish without
+    // waiting for each other, and forms w_i from them.
     const int n_prev = U.i;                                   // ratios that w_i is made of
-    const bool chain = P.prune != 0;
+    const bool chain = P.chain != 0, prune = P.prune != 0;
 #define SV_RATIO_WORD (W.ratio + seq_d + (lane < n_prev ? lane : 0))
 #define SV_LW_WORD (W.lw + seq_d + (n_prev > 0 ? n_prev - 1 : 0))
 
@@ -1200,9 +1200,15 @@ void fused_verify_kernel(const FusedParams P)
         if (P.skip_last) {
             if (wave == 0) {
                 const float eta_g = load_uniform(P.uniforms + seq_u + gb - 1);
-                const u64 wt = wait_word(SV_LW_WORD, P.spin_limit, gave_up);
-                if (clears) hand_over();                     // (the word of log2 w_gamma is such a proof)
-                const bool wanted = can_become_tau(P.algo, gb, unpack_ratio(wt), eta_g);
+                double lw_g;
+                if (chain) {
+                    lw_g = unpack_ratio(wait_word(SV_LW_WORD, P.spin_limit, gave_up));
+                } else {
+                    const u64 wt = wait_word(SV_RATIO_WORD, ld_u64(SV_RATIO_WORD), lane < n_prev, P.spin_limit, gave_up);
+                    lw_g = read_lane_double(weights_from_ratios(P.algo, wt, n_prev), n_prev - 1);
+                }
+                if (clears) hand_over();                     // (the word of log2 w_gamma, or the ratios of all positions, are such a proof)
+                const bool wanted = can_become_tau(P.algo, gb, lw_g, eta_g);
                 if (lane == 0) row_flag = gave_up ? 2 : wanted ? 0 : 1;
                 if (gave_up) report_gave_up(P);
             }
@@ -1232,8 +1238,10 @@ void fused_verify_kernel(const FusedParams P)
     // draft token X_{i+1} and its two logits: the first wave of the row's last workgroup (the one with the
     // fewest logits) publishes the row's ratio from them
     const bool leader = wave == 0 && wg_x == nwg - 1;
-    // whether the workgroup finds out right after its first sweep if the row's residual mass can matter at all
-    const bool early = chain && !P.debug_out && n_prev > 0;
+    // whether the workgroup finds out right after its first sweep if the row's residual mass can matter at all (without the
+    // chain the leader's workgroup does not: its ratio, which every later position waits for, goes out first)
+    const bool ask = prune && !P.debug_out && n_prev > 0;
+    const bool early = ask && (chain || wg_x != nwg - 1);
     u64 wt = 0;                                              // chain: the word of log2 w_i; else, first wave: lane j's ratio word
     float eta_i = 0.f, eta_next = 0.f;                       // the uniforms of test i (this position's) and test i + 1
     int tok = 0;                                             // the drafted token X_{i+1}, for the leader
@@ -1286,14 +1294,18 @@ void fused_verify_kernel(const FusedParams P)
         const Words W = SV_WORDS;
         // (where the look at the start came too early for the chain's word, the second look goes out in front of the
         // workgroup's own words: one round trip for both, not one after the other)
-        if (early) SV_NOTE(14, read_lane_u64(wt, 0) != 0 ? 1 : 2);
-        if (early && read_lane_u64(wt, 0) == 0) wt = ld_u64(SV_LW_WORD);
+        if (early && chain) wt = ld_u64(SV_LW_WORD);
         publish_group_words(wave_words, W.pgrp + 2 * (drow * nwg + wg_x), W.qgrp + 2 * (drow * nwg + wg_x));
         bool wanted = true;
         if (early) {
-            wt = wait_word(SV_LW_WORD, wt, true, P.spin_limit, gave_up);
+            if (chain) {
+                wt = wait_word(SV_LW_WORD, wt, true, P.spin_limit, gave_up);
+                log2w = unpack_ratio(read_lane_u64(wt, 0));
+            } else {
+                wt = wait_word(SV_RATIO_WORD, wt, lane < n_prev, P.spin_limit, gave_up);
+                log2w = read_lane_double(weights_from_ratios(P.algo, wt, n_prev), n_prev - 1);
+            }
             SV_STAMP(13);
-            log2w = unpack_ratio(read_lane_u64(wt, 0));
             wanted = gave_up || can_become_tau(P.algo, U.i, log2w, eta_i);
         }
         if (lane == 0) row_flag = wanted ? 1 : 0;
@@ -1321,7 +1333,7 @@ void fused_verify_kernel(const FusedParams P)
         // is not needed either.  w_{i+1} = w_i r_{i+1} takes this row's normalisers, which a workgroup that forms S_i waits
         // for anyway: its first wave asks for the drafted token's two logits with them and judges like the leader does,
         // on the same words with the same arithmetic (calls larger than one resident set; not with the debug block).
-        const bool may_skip = needed && chain && !P.debug_out && P.algo != kToken;
+        const bool may_skip = needed && prune && !P.debug_out && P.algo != kToken;
         if (may_skip && !leader) { ya_bits = logit_bits(rowA + tok); yb_bits = logit_bits(rowB + tok); }
         float Mp, Mq;
         double Lp, Lq;
@@ -1390,15 +1402,19 @@ void fused_verify_kernel(const FusedParams P)
         }
         SV_STAMP(9);
         candidate = can_become_tau(P.algo, U.i, log2w, eta_i);
+        // log2 w_{i+1} as the next position's workgroups will have it, whichever way they get it: rounded as its word holds
+        // it, or from the scan over the same words
+        if (chain || P.algo == kToken) {
+            lw_next = unpack_ratio(pack_ratio(next_weight(P.algo, log2w, lr_row, ratio_passes(own_word)), false));
+        } else if (may_skip || finisher) {
+            const u64 mine = pack_ratio(lr_row, false);
+            lw_next = read_lane_double(weights_from_ratios(P.algo, lane == n_prev ? mine : wt, n_prev + 1), n_prev);
+        }
         if (leader && (chain || finisher)) {
-            // (rounded as the word holds it: everybody goes by the same number)
-            lw_next = unpack_ratio(pack_ratio(next_weight(P.algo, log2w, unpack_ratio(own_word), ratio_passes(own_word)), false));
             if (gave_up) report_gave_up(P);
             if (chain && lane == 0) st_u64(W.lw + drow, gave_up ? kPoison64 : pack_ratio(lw_next, false));
         }
-        // (log2 w_{i+1} rounded as its word holds it, as the next position's leader and the finishing wave will read it)
-        const bool sweep = needed && !(may_skip && !gave_up &&
-                                       unpack_ratio(pack_ratio(next_weight(P.algo, log2w, lr_row, false), false)) >= 0.0);
+        const bool sweep = needed && (gave_up || !((ask && !candidate) || (may_skip && lw_next >= 0.0)));
         if (P.algo == kToken) log2w = 0.0;                          // the residual of token verification is p - q
         if (P.algo == kGreedy) log2w = fmin(log2w, 100.0);          // keeps w p finite in float
         // the second sweep's row constants: w p(x) = 2^(y_p - A) with A = L_p - log2 w, q(x) = 2^(y_q - L_q).  Their

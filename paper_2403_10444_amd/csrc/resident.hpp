@@ -21,21 +21,22 @@ namespace sv {
 constexpr int kResidentMaxGroups = 32;        // workgroups per row: one poll of a wave covers the words of both rows
 // Up to how many times the workgroups that the device keeps resident the library takes this kernel by itself.  Its
 // workgroups hold their registers until the row's S_i is there, which costs nothing while everything runs at once and
-// more and more as workgroups queue for the compute units (about 9 us a set, against 4 in the large kernel); the large
-// kernel pays a price per position instead, its chain of row leaders (about 2 us each).  So the line rises with the draft
-// length, and a little for narrow rows, which wait for fewer workgroups; where sequences bring their own draft lengths,
-// half of the positions are empty and only their leaders' chain is as long.  Measured, this kernel / the large one, bf16:
-//   gamma = 1,  V = 128256: 1.3 sets 19 / 19 us, 3.1 sets 32 / 27      gamma = 2: 1.8 sets 25 / 21
-//   gamma = 4:  1.8 sets 23 / 25, 3.1 sets 34 / 32                     gamma = 8: 2.7 sets 30 / 32, 3.6 sets 37 / 35
-//   gamma = 16: 1.7 sets 22 / 44, 3.8 sets 39 / 49, 6.4 sets 60 / 57   (V = 32000: 5.0 sets 47 / 55)
-//   with draft lengths: gamma = 2: 1.3 sets 17 / 17, 2.4 sets 24 / 21; gamma = 6: 3.1 sets 26 / 26, 3.9 sets 31 / 28;
-//   gamma = 16: 3.8 sets 30 / 44, 6.4 sets 40 / 46
+// more and more as workgroups queue for the compute units; the large kernel has its row leaders read the logits once more
+// instead.  Measured, this kernel / the large one:
+//   bf16, V = 128256: gamma = 2: 1.3 sets 18 / 22 us, 2.4 sets 27 / 26; gamma = 8: 1.2 sets 19 / 21, 2.4 sets 27 / 29,
+//   3.9 sets 40 / 37; gamma = 16: 2.3 sets 28 / 29, 3.8 sets 38 / 35
+//   bf16, V = 32000: gamma = 2: 2.4 sets 26 / 26; gamma = 8: 2.4 sets 28 / 31, 4.0 sets 40 / 40; gamma = 16: 4.0 sets 39 / 42
+//   float32 (a quarter fewer workgroups resident), V = 128256: gamma = 4: 1.2 sets 21 / 23, 2.3 sets 32 / 30; gamma = 16:
+//   2.4 sets 33 / 33; V = 32000: gamma = 8: 1.3 sets 23 / 25, 2.4 sets 34 / 34
+//   with draft lengths of the sequences' own (half of the workgroups have nothing to do): bf16, V = 32000, gamma = 8: 2.4 sets
+//   22 / 26, 4.0 sets 28 / 28; V = 100277, gamma = 6: 3.4 sets 27.8 / 29.0
 // The line is the same with and without the report of every S_i, so that the report changes no decision (it favours the
-// large kernel: gamma = 8: 2.7 sets 34 / 30; gamma = 16: 3.8 sets 47 / 42).
-__host__ inline double resident_sets(int gamma, int groups, bool own_lengths)
+// large kernel: gamma = 8, V = 128256: 2.4 sets 32 / 30).
+inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths)
 {
-    const double narrow = groups < 16 ? 1.0 + (16 - groups) / 48.0 : 1.0;
-    return (1.0 + (own_lengths ? 0.38 : 0.22) * gamma) * narrow;
+    const double narrow = groups < 16 ? 1.0 + (16 - groups) / 40.0 : 1.0;
+    const double sets = (f32 ? 1.8 : 2.6) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
+    return (sets < few_positions ? sets : few_positions) * narrow;
 }
 constexpr int kResidentSetsForced = 8;        // the same when the testing hook asks for this kernel
 

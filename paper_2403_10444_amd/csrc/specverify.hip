@@ -26,10 +26,11 @@ using namespace sv;
 
 constexpr int kDefaultSpinLimit = 1 << 20;
 
-std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of one resident set (testing hook; 3 / 4: fused with small / large units)
+std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of one resident set (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
 std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
 std::atomic<int> g_lane{0};                        // 0 auto, 32 or 64: logits per lane of the fused kernel's units (testing hook)
+std::atomic<int> g_chain{-1};                      // -1 auto, 0 / 1: whether the fused kernel's leaders hand w_i on in a chain (testing hook)
 #ifdef SV_PROFILE
 std::atomic<long long *> g_prof{nullptr};          // device buffer for per-workgroup timestamps (tuning builds only)
 #endif
@@ -271,7 +272,7 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     void (*kernel)(const FusedParams) = resident_verify_kernel<T, ALIGNED>;
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
-    const double sets = g_path.load() == 7 ? kResidentSetsForced : resident_sets(gamma, nwg, draft_lens != nullptr);
+    const double sets = g_path.load() == 7 ? kResidentSetsForced : resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr);
     if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,
                                       ws, accept_len, next_token, debug_out);
@@ -323,8 +324,17 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     if ((size_t)n_groups * (gamma + 1) > 65535u || P.group_seqs > 65535) return SV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)wpr, (unsigned)P.group_seqs, (unsigned)(n_groups * (gamma + 1)));
     // (the testing hook's forced unit sizes also force the pruning, so that small test shapes exercise it)
-    P.prune = g_lane.load() != 0 || (size_t)wpr * P.group_seqs * n_groups * (gamma + 1) > (size_t)capacity ? 1 : 0;
+    const double sets = (double)((size_t)wpr * P.group_seqs * n_groups * (gamma + 1)) / (double)capacity;
+    P.prune = g_lane.load() != 0 || sets > 1.0 ? 1 : 0;
     P.skip_last = P.prune;
+    // How a position learns w_i.  From the leader of the position before, one word handed on from position to position, where a
+    // position takes longer than that trip (about 2 us): the least to read (B = 1024, gamma = 8, V = 256000 1365 us against 1400, B = 64,
+    // V = 128256 48.7 against 51.5).  Else from the ratios of all earlier positions, which their leaders publish without
+    // waiting for each other: gamma = 16, V = 128256, bf16, 1.3 / 3.8 / 6.4 resident sets 20 / 35 / 51 us against 43 / 49 / 58 with the
+    // chain, gamma = 8 21 / 37 / 52 against 29 / 37 / 50, gamma = 2 the same either way; half as many workgroups are
+    // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37).
+    const int forced_chain = g_chain.load();
+    P.chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma) ? 1 : 0;
     kernel<<<grid, kThreads, 0, stream>>>(P);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
@@ -476,8 +486,10 @@ int32_t spec_verify_debug_last_kernel(void) { return g_last_kernel.load(); }
 
 void spec_verify_debug_config(int32_t path, int32_t spin_limit)
 {
-    g_path.store((path >= 0 && path <= 2) || path == 5 || path == 7 ? path : path == 3 || path == 4 ? 2 : 0);
-    g_lane.store(path == 3 ? kLaneSmall : path == 4 ? kLaneLarge : 0);
+    const bool fused_form = path == 3 || path == 4 || path == 6;
+    g_path.store((path >= 0 && path <= 2) || path == 5 || path == 7 ? path : fused_form ? 2 : 0);
+    g_lane.store(path == 4 ? kLaneLarge : fused_form ? kLaneSmall : 0);
+    g_chain.store(fused_form ? path != 6 : -1);
     g_spin_limit.store(spin_limit >= 0 ? spin_limit : kDefaultSpinLimit);
 }
 

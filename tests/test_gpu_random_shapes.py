@@ -108,3 +108,27 @@ def test_random_shapes_and_options(block, probs):
     for j in range(25):
         it = 100 * block + j
         _check(_draw_case(rng, it, probs), it, probs)
+
+
+@pytest.mark.parametrize("block", range(2))
+def test_weights_from_the_ratios_of_all_positions(block, monkeypatch):
+    """The fused kernel with its pruning where every position forms w_i from the earlier positions' ratios itself (calls
+    whose positions follow each other faster than a word travels): random shapes, longer drafts among them."""
+    monkeypatch.setitem(PATHS, "fused-ratios", 6)
+    rng = np.random.default_rng(7900 + block)
+    for j in range(20):
+        case = _draw_case(rng, 900 + 20 * block + j, False)
+        if j % 4 == 0:
+            case["cfg"] = workloads.with_overrides(case["cfg"], B=3, gamma=int(rng.choice([16, 33, 64])), V=min(case["cfg"].V, 20000))
+        _check(dict(case, path="fused-ratios"), 900 + 20 * block + j, False)
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype,lens", [(40, 16, 20000, "bf16", False), (64, 8, 70001, "bf16", True), (150, 6, 9000, "f32", False),
+                                                  (512, 2, 17000, "bf16", False)])
+def test_calls_of_a_few_resident_sets_on_the_fused_kernel(algo, B, gamma, V, dtype, lens, monkeypatch):
+    """Both ways to w_i as the library picks them (1.6 to 3.6 sets), and the same call on the kernel for few resident sets."""
+    monkeypatch.setitem(PATHS, "fused-auto", 2)
+    cfg = workloads.Config(f"sets_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 3.0, 0.7, 0.9, False, 1)
+    for path in ("fused-auto", "default"):
+        _check(dict(cfg=cfg, algo=algo, path=path, top_k=0, use_lens=lens, pad_t=0, pad_d=0, lens_seed=B), 950 + B, False)
