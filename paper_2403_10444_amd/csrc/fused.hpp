@@ -18,7 +18,7 @@
 //      published (Alg. 2: w_i = min(w_{i-1} r_i, 1), evaluated as a scan over the ratios: no position waits
 //      for a chain of earlier ones, only for their rows).  The acceptance probability of Alg. 2 / 4 never
 //      exceeds w_i, so where the position's uniform is not below w_i its residual mass cannot matter
-//      (residual_needed) and the workgroup is done.  Otherwise the first wave waits for the words of the other
+//      (can_become_tau) and the workgroup is done.  Otherwise the first wave waits for the words of the other
 //      workgroups of the row, which give L_p and L_q.  The first wave of the row's last workgroup is the
 //      row's leader and always stays: it publishes the row's ratio log2 r_{i+1},
 //   4. forms its share of S_i from the registers and publishes it; the row's leader then sums the row's
@@ -119,9 +119,8 @@ struct FusedParams {
     int nu;               // units (wave chunks) per row = 4 * workgroups per row
     int group_seqs;       // sequences per group of the row order
     unsigned inv_slots, inv_wpr;   // floor(2^32 / d) + 1 for d = gamma + 1 and d = workgroups per row: n / d = mulhi(n, .) for the n that occur
-    int prune;            // leave out what cannot matter (residual_needed, the last target row); off for calls so small
+    int prune;            // leave out what cannot matter (can_become_tau, the last target row); off for calls so small
                           // that all positions run at once, where asking for the ratios first only lengthens the chain
-    int chain;            // w_i comes as one word from the leader of the position before (else everybody scans the ratios)
     int skip_last;        // the last target row is read only where every token can be accepted (its workgroups ask first)
     int spin_limit;
     int magic;            // workspace_magic(B, gamma, V)
@@ -582,13 +581,6 @@ __device__ __forceinline__ bool can_become_tau(int algo, int i, double log2w_i, 
     if (algo == kToken) return log2w_i > 0.5 * kLog2RatioFloor;
     return (double)__builtin_amdgcn_logf(eta_i) < log2w_i + 1.0e-3;
 }
-// Whether position i's residual mass is formed: where the position can become tau, and everywhere when the caller
-// wants every S_i reported or the call is too small for leaving any out to pay.
-__device__ __forceinline__ bool residual_needed(const FusedParams &P, int i, double log2w_i, float eta_i)
-{
-    return !P.prune || P.debug_out || can_become_tau(P.algo, i, log2w_i, eta_i);
-}
-
 // The workgroup's two words from its four waves' words in LDS (one wave: lanes 0..3 take the target row's, lanes 4..7
 // the draft row's; each quad combines its four in a fixed order, the sums through exact powers of two).
 __device__ __forceinline__ void publish_group_words(const u64 (&wave_words)[2][kWaves], u64 *pgrp_word, u64 *qgrp_word)
@@ -973,7 +965,7 @@ __device__ __forceinline__ FusedParams reread_params()
 #define SV_ARG(f) Q.f = *reinterpret_cast<__attribute__((address_space(4))) const decltype(Q.f) *>(kp + offsetof(FusedParams, f))
     SV_ARG(target); SV_ARG(draft); SV_ARG(tokens); SV_ARG(draft_lens); SV_ARG(uniforms); SV_ARG(B); SV_ARG(gamma); SV_ARG(V);
     SV_ARG(tstride); SV_ARG(dstride); SV_ARG(k); SV_ARG(kd); SV_ARG(k_eps); SV_ARG(algo); SV_ARG(nu); SV_ARG(group_seqs);
-    SV_ARG(inv_slots); SV_ARG(inv_wpr); SV_ARG(prune); SV_ARG(chain); SV_ARG(skip_last); SV_ARG(spin_limit);
+    SV_ARG(inv_slots); SV_ARG(inv_wpr); SV_ARG(prune); SV_ARG(skip_last); SV_ARG(spin_limit);
     SV_ARG(magic); SV_ARG(header); SV_ARG(gen); SV_ARG(copy_bytes); SV_ARG(accept_len); SV_ARG(next_token); SV_ARG(debug_out);
     SV_ARG(words.ratio); SV_ARG(words.lw); SV_ARG(words.rowres); SV_ARG(words.pstat); SV_ARG(words.plast);
     SV_ARG(words.pgrp); SV_ARG(words.qgrp); SV_ARG(words.spart); SV_ARG(words.lseen);
@@ -1093,7 +1085,10 @@ __device__ __forceinline__ void lead_row(int b, int i_own, int gb, unsigned par,
     SV_STAMP(6);
 }
 
-template <typename T, bool ALIGNED, int NW, int LANE>
+// CHAIN: how a position learns w_i (below).  A template parameter, not an argument: as an argument it cost the calls that
+// report every S_i 2 - 4 % (B = 256, gamma = 16, V = 64000: 215 -> 223 us).  (P.prune is always set with the chain, but left for
+// the kernel to read: known at compile time, the kernel came out 0.3 % slower.)
+template <typename T, bool ALIGNED, int NW, int LANE, bool CHAIN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LANE == kLaneLarge ? 3 : ElemTraits<T>::kVec == 8 ? SV_WAVES_SMALL : 4)))
 void fused_verify_kernel(const FusedParams P)
 {
@@ -1172,7 +1167,8 @@ void fused_verify_kernel(const FusedParams P)
     // the ratios of all earlier positions (lane j: the word of log2 r_{j+1}), which their leaders publish without
     // waiting for each other, and forms w_i from them.
     const int n_prev = U.i;                                   // ratios that w_i is made of
-    const bool chain = P.chain != 0, prune = P.prune != 0;
+    constexpr bool chain = CHAIN;
+    const bool prune = P.prune != 0;
 #define SV_RATIO_WORD (W.ratio + seq_d + (lane < n_prev ? lane : 0))
 #define SV_LW_WORD (W.lw + seq_d + (n_prev > 0 ? n_prev - 1 : 0))
 
@@ -1405,7 +1401,7 @@ void fused_verify_kernel(const FusedParams P)
         // log2 w_{i+1} as the next position's workgroups will have it, whichever way they get it: rounded as its word holds
         // it, or from the scan over the same words
         if (chain || P.algo == kToken) {
-            lw_next = unpack_ratio(pack_ratio(next_weight(P.algo, log2w, lr_row, ratio_passes(own_word)), false));
+            if (leader) lw_next = unpack_ratio(pack_ratio(next_weight(P.algo, log2w, unpack_ratio(own_word), ratio_passes(own_word)), false));
         } else if (may_skip || finisher) {
             const u64 mine = pack_ratio(lr_row, false);
             lw_next = read_lane_double(weights_from_ratios(P.algo, lane == n_prev ? mine : wt, n_prev + 1), n_prev);
@@ -1414,7 +1410,8 @@ void fused_verify_kernel(const FusedParams P)
             if (gave_up) report_gave_up(P);
             if (chain && lane == 0) st_u64(W.lw + drow, gave_up ? kPoison64 : pack_ratio(lw_next, false));
         }
-        const bool sweep = needed && (gave_up || !((ask && !candidate) || (may_skip && lw_next >= 0.0)));
+        const bool beyond = may_skip && (chain ? unpack_ratio(pack_ratio(next_weight(P.algo, log2w, lr_row, false), false)) : lw_next) >= 0.0;
+        const bool sweep = needed && (gave_up || !((!chain && ask && !candidate) || beyond));
         if (P.algo == kToken) log2w = 0.0;                          // the residual of token verification is p - q
         if (P.algo == kGreedy) log2w = fmin(log2w, 100.0);          // keeps w p finite in float
         // the second sweep's row constants: w p(x) = 2^(y_p - A) with A = L_p - log2 w, q(x) = 2^(y_q - L_q).  Their

@@ -35,7 +35,7 @@ constexpr int kResidentMaxGroups = 32;        // workgroups per row: one poll of
 inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths)
 {
     const double narrow = groups < 16 ? 1.0 + (16 - groups) / 40.0 : 1.0;
-    const double sets = (f32 ? 1.8 : 2.6) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
+    const double sets = (f32 ? 1.8 : 2.5) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
     return (sets < few_positions ? sets : few_positions) * narrow;
 }
 constexpr int kResidentSetsForced = 8;        // the same when the testing hook asks for this kernel

@@ -295,19 +295,20 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     const bool large = kLargeOk && g_lane.load() == kLaneLarge;
     const int lane_logits = large ? kLaneLarge : kLaneSmall;
     const int nu = (V + kWaves * kWave * lane_logits - 1) / (kWaves * kWave * lane_logits) * kWaves;
-    // the instantiation for this row width (one or two words of a row per lane of the collecting wave) and its
-    // resident workgroups
-    static std::atomic<int> cap[2][2];
+    // the instantiations for this row width (one or two words of a row per lane of the collecting wave), with and without
+    // the chain, and their resident workgroups
+    static std::atomic<int> cap[2][2], cap_chain[2][2];
     const int nwg = nu / kWaves;
     const int nw_log = nwg <= kWave ? 0 : 1;
-    void (*kernel)(const FusedParams) = nullptr;
-#define SV_PICK(LN) (nw_log == 0 ? fused_verify_kernel<T, ALIGNED, 1, LN> : fused_verify_kernel<T, ALIGNED, 2, LN>)
+    void (*ratios)(const FusedParams) = nullptr, (*chain)(const FusedParams) = nullptr;
+#define SV_PICK(LN, CH) (nw_log == 0 ? fused_verify_kernel<T, ALIGNED, 1, LN, CH> : fused_verify_kernel<T, ALIGNED, 2, LN, CH>)
     if constexpr (kLargeOk) {
-        if (large) kernel = SV_PICK(kLaneLarge);
+        if (large) { ratios = SV_PICK(kLaneLarge, false); chain = SV_PICK(kLaneLarge, true); }
     }
-    if (!kernel) kernel = SV_PICK(kLaneSmall);
+    if (!large) { ratios = SV_PICK(kLaneSmall, false); chain = SV_PICK(kLaneSmall, true); }
 #undef SV_PICK
-    const int capacity = resident_workgroups(kernel, cap[nw_log][large ? 1 : 0]);
+    const int with_ratios = resident_workgroups(ratios, cap[nw_log][large ? 1 : 0]), with_chain = resident_workgroups(chain, cap_chain[nw_log][large ? 1 : 0]);
+    const int capacity = with_ratios < with_chain ? with_ratios : with_chain;
     const int wpr = nwg;
     // a row's workgroups wait for each other and must fit on the device together, with room to spare
     if (capacity < 4 * wpr) return capacity < 1 ? SV_ERR_HIP : SV_ERR_UNSUPPORTED;
@@ -332,10 +333,11 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     // V = 128256 48.7 against 51.5).  Else from the ratios of all earlier positions, which their leaders publish without
     // waiting for each other: gamma = 16, V = 128256, bf16, 1.3 / 3.8 / 6.4 resident sets 20 / 35 / 51 us against 43 / 49 / 58 with the
     // chain, gamma = 8 21 / 37 / 52 against 29 / 37 / 50, gamma = 2 the same either way; half as many workgroups are
-    // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37).
+    // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37), and where every
+    // S_i is reported nobody asks for w_i before the row's words are in (gamma = 8: 2.4 sets 30 / 30, 3.6 sets 37 / 35).
     const int forced_chain = g_chain.load();
-    P.chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma) ? 1 : 0;
-    kernel<<<grid, kThreads, 0, stream>>>(P);
+    const bool in_chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * (debug_out ? 0.6 : 1.0) * gamma);
+    (in_chain ? chain : ratios)<<<grid, kThreads, 0, stream>>>(P);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
