@@ -184,8 +184,8 @@ sv_status_t spec_verify_debug_stream_probe(const void *a, const void *b, size_t 
  *   next_token     [B] out: Y in [0, V)
  *   debug_out      NULL, or [B, gamma+1, 3] floats out: w_i, S_i, h_i (S_gamma = w_gamma,
  *                  h_0 = 1)
- * 16-byte loads are used when both logit pointers and V*sizeof(dtype) are multiples of 16;
- * any other V or alignment is served by an element-wise path with the same results.
+ * Rows are read with 16-byte loads whatever V and the pointers' alignment are (fastest where both logit
+ * pointers and V*sizeof(dtype) are multiples of 16), with the same results.
  */
 sv_status_t spec_verify_block(const void *target_logits, const void *draft_logits,
                               const int32_t *draft_tokens, const float *uniforms,
@@ -230,8 +230,7 @@ sv_status_t spec_verify_greedy(const void *target_logits, const void *draft_logi
  *    from one row of V logits to the next, e.g. a vocabulary padded for the GEMM that produced
  *    the logits.  Row (b, i) of the target starts (b * (gamma + 1) + i) * target_row_stride
  *    elements after target_logits, row (b, i) of the draft (b * gamma + i) * draft_row_stride
- *    after draft_logits; what lies between rows is never read.  16-byte loads need both strides
- *    in bytes to be multiples of 16 besides the conditions on V and the base pointers.
+ *    after draft_logits; what lies between rows is never read.
  *
  * SV_ERR_INVALID_ARG also for an unknown algo, a negative stride or a stride below V.  Everything
  * else as for spec_verify_block.
@@ -283,6 +282,30 @@ sv_status_t spec_verify_probs(sv_algo_t algo, const void *target_probs, const vo
                               int32_t B, int32_t gamma, int32_t V, sv_dtype_t dtype,
                               void *workspace, size_t workspace_bytes,
                               int32_t *accept_len, int32_t *next_token, float *debug_out, void *stream);
+
+/*
+ * The verification calls above behind one pointer, for bindings that pay for every argument they hand over.
+ * `inputs` says which one: SV_CALL_LOGITS is spec_verify_ex, SV_CALL_PROBS spec_verify_probs (temperature is not
+ * read), SV_CALL_LOGITS_NOALLOC spec_verify_ex_noalloc (workspace and workspace_bytes are not read); strides of 0 and
+ * draft_lens NULL make spec_verify_ex what spec_verify_block / token / greedy are.  SV_ERR_INVALID_ARG for a NULL
+ * pointer or another value of `inputs`; everything else as for those calls.  The struct is read before the call
+ * returns and not kept.
+ */
+enum { SV_CALL_LOGITS = 0, SV_CALL_PROBS = 1, SV_CALL_LOGITS_NOALLOC = 2 };
+typedef struct {
+    const void *target, *draft;
+    const int32_t *draft_tokens, *draft_lens;
+    const float *uniforms;
+    void *workspace;
+    int32_t *accept_len, *next_token;
+    float *debug_out;
+    void *stream;
+    int64_t target_row_stride, draft_row_stride;
+    uint64_t workspace_bytes;
+    double temperature;               /* as a float to the calls above */
+    int32_t inputs, algo, B, gamma, V, dtype;
+} sv_call_t;
+sv_status_t spec_verify_call(const sv_call_t *call);
 
 const char *spec_verify_status_string(sv_status_t status);
 

@@ -684,6 +684,28 @@ sv_status_t spec_verify_ex_noalloc(sv_algo_t algo, const void *target_logits, co
                         debug_out, stream);
 }
 
+sv_status_t spec_verify_call(const sv_call_t *c)
+{
+    if (!c) return SV_ERR_INVALID_ARG;
+    const sv_algo_t algo = (sv_algo_t)c->algo;
+    const sv_dtype_t dtype = (sv_dtype_t)c->dtype;
+    switch (c->inputs) {
+    case SV_CALL_LOGITS:
+        return spec_verify_ex(algo, c->target, c->draft, c->draft_tokens, c->draft_lens, c->target_row_stride, c->draft_row_stride,
+                              c->uniforms, c->B, c->gamma, c->V, dtype, (float)c->temperature, c->workspace, (size_t)c->workspace_bytes,
+                              c->accept_len, c->next_token, c->debug_out, c->stream);
+    case SV_CALL_PROBS:
+        return spec_verify_probs(algo, c->target, c->draft, c->draft_tokens, c->draft_lens, c->target_row_stride, c->draft_row_stride,
+                                 c->uniforms, c->B, c->gamma, c->V, dtype, c->workspace, (size_t)c->workspace_bytes,
+                                 c->accept_len, c->next_token, c->debug_out, c->stream);
+    case SV_CALL_LOGITS_NOALLOC:
+        return spec_verify_ex_noalloc(algo, c->target, c->draft, c->draft_tokens, c->draft_lens, c->target_row_stride, c->draft_row_stride,
+                                      c->uniforms, c->B, c->gamma, c->V, dtype, (float)c->temperature, c->accept_len, c->next_token,
+                                      c->debug_out, c->stream);
+    }
+    return SV_ERR_INVALID_ARG;
+}
+
 const char *spec_verify_status_string(sv_status_t status)
 {
     switch (status) {

@@ -169,3 +169,38 @@ def test_probs_entry_validates_its_arguments():
     assert call(ts=50) == binding.SV_ERR_INVALID_ARG
     assert call(dtype=9) == binding.SV_ERR_INVALID_ARG
     assert call(ws_bytes=16) == binding.SV_ERR_WORKSPACE_TOO_SMALL
+
+
+def test_the_packed_call_validates_like_the_calls_it_stands_for():
+    lib = sv.load()
+
+    def packed(inputs, *, algo=0, target=0x1000, draft=0x1000, tokens=0x1000, uniforms=0x1000, ws=0x1000, ws_bytes=1 << 30, tau=0x1000,
+               y=0x1000, strides=(0, 0), T=1.0, B=2, gamma=3, V=100, dtype=0):
+        return lib.spec_verify_call(binding._pack_call(target, draft, tokens, 0, uniforms, ws, tau, y, 0, 0, *strides, ws_bytes, T,
+                                                       inputs, algo, B, gamma, V, dtype))
+
+    class CallStruct(ctypes.Structure):
+        _fields_ = ([(n, ctypes.c_void_p) for n in "target draft draft_tokens draft_lens uniforms workspace accept_len next_token debug_out stream".split()]
+                    + [("target_row_stride", ctypes.c_int64), ("draft_row_stride", ctypes.c_int64), ("workspace_bytes", ctypes.c_uint64),
+                       ("temperature", ctypes.c_double)] + [(n, ctypes.c_int32) for n in "inputs algo B gamma V dtype".split()])
+    blob = binding._pack_call(1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 0.5, 14, 15, 16, 17, 18, 19)
+    assert len(blob) == ctypes.sizeof(CallStruct)
+    c = CallStruct.from_buffer_copy(blob)
+    assert [getattr(c, f[0]) for f in CallStruct._fields_] == [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 0.5, 14, 15, 16, 17, 18, 19]
+
+    assert lib.spec_verify_call(None) == binding.SV_ERR_INVALID_ARG
+    for inputs in (-1, 3):
+        assert packed(inputs) == binding.SV_ERR_INVALID_ARG
+    for inputs in (0, 1, 2):
+        assert packed(inputs, algo=7) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, B=0) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, gamma=65) == binding.SV_ERR_UNSUPPORTED
+    for inputs in (0, 1):
+        assert packed(inputs, dtype=7) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, target=0) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, ws=0x1010) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, strides=(99, 0)) == binding.SV_ERR_INVALID_ARG
+        assert packed(inputs, ws_bytes=16) == binding.SV_ERR_WORKSPACE_TOO_SMALL
+    for T in (0.0, -1.0, float("inf"), float("nan"), 1e39):
+        assert packed(0, T=T) == binding.SV_ERR_INVALID_ARG
+    assert packed(2, B=1024, gamma=8, V=256000) == binding.SV_ERR_STATIC_SCRATCH_TOO_SMALL
