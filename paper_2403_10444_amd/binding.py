@@ -37,6 +37,8 @@ EXPORTED = (
     "spec_verify_debug_copy",
     "spec_verify_debug_stream_probe",
     "spec_sample_tokens",
+    "spec_sample_tokens_ws",
+    "spec_sample_workspace_bytes",
     "spec_verify_block",
     "spec_verify_token",
     "spec_verify_greedy",
@@ -121,6 +123,10 @@ def load() -> ctypes.CDLL:
         lib.spec_sample_tokens.restype = ctypes.c_int
         lib.spec_sample_tokens.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int, ctypes.c_float,
                                            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+        lib.spec_sample_workspace_bytes.restype = ctypes.c_size_t
+        lib.spec_sample_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int32]
+        lib.spec_sample_tokens_ws.restype = ctypes.c_int
+        lib.spec_sample_tokens_ws.argtypes = lib.spec_sample_tokens.argtypes[:-1] + [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
         lib.spec_verify_status_string.restype = ctypes.c_char_p
         lib.spec_verify_status_string.argtypes = [ctypes.c_int]
         _lib = lib
@@ -212,10 +218,17 @@ def spec_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature
         raise ValueError("one float32 uniform per row")
     if tokens is None:
         tokens = torch.empty(uniforms.shape, dtype=torch.int32, device=logits.device)
+    lib = _lib or load()
+    scratch, n = None, 0
     if stream is None:
+        # Scratch memory comes from torch's allocator, which keeps it for this stream; a call on a stream that torch does
+        # not know of, or under graph capture, does without.
         stream = _current_stream(logits.get_device())
-    code = (_lib or load()).spec_sample_tokens(logits.data_ptr(), rows, V, _dtype_code(logits), float(temperature),
-                                     uniforms.data_ptr(), tokens.data_ptr(), stream)
+        n = lib.spec_sample_workspace_bytes(rows, V)
+        if n and not torch.cuda.is_current_stream_capturing():
+            scratch = torch.empty(n, dtype=torch.uint8, device=logits.device)
+    code = lib.spec_sample_tokens_ws(logits.data_ptr(), rows, V, _dtype_code(logits), float(temperature), uniforms.data_ptr(),
+                                     tokens.data_ptr(), None if scratch is None else scratch.data_ptr(), n, stream)
     if code != SV_OK:
         raise SpecVerifyError(code, status_string(code))
     return tokens

@@ -29,94 +29,74 @@ constexpr int kSampleSerial = 32;
 // four let the draws of some rows run under the sweeps of others once every compute unit has several rows (512 rows 32.1 us with
 // sixteen, 31.8 with four; 4096 rows of 32000: 49 with four).  Rows of up to four units have no work for more than four.
 constexpr int kSampleManyRows = 512;
+// With scratch memory the units of a row go to any compute unit, for a second launch (about 2 us): worth it for rows wide
+// enough to keep one compute unit busy for longer than that, until the rows fill the device by themselves.  One workgroup
+// per row / two launches, bf16: V = 32000: 64 rows 6.3 / 7.1 us; V = 50257: 8 rows 8.2 / 7.0, 64 9.0 / 8.0, 128 9.5 / 9.1, 256 10.1 / 11.1;
+// V = 128256: 1 row 12.7 / 6.8, 64 13.4 / 8.8, 256 17.0 / 15.9; V = 256000: 64 22.1 / 11.0, 512 50.4 / 46.2; float32 alike.
+constexpr int kSampleMinSplit = 24;                          // units of a row: from more than this on
+constexpr int kSampleSplitUnits = 8 * kWave;                 // ... to this many (V <= 1 Mi)
+constexpr int kSampleSplitRows = 4;                          // rows: up to this many per unit
 
-// Rows of more than one unit: one workgroup of WPR waves per row.
-template <typename T, int WPR>
-__global__ __launch_bounds__(WPR * kWave)
-void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, int32_t *tokens)
+// (largest scaled logit, sum of the exponentials relative to its integer shift) of a stretch of the row.
+struct SampleEntry {
+    float m;
+    double z;
+    // another stretch's added, through exact powers of two
+    __device__ __forceinline__ void add(const SampleEntry &other)
+    {
+        if (!(other.m > -INFINITY)) return;
+        const float top = fmaxf(m, other.m);
+        z = (m > -INFINITY ? ldexp(z, (int)(shift_of(m) - shift_of(top))) : 0.0) + ldexp(other.z, (int)(shift_of(other.m) - shift_of(top)));
+        m = top;
+    }
+    __device__ __forceinline__ double relative_to(float M) const { return m > -INFINITY ? ldexp(z, (int)(shift_of(m) - shift_of(M))) : 0.0; }
+};
+
+// One unit of a row as loaded -> its entry (every lane gets it).  `left`: logits of the row from the unit's start on.
+template <typename T>
+__device__ __forceinline__ SampleEntry sweep_unit(RawSlice<T, false, kLaneSmall> &raw, int left, float k)
+{
+    constexpr int LANE = kLaneSmall;
+    float x[LANE];
+    unpack_slice<T, false, LANE>(0, left, raw, x);
+    float m = x[0];
+#pragma unroll
+    for (int j = 1; j < LANE; ++j) m = fmaxf(m, x[j]);
+    SampleEntry e;
+    e.m = wave_max(m * k);
+    const float shift = shift_of(e.m);
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < LANE; ++j) acc[j & 1] += (double)fast_exp2(__builtin_fmaf(x[j], k, -shift));
+    double z0, z1;
+    halves_sum_f64(acc[0] + acc[1], z0, z1);
+    e.z = z0 + z1;
+    return e;
+}
+
+// Where t falls among the lanes' sums z (inclusive running sums `inc`): the first lane whose running sum exceeds t, with
+// what is left of t there; rounding may leave none: then the last with any weight, and all of it.
+__device__ __forceinline__ int locate_sum(double z, double inc, double t, double &left)
+{
+    const u64 hit = __ballot(inc > t), nz = __ballot(z > 0.0);
+    if (hit) {
+        const int l = __ffsll((long long)hit) - 1;
+        left = t - read_lane_double(inc - z, l);
+        return l;
+    }
+    left = INFINITY;
+    return nz ? 63 - __clzll((long long)nz) : 0;
+}
+
+// The token, by one wave: units `from` to `end` of the row again, in vocabulary order (vector, lane, element), weights
+// relative to `shift`, the first whose running sum exceeds t (else the last with weight, token 0 if there is none).
+template <typename T>
+__device__ __forceinline__ int walk_units(const T *row, int V, float k, float shift, double t, int from, int end)
 {
     constexpr int LANE = kLaneSmall, kVec = ElemTraits<T>::kVec, kNV = LANE / kVec;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const size_t r = blockIdx.x;
-    const T *const row = logits + r * (size_t)V;
-    const float u = load_uniform(uniforms + r);
-
-    // the wave's entries (at most one per lane): `span` units each, neighbours
-    const int units = (V - 1) / kSampleUnit + 1;
-    const int span = (units - 1) / (WPR * kWave) + 1;
-    const int entries = (units - 1) / span + 1;
-    const int per = (entries - 1) / WPR + 1;
-    const int first_unit = min((long long)w * per * span, (long long)units), end_unit = min((long long)(w + 1) * per * span, (long long)units);
-
-    float my_m = -INFINITY;                                  // lane j: the wave's entry j
-    double my_z = 0.0;
-    {
-        // (a unit is addressed from its own start: offsets stay small whatever V is)
-        auto issue = [&](int unit, RawSlice<T, false, LANE> &raw) {
-            const int at = unit * kSampleUnit;
-            issue_loads<T, false, LANE>(row + at, 0, V - at, raw);
-        };
-        RawSlice<T, false, LANE> raw, next;
-        if (first_unit < end_unit) issue(first_unit, raw);
-        int entry = 0, in_entry = 0;
-        for (int unit = first_unit; unit < end_unit; ++unit) {
-            if (unit + 1 < end_unit) issue(unit + 1, next);
-            const int left = V - unit * kSampleUnit;
-            float x[LANE];
-            unpack_slice<T, false, LANE>(0, left, raw, x);
-            float m = x[0];
-#pragma unroll
-            for (int j = 1; j < LANE; ++j) m = fmaxf(m, x[j]);
-            const float M = wave_max(m * k), shift = shift_of(M);
-            double acc[2] = {0.0, 0.0};
-#pragma unroll
-            for (int j = 0; j < LANE; ++j) acc[j & 1] += (double)fast_exp2(__builtin_fmaf(x[j], k, -shift));
-            double z0, z1;
-            halves_sum_f64(acc[0] + acc[1], z0, z1);
-            if (lane == entry && M > -INFINITY) {
-                const double z = z0 + z1;
-                const float top = fmaxf(my_m, M);
-                my_z = (my_m > -INFINITY ? ldexp(my_z, (int)(shift_of(my_m) - shift_of(top))) : 0.0) + ldexp(z, (int)(shift - shift_of(top)));
-                my_m = top;
-            }
-            if (++in_entry == span) { in_entry = 0; ++entry; }
-            raw = next;
-        }
-    }
-
-    // ---- the waves' totals, relative to the integer shift of the wave's largest
-    const float Mw = wave_max(my_m);
-    const double z_lane = my_m > -INFINITY ? ldexp(my_z, (int)(shift_of(my_m) - shift_of(Mw))) : 0.0;
-    const double inc_lane = wave_scan(z_lane);
-    const double z_wave = read_lane_double(inc_lane, kWave - 1);
-    double t;                                                // what is left of u * C_total where the wave's stretch begins
-    {
-        __shared__ float wave_m[WPR];
-        __shared__ double wave_z[WPR];
-        if (lane == 0) { wave_m[w] = Mw; wave_z[w] = z_wave; }
-        __syncthreads();
-        const float m = lane < WPR ? wave_m[lane] : -INFINITY;
-        const float M = wave_max(m);
-        const double z = m > -INFINITY ? ldexp(wave_z[lane & (WPR - 1)], (int)(shift_of(m) - shift_of(M))) : 0.0;
-        const double inc = wave_scan(z);
-        const double target = (double)u * read_lane_double(inc, kWave - 1);
-        // the first wave whose running sum exceeds the target (rounding may leave none: then the last with any weight)
-        const u64 hit = __ballot(inc > target), nz = __ballot(z > 0.0);
-        const int holder = hit ? __ffsll((long long)hit) - 1 : nz ? 63 - __clzll((long long)nz) : 0;
-        if (holder != w) return;
-        t = hit ? ldexp(target - read_lane_double(inc - z, holder), (int)(shift_of(M) - shift_of(Mw))) : (double)INFINITY;
-        if (!(Mw > -INFINITY)) t = INFINITY;
-    }
-    // ---- the entry of the wave's stretch, the same way
-    const u64 hit = __ballot(inc_lane > t), nz = __ballot(z_lane > 0.0);
-    const int entry = hit ? __ffsll((long long)hit) - 1 : nz ? 63 - __clzll((long long)nz) : 0;
-    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_m), entry)));
-    t = hit ? ldexp(t - read_lane_double(inc_lane - z_lane, entry), (int)(shift_of(Mw) - shift)) : (double)INFINITY;
-
-    // ---- and the token: the entry's units again, in vocabulary order (vector, lane, element)
+    const int lane = threadIdx.x & 63;
     int y = -1, last_positive = -1;
-    const int from = first_unit + entry * span;
-    for (int unit = from; unit < from + span && unit < end_unit && y < 0; ++unit) {
+    for (int unit = from; unit < end && y < 0; ++unit) {
         const int at = unit * kSampleUnit, left = V - at;
         RawSlice<T, false, LANE> raw;
         issue_loads<T, false, LANE>(row + at, 0, left, raw);
@@ -153,11 +133,127 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
         }
     }
     if (y < 0) {
-        // rounding pushed t to the end: the last token with weight (none in the row: token 0)
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) last_positive = max(last_positive, __shfl_xor(last_positive, off, kWave));
         y = last_positive < 0 ? 0 : last_positive;
     }
+    return y;
+}
+
+// Rows of more than one unit: one workgroup of WPR waves per row.
+template <typename T, int WPR>
+__global__ __launch_bounds__(WPR * kWave)
+void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, int32_t *tokens)
+{
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t r = blockIdx.x;
+    const T *const row = logits + r * (size_t)V;
+    const float u = load_uniform(uniforms + r);
+
+    // the wave's entries (at most one per lane): `span` units each, neighbours
+    const int units = (V - 1) / kSampleUnit + 1;
+    const int span = (units - 1) / (WPR * kWave) + 1;
+    const int entries = (units - 1) / span + 1;
+    const int per = (entries - 1) / WPR + 1;
+    const int first_unit = min((long long)w * per * span, (long long)units), end_unit = min((long long)(w + 1) * per * span, (long long)units);
+
+    SampleEntry own = {-INFINITY, 0.0};                      // lane j: the wave's entry j
+    {
+        // (a unit is addressed from its own start: offsets stay small whatever V is)
+        auto issue = [&](int unit, RawSlice<T, false, kLaneSmall> &raw) {
+            const int at = unit * kSampleUnit;
+            issue_loads<T, false, kLaneSmall>(row + at, 0, V - at, raw);
+        };
+        RawSlice<T, false, kLaneSmall> raw, next;
+        if (first_unit < end_unit) issue(first_unit, raw);
+        int entry = 0, in_entry = 0;
+        for (int unit = first_unit; unit < end_unit; ++unit) {
+            if (unit + 1 < end_unit) issue(unit + 1, next);
+            const SampleEntry e = sweep_unit<T>(raw, V - unit * kSampleUnit, k);
+            if (lane == entry) own.add(e);
+            if (++in_entry == span) { in_entry = 0; ++entry; }
+            raw = next;
+        }
+    }
+
+    // ---- the waves' totals, relative to the integer shift of the wave's largest
+    const float Mw = wave_max(own.m);
+    const double z_lane = own.relative_to(Mw);
+    const double inc_lane = wave_scan(z_lane);
+    __shared__ float wave_m[WPR];
+    __shared__ double wave_z[WPR];
+    if (lane == 0) { wave_m[w] = Mw; wave_z[w] = read_lane_double(inc_lane, kWave - 1); }
+    __syncthreads();
+    const SampleEntry of_wave = {lane < WPR ? wave_m[lane] : -INFINITY, wave_z[lane & (WPR - 1)]};
+    const float M = wave_max(of_wave.m);
+    const double z = of_wave.relative_to(M);
+    const double inc = wave_scan(z);
+    double t;                                                // what is left of u * C_total where the wave's stretch begins
+    if (locate_sum(z, inc, (double)u * read_lane_double(inc, kWave - 1), t) != w) return;
+    // ---- the entry of the wave's stretch, then the token
+    const int entry = locate_sum(z_lane, inc_lane, ldexp(t, (int)(shift_of(M) - shift_of(Mw))), t);
+    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.m), entry)));
+    const int from = first_unit + entry * span;
+    const int y = walk_units(row, V, k, shift, ldexp(t, (int)(shift_of(Mw) - shift)), from, min(from + span, end_unit));
+    if (lane == 0) tokens[r] = y;
+}
+
+// The same in two launches, for rows too few to fill the device: every wave sweeps one unit and leaves its entry in
+// `entries` [rows, units]; then one wave per row scans them (up to kSampleSplitUnits units, a stretch of neighbours per
+// lane), finds the unit and walks it.
+template <typename T>
+__global__ __launch_bounds__(kThreads)
+void sample_units_kernel(const T *logits, int V, int units, float k, SampleEntry *entries)
+{
+    const int unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+    const size_t r = blockIdx.y;
+    if (unit >= units) return;
+    const int at = unit * kSampleUnit;
+    RawSlice<T, false, kLaneSmall> raw;
+    issue_loads<T, false, kLaneSmall>(logits + r * (size_t)V + at, 0, V - at, raw);
+    const SampleEntry e = sweep_unit<T>(raw, V - at, k);
+    if ((threadIdx.x & 63) == 0) entries[r * units + unit] = e;
+}
+template <typename T>
+__global__ __launch_bounds__(kWave)
+void sample_finish_kernel(const T *logits, int V, int units, float k, const float *uniforms, const SampleEntry *entries, int32_t *tokens)
+{
+    constexpr int kPer = kSampleSplitUnits / kWave;
+    const int lane = threadIdx.x;
+    const size_t r = blockIdx.x;
+    const float u = load_uniform(uniforms + r);
+    const int per = (units - 1) / kWave + 1;
+    SampleEntry mine[kPer], own = {-INFINITY, 0.0};
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        mine[j] = {-INFINITY, 0.0};
+        if (j < per && lane * per + j < units) mine[j] = entries[r * units + lane * per + j];
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) own.add(mine[j]);
+    const float M = wave_max(own.m);
+    const double z = own.relative_to(M), inc = wave_scan(z);
+    double t;
+    const int holder = locate_sum(z, inc, (double)u * read_lane_double(inc, kWave - 1), t);
+    // the unit among the holder's neighbours: the first whose running sum exceeds t, else its last with weight
+    int unit = 0;
+    double left = INFINITY, running = 0.0;
+    float m_unit = -INFINITY;
+    bool found = false;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const double zj = mine[j].relative_to(M);
+        if (!found && zj > 0.0) {
+            unit = lane * per + j;
+            m_unit = mine[j].m;
+            if (running + zj > t) { found = true; left = t - running; }
+        }
+        running += zj;
+    }
+    unit = __builtin_amdgcn_readlane(unit, holder);
+    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(m_unit), holder)));
+    left = ldexp(read_lane_double(left, holder), (int)(shift_of(M) - shift));
+    const int y = walk_units(logits + r * (size_t)V, V, k, shift, left, unit, unit + 1);
     if (lane == 0) tokens[r] = y;
 }
 

@@ -343,9 +343,15 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
 
 // The drafting step: how many waves share a row.
 template <typename T>
-sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, hipStream_t stream)
+sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, SampleEntry *entries, hipStream_t stream)
 {
     const T *logits = static_cast<const T *>(logits_v);
+    if (entries) {
+        const int units = (V - 1) / kSampleUnit + 1;
+        sample_units_kernel<T><<<dim3((unsigned)((units - 1) / kWaves + 1), (unsigned)rows), kThreads, 0, stream>>>(logits, V, units, k, entries);
+        sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
+        return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
+    }
     if (V <= kSampleSerial)
         sample_short_rows_kernel<T><<<(unsigned)((rows - 1) / kThreads + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
     else if (V <= 16 * kLaneSmall)
@@ -565,19 +571,36 @@ sv_status_t spec_verify_debug_stream_probe(const void *a, const void *b, size_t 
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
-sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype, float temperature,
-                               const float *uniforms, int32_t *tokens, void *stream_v)
+size_t spec_sample_workspace_bytes(int64_t rows, int32_t V)
+{
+    if (rows < 1 || V < 1) return 0;
+    const int units = (V - 1) / kSampleUnit + 1;
+    return units > kSampleMinSplit && units <= kSampleSplitUnits && rows <= (int64_t)kSampleSplitRows * units ? (size_t)rows * units * sizeof(SampleEntry) : 0;
+}
+
+sv_status_t spec_sample_tokens_ws(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype, float temperature,
+                                  const float *uniforms, int32_t *tokens, void *workspace, size_t workspace_bytes, void *stream_v)
 {
     if (!logits || !uniforms || !tokens) return SV_ERR_INVALID_ARG;
     if (rows < 1 || V < 1) return SV_ERR_INVALID_ARG;
     if (!(temperature > 0.f) || !isfinite(temperature)) return SV_ERR_INVALID_ARG;
     if (dtype != SV_DTYPE_F32 && dtype != SV_DTYPE_BF16) return SV_ERR_INVALID_ARG;
     if (rows > 0x7fffffffll) return SV_ERR_UNSUPPORTED;
+    const size_t wanted = workspace ? spec_sample_workspace_bytes(rows, V) : 0;
+    if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return SV_ERR_INVALID_ARG;
+    if (workspace_bytes < wanted) return SV_ERR_WORKSPACE_TOO_SMALL;
+    SampleEntry *const entries = wanted ? static_cast<SampleEntry *>(workspace) : nullptr;
     const float k = (float)(1.4426950408889634074 / (double)temperature);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     return dtype == SV_DTYPE_F32
-        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, stream)
-        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, stream);
+        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, entries, stream)
+        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, entries, stream);
+}
+
+sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype, float temperature,
+                               const float *uniforms, int32_t *tokens, void *stream_v)
+{
+    return spec_sample_tokens_ws(logits, rows, V, dtype, temperature, uniforms, tokens, nullptr, 0, stream_v);
 }
 
 #ifdef SV_PROFILE

@@ -204,3 +204,18 @@ def test_the_packed_call_validates_like_the_calls_it_stands_for():
     for T in (0.0, -1.0, float("inf"), float("nan"), 1e39):
         assert packed(0, T=T) == binding.SV_ERR_INVALID_ARG
     assert packed(2, B=1024, gamma=8, V=256000) == binding.SV_ERR_STATIC_SCRATCH_TOO_SMALL
+
+
+def test_sampling_with_scratch_memory_validates_on_the_host():
+    lib = sv.load()
+    want = lib.spec_sample_workspace_bytes(64, 128256)
+    assert want == 64 * 63 * 16
+    assert lib.spec_sample_workspace_bytes(0, 128256) == 0 and lib.spec_sample_workspace_bytes(64, 0) == 0
+    assert lib.spec_sample_workspace_bytes(64, 32000) == 0 and lib.spec_sample_workspace_bytes(4096, 128256) == 0
+
+    def call(logits=0x1000, ws=0x1000, n=want, T=1.0, rows=64, dtype=1):
+        return lib.spec_sample_tokens_ws(logits, rows, 128256, dtype, T, 0x1000, 0x1000, ws, n, None)
+    assert call(n=want - 1) == binding.SV_ERR_WORKSPACE_TOO_SMALL
+    assert call(ws=0x1008) == binding.SV_ERR_INVALID_ARG
+    assert call(logits=None) == call(T=0.0) == call(rows=0) == call(dtype=5) == binding.SV_ERR_INVALID_ARG
+    assert call(rows=1 << 40) == binding.SV_ERR_UNSUPPORTED

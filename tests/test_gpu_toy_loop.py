@@ -52,8 +52,31 @@ def test_sample_tokens_at_the_edges_of_its_kernels(rows, V, dtype):
     assert not np.any(bad & (margins >= MARGIN)), (np.nonzero(bad)[0], got[bad], want[bad], margins[bad])
 
 
+# (rows spread over the device through scratch memory: the edges of the units and of the rule, a stretch of several units per
+# lane; the same rows by one workgroup each, on an explicit stream, give the same tokens)
+@pytest.mark.parametrize("rows,V,dtype", [(100, 49153, "bf16"), (101, 50257, "f32"), (104, 51200, "bf16"), (105, 51200, "f32"), (7, 131073, "bf16"),
+                                          (64, 128256, "bf16"), (3, 262145, "f32"), (2, 1048576, "bf16"), (2, 1048577, "bf16")])
+def test_sample_tokens_in_two_launches(rows, V, dtype):
+    g = torch.Generator(device=DEV).manual_seed(rows * 13 + V)
+    logits = torch.randn((rows, V), generator=g, device=DEV) * 4.0
+    logits[rows // 2, V // 3:] = float("-inf")
+    logits[0, : V - 3000] = float("-inf")
+    logits = logits.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    u = workloads.philox_uniforms(rows + V, (rows,))
+    u[-1], u[0] = 0.0, 1.0 - 2.0 ** -24
+    ud = torch.as_tensor(u, device=DEV)
+    units = (V + 2047) // 2048
+    wanted = sv.load().spec_sample_workspace_bytes(rows, V)
+    assert wanted == (rows * units * 16 if 24 < units <= 512 and rows <= 4 * units else 0)
+    got = sv.spec_sample_tokens(logits, ud, 0.7).cpu().numpy()
+    alone = sv.spec_sample_tokens(logits, ud, 0.7, stream=torch.cuda.current_stream().cuda_stream).cpu().numpy()
+    want, margins = oracle.sample_rows(workloads.logits_to_numpy(logits), u, 0.7, dtype=oracle.BF16 if dtype == "bf16" else oracle.F32)
+    safe = margins >= MARGIN
+    assert np.array_equal(got[safe], want[safe]) and np.array_equal(alone[safe], want[safe])
+
+
 def test_sample_tokens_of_rows_without_weight_is_token_0():
-    for V in (2, 300, 1500, 9000, 40000):
+    for V in (2, 300, 1500, 9000, 40000, 60000):
         logits = torch.full((3, V), float("-inf"), device=DEV)
         assert sv.spec_sample_tokens(logits, torch.tensor([0.0, 0.5, 0.99], device=DEV), 1.0).tolist() == [0, 0, 0]
 
