@@ -186,7 +186,7 @@ SmallLaunch small_launch_of(int B, int gamma)
     const int threads = ((gamma + 1) * G + kWave - 1) / kWave * kWave;           // a group per row pair and one for the last target row
     if constexpr (G == 4) {
         if (threads == kWave) return {small_verify_kernel<T, G, LANE, 4, false>, (unsigned)((B - 1) / 4 + 1), 4 * kWave};
-    } else {
+    } else if constexpr (G != 64 || LANE != 8) {         // (those take no draft that fills the workgroup)
         if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, 1, true>, (unsigned)B, kTinyThreads};
     }
     if (threads > kTinyThreads) return {nullptr, 0, 0};

@@ -35,13 +35,14 @@ struct TinyCoef {
     bool q_units;          // terms in units of cq: max(xa f - xb, 0); else in units of cp: max(xa - xb f, 0)
     double scale;
 };
+template <bool FMA = false>
 __device__ __forceinline__ TinyCoef tiny_coef(double log2_cp, double log2_cq)
 {
     TinyCoef c;
     const double d = log2_cp - log2_cq;
     c.q_units = d <= 0.0;
-    c.f = (float)exp2_precise(c.q_units ? d : -d);
-    c.scale = exp2_precise(c.q_units ? log2_cq : log2_cp);
+    c.f = (float)exp2_precise<FMA>(c.q_units ? d : -d);
+    c.scale = exp2_precise<FMA>(c.q_units ? log2_cq : log2_cp);
     return c;
 }
 __device__ __forceinline__ float tiny_term(const float *xa, const float *xb, int x, const TinyCoef &c)
@@ -310,6 +311,7 @@ template <typename T, int G, int LANE, int SEQS, bool LATE>
 __global__ __launch_bounds__(SEQS == 1 ? kTinyThreads : SEQS * kWave)
 void small_verify_kernel(const FusedParams P)
 {
+    constexpr bool kFma = LANE == 8;                // (see series_step)
     constexpr int kPositions = SEQS == 1 ? SV_MAX_GAMMA : kWave / G;
     constexpr int kVec = ElemTraits<T>::kVec, kNV = LANE / kVec;
     // per row pair, as its group leaves them: the sums of both rows' exponentials, their largest scaled logits, the drafted
@@ -405,18 +407,18 @@ void small_verify_kernel(const FusedParams P)
     if (wave == 0) {
         const int j = lane < gb ? lane : 0;
         const float Mp = own.max_p[j], Mq = own.max_q[j], sp = shift_of(Mp), sq = shift_of(Mq);
-        const double log2_zp = log2_precise(own.sum_p[j]), log2_zq = log2_precise(own.sum_q[j]);
+        const double log2_zp = log2_precise<kFma>(own.sum_p[j]), log2_zq = log2_precise<kFma>(own.sum_q[j]);
         // (see the large kernel for the correction by k_eps)
         const double lp = (double)own.tok_p[j] * P.kd - ((double)sp + log2_zp + P.k_eps * (double)Mp);
         const double lq = (double)own.tok_q[j] * P.kd - ((double)sq + log2_zq + P.k_eps * (double)Mq);
         const double lr = fmax(lp - lq, kLog2RatioFloor);
-        ratio_word = pack_ratio(lr, token_algo && (double)eta_next < exp2_precise(fmin(lr, 0.0)));
+        ratio_word = pack_ratio(lr, token_algo && (double)eta_next < exp2_precise<kFma>(fmin(lr, 0.0)));
         lw_next = weights_from_ratios(algo, ratio_word, gb);
         lw = __shfl_up(lw_next, 1, kWave);
         // (the residual of token verification is p - q; Alg. 4: w stays finite)
         if (lane == 0 || token_algo) lw = 0.0;
         if (algo == kGreedy) { lw = fmin(lw, 100.0); lw_next = fmin(lw_next, 100.0); }
-        const TinyCoef c = tiny_coef(lw - log2_zp, -log2_zq);
+        const TinyCoef c = tiny_coef<kFma>(lw - log2_zp, -log2_zq);
         scale = c.scale;
         if (lane < gb) own.factor[lane] = c.q_units ? c.f : -c.f;
     }
@@ -445,7 +447,7 @@ void small_verify_kernel(const FusedParams P)
         const double S = (lane < gb ? own.mass[lane] : 0.0) * scale;
         // Alg. 2 / 4, lane j judges position j >= 1: eta_j < h_j = S_j / (S_j + 1 - w_j), 1 where w_j >= 1 (see AcceptTest),
         // without the division; the last position, by lane gb - 1: eta_gb < w_gb.  Alg. 1: the tests came with the ratios
-        const double one_minus_w = one_minus_exp2(fmin(lw, 0.0));
+        const double one_minus_w = one_minus_exp2<kFma>(fmin(lw, 0.0));
         u64 tests = __ballot(token_algo ? lane < gb && ratio_passes(ratio_word)
                                         : lane > 0 && lane < gb && (lw >= 0.0 || (double)eta * (S + one_minus_w) < S));
         int tau;
@@ -453,19 +455,19 @@ void small_verify_kernel(const FusedParams P)
             tau = __ffsll((long long)~tests) - 1;                                    // leading run of passes
             if (tau < 0 || tau > gb) tau = gb;
         } else {
-            const bool last = lane == gb - 1 && (lw_next >= 0.0 || (double)eta_next < exp2_precise(lw_next));
+            const bool last = lane == gb - 1 && (lw_next >= 0.0 || (double)eta_next < exp2_precise<kFma>(lw_next));
             tau = __any(last) ? gb : tests ? 63 - __clzll((long long)tests) : 0;     // last passing sub-block
         }
         if (P.debug_out && lane < gb) {
-            const double next_h = exp2_precise(fmin(token_algo ? unpack_ratio(ratio_word) : lw_next, 0.0));
+            const double next_h = exp2_precise<kFma>(fmin(token_algo ? unpack_ratio(ratio_word) : lw_next, 0.0));
             const double h = lane == 0 || lw >= 0.0 ? 1.0 : S / (S + one_minus_w);
             float *d = P.debug_out + (seq_u + lane) * 3;
-            d[0] = (float)exp2_precise(lw); d[1] = (float)S;
+            d[0] = (float)exp2_precise<kFma>(lw); d[1] = (float)S;
             if (!token_algo || lane == 0) d[2] = (float)h;
             // (Alg. 1 has no w; its h_i = min(r_i, 1).  S_gamma = w_gamma: q_gamma == 0)
             if (token_algo) d[5] = (float)next_h;
             if (lane == gb - 1) {
-                d[3] = d[4] = token_algo ? 1.f : (float)exp2_precise(lw_next);
+                d[3] = d[4] = token_algo ? 1.f : (float)exp2_precise<kFma>(lw_next);
                 d[5] = (float)next_h;
             }
         }
