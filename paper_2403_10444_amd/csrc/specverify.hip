@@ -1,9 +1,10 @@
 // Draft verification for speculative decoding on gfx950: the C ABI of include/specverify.h.
 //
 // Host side only: argument checks, workspace layout and kernel launches.  The kernels are in
-// fused.hpp (one launch, every logit read from HBM once; the default) and staged.hpp (four
-// launches, no limit on the vocabulary size); probs.hpp holds the kernels for inputs that are
-// probabilities already.
+// fused.hpp (one launch, every logit read from HBM once; the default), resident.hpp (calls of few
+// resident sets), tiny.hpp (one workgroup or wave per sequence) and staged.hpp (four launches, no limit
+// on the vocabulary size); probs.hpp holds the kernels for inputs that are probabilities already,
+// sample.hpp those of the drafting step.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>

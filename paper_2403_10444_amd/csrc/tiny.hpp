@@ -1,4 +1,5 @@
-// Small sequences: ONE workgroup per sequence, nothing between workgroups.
+// Small sequences: ONE workgroup (or wave) per sequence, nothing between workgroups.  First the kernel for sequences that fit
+// LDS, which the library takes for rows of more than 2048 logits; then the one that keeps shorter rows in registers.
 //
 // Where the 2 gamma + 1 rows of a sequence fit into LDS together ((2 gamma + 1) V <= kTinyMaxFloats logits: a few
 // positions over a vocabulary of a thousand tokens, the shape of the worked example of Sec. 2 scaled up), the whole
