@@ -330,8 +330,8 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     P.prune = g_lane.load() != 0 || sets > 1.0 ? 1 : 0;
     P.skip_last = P.prune;
     // How a position learns w_i.  From the leader of the position before, one word handed on from position to position, where a
-    // position takes longer than that trip (about 2 us): the least to read (B = 1024, gamma = 8, V = 256000 1365 us against 1400, B = 64,
-    // V = 128256 48.7 against 51.5).  Else from the ratios of all earlier positions, which their leaders publish without
+    // position takes longer than that trip (about 2 us): the least to read (B = 1024, gamma = 8, V = 256000 1369 us against 1401, B = 64,
+    // V = 128256 50.1 against 52.9, host included).  Else from the ratios of all earlier positions, which their leaders publish without
     // waiting for each other: gamma = 16, V = 128256, bf16, 1.3 / 3.8 / 6.4 resident sets 20 / 35 / 51 us against 43 / 49 / 58 with the
     // chain, gamma = 8 21 / 37 / 52 against 29 / 37 / 50, gamma = 2 the same either way; half as many workgroups are
     // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37), and where every
