@@ -1490,8 +1490,8 @@ void fused_verify_kernel(const FusedParams P)
 // Clears the control words of a workspace and marks it initialised.
 __global__ void workspace_init_kernel(int *words, size_t n, int magic)
 {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < n) words[idx] = idx == kHdrMagic ? magic : 0;
+    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x)
+        words[idx] = idx == kHdrMagic ? magic : 0;
 }
 
 }  // namespace sv

@@ -27,6 +27,10 @@ using namespace sv;
 
 constexpr int kDefaultSpinLimit = 1 << 20;
 
+// Threads of one launch along x.  HIP refuses none beyond 2^32 - 1 but runs their number modulo 2^32, so a call of more is cut into
+// launches of whole sequences or rows (2^24 + 3 rows of 2049 logits to draw from, 256 threads each: three rows were drawn).
+constexpr unsigned long long kMaxLaunchThreads = 0xffffffffull;
+
 std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of one resident set (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
 std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
@@ -117,7 +121,7 @@ sv_status_t launch_staged(int algo, const void *target_v, const void *draft_v, c
     float *spart = reinterpret_cast<float *>(ws + L.off_sspart);
     const int n_target_rows = B * (gamma + 1);
 
-    row_stats_kernel<T, ALIGNED><<<(unsigned)(L.rows_total * L.nchunks), kThreads, 0, stream>>>(
+    row_stats_kernel<T, ALIGNED><<<(unsigned)((size_t)B * (2 * gamma + 1) * L.nchunks), kThreads, 0, stream>>>(
         target, draft, tstride, dstride, B, gamma, V, k, L.nchunks, stats);
     const size_t sm2 = 2 * (gamma + 1) * sizeof(double) + 2 * (gamma + 1) * sizeof(float);
     prefix_weights_kernel<T><<<B, 64, sm2, stream>>>(target, draft, tstride, dstride, tokens, gamma, V, k, kd, kd / (double)k - 1.0, L.nchunks,
@@ -209,7 +213,7 @@ SmallLaunch small_launch(int B, int gamma, int V)
 template <typename T>
 sv_status_t launch_tiny(int algo, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
                         size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd,
-                        char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
+                        int magic, char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
     const SmallLaunch small = small_launch<T>(B, gamma, V);
     if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
@@ -217,7 +221,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
     P.target = target; P.draft = draft; P.tokens = tokens; P.draft_lens = draft_lens; P.uniforms = uniforms;
     P.B = B; P.gamma = gamma; P.V = V; P.tstride = tstride; P.dstride = dstride;
     P.k = k; P.kd = kd; P.k_eps = kd / (double)k - 1.0; P.algo = algo;
-    P.magic = workspace_magic(B, gamma, V);
+    P.magic = magic;
     P.inv_wpr = V > 1 ? (unsigned)(0x100000000ull / (unsigned)V) + 1u : 0u;
     P.header = reinterpret_cast<int *>(ws);
     P.accept_len = accept_len; P.next_token = next_token; P.debug_out = debug_out;
@@ -353,17 +357,25 @@ sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const 
         sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }
-    if (V <= kSampleSerial)
-        sample_short_rows_kernel<T><<<(unsigned)((rows - 1) / kThreads + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
-    else if (V <= 16 * kLaneSmall)
-        sample_small_rows_kernel<T, 16><<<(unsigned)((rows - 1) / (kThreads / 16) + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
-    else if (V <= kSampleUnit)
-        sample_small_rows_kernel<T, 64><<<(unsigned)((rows - 1) / kWaves + 1), kThreads, 0, stream>>>(logits, rows, V, k, uniforms, tokens);
-    else if (V <= 4 * kSampleUnit || rows >= kSampleManyRows)
-        sample_rows_kernel<T, 4><<<(unsigned)rows, 4 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
-    else
-        sample_rows_kernel<T, 16><<<(unsigned)rows, 16 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
-    return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
+    // (no kernel that takes more than kSampleManyRows rows has more than 256 threads for one)
+    constexpr int kStep = 1 << 23;
+    static_assert((unsigned long long)kStep * kThreads <= kMaxLaunchThreads, "one launch per step");
+    for (int left = rows; left > 0; left -= kStep) {
+        const int n = left < kStep ? left : kStep;
+        if (V <= kSampleSerial)
+            sample_short_rows_kernel<T><<<(unsigned)((n - 1) / kThreads + 1), kThreads, 0, stream>>>(logits, n, V, k, uniforms, tokens);
+        else if (V <= 16 * kLaneSmall)
+            sample_small_rows_kernel<T, 16><<<(unsigned)((n - 1) / (kThreads / 16) + 1), kThreads, 0, stream>>>(logits, n, V, k, uniforms, tokens);
+        else if (V <= kSampleUnit)
+            sample_small_rows_kernel<T, 64><<<(unsigned)((n - 1) / kWaves + 1), kThreads, 0, stream>>>(logits, n, V, k, uniforms, tokens);
+        else if (V <= 4 * kSampleUnit || rows >= kSampleManyRows)
+            sample_rows_kernel<T, 4><<<(unsigned)n, 4 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
+        else
+            sample_rows_kernel<T, 16><<<(unsigned)n, 16 * kWave, 0, stream>>>(logits, V, k, uniforms, tokens);
+        if (hipGetLastError() != hipSuccess) return SV_ERR_HIP;
+        logits += (size_t)n * V; uniforms += n; tokens += n;
+    }
+    return SV_OK;
 }
 
 sv_status_t verify_entry(int algo, bool probs, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
@@ -394,12 +406,32 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
                          ((size_t)V * esize) % 16 == 0 && (tstride * esize) % 16 == 0 && (dstride * esize) % 16 == 0;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     char *ws = static_cast<char *>(workspace);
+    // Launches of `threads` threads per sequence along x, as many as kMaxLaunchThreads asks for (nearly always one), equally
+    // large: `launch` gets the arguments of its sequences.  What they leave in the scratch areas is their own.
+    auto in_slices = [&](unsigned long long threads, auto launch) {
+        if (threads > kMaxLaunchThreads) return SV_ERR_UNSUPPORTED;
+        const long long most = (long long)(kMaxLaunchThreads / threads), slices = (B - 1) / most + 1, step = (B - 1) / slices + 1;
+        for (long long b = 0; b < B; b += step) {
+            const size_t t = (size_t)b * (gamma + 1), d = (size_t)b * gamma;
+            const sv_status_t st = launch(static_cast<const void *>(static_cast<const char *>(target) + t * tstride * esize),
+                                          static_cast<const void *>(static_cast<const char *>(draft) + d * dstride * esize), tokens + d,
+                                          draft_lens ? draft_lens + b : nullptr, uniforms + t, (int)(b + step < B ? step : B - b),
+                                          accept_len + b, next_token + b, debug_out ? debug_out + 3 * t : nullptr);
+            if (st != SV_OK) return st;
+        }
+        return SV_OK;
+    };
+    // (what `launch` takes: the names of this function's arguments, of the slice)
+#define SV_SLICE const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens, const float *uniforms, \
+                 int B, int32_t *accept_len, int32_t *next_token, float *debug_out
+    const unsigned long long chunk_threads = (2ull * gamma + 1) * L.nchunks * kThreads;      // a workgroup per chunk of every row
     if (probs) {
 #define SV_PROBS(TT, AL) launch_probs<TT, AL>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, \
                                               L, ws, accept_len, next_token, debug_out, stream)
         g_last_kernel.store(SV_KERNEL_PROBS);
-        return dtype == SV_DTYPE_F32 ? (aligned ? SV_PROBS(float, true) : SV_PROBS(float, false))
-                                     : (aligned ? SV_PROBS(bf16_t, true) : SV_PROBS(bf16_t, false));
+        return in_slices(chunk_threads, [&](SV_SLICE) {
+            return dtype == SV_DTYPE_F32 ? (aligned ? SV_PROBS(float, true) : SV_PROBS(float, false))
+                                         : (aligned ? SV_PROBS(bf16_t, true) : SV_PROBS(bf16_t, false)); });
 #undef SV_PROBS
     }
     const int path = g_path.load();
@@ -408,9 +440,11 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
     // them that fit LDS)
     if (path == 5 && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     if (path == 5 || path == 0) {
-        const sv_status_t st = dtype == SV_DTYPE_F32
-            ? launch_tiny<float>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, ws, accept_len, next_token, debug_out, stream)
-            : launch_tiny<bf16_t>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, ws, accept_len, next_token, debug_out, stream);
+        const int magic = workspace_magic(B, gamma, V);
+#define SV_TINY(TT) launch_tiny<TT>(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, magic, ws, \
+                                    accept_len, next_token, debug_out, stream)
+        const sv_status_t st = in_slices(kTinyThreads, [&](SV_SLICE) { return dtype == SV_DTYPE_F32 ? SV_TINY(float) : SV_TINY(bf16_t); });
+#undef SV_TINY
         if (st != SV_ERR_UNSUPPORTED) { g_last_kernel.store(SV_KERNEL_TINY); return st; }
     }
 
@@ -438,9 +472,10 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
         return SV_ERR_UNSUPPORTED;
     }
     g_last_kernel.store(SV_KERNEL_STAGED);
-    return SV_DISPATCH(launch_staged);
+    return in_slices(chunk_threads, [&](SV_SLICE) { return SV_DISPATCH(launch_staged); });
 #undef SV_DISPATCH
 #undef SV_ARGS
+#undef SV_SLICE
 }
 
 // ---- the workspace of spec_verify_ex_noalloc: device memory that belongs to the library's code object, one copy per
@@ -474,7 +509,8 @@ sv_status_t spec_verify_workspace_init(void *workspace, size_t workspace_bytes,
     Layout L;
     if (!make_layout(B, gamma, V, L)) return SV_ERR_UNSUPPORTED;
     if (workspace_bytes < L.total) return SV_ERR_WORKSPACE_TOO_SMALL;
-    const unsigned grid = (unsigned)((L.control_words + 255) / 256);
+    const size_t blocks = (L.control_words + 255) / 256;
+    const unsigned grid = (unsigned)(blocks < 65536 ? blocks : 65536);
     workspace_init_kernel<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(
         static_cast<int *>(workspace), L.control_words, workspace_magic(B, gamma, V));
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
