@@ -207,28 +207,41 @@ def spec_verify_debug_stream_probe(a: torch.Tensor, b: torch.Tensor, out: torch.
         raise SpecVerifyError(code, status_string(code))
 
 
-def spec_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature: float, tokens=None, stream=None):
+def spec_sample_workspace_bytes(rows: int, V: int) -> int:
+    """Bytes of scratch memory that `spec_sample_tokens` can use for this many rows of V logits (0: none)."""
+    return int(load().spec_sample_workspace_bytes(rows, V))
+
+
+def spec_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature: float, tokens=None, stream=None,
+                       workspace=None):
     """One token per row of ``logits`` [..., V] from softmax(logits / T) by the inverse CDF at ``uniforms``
-    [...] (the drafting step of Alg. 3).  Returns int32 tokens of the shape of ``uniforms``."""
+    [...] (the drafting step of Alg. 3).  Returns int32 tokens of the shape of ``uniforms``.
+
+    Rows too few to fill the device are spread over it where there is scratch memory: ``workspace`` (contiguous uint8 device
+    tensor of `spec_sample_workspace_bytes`; calls that overlap need one each), on any stream and under graph capture.
+    A call that hands over ``tokens`` allocates nothing, so without a ``workspace`` it does without; a call that makes its
+    own output takes scratch memory from the same allocator."""
     V = logits.shape[-1]
     rows = logits.numel() // V
     if not logits.is_cuda or not logits.is_contiguous() or not uniforms.is_contiguous():
         raise ValueError("logits and uniforms must be contiguous cuda tensors")
     if uniforms.numel() != rows or uniforms.dtype is not torch.float32:
         raise ValueError("one float32 uniform per row")
+    if workspace is not None and (workspace.get_device() != logits.get_device() or not workspace.is_contiguous()):
+        raise ValueError("the workspace must be a contiguous tensor on the logits' device")
+    lib = _lib or load()
     if tokens is None:
         tokens = torch.empty(uniforms.shape, dtype=torch.int32, device=logits.device)
-    lib = _lib or load()
-    scratch, n = None, 0
+        if workspace is None and stream is None:
+            # (the allocator keeps both for the current stream: a stream of the caller's own is not known to it)
+            n = lib.spec_sample_workspace_bytes(rows, V)
+            if n:
+                workspace = torch.empty(n, dtype=torch.uint8, device=logits.device)
     if stream is None:
-        # Scratch memory comes from torch's allocator, which keeps it for this stream; a call on a stream that torch does
-        # not know of, or under graph capture, does without.
         stream = _current_stream(logits.get_device())
-        n = lib.spec_sample_workspace_bytes(rows, V)
-        if n and not torch.cuda.is_current_stream_capturing():
-            scratch = torch.empty(n, dtype=torch.uint8, device=logits.device)
     code = lib.spec_sample_tokens_ws(logits.data_ptr(), rows, V, _dtype_code(logits), float(temperature), uniforms.data_ptr(),
-                                     tokens.data_ptr(), None if scratch is None else scratch.data_ptr(), n, stream)
+                                     tokens.data_ptr(), None if workspace is None else workspace.data_ptr(),
+                                     0 if workspace is None else workspace.nbytes, stream)
     if code != SV_OK:
         raise SpecVerifyError(code, status_string(code))
     return tokens

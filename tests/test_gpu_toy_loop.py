@@ -75,6 +75,48 @@ def test_sample_tokens_in_two_launches(rows, V, dtype):
     assert np.array_equal(got[safe], want[safe]) and np.array_equal(alone[safe], want[safe])
 
 
+def test_sample_tokens_into_given_tokens_allocates_nothing():
+    """With the output handed over a call touches no allocator, with and without a workspace, on the current stream, on one
+    handed over and under capture; the tokens are the same ones."""
+    rows, V = 64, 50257
+    g = torch.Generator(device=DEV).manual_seed(5)
+    logits = torch.randn((3, rows, V), generator=g, device=DEV).mul_(4.0).to(torch.bfloat16)
+    u = workloads.philox_uniforms(77, (3, rows))
+    ud = torch.as_tensor(u, device=DEV)
+    ws = torch.empty(sv.spec_sample_workspace_bytes(rows, V), dtype=torch.uint8, device=DEV)
+    assert ws.numel() > 0
+    want, margins = oracle.sample_rows(workloads.logits_to_numpy(logits.view(3 * rows, V)), u.reshape(-1), 0.7, dtype=oracle.BF16)
+    want, safe = want.reshape(3, rows), margins.reshape(3, rows) >= MARGIN
+    assert safe.sum() > 0.9 * safe.size
+    tokens = torch.empty((rows,), dtype=torch.int32, device=DEV)
+    side = torch.cuda.Stream()
+    for workspace in (None, ws):
+        for stream in (None, side.cuda_stream):
+            tokens.fill_(-1)
+            torch.cuda.synchronize()
+            before = torch.cuda.memory_stats()["allocation.all.allocated"]
+            out = sv.spec_sample_tokens(logits[0], ud[0], 0.7, tokens=tokens, stream=stream, workspace=workspace)
+            assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+            torch.cuda.synchronize()
+            assert out is tokens and np.array_equal(tokens.cpu().numpy()[safe[0]], want[0][safe[0]])
+    with pytest.raises(sv.SpecVerifyError):
+        sv.spec_sample_tokens(logits[0], ud[0], 0.7, tokens=tokens, workspace=ws[:-16])
+    with pytest.raises(ValueError):
+        sv.spec_sample_tokens(logits[0], ud[0], 0.7, tokens=tokens, workspace=ws.cpu())
+    # (the two launches recorded, replayed on other rows, with eager work between the replays)
+    rows_in, u_in = logits[0].clone(), ud[0].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sv.spec_sample_tokens(rows_in, u_in, 0.7, tokens=tokens, workspace=ws)
+    for n in (1, 2, 0, 1):
+        rows_in.copy_(logits[n])
+        u_in.copy_(ud[n])
+        tokens.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(tokens.cpu().numpy()[safe[n]], want[n][safe[n]]), n
+
+
 def test_sample_tokens_of_rows_without_weight_is_token_0():
     for V in (2, 300, 1500, 9000, 40000, 60000):
         logits = torch.full((3, V), float("-inf"), device=DEV)
