@@ -123,6 +123,10 @@ enum {
 };
 int32_t spec_verify_debug_last_kernel(void);
 
+/* Testing hook: how positions learned w_i in the last call of this process that took the fused kernel: 1 = as one published
+ * word that travels from position to position, 0 = from the ratios of the earlier ones (-1 before the first such call).  */
+int32_t spec_verify_debug_last_chain(void);
+
 #ifdef SPECVERIFY_PROFILE_BUILD
 /* Tuning builds of the library only (compiled with -DSV_PROFILE; the product library exports no such symbol and
  * its kernels hold no such stores).  Process-wide: when `device_buffer` is not NULL the fused kernel stores up to

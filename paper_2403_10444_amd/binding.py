@@ -34,6 +34,7 @@ EXPORTED = (
     "spec_verify_workspace_check",
     "spec_verify_debug_config",
     "spec_verify_debug_last_kernel",
+    "spec_verify_debug_last_chain",
     "spec_verify_debug_copy",
     "spec_verify_debug_stream_probe",
     "spec_sample_tokens",
@@ -110,6 +111,8 @@ def load() -> ctypes.CDLL:
                                                     ctypes.c_int32, ctypes.c_void_p]
         lib.spec_verify_debug_last_kernel.restype = ctypes.c_int32
         lib.spec_verify_debug_last_kernel.argtypes = []
+        lib.spec_verify_debug_last_chain.restype = ctypes.c_int32
+        lib.spec_verify_debug_last_chain.argtypes = []
         lib.spec_verify_debug_config.restype = None
         lib.spec_verify_debug_config.argtypes = [ctypes.c_int32, ctypes.c_int32]
         if hasattr(lib, "spec_verify_debug_profile"):          # tuning builds only
@@ -167,6 +170,11 @@ SV_KERNEL_STAGED, SV_KERNEL_FUSED, SV_KERNEL_TINY, SV_KERNEL_RESIDENT, SV_KERNEL
 def spec_verify_debug_last_kernel() -> int:
     """Which kernels the last verification call of this process launched (SV_KERNEL_*; 0 before the first)."""
     return int(load().spec_verify_debug_last_kernel())
+
+
+def spec_verify_debug_last_chain() -> int:
+    """Testing hook: whether the last call on the fused kernel handed w_i on in a chain (see the header)."""
+    return int(load().spec_verify_debug_last_chain())
 
 
 def spec_verify_debug_profile(buffer) -> None:

@@ -34,6 +34,7 @@ constexpr unsigned long long kMaxLaunchThreads = 0xffffffffull;
 std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of one resident set (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
 std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
+std::atomic<int> g_last_chain{-1};                  // whether the last call on the fused kernel had the chain
 std::atomic<int> g_lane{0};                        // 0 auto, 32 or 64: logits per lane of the fused kernel's units (testing hook)
 std::atomic<int> g_chain{-1};                      // -1 auto, 0 / 1: whether the fused kernel's leaders hand w_i on in a chain (testing hook)
 #ifdef SV_PROFILE
@@ -338,11 +339,13 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     // V = 128256 50.1 against 52.9, host included).  Else from the ratios of all earlier positions, which their leaders publish without
     // waiting for each other: gamma = 16, V = 128256, bf16, 1.3 / 3.8 / 6.4 resident sets 20 / 35 / 51 us against 43 / 49 / 58 with the
     // chain, gamma = 8 21 / 37 / 52 against 29 / 37 / 50, gamma = 2 the same either way; half as many workgroups are
-    // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37), and where every
-    // S_i is reported nobody asks for w_i before the row's words are in (gamma = 8: 2.4 sets 30 / 30, 3.6 sets 37 / 35).
+    // there to pass the time where sequences bring their own draft lengths (gamma = 8, 6.4 sets: 37 / 37).  Where every S_i is
+    // reported nobody asks for w_i before the row's words are in, which favours the chain earlier (gamma = 8: 2.4 sets 30 / 30, 3.6 sets
+    // 37 / 35); the line is the same nevertheless: the two ways round log2 w_i differently, and the report changes no decision.
     const int forced_chain = g_chain.load();
-    const bool in_chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * (debug_out ? 0.6 : 1.0) * gamma);
+    const bool in_chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma);
     (in_chain ? chain : ratios)<<<grid, kThreads, 0, stream>>>(P);
+    g_last_chain.store(in_chain ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
@@ -528,6 +531,8 @@ sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_
 }
 
 int32_t spec_verify_debug_last_kernel(void) { return g_last_kernel.load(); }
+
+int32_t spec_verify_debug_last_chain(void) { return g_last_chain.load(); }
 
 void spec_verify_debug_config(int32_t path, int32_t spin_limit)
 {

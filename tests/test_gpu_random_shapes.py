@@ -123,6 +123,28 @@ def test_weights_from_the_ratios_of_all_positions(block, monkeypatch):
         _check(dict(case, path="fused-ratios"), 900 + 20 * block + j, False)
 
 
+@pytest.mark.parametrize("lens", [False, True])
+@pytest.mark.parametrize("gamma,V,dtype", [(8, 9000, "bf16"), (16, 3000, "f32"), (4, 70000, "bf16")])
+def test_the_report_changes_neither_the_kernel_nor_the_way_to_w(gamma, V, dtype, lens):
+    """Whether the caller asks for every S_i decides about neither (a uniform next to an edge would otherwise fall to one side
+    with the report and to the other without): calls from less than one resident set to a dozen."""
+    groups, forms = (V + 8191) // 8192, set()
+    for sets in (0.7, 1.3, 1.8, 2.2, 2.6, 3.0, 3.5, 4.2, 5.0, 6.0, 7.0, 8.5, 10.0, 12.0):
+        B = int(sets * 1280 / (groups * (gamma + 1))) + 1
+        rows = torch.zeros((B, gamma + 1, V), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device=DEV)
+        tokens = torch.zeros((B, gamma), dtype=torch.int32, device=DEV)
+        uniforms = torch.full((B, gamma + 1), 0.5, device=DEV)
+        dl = torch.full((B,), gamma, dtype=torch.int32, device=DEV) if lens else None
+        ws, seen = sv.alloc_workspace(B, gamma, V, DEV), []
+        for dbg in (None, torch.empty((B, gamma + 1, 3), device=DEV)):
+            sv.spec_verify_ex("block", rows, rows[:, 1:].contiguous(), tokens, uniforms, 1.0, draft_lens=dl, workspace=ws, debug_out=dbg)
+            kernel = sv.spec_verify_debug_last_kernel()
+            seen.append((kernel, sv.spec_verify_debug_last_chain() if kernel == sv.binding.SV_KERNEL_FUSED else None))
+        assert seen[0] == seen[1], (B, sets)
+        forms.add(seen[0])
+    assert len(forms) == (3 if gamma > 4 else 2)             # the kernel for few resident sets, both forms of the fused one (short drafts: the chain)
+
+
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma,V,dtype,lens", [(40, 16, 20000, "bf16", False), (64, 8, 70001, "bf16", True), (150, 6, 9000, "f32", False),
                                                   (512, 2, 17000, "bf16", False)])
