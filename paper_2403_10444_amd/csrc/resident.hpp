@@ -38,7 +38,7 @@ inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths)
     const double sets = (f32 ? 1.8 : 2.5) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
     return (sets < few_positions ? sets : few_positions) * narrow;
 }
-constexpr int kResidentSetsForced = 3;        // the same when the testing hook asks for this kernel
+constexpr double kResidentSetsForced = 3.0;   // at least this where the testing hook asks for this kernel
 
 // (largest scaled logit, sum) of four words, one per lane of a quad: every lane of the quad gets the combination
 // (fixed order, the sums through exact powers of two).

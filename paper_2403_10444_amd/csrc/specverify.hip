@@ -266,7 +266,8 @@ FusedParams word_params(int algo, const void *target, const void *draft, const i
 }
 
 // The kernel for calls of few resident sets; SV_ERR_UNSUPPORTED for the calls it does not take (more workgroups than
-// resident_sets() times what the device keeps resident, rows of more than kResidentMaxGroups workgroups).
+// resident_sets() times what the device keeps resident - kResidentSetsForced where the testing hook asks for it and that is more -,
+// rows of more than kResidentMaxGroups workgroups).
 template <typename T, bool ALIGNED>
 sv_status_t launch_resident(int algo, const void *target, const void *draft, const int32_t *tokens, const int32_t *draft_lens,
                             size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd, const Layout &L,
@@ -278,7 +279,8 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     void (*kernel)(const FusedParams) = resident_verify_kernel<T, ALIGNED>;
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
-    const double sets = g_path.load() == 7 ? kResidentSetsForced : resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr);
+    double sets = resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr);
+    if (g_path.load() == 7 && sets < kResidentSetsForced) sets = kResidentSetsForced;
     if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,
                                       ws, accept_len, next_token, debug_out);

@@ -126,6 +126,22 @@ def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_ker
         sv.spec_verify_debug_config(RESIDENT, -1)
 
 
+@pytest.mark.parametrize("B,gamma,V,dtype,lens", [(560, 8, 5000, "bf16", True), (270, 8, 9000, "bf16", True), (440, 8, 3000, "bf16", False),
+                                                  (340, 8, 5000, "f32", True)])
+def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype, lens):
+    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths)."""
+    cfg = workloads.Config(f"forced_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 1.0, 0.8, False, 1)
+    inp = workloads.generate(cfg, seed=B, device=DEV)
+    dl = torch.tensor([1 + (b * 5) % gamma for b in range(B)], dtype=torch.int32, device=DEV) if lens else None
+    out = []
+    for path in (0, RESIDENT):
+        sv.spec_verify_debug_config(path, -1)
+        tau, y = sv.spec_verify_ex("block", inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 0.8, draft_lens=dl)
+        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT
+        out.append((tau.cpu().numpy(), y.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma", [(6, 5), (6, 64), (60, 8)])           # (60 x 9 x 3 workgroups: more than run at once)
 def test_identical_models_accept_everything(algo, B, gamma):
