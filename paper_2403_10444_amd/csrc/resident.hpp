@@ -32,11 +32,22 @@ constexpr int kResidentMaxGroups = 32;        // workgroups per row: one poll of
 //   22 / 26, 4.0 sets 28 / 28; V = 100277, gamma = 6: 3.4 sets 27.8 / 29.0
 // The line is the same with and without the report of every S_i, so that the report changes no decision (it favours the
 // large kernel: gamma = 8, V = 128256: 2.4 sets 32 / 30).
-inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths)
+inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths, bool aligned)
 {
     const double narrow = groups < 16 ? 1.0 + (16 - groups) / 40.0 : 1.0;
     const double sets = (f32 ? 1.8 : 2.5) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
-    return (sets < few_positions ? sets : few_positions) * narrow;
+    double line = (sets < few_positions ? sets : few_positions) * narrow;
+    // What that line misses for rows of a few workgroups, where the large kernel has less to gain, above all where rows are not
+    // 16-byte aligned.  3.0 sets of rows of one workgroup: float32, V = 2500, gamma = 8 28.1 / 31.2, gamma = 2 26.6 / 27.9; V = 8192, gamma = 8
+    // 39.7 / 42.0; bf16, V = 2500, gamma = 2 27.9 / 30.8.  Not aligned: float32, gamma = 8, V = 9001, 2.9 sets 30.9 / 34.1, V = 30001 35.2 / 36.8; bf16,
+    // V = 9001, gamma = 2, 2.9 sets 30.1 / 31.6.  Aligned float32: gamma = 8, 2.7 sets, V = 16000 34.2 / 36.3, V = 32000 35.0 / 33.9, 2.6 sets 33.2 / 34.9,
+    // gamma = 4 33.2 / 32.6; own lengths, gamma = 8, V = 32000, 3.0 sets 26.4 / 27.5.
+    if (groups == 1 || (!aligned && groups <= (f32 ? 4 : 2))) line = line > 3.0 ? line : 3.0;
+    else if (f32 && groups <= 4 && gamma >= 6) { const double to = own_lengths ? 3.0 : groups == 2 ? 2.8 : 2.6; line = line > to ? line : to; }
+    // ... and where it goes beyond three sets though the large kernel is the faster one there: bf16, V = 24000, 3.2 sets, gamma = 4 32.2 / 29.3, gamma = 6
+    // 32.7 / 30.8; own lengths, V = 65536, 3.6 sets, gamma = 4 27.3 / 25.9, gamma = 8 25.3 / 23.8
+    if (own_lengths ? groups >= 5 : groups >= 3 && gamma < 8) line = line < 3.0 ? line : 3.0;
+    return line;
 }
 constexpr double kResidentSetsForced = 3.0;   // at least this where the testing hook asks for this kernel
 

@@ -279,7 +279,7 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     void (*kernel)(const FusedParams) = resident_verify_kernel<T, ALIGNED>;
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
-    double sets = resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr);
+    double sets = resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr, ALIGNED);
     if (g_path.load() == 7 && sets < kResidentSetsForced) sets = kResidentSetsForced;
     if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,

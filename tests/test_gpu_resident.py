@@ -142,6 +142,21 @@ def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
+# (both sides of the line between this kernel and the large one where rows are a few workgroups wide, and where drafts have
+# their own lengths: B such that the call is just below or above so many resident sets)
+@pytest.mark.parametrize("B,gamma,V,dtype,lens,kernel", [
+    (340, 8, 2500, "f32", False, "RESIDENT"), (342, 8, 2500, "f32", False, "FUSED"),          # rows of one workgroup: 3.0 sets
+    (1279, 2, 3000, "bf16", False, "RESIDENT"), (1282, 2, 3000, "bf16", False, "FUSED"),
+    (169, 8, 9001, "f32", False, "RESIDENT"), (158, 8, 9000, "f32", False, "RESIDENT"),       # two: 3.0, aligned 2.8
+    (162, 8, 9000, "f32", False, "FUSED"), (73, 8, 25000, "f32", False, "RESIDENT"), (75, 8, 25000, "f32", False, "FUSED"),
+    (52, 8, 65536, "bf16", True, "RESIDENT"), (56, 8, 65536, "bf16", True, "FUSED")])         # own lengths, eight: 3.0
+def test_the_line_to_the_large_kernel(B, gamma, V, dtype, lens, kernel):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"line_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 0.7, 0.9, False, 1)
+    _check(dict(cfg=cfg, algo="block", path="default", top_k=0, use_lens=lens, pad_t=0, pad_d=0, lens_seed=B), B + V, False)
+    assert sv.spec_verify_debug_last_kernel() == getattr(binding, "SV_KERNEL_" + kernel)
+
+
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma", [(6, 5), (6, 64), (60, 8)])           # (60 x 9 x 3 workgroups: more than run at once)
 def test_identical_models_accept_everything(algo, B, gamma):
