@@ -24,7 +24,12 @@
 namespace sv {
 
 constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: up to how many each workgroup forms its position's weight
-constexpr unsigned kProbsAtOnce = 1280;   // workgroups that run at once, or nearly
+// Workgroups that run at once, or nearly, and what they read of the target rows: up to there forming the weights in every workgroup
+// costs no more than a launch in front (Alg. 1; every workgroup / in front, gamma = 8: V = 128256: bf16 864 workgroups 13.2 / 14.2 us, 1152
+// 14.4 / 14.3, 1440 15.3 / 14.9; float32 432 14.1 / 15.6, 576 15.1 / 14.7, 1152 20.1 / 16.6; V = 8192: bf16 1098 15.1 / 15.3, 1494 16.4 / 15.4; float32
+// 693 17.0 / 16.9, 1098 21.3 / 18.2; gamma = 16, V = 500, float32: 816 12.3 / 14.7)
+constexpr unsigned kProbsAtOnce = 1280;
+constexpr size_t kProbsAtOnceBytes = 20u << 20;
 constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the finishing kernel keeps in LDS (32 KB)
 
 struct ProbWeight {

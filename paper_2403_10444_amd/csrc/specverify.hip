@@ -151,14 +151,14 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     ProbWeight *weights = reinterpret_cast<ProbWeight *>(ws + L.off_coef);
     const unsigned blocks = (unsigned)((size_t)B * (gamma + 1) * L.nchunks);
     // A position's weight: formed by each of its workgroups under its loads (B = 64, gamma = 8, V = 128256, bf16: 58 -> 51 us,
-    // 1 sequence 18 -> 14), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
-    // (Alg. 1 unless every sum is reported: 25 us against 48 there, unless the call runs at once anyway: 8 sequences of
-    // V = 32000 16.8 against 12.7) and where there are many of them with less to read
+    // 1 sequence 18 -> 14; float32, B = 48 83 -> 69, 72 with the kernel in front), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
+    // (Alg. 1 unless every sum is reported: 25 us against 48 there, unless the call runs at once anyway: kProbsAtOnce) and where there are many of them with less to read
     // than the weight takes to form (4096 sequences of 8 over 500 tokens: 150 us against 185, and 89 since short rows leave
     // out the vectors beyond them).
     const int every_sum = debug_out ? 1 : 0;
     const bool many_short = V <= kChunk / 2 && (long long)B * (gamma + 1) > kProbsFormMax;
-    const bool in_front = (algo == kToken && !every_sum && blocks > kProbsAtOnce) || many_short;
+    const size_t row_bytes = (size_t)blocks * (V < kChunk ? V : kChunk) * sizeof(T);       // the target rows' (the last chunk counted whole)
+    const bool in_front = (algo == kToken && !every_sum && (blocks > kProbsAtOnce || row_bytes > kProbsAtOnceBytes)) || many_short;
     if (in_front)
         probs_weights_kernel<T><<<B, 64, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, gamma, algo, weights, uniforms, every_sum);
     void (*const residual)(const T *, const T *, size_t, size_t, const int32_t *, const int32_t *, const float *, int, int, int, int, int, float2 *, ProbWeight *) =

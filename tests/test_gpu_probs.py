@@ -148,3 +148,16 @@ def test_weights_and_walk_at_their_edges(algo, B, gamma, V, dtype):
     for key, plain in (("accept_len", tau), ("next_token", y)):
         assert np.array_equal(got[key][safe], ref[key][safe]), key
         assert np.array_equal(got[key], plain.cpu().numpy()), key
+
+
+@pytest.mark.parametrize("B,dtype", [(80, "f32"), (81, "f32"), (160, "bf16"), (161, "bf16")])
+def test_token_verification_on_both_sides_of_what_runs_at_once(B, dtype):
+    """Without the report the weights of Alg. 1 come from a kernel in front from that many workgroups on (eight per sequence here)."""
+    import paper_2403_10444_amd as sv
+    cfg = _custom(B, 3, 9000, dtype, sigma_t=2.0, sigma_d=0.6, T=1.0)
+    P, Q, inp = _probs_inputs(cfg, seed=B)
+    ref = _run_oracle("token", P, Q, inp)
+    safe = ref["margins"].min(axis=1) >= parity.MARGIN
+    assert safe.mean() > 0.95
+    tau, y = sv.spec_verify_probs("token", P, Q, inp["draft_tokens"], inp["uniforms"])
+    assert np.array_equal(tau.cpu().numpy()[safe], ref["accept_len"][safe]) and np.array_equal(y.cpu().numpy()[safe], ref["next_token"][safe])
