@@ -89,7 +89,7 @@ typedef unsigned long long u64;
 // The words of one copy (see the head of this file).
 struct Words {
     u64 *ratio;           // [B, gamma]               log2 r_{i+1} as double bits, two lowest bits: flags (pack_ratio); by the leader of row pair i
-    u64 *lw;              // [B, gamma]               calls larger than one resident set: log2 w_{i+1} as double bits, lowest bit set
+    u64 *lw;              // [B, gamma]               calls with the chain (see the kernel): log2 w_{i+1} as double bits, lowest bit set
                           //                          (Alg. 1: 0 while every test up to i + 1 has passed, kLog2RatioFloor afterwards); by
                           //                          the leader of row pair i
     u64 *rowres;          // [B, gamma]               what position i contributes to tau and Y (pack_rowres): whether its accept test
@@ -720,10 +720,8 @@ __device__ __forceinline__ u64 first_sweep_row(float (&x)[LANE], float k, float 
 // workgroup's record `stamps`; the default build has none of it.
 #ifdef SV_PROFILE
 #define SV_STAMP(slot) do { if (stamps && threadIdx.x == 0) stamps[slot] = wall_clock64(); } while (0)
-#define SV_NOTE(slot, value) do { if (stamps && threadIdx.x == 0) stamps[slot] = (value); } while (0)
 #else
 #define SV_STAMP(slot) do { } while (0)
-#define SV_NOTE(slot, value) do { } while (0)
 #endif
 
 // ------------------------------------------------------------------ the accept test of one position
@@ -1299,8 +1297,8 @@ void fused_verify_kernel(const FusedParams P)
     if (wave == 0) {
         SV_STAMP(1);
         const Words W = SV_WORDS;
-        // (where the look at the start came too early for the chain's word, the second look goes out in front of the
-        // workgroup's own words: one round trip for both, not one after the other)
+        // (the first look at the chain's word goes out in front of the workgroup's own words: one round trip for both, not one
+        // after the other)
         if (early && chain) wt = ld_u64(SV_LW_WORD);
         publish_group_words(wave_words, W.pgrp + 2 * (drow * nwg + wg_x), W.qgrp + 2 * (drow * nwg + wg_x));
         bool wanted = true;

@@ -31,7 +31,7 @@ constexpr int kDefaultSpinLimit = 1 << 20;
 // launches of whole sequences or rows (2^24 + 3 rows of 2049 logits to draw from, 256 threads each: three rows were drawn).
 constexpr unsigned long long kMaxLaunchThreads = 0xffffffffull;
 
-std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of one resident set (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
+std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of few resident sets (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
 std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
 std::atomic<int> g_last_chain{-1};                  // whether the last call on the fused kernel had the chain
@@ -304,18 +304,18 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     const int lane_logits = large ? kLaneLarge : kLaneSmall;
     const int nu = (V + kWaves * kWave * lane_logits - 1) / (kWaves * kWave * lane_logits) * kWaves;
     // the instantiations for this row width (one or two words of a row per lane of the collecting wave), with and without
-    // the chain, and their resident workgroups
-    static std::atomic<int> cap[2][2], cap_chain[2][2];
+    // the chain (the hook's larger units always have it), and their resident workgroups
+    static std::atomic<int> cap[2], cap_chain[2][2];
     const int nwg = nu / kWaves;
     const int nw_log = nwg <= kWave ? 0 : 1;
     void (*ratios)(const FusedParams) = nullptr, (*chain)(const FusedParams) = nullptr;
 #define SV_PICK(LN, CH) (nw_log == 0 ? fused_verify_kernel<T, ALIGNED, 1, LN, CH> : fused_verify_kernel<T, ALIGNED, 2, LN, CH>)
     if constexpr (kLargeOk) {
-        if (large) { ratios = SV_PICK(kLaneLarge, false); chain = SV_PICK(kLaneLarge, true); }
+        if (large) chain = SV_PICK(kLaneLarge, true);
     }
     if (!large) { ratios = SV_PICK(kLaneSmall, false); chain = SV_PICK(kLaneSmall, true); }
 #undef SV_PICK
-    const int with_ratios = resident_workgroups(ratios, cap[nw_log][large ? 1 : 0]), with_chain = resident_workgroups(chain, cap_chain[nw_log][large ? 1 : 0]);
+    const int with_chain = resident_workgroups(chain, cap_chain[nw_log][large ? 1 : 0]), with_ratios = large ? with_chain : resident_workgroups(ratios, cap[nw_log]);
     const int capacity = with_ratios < with_chain ? with_ratios : with_chain;
     const int wpr = nwg;
     // a row's workgroups wait for each other and must fit on the device together, with room to spare
@@ -345,7 +345,7 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     // reported nobody asks for w_i before the row's words are in, which favours the chain earlier (gamma = 8: 2.4 sets 30 / 30, 3.6 sets
     // 37 / 35); the line is the same nevertheless: the two ways round log2 w_i differently, and the report changes no decision.
     const int forced_chain = g_chain.load();
-    const bool in_chain = P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma);
+    const bool in_chain = large || (P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma));
     (in_chain ? chain : ratios)<<<grid, kThreads, 0, stream>>>(P);
     g_last_chain.store(in_chain ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;

@@ -155,7 +155,7 @@ void tiny_verify_kernel(const FusedParams P)
     }
     __syncthreads();
     SV_STAMP(3);
-    // ---- log2 r_{i+1} (lane i) and the weights: as the large kernel forms them for calls of one resident set
+    // ---- log2 r_{i+1} (lane i) and the weights: as the large kernel forms them without the chain
     u64 ratio_word = 0;
     if (wave == 0) {
         if (lane < gb) {
