@@ -123,6 +123,36 @@ def test_weights_from_the_ratios_of_all_positions(block, monkeypatch):
         _check(dict(case, path="fused-ratios"), 900 + 20 * block + j, False)
 
 
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", [(16, 8, 40000, "bf16"), (40, 16, 9000, "f32"), (300, 4, 20000, "bf16")])
+def test_a_wait_for_ratios_that_runs_out_is_reported_not_hung(B, gamma, V, dtype, algo):
+    """The same form with a spin limit of zero: every wave that finds a word missing gives up at once, the kernel ends normally,
+    a sequence that any of them belongs to reports -1 for both outputs and every other one is complete and right."""
+    cfg = workloads.Config(f"out_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 3.0, 1.0, 1.0, False, 1)
+    inp = workloads.generate(cfg, seed=14 + B, device=DEV)
+    ws = sv.alloc_workspace(B, gamma, V, DEV)
+    ref = parity.run_oracle(algo, inp, 1.0)
+    safe = ref["margins"].min(axis=1) >= parity.MARGIN
+    for limit in (0, 3, -1):                                 # (negative: the library's own limit, nothing runs out)
+        sv.spec_verify_workspace_init(ws, B, gamma, V)
+        sv.spec_verify_debug_config(6, limit)
+        try:
+            tau, y = parity.ALGOS[algo][1](inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 1.0, workspace=ws)
+            torch.cuda.synchronize()
+            status = sv.spec_verify_workspace_check(ws, B, gamma, V)
+        finally:
+            sv.spec_verify_debug_config(0, -1)
+        assert sv.spec_verify_debug_last_chain() == 0
+        tau, y = tau.cpu().numpy(), y.cpu().numpy()
+        failed = tau < 0
+        assert np.array_equal(failed, y < 0)
+        assert status in (0, 5) and (status == 5 or not failed.any())
+        if limit < 0:
+            assert status == 0
+        right = safe & ~failed
+        assert np.array_equal(tau[right], ref["accept_len"][right]) and np.array_equal(y[right], ref["next_token"][right])
+
+
 @pytest.mark.parametrize("lens", [False, True])
 @pytest.mark.parametrize("gamma,V,dtype", [(8, 9000, "bf16"), (16, 3000, "f32"), (4, 70000, "bf16")])
 def test_the_report_changes_neither_the_kernel_nor_the_way_to_w(gamma, V, dtype, lens):
