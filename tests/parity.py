@@ -40,6 +40,14 @@ ALGOS = {"block": (oracle.BLOCK, sv.spec_verify_block),
          "greedy": (oracle.GREEDY, sv.spec_verify_greedy)}
 
 
+def in_cell(weights, u, y):
+    """Whether token y can be the draw at uniform u from these weights (float64): it has weight, and u lies in its cell of the
+    normalised running sum or within MARGIN of it.  Decides about the uniforms next to an edge that `margins` excuses."""
+    c = np.cumsum(weights, dtype=np.float64)
+    below = c[y - 1] if y > 0 else 0.0
+    return bool(weights[y] > 0) and below / c[-1] - MARGIN <= u <= c[y] / c[-1] + MARGIN
+
+
 def run_gpu(algo, inputs, temperature, workspace=None):
     B, g1, V = inputs["target_logits"].shape
     dbg = torch.full((B, g1, 3), float("nan"), dtype=torch.float32, device=inputs["target_logits"].device)

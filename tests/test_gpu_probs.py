@@ -138,8 +138,9 @@ def test_weights_and_walk_at_their_edges(algo, B, gamma, V, dtype):
     import paper_2403_10444_amd as sv
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.0, sigma_d=0.4, T=1.0)
     P, Q, inp = _probs_inputs(cfg, seed=B + V)
-    inp["uniforms"][0, :] = 0.0                                       # the first tokens with weight
-    inp["uniforms"][1, gamma] = 1.0 - 2.0 ** -24                      # the last one, or next to it
+    inp["uniforms"][0, :] = 0.0                                       # the whole draft, then the first token with weight
+    P[0, gamma, :5] = 0.0
+    inp["uniforms"][1, gamma] = 1.0 - 2.0 ** -24                      # the last token with weight, or next to it
     ref = _run_oracle(algo, P, Q, inp)
     safe = ref["margins"].min(axis=1) >= parity.MARGIN
     assert safe[2:].all() or safe[2:].mean() > 0.99
@@ -148,6 +149,14 @@ def test_weights_and_walk_at_their_edges(algo, B, gamma, V, dtype):
     for key, plain in (("accept_len", tau), ("next_token", y)):
         assert np.array_equal(got[key][safe], ref[key][safe]), key
         assert np.array_equal(got[key], plain.cpu().numpy()), key
+    # the two rows of extreme uniforms, next to an edge by their nature
+    assert (got["accept_len"][0], got["next_token"][0]) == (gamma, 5)
+    assert ref["margins"][1, 0] >= parity.MARGIN and got["accept_len"][1] == ref["accept_len"][1]
+    t = int(ref["accept_len"][1])
+    weights = P[1, t].double().cpu().numpy()
+    if t < gamma:
+        weights = np.maximum(ref["dbg"][1, t, 0] * weights - Q[1, t].double().cpu().numpy(), 0.0)
+    assert parity.in_cell(weights, 1.0 - 2.0 ** -24, int(got["next_token"][1]))
 
 
 @pytest.mark.parametrize("B,dtype", [(80, "f32"), (81, "f32"), (160, "bf16"), (161, "bf16")])
