@@ -206,7 +206,7 @@ SmallLaunch small_launch(int B, int gamma, int V)
     if (V <= 64 * 8 && gamma < kTinyWaves) return small_launch_of<T, 64, 8>(B, gamma);
     if (V <= 16 * 32) return small_launch_of<T, 16, 32>(B, gamma);
     if (V <= 64 * 16) return small_launch_of<T, 64, 16>(B, gamma);
-    if (V <= 64 * 32 && (tiny_ok(gamma, V) || B > kSmallMinWide)) return small_launch_of<T, 64, 32>(B, gamma);
+    if (V <= kSmallMaxRow && (tiny_ok(gamma, V) || B > kSmallMinWide)) return small_launch_of<T, 64, 32>(B, gamma);
     return {nullptr, 0, 0};
 }
 

@@ -1,13 +1,18 @@
 // Small sequences: ONE workgroup (or wave) per sequence, nothing between workgroups.  First the kernel for sequences that fit
 // LDS, which the library takes for rows of more than 2048 logits; then the one that keeps shorter rows in registers.
 //
-// Where the 2 gamma + 1 rows of a sequence fit into LDS together ((2 gamma + 1) V <= kTinyMaxFloats logits: a few
-// positions over a vocabulary of a thousand tokens, the shape of the worked example of Sec. 2 scaled up), the whole
+// Where the 2 gamma + 1 rows of a sequence fit into LDS together ((2 gamma + 1) V <= kTinyMaxFloats logits; with V > 2048:
+// drafts of one token up to V = 4778, of two up to 2867), the whole
 // of Alg. 1 / Alg. 2 / Alg. 4 for that sequence is a handful of passes over LDS by one workgroup of sixteen waves, with
 // barriers where the large kernel has words that travel through device memory: a call is one read of the logits and
 // seven barriers long instead of six dependent round trips through memory.  The arithmetic is the large kernel's:
 // base-2 exponentials in float against an integer shift per row, sums of them in double, log2 r_i, w_i, h_i in double,
 // residual terms in float with the larger of the two row factors taken out, the draw of Y in vocabulary order.
+// What bounds it: its chain for a few sequences; for many, that two workgroups of 1024 threads and 56 KB share a compute unit.
+// Against the kernel for few resident sets / the large one (us): V = 2049, gamma = 2, float32: 1 sequence 9.8 / 9.0 / 15, 1000 25 / 29 / 33,
+// 8192 175 / - / 215; gamma = 1, bf16: 64 10.4 / 10.7 / 12.9, 8192 158 / - / 113; V = 4778, gamma = 1, bf16: 1 14.5 / 9.1 / 10.9, 8192 256 / - / 110.
+// It is the better one for float32 drafts of two only, by up to a fifth; elsewhere the others have overtaken it since rows of any alignment
+// are read with sixteen-byte loads.
 #pragma once
 
 #include "fused.hpp"
@@ -16,6 +21,9 @@ namespace sv {
 
 constexpr int kTinyThreads = 1024, kTinyWaves = kTinyThreads / kWave;
 constexpr int kTinyMaxFloats = 14336;               // logits of one sequence that the workgroup keeps in LDS (56 KB)
+constexpr int kSmallMaxRow = 64 * 32;               // logits of the widest row that the other kernel takes
+// (rows here are longer, so that drafts are of one or two tokens; with the arrays below sized for five rows the kernel came out
+// 1 % slower in 140 calls)
 constexpr int kTinyMaxRows = 2 * SV_MAX_GAMMA + 1;
 constexpr int kTinyMaxChunks = (kTinyMaxFloats / 3 + kWave - 1) / kWave;     // 64-token chunks of the widest row (gamma = 1)
 

@@ -194,6 +194,43 @@ def test_workspace_must_be_initialised_for_the_shape():
     assert bool((tau == -1).all()) and bool((y == -1).all())
 
 
+# ---- the kernel that keeps the rows in LDS, which rows of more than 2048 logits reach (shorter ones, above and below, stay in
+# registers): the edges of its range, draft lengths, masked logits, padded rows, the degenerate inputs, the workspace's contract
+LDS_SHAPES = [(40, 1, 2049, "f32"), (33, 1, 4778, "bf16"), (17, 2, 2867, "f32"), (24, 2, 2053, "bf16"), (1, 1, 3001, "bf16")]
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", LDS_SHAPES)
+def test_rows_in_lds(B, gamma, V, dtype, algo):
+    from tests.test_gpu_random_shapes import _check
+    cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=0.8, T=0.9)
+    for n, (lens, pad_t, pad_d, top_k) in enumerate([(False, 0, 0, 0), (True, 3, 8, 0), (True, 16, 5, 20), (False, 0, 0, 3)]):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, False)
+        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_TINY
+    sv.spec_verify_debug_config(TINY, -1)
+    inp = workloads.generate(cfg, seed=V, device=DEV)
+    for value in (0.0, 1.0 - 2.0 ** -24):
+        inp2 = dict(inp, uniforms=torch.full_like(inp["uniforms"], value))
+        parity.compare(parity.run_gpu(algo, inp2, 1.0), parity.run_oracle(algo, inp2, 1.0), greedy=algo == "greedy")
+    # the same distributions: everything is accepted; disjoint ones: nothing is
+    same = dict(inp, draft_logits=inp["target_logits"][:, :gamma].contiguous())
+    got = parity.run_gpu(algo, same, 0.7)
+    assert np.all(got["accept_len"] == gamma)
+    parity.compare(got, parity.run_oracle(algo, same, 0.7), greedy=algo == "greedy")
+    if algo != "greedy":
+        apart = {k: v.clone() for k, v in inp.items()}
+        apart["target_logits"][..., : V // 2] -= 60.0
+        apart["draft_logits"][..., V // 2:] -= 60.0
+        q = torch.softmax(apart["draft_logits"].double(), -1)
+        apart["draft_tokens"] = torch.multinomial(q.view(-1, V), 1).view(B, gamma).to(torch.int32)
+        got = parity.run_gpu(algo, apart, 1.0)
+        assert np.all(got["accept_len"] == 0) and np.all(got["next_token"] >= V // 2)
+        parity.compare(got, parity.run_oracle(algo, apart, 1.0))
+    ws = sv.alloc_workspace(B + 1, gamma, V, DEV)                # prepared for another shape
+    tau, y = parity.ALGOS[algo][1](inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 1.0, workspace=ws)
+    assert bool((tau == -1).all()) and bool((y == -1).all())
+
+
 # ---- rows in the registers of groups of lanes: every group size and register count at its edges, drafts that fill a wave or
 # the workgroup (the last target row then has no group of its own), sequences that leave a shared workgroup partly empty,
 # draft lengths, padded and unaligned rows.  (The library's own choice: path 0.)
