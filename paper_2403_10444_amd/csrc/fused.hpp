@@ -477,6 +477,20 @@ template <int G> __device__ __forceinline__ double group_scan(double v)
     v += dpp_shift_double<0x118>(v);
     return v;
 }
+// Where t falls among the entries z of the lanes (inclusive running sums `inc`; lanes beyond the entries hold 0):
+// the first entry whose running sum exceeds t, with what is left of t inside it; when rounding leaves none, the last
+// entry that has any mass, and all of it.
+__device__ __forceinline__ int locate_entry(double z, double inc, double t, double &t_inside)
+{
+    const u64 hit = __ballot(inc > t), nz = __ballot(z > 0.0);
+    if (hit) {
+        const int e = __ffsll((long long)hit) - 1;
+        t_inside = t - read_lane_double(inc - z, e);
+        return e;
+    }
+    t_inside = INFINITY;
+    return nz ? 63 - __clzll((long long)nz) : 0;
+}
 // The draw from weights that a group holds in registers: weight(j), j = v * KVEC + e, is the lane's weight of token
 // (v * G + lane in the group) * KVEC + e, v < nv.  The first token whose running sum (in double, in vocabulary order:
 // vector, lane, element) exceeds `threshold` (of the weights' total); where rounding leaves none, the last with weight, and

@@ -234,15 +234,6 @@ __device__ __forceinline__ void prob_wave_weights(const T *prow, const T *qrow, 
     }
 }
 
-// Sums and inclusive sums over the lanes of a wave in double, through DPP (fixed orders).
-__device__ __forceinline__ double wave_total_double(double v)
-{
-    double first, second;
-    halves_sum_f64(v, first, second);
-    return first + second;
-}
-__device__ __forceinline__ double wave_inclusive_scan_double(double v) { return wave_scan(v); }
-
 template <typename T, bool ALIGNED>
 __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
     const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
@@ -301,8 +292,8 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
                 acc += (double)v.x; rej += (double)v.y;
             }
         }
-        acc = wave_total_double(acc);
-        if (algo == kGreedy) rej = wave_total_double(rej);
+        acc = group_sum<kWave>(acc);
+        if (algo == kGreedy) rej = group_sum<kWave>(rej);
         if (lane == 0) { S[i] = acc; R[i] = rej; }
     }
     __syncthreads();
@@ -355,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         double sum = 0.0;
 #pragma unroll
         for (int e = 0; e < kPerThread; ++e) sum += (double)wgt[e];
-        sum = wave_total_double(sum);
+        sum = group_sum<kWave>(sum);
         __syncthreads();
         if (lane == 0) wave_tot[wave] = sum;
         __syncthreads();
@@ -383,7 +374,7 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         for (int c0 = 0; c0 < nchunks && chunk < 0; c0 += 64) {
             const int c = c0 + lane;
             const double v = c < nchunks ? (double)(keep ? kept[tau * nchunks + c] : pp[c].x) : 0.0;
-            const double inc = wave_inclusive_scan_double(v) + carry;
+            const double inc = wave_scan(v) + carry;
             const unsigned long long nz = __ballot(v > 0.0), hit = __ballot(c < nchunks && inc > t);
             if (nz) last_nonzero = c0 + 63 - __clzll((long long)nz);
             if (hit) {

@@ -72,21 +72,6 @@ __device__ __forceinline__ double late_double(float v)
     return (double)v;
 }
 
-// Where t falls among the entries z of the lanes (inclusive running sums `inc`; lanes beyond the entries hold 0):
-// the first entry whose running sum exceeds t, with what is left of t inside it; when rounding leaves none, the last
-// entry that has any mass, and all of it.
-__device__ __forceinline__ int locate_entry(double z, double inc, double t, double &t_inside)
-{
-    const u64 hit = __ballot(inc > t), nz = __ballot(z > 0.0);
-    if (hit) {
-        const int e = __ffsll((long long)hit) - 1;
-        t_inside = t - read_lane_double(inc - z, e);
-        return e;
-    }
-    t_inside = INFINITY;
-    return nz ? 63 - __clzll((long long)nz) : 0;
-}
-
 // The draw inside one wave's unit of 64 * LANE logits (vocabulary order inside the unit: vector, lane, element), in two
 // steps.  First, by any wave: `sums` holds the unit's weights summed per (vector, lane), in that order (64 * NV floats
 // in LDS); every lane takes NV consecutive ones, one scan over the wave finds the lane and that lane the entry whose

@@ -74,20 +74,6 @@ __device__ __forceinline__ SampleEntry sweep_unit(RawSlice<T, false, kLaneSmall>
     return e;
 }
 
-// Where t falls among the lanes' sums z (inclusive running sums `inc`): the first lane whose running sum exceeds t, with
-// what is left of t there; rounding may leave none: then the last with any weight, and all of it.
-__device__ __forceinline__ int locate_sum(double z, double inc, double t, double &left)
-{
-    const u64 hit = __ballot(inc > t), nz = __ballot(z > 0.0);
-    if (hit) {
-        const int l = __ffsll((long long)hit) - 1;
-        left = t - read_lane_double(inc - z, l);
-        return l;
-    }
-    left = INFINITY;
-    return nz ? 63 - __clzll((long long)nz) : 0;
-}
-
 // The token, by one wave: units `from` to `end` of the row again, in vocabulary order (vector, lane, element), weights
 // relative to `shift`, the first whose running sum exceeds t (else the last with weight, token 0 if there is none).
 template <typename T>
@@ -189,9 +175,9 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
     const double z = of_wave.relative_to(M);
     const double inc = wave_scan(z);
     double t;                                                // what is left of u * C_total where the wave's stretch begins
-    if (locate_sum(z, inc, (double)u * read_lane_double(inc, kWave - 1), t) != w) return;
+    if (locate_entry(z, inc, (double)u * read_lane_double(inc, kWave - 1), t) != w) return;
     // ---- the entry of the wave's stretch, then the token
-    const int entry = locate_sum(z_lane, inc_lane, ldexp(t, (int)(shift_of(M) - shift_of(Mw))), t);
+    const int entry = locate_entry(z_lane, inc_lane, ldexp(t, (int)(shift_of(M) - shift_of(Mw))), t);
     const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.m), entry)));
     const int from = first_unit + entry * span;
     const int y = walk_units(row, V, k, shift, ldexp(t, (int)(shift_of(Mw) - shift)), from, min(from + span, end_unit));
@@ -234,7 +220,7 @@ void sample_finish_kernel(const T *logits, int V, int units, float k, const floa
     const float M = wave_max(own.m);
     const double z = own.relative_to(M), inc = wave_scan(z);
     double t;
-    const int holder = locate_sum(z, inc, (double)u * read_lane_double(inc, kWave - 1), t);
+    const int holder = locate_entry(z, inc, (double)u * read_lane_double(inc, kWave - 1), t);
     // the unit among the holder's neighbours: the first whose running sum exceeds t, else its last with weight
     int unit = 0;
     double left = INFINITY, running = 0.0;

@@ -27,14 +27,6 @@ constexpr int kSmallMaxRow = 64 * 32;               // logits of the widest row 
 constexpr int kTinyMaxRows = 2 * SV_MAX_GAMMA + 1;
 constexpr int kTinyMaxChunks = (kTinyMaxFloats / 3 + kWave - 1) / kWave;     // 64-token chunks of the widest row (gamma = 1)
 
-// The sum over the wave in double, through DPP (no trip through LDS per step).
-__device__ __forceinline__ double tiny_wave_sum(double v)
-{
-    double first, second;
-    halves_sum_f64(v, first, second);
-    return first + second;
-}
-
 // What turns a row pair's exponentials xa = 2^(y_p - shift_p), xb = 2^(y_q - shift_q) into residual terms
 // max(w p - q, 0): with cp = 2^(shift_p - L_p + log2 w) and cq = 2^(shift_q - L_q) the term is max(xa cp - xb cq, 0);
 // the larger factor is taken out (`scale`), so the other one, `f`, is a ratio <= 1 rounded once from double and
@@ -158,7 +150,7 @@ void tiny_verify_kernel(const FusedParams P)
             xr[j] = e;
             acc += (double)e;
         }
-        const double z = tiny_wave_sum(acc);
+        const double z = group_sum<kWave>(acc);
         if (lane == 0) { L[r] = (double)sh + log2_precise(z); Mk[r] = Mw; shift[r] = sh; }
     }
     __syncthreads();
@@ -189,7 +181,7 @@ void tiny_verify_kernel(const FusedParams P)
         double acc = 0.0;
 #pragma unroll 4
         for (int j = lane; j < V; j += kWave) acc += (double)tiny_term(xa, xb, j, c);
-        const double s = tiny_wave_sum(acc) * c.scale;
+        const double s = group_sum<kWave>(acc) * c.scale;
         if (lane == 0) S[i] = s;
     }
     __syncthreads();
@@ -250,14 +242,14 @@ void tiny_verify_kernel(const FusedParams P)
     const int chunks = (V + kWave - 1) / kWave;
     for (int ch = wave; ch < chunks; ch += kTinyWaves) {
         const int e = ch * kWave + lane;
-        const double s = tiny_wave_sum(e < V ? (double)tiny_term(xa, xb, e, c) : 0.0);
+        const double s = group_sum<kWave>(e < V ? (double)tiny_term(xa, xb, e, c) : 0.0);
         if (lane == 0) chunk_total[ch] = s;
     }
     __syncthreads();
     if (wave != 0) return;
     SV_STAMP(7);
     double total = 0.0;
-    for (int c0 = 0; c0 < chunks; c0 += kWave) total += tiny_wave_sum(c0 + lane < chunks ? chunk_total[c0 + lane] : 0.0);
+    for (int c0 = 0; c0 < chunks; c0 += kWave) total += group_sum<kWave>(c0 + lane < chunks ? chunk_total[c0 + lane] : 0.0);
     const double t = (double)eta_s[gb] * total;
     // the chunk: the first whose running sum exceeds t (rounding may leave none: then the last with any weight)
     int chunk = -1, last_chunk = 0;
