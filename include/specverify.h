@@ -152,15 +152,16 @@ void spec_verify_debug_profile(void *device_buffer);
  *   tokens    [rows]     int32 out, device
  * Asynchronous on `stream`, allocates nothing.  SV_ERR_INVALID_ARG for null pointers, rows < 1,
  * V < 1, a temperature that is not positive and finite or an unknown dtype; SV_ERR_UNSUPPORTED
- * for more than 2^31 - 1 rows.
+ * for more than 2^31 - 1 rows.  Rows too few to fill the device are spread over it in two launches where there
+ * is scratch memory for them (64 rows of 128256 bf16 logits: 8.8 us against 13.4): on the null stream
+ * (`stream` NULL) the library has 4 MiB of its own per GPU, on any other stream the next call takes the caller's.
  */
 sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype,
                                float temperature, const float *uniforms, int32_t *tokens, void *stream);
 
 /*
- * The same with scratch memory from the caller (device, 16-byte aligned, contents ignored and left undefined): rows too
- * few to fill the device are then spread over it, in two launches (64 rows of 128256 bf16 logits: 8.8 us
- * against 13.4).
+ * The same with scratch memory from the caller (device, 16-byte aligned, contents ignored and left undefined), on any
+ * stream and under graph capture.
  * spec_sample_workspace_bytes says how much is wanted; 0 where none would be used, and with a NULL workspace the call
  * is spec_sample_tokens.  SV_ERR_WORKSPACE_TOO_SMALL below that size.  Calls that overlap need a workspace each.
  */

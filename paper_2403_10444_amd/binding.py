@@ -225,10 +225,10 @@ def spec_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature
     """One token per row of ``logits`` [..., V] from softmax(logits / T) by the inverse CDF at ``uniforms``
     [...] (the drafting step of Alg. 3).  Returns int32 tokens of the shape of ``uniforms``.
 
-    Rows too few to fill the device are spread over it where there is scratch memory: ``workspace`` (contiguous uint8 device
-    tensor of `spec_sample_workspace_bytes`; calls that overlap need one each), on any stream and under graph capture.
-    A call that hands over ``tokens`` allocates nothing, so without a ``workspace`` it does without; a call that makes its
-    own output takes scratch memory from the same allocator."""
+    Rows too few to fill the device are spread over it where there is scratch memory: on the null stream (torch's default one)
+    the library has its own; elsewhere ``workspace`` (contiguous uint8 device tensor of `spec_sample_workspace_bytes`; calls
+    that overlap need one each), on any stream and under graph capture.  A call that hands over ``tokens`` allocates nothing;
+    one that makes its own output on another current stream takes scratch memory from the same allocator."""
     V = logits.shape[-1]
     rows = logits.numel() // V
     if not logits.is_cuda or not logits.is_contiguous() or not uniforms.is_contiguous():
@@ -238,15 +238,16 @@ def spec_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature
     if workspace is not None and (workspace.get_device() != logits.get_device() or not workspace.is_contiguous()):
         raise ValueError("the workspace must be a contiguous tensor on the logits' device")
     lib = _lib or load()
+    current = stream is None
+    if current:
+        stream = _current_stream(logits.get_device())
     if tokens is None:
         tokens = torch.empty(uniforms.shape, dtype=torch.int32, device=logits.device)
-        if workspace is None and stream is None:
+        if workspace is None and current and stream:
             # (the allocator keeps both for the current stream: a stream of the caller's own is not known to it)
             n = lib.spec_sample_workspace_bytes(rows, V)
             if n:
                 workspace = torch.empty(n, dtype=torch.uint8, device=logits.device)
-    if stream is None:
-        stream = _current_stream(logits.get_device())
     code = lib.spec_sample_tokens_ws(logits.data_ptr(), rows, V, _dtype_code(logits), float(temperature), uniforms.data_ptr(),
                                      tokens.data_ptr(), None if workspace is None else workspace.data_ptr(),
                                      0 if workspace is None else workspace.nbytes, stream)

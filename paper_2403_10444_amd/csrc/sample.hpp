@@ -52,6 +52,12 @@ struct SampleEntry {
     __device__ __forceinline__ double relative_to(float M) const { return m > -INFINITY ? ldexp(z, (int)(shift_of(m) - shift_of(M))) : 0.0; }
 };
 
+// Entries of the calls on the null stream that bring no scratch memory: the null stream exists once per device, is never
+// destroyed nor captured, and what runs on it runs in turn, so that one array is enough for all of them and every GPU that the
+// library runs on has its own (a call's two launches must follow each other there: the host holds a lock over them).
+constexpr int kSampleOwnEntries = 1 << 18;                   // 4 MiB
+__device__ SampleEntry g_null_stream_entries[kSampleOwnEntries];
+
 // One unit of a row as loaded -> its entry (every lane gets it).  `left`: logits of the row from the unit's start on.
 template <typename T>
 __device__ __forceinline__ SampleEntry sweep_unit(RawSlice<T, false, kLaneSmall> &raw, int left, float k)
@@ -185,7 +191,7 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
 }
 
 // The same in two launches, for rows too few to fill the device: every wave sweeps one unit and leaves its entry in
-// `entries` [rows, units]; then one wave per row scans them (up to kSampleSplitUnits units, a stretch of neighbours per
+// `entries` [rows, units] (NULL: the null stream's); then one wave per row scans them (up to kSampleSplitUnits units, a stretch of neighbours per
 // lane), finds the unit and walks it.
 template <typename T>
 __global__ __launch_bounds__(kThreads)
@@ -198,7 +204,7 @@ void sample_units_kernel(const T *logits, int V, int units, float k, SampleEntry
     RawSlice<T, false, kLaneSmall> raw;
     issue_loads<T, false, kLaneSmall>(logits + r * (size_t)V + at, 0, V - at, raw);
     const SampleEntry e = sweep_unit<T>(raw, V - at, k);
-    if ((threadIdx.x & 63) == 0) entries[r * units + unit] = e;
+    if ((threadIdx.x & 63) == 0) (entries ? entries : g_null_stream_entries)[r * units + unit] = e;
 }
 template <typename T>
 __global__ __launch_bounds__(kWave)
@@ -209,6 +215,7 @@ void sample_finish_kernel(const T *logits, int V, int units, float k, const floa
     const size_t r = blockIdx.x;
     const float u = load_uniform(uniforms + r);
     const int per = (units - 1) / kWave + 1;
+    if (!entries) entries = g_null_stream_entries;
     SampleEntry mine[kPer], own = {-INFINITY, 0.0};
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {

@@ -353,10 +353,10 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
 
 // The drafting step: how many waves share a row.
 template <typename T>
-sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, SampleEntry *entries, hipStream_t stream)
+sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, bool two_launches, SampleEntry *entries, hipStream_t stream)
 {
     const T *logits = static_cast<const T *>(logits_v);
-    if (entries) {
+    if (two_launches) {
         const int units = (V - 1) / kSampleUnit + 1;
         sample_units_kernel<T><<<dim3((unsigned)((units - 1) / kWaves + 1), (unsigned)rows), kThreads, 0, stream>>>(logits, V, units, k, entries);
         sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
@@ -495,6 +495,7 @@ struct StaticScratch {
 };
 std::mutex g_static_mutex;
 StaticScratch g_static[kMaxDevices];
+std::mutex g_null_stream_mutex;          // over the two launches of a drafting call on the null stream
 
 }  // namespace
 
@@ -630,15 +631,19 @@ sv_status_t spec_sample_tokens_ws(const void *logits, int64_t rows, int32_t V, s
     if (!(temperature > 0.f) || !isfinite(temperature)) return SV_ERR_INVALID_ARG;
     if (dtype != SV_DTYPE_F32 && dtype != SV_DTYPE_BF16) return SV_ERR_INVALID_ARG;
     if (rows > 0x7fffffffll) return SV_ERR_UNSUPPORTED;
-    const size_t wanted = workspace ? spec_sample_workspace_bytes(rows, V) : 0;
+    const size_t wanted = spec_sample_workspace_bytes(rows, V);
     if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return SV_ERR_INVALID_ARG;
-    if (workspace_bytes < wanted) return SV_ERR_WORKSPACE_TOO_SMALL;
-    SampleEntry *const entries = wanted ? static_cast<SampleEntry *>(workspace) : nullptr;
+    if (workspace && workspace_bytes < wanted) return SV_ERR_WORKSPACE_TOO_SMALL;
+    SampleEntry *const entries = static_cast<SampleEntry *>(workspace);
+    const bool null_stream = !workspace && !stream_v && wanted && wanted <= (size_t)kSampleOwnEntries * sizeof(SampleEntry);
+    const bool two_launches = wanted && (workspace || null_stream);
     const float k = (float)(1.4426950408889634074 / (double)temperature);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
+    std::unique_lock<std::mutex> lock(g_null_stream_mutex, std::defer_lock);
+    if (null_stream) lock.lock();
     return dtype == SV_DTYPE_F32
-        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, entries, stream)
-        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, entries, stream);
+        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, two_launches, entries, stream)
+        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, two_launches, entries, stream);
 }
 
 sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype, float temperature,

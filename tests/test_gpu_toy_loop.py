@@ -70,8 +70,8 @@ def test_sample_tokens_at_the_edges_of_its_kernels(rows, V, dtype):
     _check_rows(got, logits, u, 0.7, dtype)
 
 
-# (rows spread over the device through scratch memory: the edges of the units and of the rule, a stretch of several units per
-# lane; the same rows by one workgroup each, on an explicit stream, give the same tokens)
+# (rows spread over the device through scratch memory - the library's on the null stream, torch's on another current one -: the edges
+# of the units and of the rule, a stretch of several units per lane; and the same rows by one workgroup each, on an explicit stream)
 @pytest.mark.parametrize("rows,V,dtype", [(100, 49153, "bf16"), (101, 50257, "f32"), (104, 51200, "bf16"), (105, 51200, "f32"), (7, 131073, "bf16"),
                                           (64, 128256, "bf16"), (8, 262145, "f32"), (9, 1048576, "bf16"), (8, 1048577, "bf16")])
 def test_sample_tokens_in_two_launches(rows, V, dtype):
@@ -80,8 +80,47 @@ def test_sample_tokens_in_two_launches(rows, V, dtype):
     units = (V + 2047) // 2048
     wanted = sv.load().spec_sample_workspace_bytes(rows, V)
     assert wanted == (rows * units * 16 if 24 < units <= 512 and rows <= 4 * units else 0)
-    for stream in (None, torch.cuda.current_stream().cuda_stream):
-        _check_rows(sv.spec_sample_tokens(logits, ud, 0.7, stream=stream).cpu().numpy(), logits, u, 0.7, dtype)
+    side = torch.cuda.Stream()
+    assert torch.cuda.current_stream().cuda_stream == 0 and side.cuda_stream != 0
+    torch.cuda.synchronize()
+    null = sv.spec_sample_tokens(logits, ud, 0.7)
+    with torch.cuda.stream(side):
+        current = sv.spec_sample_tokens(logits, ud, 0.7)
+    one_each = sv.spec_sample_tokens(logits, ud, 0.7, tokens=torch.empty_like(null), stream=side.cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(null, current)                          # (the same kernels)
+    for tokens in (null, one_each):
+        _check_rows(tokens.cpu().numpy(), logits, u, 0.7, dtype)
+
+
+def test_sample_tokens_from_several_threads_and_streams():
+    """Threads that draw on the null stream at once share the library's scratch memory, call by call; others draw on streams
+    and workspaces of their own."""
+    import threading
+    n, rows, V = 4, 48, 60000
+    g = torch.Generator(device=DEV).manual_seed(17)
+    logits = [torch.randn((rows, V), generator=g, device=DEV).mul_(4.0).to(torch.bfloat16) for _ in range(n)]
+    uniforms = [torch.rand((rows,), generator=g, device=DEV) for _ in range(n)]
+    want = [sv.spec_sample_tokens(x, u, 0.8).clone() for x, u in zip(logits, uniforms)]
+    out = [torch.full((60, rows), -1, dtype=torch.int32, device=DEV) for _ in range(n)]
+    streams = [0, 0, 0, torch.cuda.Stream().cuda_stream]
+    ws = torch.empty(sv.spec_sample_workspace_bytes(rows, V), dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    start = threading.Barrier(n)
+
+    def draw(i):
+        start.wait()
+        for k in range(60):
+            sv.spec_sample_tokens(logits[i], uniforms[i], 0.8, tokens=out[i][k], stream=streams[i], workspace=ws if streams[i] else None)
+
+    threads = [threading.Thread(target=draw, args=(i,)) for i in range(n)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(n):
+        assert torch.equal(out[i], want[i].expand(60, rows)), i
 
 
 def test_sample_tokens_into_given_tokens_allocates_nothing():
