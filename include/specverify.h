@@ -96,10 +96,12 @@ sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_
 /* Testing hook, process-wide: `path` 0 = the library's choice by the shape of the call: sequences of rows of at
  * most 2048 logits, or whose 2 gamma + 1 rows fit into LDS together, (2 gamma + 1) V <= 14336: one workgroup
  * (or wave) per sequence; else, calls of at most a few times the workgroups that the device keeps resident
- * (two or three times) and rows of at most 32 * 8192 logits: the kernel for calls of few resident sets;
+ * (1.8 to 4.3 times, by type, row width, draft length and whether sequences bring their own) and rows of at
+ * most 32 * 8192 logits: the kernel for calls of few resident sets;
  * else the fused kernel where it takes the shape, else the staged kernels.  5 = the kernels of one workgroup
  * per sequence, as far as the sequence fits LDS; 7 = the
- * kernel for calls of few resident sets (calls beyond their limits are then refused), 1 = the
+ * kernel for calls of few resident sets, up to three times or the library's own line where that is more
+ * (calls beyond the limits of 5 and 7 are then refused), 1 = the
  * four-launch staged kernels, 2 = the
  * single-launch fused kernel (takes V <= 128 * 8192 and a device that keeps four rows'
  * workgroups resident; other shapes are then refused), 3 / 4 = the fused kernel with its

@@ -245,8 +245,8 @@ __device__ __forceinline__ unsigned wait_word32(const unsigned *p, int limit, bo
     return wait_word32(p, ld_u32(p), true, limit, gave_up);
 }
 
-// One step of a series in double.  FMA: as one operation (half the instructions and half the chain: 8192 toy sequences 12.4 ->
-// 11.8 us); the kernels at their register limit are faster, or spill less, with two (24 drafts of 4 over 50257 bf16 logits
+// One step of a series in double.  FMA: as one operation (half the instructions and half the chain: 8192 toy sequences, 12.1
+// us, 0.6 less); the kernels at their register limit are faster, or spill less, with two (24 drafts of 4 over 50257 bf16 logits
 // 14.9 against 15.1 us).
 template <bool FMA> __device__ __forceinline__ double series_step(double s, double t, double c)
 {

@@ -288,7 +288,7 @@ void tiny_verify_kernel(const FusedParams P)
 // weights, row factors, tests, all in double - is the first wave's, one position per lane; the other waves only sweep.
 // What bounds it: for a few sequences that chain of steps, for many the vector instructions.  Against one workgroup of
 // sixteen waves and 61 KB of LDS per sequence (above): one sequence, gamma = 4, V = 1000, float32 8.4 -> 6.2 us, 8192 of
-// them 152 -> 66; 8192 toy sequences, gamma = 10, V = 2, 126 -> 12.6.  Against the fused kernel, whose wave chunks such rows
+// them 152 -> 66; 8192 toy sequences, gamma = 10, V = 2, 126 -> 12.1.  Against the fused kernel, whose wave chunks such rows
 // fill by half: 8192 sequences, gamma = 10, V = 1000, bf16 544 -> 123; 1024, V = 2000 74 -> 39.
 // Rows of 1025 ... 2048 logits that do not fit LDS: from more than how many sequences on (below, the kernel for calls of
 // few resident sets spreads a sequence over several compute units: gamma = 10, V = 2000, this kernel / that one: 1 sequence
