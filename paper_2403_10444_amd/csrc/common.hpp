@@ -16,6 +16,10 @@ constexpr int kWaves = kThreads / 64;
 // log2 of the ratio r_i never goes below this: a drafted token whose target logit is -inf (masked out by
 // top-k / top-p warping) has r_i = 0, and exp2 of this is exactly 0 in double while sums of it stay finite
 constexpr double kLog2RatioFloor = -1.0e6;
+// A stretch of a row whose largest scaled logit is not above this carries no weight: masks are not always -inf (-1e9, -1e10 or the
+// type's lowest value are as common).  Above it the shift m k is rounded by at most 64, so that exponentials relative to it stay
+// finite; further down they would overflow float before the stretch is scaled to nothing.
+constexpr float kNoWeight = -0x1p31f;
 constexpr int kChunk = 8192;              // logits of one row handled by one workgroup
 constexpr int kWaveChunk = kChunk / kWaves;   // contiguous logits of one row handled by one wavefront
 constexpr int kPerThread = kChunk / kThreads; // logits of one row held by one thread

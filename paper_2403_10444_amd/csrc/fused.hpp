@@ -310,8 +310,9 @@ __device__ __forceinline__ double log2_precise(double z)
 
 // A unit's exponentials are taken relative to an INTEGER shift, the smallest one that keeps them at or below 1:
 // then sums of different units combine through exact powers of two.  The words carry the unit's largest scaled
-// logit itself (the row's maximum is wanted too); this is the shift that belongs to it.
-__device__ __forceinline__ float shift_of(float largest) { return largest > -INFINITY ? ceilf(largest) : 0.f; }
+// logit itself (the row's maximum is wanted too); this is the shift that belongs to it (0 where the unit carries no weight: its
+// exponentials are 0 then).
+__device__ __forceinline__ float shift_of(float largest) { return largest > kNoWeight ? ceilf(largest) : 0.f; }
 
 // Running combination of (largest scaled logit, sum) words: the sum of exp2 relative to the integer shift of the
 // largest so far, in double (the factors between units are exact).
@@ -711,7 +712,7 @@ __device__ __forceinline__ void unpack_slice(int unit_first, int V, RawSlice<T, 
 
 // First sweep over the logits the wave holds of one row: x[j] becomes exp2(x[j] * k - shift) with
 // the wave-uniform integer shift that belongs to the unit's largest scaled logit (shift_of; 0 when the whole unit
-// lies beyond the row).  Returns the unit's word: (k * largest logit, sum of the exponentials); (-inf, 0) beyond.
+// is masked out or lies beyond the row).  Returns the unit's word: (k * largest logit, sum of the exponentials); (-inf, 0) beyond.
 template <int LANE>
 __device__ __forceinline__ u64 first_sweep_row(float (&x)[LANE], float k, float &shift)
 {

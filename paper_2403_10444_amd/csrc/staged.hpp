@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kThreads) void row_stats_kernel(
         for (int e = 0; e < kVec; ++e) m = fmaxf(m, x[u][e]);
     m = block_max(m, lds);
     const float mk = m * k;
-    const float shift = m > -INFINITY ? mk : 0.f;       // a chunk without a finite logit (masked out, or beyond the row)
+    const float shift = mk > kNoWeight ? mk : 0.f;      // (a chunk that is masked out, or beyond the row)
 
     float s = 0.f;
 #pragma unroll
