@@ -310,9 +310,12 @@ __device__ __forceinline__ double log2_precise(double z)
 
 // A unit's exponentials are taken relative to an INTEGER shift, the smallest one that keeps them at or below 1:
 // then sums of different units combine through exact powers of two.  The words carry the unit's largest scaled
-// logit itself (the row's maximum is wanted too); this is the shift that belongs to it (0 where the unit carries no weight: its
-// exponentials are 0 then).
-__device__ __forceinline__ float shift_of(float largest) { return largest > kNoWeight ? ceilf(largest) : 0.f; }
+// logit itself (the row's maximum is wanted too); this is the shift that belongs to it.  A unit that carries no weight (masked
+// out, or beyond the row) has the lowest shift: its exponentials are 0 there, and so is the unit of its terms in every row,
+// however far below 0 the row's logits lie (a shift of 0 would make that unit 2^200 in a row of -200 and less: infinite).
+__device__ __forceinline__ float shift_of(float largest) { return fmaxf(ceilf(largest), kNoWeight); }
+// The exponent of a unit's terms relative to the row's factor (`row`: L_p or L_q, rounded); differences of two do not overflow.
+__device__ __forceinline__ int unit_exponent(float shift, double row) { return (int)fmax((double)shift - row, -0x1p30); }
 
 // Running combination of (largest scaled logit, sum) words: the sum of exp2 relative to the integer shift of the
 // largest so far, in double (the factors between units are exact).
@@ -710,9 +713,9 @@ __device__ __forceinline__ void unpack_slice(int unit_first, int V, RawSlice<T, 
     }
 }
 
-// First sweep over the logits the wave holds of one row: x[j] becomes exp2(x[j] * k - shift) with
-// the wave-uniform integer shift that belongs to the unit's largest scaled logit (shift_of; 0 when the whole unit
-// is masked out or lies beyond the row).  Returns the unit's word: (k * largest logit, sum of the exponentials); (-inf, 0) beyond.
+// First sweep over the logits the wave holds of one row: x[j] becomes exp2(x[j] * k - shift) with the wave-uniform integer
+// shift that belongs to the unit's largest scaled logit (shift_of).  Returns the unit's word: (k * largest logit, sum of the
+// exponentials); (-inf, 0) when the whole unit lies beyond the row.
 template <int LANE>
 __device__ __forceinline__ u64 first_sweep_row(float (&x)[LANE], float k, float &shift)
 {
@@ -1464,7 +1467,7 @@ void fused_verify_kernel(const FusedParams P)
 
         // ---- second sweep, from registers: w p(x) = xa * cp, q(x) = xb * cq with the wave-uniform cp = 2^(shiftA - A),
         // cq = 2^(shiftB - L_q): powers of two times the row's two fractions
-        const int ea = (int)((double)shiftA - row_values[3]), eq = (int)((double)shiftB - row_values[4]);
+        const int ea = unit_exponent(shiftA, row_values[3]), eq = unit_exponent(shiftB, row_values[4]);
         const double fq = row_values[5], frho = row_values[6];
         float acc = 0.f;
         {

@@ -420,7 +420,7 @@ void resident_verify_kernel(const FusedParams P)
     if (!row_flag[0]) return;
 
     // ---- second sweep, from registers (as in the large kernel): terms in [0, 1] in units of the larger row factor
-    const int ea = (int)((double)shiftA - row_values[3]), eq = (int)((double)shiftB - row_values[4]);
+    const int ea = unit_exponent(shiftA, row_values[3]), eq = unit_exponent(shiftB, row_values[4]);
     const double rho = ldexp(row_values[6], ea - eq);
     const bool q_units = rho <= 1.0;
     const float factor = q_units ? (float)rho : -(float)ldexp(row_values[7], eq - ea);
