@@ -287,7 +287,7 @@ void resident_verify_kernel(const FusedParams P)
         __syncthreads();
         if (row_flag[0] == 1 && wave == row_flag[1]) {
             const int off = draw_in_unit<kVec, LANE>([&](int j) { return xa[j]; }, row_values[0], draw_sums[wave]);
-            if (lane == 0) st_u64(y_word, pack_rowres(true, unit_first + off));
+            if (lane == 0) st_u64(y_word, pack_rowres(true, min(unit_first + off, V - 1)));
         }
         if (!leader) return;
 
@@ -411,6 +411,7 @@ void resident_verify_kernel(const FusedParams P)
                 kept_words[0] = own_word; kept_words[1] = prev_word; kept_words[2] = (u64)__double_as_longlong(log2w);
                 kept_words[3] = candidate ? 1 : 0;
                 kept_Mp = Mp;
+                draw_entry = 0;       // (never left to chance: with NaN sums the two looks at from_p below need not agree)
             }
         }
         if (lane == 0) row_flag[0] = needed ? 1 : 0;
@@ -540,7 +541,8 @@ void resident_verify_kernel(const FusedParams P)
         const int entry = __builtin_amdgcn_readfirstlane(draw_entry);      // (the same for the whole wave, and known to be)
         off = entry * kVec + walk_entry<kVec, LANE>(term, entry, row_values[0]);
     }
-    if (lane == 0) st_u64(W.rowres + drow, pack_rowres(row_flag[3] != 0, unit_first + off));
+    // (a row of which the arithmetic makes NaNs still ends inside the vocabulary)
+    if (lane == 0) st_u64(W.rowres + drow, pack_rowres(row_flag[3] != 0, min(unit_first + off, V - 1)));
     SV_STAMP(15);
 }
 

@@ -59,3 +59,23 @@ def test_drafting(T, added, dtype):
             got = sv.spec_sample_tokens(x, ud, T, tokens=torch.empty((rows,), dtype=torch.int32, device=DEV), stream=stream)
             torch.cuda.synchronize()
             assert np.array_equal(got.cpu().numpy()[safe], want[safe]), (V, stream)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_tokens_stay_inside_the_vocabulary_beyond_the_range_of_logits(dtype):
+    # (a row's largest scaled logit beyond 2^31: its exponentials overflow, what is accepted is not defined)
+    for V in (300, 2500, 5000, 50257):
+        cfg = workloads.Config(f"beyond_V{V}", 12, 4, V, dtype, 1.0, 0.5, 1.0, False, 1)
+        inp = workloads.generate(cfg, seed=V, device=DEV)
+        inp["target_logits"][::2, :, 3] = 1e10
+        inp["draft_logits"][::3, :, 5] = 1e10
+        for algo in ("block", "token", "greedy"):
+            for path in (0, 1, 3, 4, 6, 7):
+                sv.spec_verify_debug_config(path, -1)
+                try:
+                    tau, y = parity.ALGOS[algo][1](inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 1.0)
+                    torch.cuda.synchronize()
+                finally:
+                    sv.spec_verify_debug_config(0, -1)
+                assert 0 <= int(tau.min()) and int(tau.max()) <= cfg.gamma, (V, algo, path)
+                assert 0 <= int(y.min()) and int(y.max()) < V, (V, algo, path)
