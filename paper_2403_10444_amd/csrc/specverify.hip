@@ -1,8 +1,8 @@
 // Draft verification for speculative decoding on gfx950: the C ABI of include/specverify.h.
 //
 // Host side only: argument checks, workspace layout and kernel launches.  The kernels are in
-// fused.hpp (one launch, every logit read from HBM once; the default), resident.hpp (calls of few
-// resident sets), tiny.hpp (one workgroup or wave per sequence) and staged.hpp (four launches, no limit
+// fused.hpp (one launch, every logit read from HBM once; the default), resident.hpp and together.hpp (calls of few
+// resident sets, of one), tiny.hpp (one workgroup or wave per sequence) and staged.hpp (four launches, no limit
 // on the vocabulary size); probs.hpp holds the kernels for inputs that are probabilities already,
 // sample.hpp those of the drafting step.
 
@@ -20,6 +20,7 @@
 #include "staged.hpp"
 #include "tiny.hpp"
 #include "resident.hpp"
+#include "together.hpp"
 
 namespace {
 
@@ -275,13 +276,16 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
 {
     const int nwg = L.nu / kWaves;
     if (nwg > kResidentMaxGroups || B > 65535) return SV_ERR_UNSUPPORTED;
-    static std::atomic<int> cap;
+    static std::atomic<int> cap, cap_together;
     void (*kernel)(const FusedParams) = resident_verify_kernel<T, ALIGNED>;
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
     double sets = resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr, ALIGNED);
     if (g_path.load() == 7 && sets < kResidentSetsForced) sets = kResidentSetsForced;
     if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
+    // (a rule without the report, which changes no decision)
+    if (runs_together((long long)nwg * B * (gamma + 1), resident_workgroups(together_verify_kernel<T, ALIGNED, 1>, cap_together), nwg, gamma, ElemTraits<T>::kVec == 4))
+        kernel = nwg <= 4 ? together_verify_kernel<T, ALIGNED, 0> : nwg <= 16 ? together_verify_kernel<T, ALIGNED, 1> : together_verify_kernel<T, ALIGNED, 2>;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,
                                       ws, accept_len, next_token, debug_out);
     kernel<<<dim3((unsigned)nwg, (unsigned)B, (unsigned)(gamma + 1)), kThreads, 0, stream>>>(P);
