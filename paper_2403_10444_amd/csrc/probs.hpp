@@ -10,10 +10,12 @@
 //                             (numerator of the block acceptance formula; for greedy block verification,
 //                             Alg. 4, also the rejected mass sum_x max(q_i - w_i p_i, 0)); at the
 //                             sequence's last position the chunk's share of sum_x p(x)
-//   2. probs_finalize_kernel  one workgroup per sequence: S_i, h_i, the accept tests of Alg. 1 / 2 / 4,
+//   2. probs_finish           one workgroup per sequence: S_i, h_i, the accept tests of Alg. 1 / 2 / 4,
 //                             then the inverse-CDF draw of Y (pick the chunk from the partial sums,
 //                             re-read that one chunk)
-// (In some calls the weights come from a kernel in front, probs_weights_kernel, one wave per sequence.)
+// Calls whose workgroups all run at once have one launch: a sequence's last workgroup goes on with step 2.  Larger ones have a launch for it
+// (probs_finish_kernel): there the waiting workgroups, and the registers of step 2 in all of them, cost more than the second launch
+// (probs_at_once).  (In some calls the weights come from a kernel in front, probs_weights_kernel, one wave per sequence.)
 // What bounds it: the bytes, then the second launch.  B = 64, gamma = 8, V = 128256, bf16: 42.2 us (6.6 TB/s) for the first
 // kernel, 7.0 for the second, which took 10.7 while its threads read the chunk in stretches of 64 bytes each (uncoalesced)
 // and scanned all of it; now each wave reads a quarter, and the one that holds the token draws from its registers.
@@ -30,7 +32,12 @@ constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: u
 // 693 17.0 / 16.9, 1098 21.3 / 18.2; gamma = 16, V = 500, float32: 816 12.3 / 14.7)
 constexpr unsigned kProbsAtOnce = 1280;
 constexpr size_t kProbsAtOnceBytes = 20u << 20;
-constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the finishing kernel keeps in LDS (32 KB)
+// Calls of up to this many workgroups have one launch (`resident`: how many of that launch's run at once).  Two / one, us: bf16: B = 10, gamma = 4, V = 16000
+// 11.0 / 9.1; B = 1, gamma = 8, V = 50257 11.7 / 10.5; B = 4, gamma = 4, V = 256000 (640 workgroups) 13.5 / 11.7; B = 25, gamma = 1, V = 128256 (800) 12.3 / 12.0;
+// float32: B = 34, gamma = 4, V = 16000 16.1 / 13.8; B = 21, gamma = 4, V = 128256 (1680) 25.7 / 23.6.  Beyond: B = 64, gamma = 1, V = 128256,
+// float32 (2048) 25.7 / 31.0, bf16, gamma = 16, B = 11, V = 128256 (2992) 26.3 / 25.6, gamma = 8, B = 64, V = 128256 (9216) 51.0 / 53.5
+inline long long probs_at_once(long long resident, int gamma) { return gamma >= 4 ? 2 * resident : resident; }
+constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the workgroup that finishes it keeps in LDS (32 KB)
 
 struct ProbWeight {
     double w;            // w_i (1 for token verification, whose residual is p - q)
@@ -62,6 +69,9 @@ __device__ __forceinline__ int clamped_draft_len(const int32_t *draft_lens, int 
     const int g = draft_lens[b];
     return g < 1 ? 1 : g > gamma ? gamma : g;
 }
+
+// doubles of LDS in front of the kept sums: S_i and the rejected masses, the constants
+__host__ __device__ inline int probs_finish_doubles(int gamma) { return (2 + (int)(sizeof(ProbWeight) / sizeof(double))) * (gamma + 1); }
 
 constexpr ProbWeight kFirstWeight = {1.0, 0.0, 1.0, 1.f, 0.f, 1};      // position 0: w_0 = 1; tau = 0 draws from the residual of rows 0
 
@@ -127,28 +137,70 @@ __global__ __launch_bounds__(64) void probs_weights_kernel(
     if (lane < gb) wb[lane + 1] = pw;
 }
 
-// FORM: the workgroup forms its position's weight itself, under its loads; a sequence's chunk-0 workgroups leave them for
-// the finishing kernel.  (Without: they come from probs_weights_kernel.)
-template <typename T, bool ALIGNED, bool GREEDY, bool FORM>
-__global__ __launch_bounds__(kThreads) void probs_residual_kernel(
-    const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
-    const int32_t *__restrict__ tokens, const int32_t *__restrict__ draft_lens, const float *__restrict__ uniforms,
-    int gamma, int V, int nchunks, int algo, int every_sum, float2 *__restrict__ part, ProbWeight *__restrict__ weights)
+struct ProbsParams {
+    const void *target, *draft;
+    size_t tstride, dstride;
+    const int32_t *tokens, *draft_lens;
+    const float *uniforms;
+    int gamma, V, nchunks, algo, every_sum, keep;      // keep: whether a sequence's chunk sums fit the launch's LDS
+    int spin_limit;
+    unsigned call;                // this call's number (never 0)
+    u64 *part, *rejected;         // [B, gamma + 1, nchunks], [B, gamma, nchunks]: a chunk's share of S_i, of the rejected mass (Alg. 4): a float
+                                  // below the call's number; calls of more launches: both in `part`
+    ProbWeight *weights;          // [B, gamma + 1], calls of more launches than one
+    int32_t *accept_len, *next_token;
+    float *debug_out;
+};
+
+// ------------------------------------------------------------------ calls of one launch: how the shares reach the workgroup that finishes a sequence
+// That is its last one, which waits for the words of the others (all of them started before it) and leaves zeros behind.  A word counts
+// once its upper half is the number of this call: the memory need not be prepared, whatever it held before - and a captured
+// call, which has the same number every time, finds the zeros of the time before.  (The last to arrive finishing it, found by a count per
+// sequence, was 7 times slower: read-modify-writes of one line by workgroups all over the device take 40 ns each, one after the other.)
+__device__ __forceinline__ void leave_share(u64 *word, unsigned call, float v) { st_u64(word, (u64)call << 32 | __float_as_uint(v)); }
+__device__ __forceinline__ float await_share(const u64 *word, unsigned call, int limit, bool &gave_up)
+{
+    u64 v = ld_u64(word);
+    for (int spins = 0; (unsigned)(v >> 32) != call; v = ld_u64(word)) {
+        if (++spins > limit) { gave_up = true; return 0.f; }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return __uint_as_float((unsigned)v);
+}
+// A chunk's share of S_i and, for Alg. 4 (`rej_word`: not at the last position), of the rejected mass, as the workgroup that finishes the
+// sequence takes them (ONE: calls of one launch; else both are in one word, plain memory between two launches).
+template <bool GREEDY, bool ONE>
+__device__ __forceinline__ float2 take_shares(const u64 *word, const u64 *rej_word, unsigned call, int limit, bool &gave_up)
+{
+    if constexpr (ONE) return make_float2(await_share(word, call, limit, gave_up), GREEDY && rej_word ? await_share(rej_word, call, limit, gave_up) : 0.f);
+    else { const u64 w = *word; return make_float2(stat_shift(w), stat_sum(w)); }
+}
+
+template <typename T, bool ALIGNED, bool GREEDY, bool ONE>
+__device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb, const ProbWeight &mine);
+
+// A position's share: one workgroup per (sequence, position, chunk).  FORM: the workgroup forms its position's weight itself, under its
+// loads.  (Without: it comes from probs_weights_kernel.)  ONE: the last workgroup of a sequence goes on with probs_finish; else a
+// sequence's chunk-0 workgroups leave the weights for the kernel that finishes it.
+template <typename T, bool ALIGNED, bool GREEDY, bool FORM, bool ONE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : 1))) void probs_residual_kernel(const ProbsParams P)
 {
     constexpr int kVec = ElemTraits<T>::kVec;
     constexpr int kU = kChunk / (kThreads * kVec);
     __shared__ float lds[kWaves];
     __shared__ ProbWeight formed;
+    const int gamma = P.gamma, V = P.V, nchunks = P.nchunks, algo = P.algo, every_sum = P.every_sum;
+    const size_t tstride = P.tstride, dstride = P.dstride;
     const int pr = blockIdx.x / nchunks, c = blockIdx.x - pr * nchunks, tid = threadIdx.x;
     const int b = pr / (gamma + 1), i = pr - b * (gamma + 1);
-    const int gb = clamped_draft_len(draft_lens, b, gamma);
+    const int gb = clamped_draft_len(P.draft_lens, b, gamma);
     if (i > gb) return;                                          // a position this sequence does not use
-    if (!FORM && !weights[pr].needed) return;                    // sums that cannot matter (whole workgroup)
-    const T *target_seq = target + (size_t)b * (gamma + 1) * tstride;
-    const T *draft_seq = draft + (size_t)b * gamma * dstride;
+    const T *target_seq = static_cast<const T *>(P.target) + (size_t)b * (gamma + 1) * tstride;
+    const T *draft_seq = static_cast<const T *>(P.draft) + (size_t)b * gamma * dstride;
     const T *prow = target_seq + (size_t)i * tstride;
     const bool last = i == gb;                                   // no draft row: q == 0
     const T *qrow = draft_seq + (size_t)(last ? 0 : i) * dstride;
+    ProbWeight mine;                                             // ONE, the last target row, first wave: lane j, position j + 1's
 
     uint4 rp[kU], rq[kU];
     const int in_row = V - c * kChunk;                           // (short rows: vectors beyond the row are left out, for the whole workgroup)
@@ -161,6 +213,7 @@ __global__ __launch_bounds__(kThreads) void probs_residual_kernel(
             if (!last) rq[u] = load_raw<T, ALIGNED, true>(qrow, V, idx);
         }
     };
+    bool wanted = true;                                          // (else: sums that cannot matter, for the whole workgroup)
     if constexpr (FORM) {
         // (the drafted tokens are asked for in front of the rows, so that their probabilities follow under the rows' loads;
         // a last target row, which is needed only where the last test passes, waits for its weight)
@@ -168,46 +221,69 @@ __global__ __launch_bounds__(kThreads) void probs_residual_kernel(
         const bool forms = tid < kWave && i > 0;
         int tok = 0;
         float eta = 1.f;
-        if (forms && tid < i) { tok = tokens[(size_t)b * gamma + tid]; eta = uniforms[(size_t)b * (gamma + 1) + tid]; }
+        if (forms && tid < i) { tok = P.tokens[(size_t)b * gamma + tid]; eta = P.uniforms[(size_t)b * (gamma + 1) + tid]; }
         if (at_once) load();
         if (forms) {
             const ProbWeight pw = form_weights(target_seq, draft_seq, tstride, dstride, tok, eta, i, gb, algo, every_sum != 0);
-            if (tid == i - 1) { formed = pw; if (c == 0) weights[pr] = pw; }
+            if (tid == i - 1) { formed = pw; if (!ONE && c == 0) P.weights[pr] = pw; }
+            if constexpr (ONE) mine = pw;
         } else if (tid == 0) {
             formed = kFirstWeight;
-            if (c == 0) weights[pr] = kFirstWeight;
+            if (!ONE && c == 0) P.weights[pr] = kFirstWeight;
         }
         __syncthreads();
-        if (!formed.needed) return;
-        if (!at_once) load();
+        wanted = formed.needed != 0;
+        if (wanted && !at_once) load();
     } else {
-        load();
+        wanted = P.weights[pr].needed != 0;
+        if (wanted) load();
     }
-    const float w_hi = FORM ? formed.w_hi : weights[pr].w_hi, w_lo = FORM ? formed.w_lo : weights[pr].w_lo;
-
-    float acc = 0.f, rej = 0.f;
+    if (wanted) {
+        const float w_hi = FORM ? formed.w_hi : P.weights[pr].w_hi, w_lo = FORM ? formed.w_lo : P.weights[pr].w_lo;
+        float acc = 0.f, rej = 0.f;
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        if (u * kThreads * kVec >= in_row) continue;
-        const int idx = c * kChunk + (u * kThreads + tid) * kVec;
-        float xp[kVec], xq[kVec];
-        unpack_probs<T, ALIGNED>(rp[u], V, idx, xp);
-        if (last) {
+        for (int u = 0; u < kU; ++u) {
+            if (u * kThreads * kVec >= in_row) continue;
+            const int idx = c * kChunk + (u * kThreads + tid) * kVec;
+            float xp[kVec], xq[kVec];
+            unpack_probs<T, ALIGNED>(rp[u], V, idx, xp);
+            if (last) {
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) acc += xp[e];
-        } else {
-            unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
+                for (int e = 0; e < kVec; ++e) acc += xp[e];
+            } else {
+                unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) {
-                const float d = prob_residual(xp[e], xq[e], w_hi, w_lo);
-                acc += fmaxf(d, 0.f);
-                if constexpr (GREEDY) rej += fmaxf(-d, 0.f);
+                for (int e = 0; e < kVec; ++e) {
+                    const float d = prob_residual(xp[e], xq[e], w_hi, w_lo);
+                    acc += fmaxf(d, 0.f);
+                    if constexpr (GREEDY) rej += fmaxf(-d, 0.f);
+                }
+            }
+        }
+        acc = block_sum(acc, lds);
+        if constexpr (GREEDY) rej = block_sum(rej, lds);
+        if (tid == 0) {
+            u64 *const word = P.part + (size_t)pr * nchunks + c;
+            if constexpr (ONE) {
+                leave_share(word, P.call, acc);
+                if (GREEDY && !last) leave_share(P.rejected + ((size_t)b * gamma + i) * nchunks + c, P.call, rej);
+            } else {
+                *word = pack_stat(acc, rej);
             }
         }
     }
-    acc = block_sum(acc, lds);
-    if constexpr (GREEDY) rej = block_sum(rej, lds);
-    if (tid == 0) part[(size_t)pr * nchunks + c] = make_float2(acc, rej);
+    if constexpr (ONE) {
+        if (last && c == nchunks - 1) probs_finish<T, ALIGNED, GREEDY, true>(P, b, gb, mine);
+    }
+}
+// One workgroup per sequence, after probs_residual_kernel.
+template <typename T, bool ALIGNED, bool GREEDY>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ElemTraits<T>::kVec == 8 ? 4 : 3))) void probs_finish_kernel(const ProbsParams P)
+{
+    const int b = blockIdx.x, tid = threadIdx.x, gb = clamped_draft_len(P.draft_lens, b, P.gamma);
+    ProbWeight pw = kFirstWeight;
+    if (tid < gb) pw = P.weights[(size_t)b * (P.gamma + 1) + tid + 1];
+    probs_finish<T, ALIGNED, GREEDY, false>(P, b, gb, pw);
 }
 
 // The weights of a wave's kWaveChunk consecutive tokens of a row pair from `start` on, in its registers: element
@@ -234,50 +310,55 @@ __device__ __forceinline__ void prob_wave_weights(const T *prow, const T *qrow, 
     }
 }
 
-template <typename T, bool ALIGNED>
-__global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
-    const T *__restrict__ target, const T *__restrict__ draft, size_t tstride, size_t dstride,
-    const float *__restrict__ uniforms, const int32_t *__restrict__ draft_lens,
-    int gamma, int V, int nchunks, int algo, const float2 *__restrict__ part, const ProbWeight *__restrict__ weights,
-    int32_t *__restrict__ accept_len, int32_t *__restrict__ next_token, float *__restrict__ debug_out)
+// S_i, h_i, the accept tests and the draw of Y of a sequence, by one workgroup (`mine`: first wave, lane j: position j + 1's constants).
+template <typename T, bool ALIGNED, bool GREEDY, bool ONE>
+__device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb, const ProbWeight &mine)
 {
-    extern __shared__ double smd[];                     // [gamma+1] S_i, [gamma+1] rejected mass, then the kept partial sums
+    extern __shared__ double smd[];                     // [gamma+1] S_i, [gamma+1] rejected mass, the constants, then the kept partial sums
     __shared__ double wave_tot[kWaves];
-    __shared__ int s_tau, s_chunk, s_mode;
+    __shared__ int s_tau, s_chunk, s_mode, s_gave_up;
     __shared__ double s_t, s_total;
+    const int gamma = P.gamma, V = P.V, nchunks = P.nchunks, algo = P.algo;
+    const size_t tstride = P.tstride, dstride = P.dstride;
+    const T *const target = static_cast<const T *>(P.target), *const draft = static_cast<const T *>(P.draft);
+    int32_t *const accept_len = P.accept_len, *const next_token = P.next_token;
+    float *const debug_out = P.debug_out;
     double *S = smd, *R = smd + (gamma + 1);
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int gb = clamped_draft_len(draft_lens, b, gamma);
-    const float2 *pb = part + (size_t)b * (gamma + 1) * nchunks;
-    const float *eta = uniforms + (size_t)b * (gamma + 1);
+    ProbWeight *const wb = reinterpret_cast<ProbWeight *>(smd + 2 * (gamma + 1));          // the sequence's constants, read once
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    u64 *const pb = P.part + (size_t)b * (gamma + 1) * nchunks, *const rb = P.rejected + (size_t)b * gamma * nchunks;
+    const float *eta = P.uniforms + (size_t)b * (gamma + 1);
     // the chunk sums stay in LDS for the draw when they fit (the host sizes the dynamic LDS to match: one float per
     // sum, a second one per chunk for Alg. 4's rejected mass)
-    const bool keep = (gamma + 1) * nchunks * (algo == kGreedy ? 2 : 1) <= kProbsKeepMax;
-    float *kept = reinterpret_cast<float *>(smd + 2 * (gamma + 1));
+    const bool keep = P.keep != 0;
+    float *kept = reinterpret_cast<float *>(smd + probs_finish_doubles(gamma));
     float *kept_rej = kept + (gamma + 1) * nchunks;
-    __shared__ ProbWeight wbs[SV_MAX_GAMMA + 1];                 // the sequence's constants, read once
 
-    // Everything that comes from memory is asked for at once - the sequence's constants, the uniforms, every chunk sum
-    // of its positions (those of rows whose sums were not formed are stale and never used) - so that the kernel has
-    // one trip to memory here and one for the chunk that holds the token.
     float eta_i = 0.f, u = 0.f;
-    if (wave == 0) {
-        if (lane + 1 <= gb) eta_i = eta[lane];
+    ProbWeight pw = mine;
+    auto constants = [&]() {
+        if (wave != 0) return;
+        if (lane + 1 <= gb) { eta_i = eta[lane]; wb[lane + 1] = pw; }
+        if (lane == 0) { wb[0] = kFirstWeight; s_gave_up = 0; }
         u = eta[gb];
-    }
-    if (tid <= gb) wbs[tid] = weights[(size_t)b * (gamma + 1) + tid];
+    };
+    // every chunk sum (ONE: of the positions that have any; else all are read, stale ones of the others among them, which are
+    // never used: one trip to memory for the sums and the constants)
+    bool gave_up = false;
+    const int n_words = (gb + 1) * nchunks;
+    if (ONE) { constants(); __syncthreads(); }
     if (keep) {
-        const int n_words = (gb + 1) * nchunks;
         for (int w = tid; w < n_words; w += kThreads) {
-            const float2 v = pb[w];
+            const int i = w / nchunks;
+            const bool is = !ONE || wb[i].needed != 0;
+            const float2 v = is ? take_shares<GREEDY, ONE>(pb + w, i < gb ? rb + w : nullptr, P.call, P.spin_limit, gave_up) : make_float2(0.f, 0.f);
             kept[w] = v.x;
-            if (algo == kGreedy) kept_rej[w] = v.y;
+            if constexpr (GREEDY) kept_rej[w] = v.y;
+            if (ONE && is) { st_u64(pb + w, 0); if (GREEDY && i < gb) st_u64(rb + w, 0); }
         }
     }
+    if (!ONE) constants();
     __syncthreads();
-    const ProbWeight *wb = wbs;
-    ProbWeight pw = {};
-    if (wave == 0 && lane + 1 <= gb) pw = wb[lane + 1];
 
     // S_i = sum over the chunks: wave (i mod 4) takes position i, lanes stride over the chunks
     for (int i = wave; i <= gb; i += kWaves) {
@@ -286,17 +367,23 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         if (wb[i].needed) for (int c = lane; c < nchunks; c += 64) {
             if (keep) {
                 acc += (double)kept[i * nchunks + c];
-                if (algo == kGreedy) rej += (double)kept_rej[i * nchunks + c];
+                if (GREEDY) rej += (double)kept_rej[i * nchunks + c];
             } else {
-                const float2 v = pb[(size_t)i * nchunks + c];
+                const size_t w = (size_t)i * nchunks + c;
+                const float2 v = take_shares<GREEDY, ONE>(pb + w, i < gb ? rb + w : nullptr, P.call, P.spin_limit, gave_up);
                 acc += (double)v.x; rej += (double)v.y;
             }
         }
         acc = group_sum<kWave>(acc);
-        if (algo == kGreedy) rej = group_sum<kWave>(rej);
+        if (GREEDY) rej = group_sum<kWave>(rej);
         if (lane == 0) { S[i] = acc; R[i] = rej; }
     }
+    if (ONE && gave_up) s_gave_up = 1;
     __syncthreads();
+    if (ONE && s_gave_up) {
+        if (tid == 0) { accept_len[b] = -1; next_token[b] = -1; }
+        return;
+    }
 
     if (wave == 0) {
         // accept tests eta_i < h_i: lane l judges position l + 1 (positions 1 .. gb <= 64)
@@ -368,12 +455,12 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         // pick the chunk of row tau that holds t = u * (total weight): 64 chunk sums at a time, scanned in order
         const double total = mode == 1 ? S[gb] : S[tau];
         const double t = (double)u * total;
-        const float2 *pp = pb + (size_t)tau * nchunks;
+        const u64 *pp = pb + (size_t)tau * nchunks;
         int chunk = -1, last_nonzero = 0;
         double carry = 0.0, t_in = INFINITY;
         for (int c0 = 0; c0 < nchunks && chunk < 0; c0 += 64) {
             const int c = c0 + lane;
-            const double v = c < nchunks ? (double)(keep ? kept[tau * nchunks + c] : pp[c].x) : 0.0;
+            const double v = c < nchunks ? (double)(keep ? kept[tau * nchunks + c] : __uint_as_float((unsigned)(ONE ? ld_u64(pp + c) : pp[c]))) : 0.0;
             const double inc = wave_scan(v) + carry;
             const unsigned long long nz = __ballot(v > 0.0), hit = __ballot(c < nchunks && inc > t);
             if (nz) last_nonzero = c0 + 63 - __clzll((long long)nz);
@@ -410,6 +497,11 @@ __global__ __launch_bounds__(kThreads) void probs_finalize_kernel(
         }
         t_in -= total;
         ++c;
+    }
+    // (sums too many to keep: zeros are left behind now that they have been read for the last time)
+    if (ONE && !keep) {
+        for (int w = tid; w < n_words; w += kThreads) st_u64(pb + w, 0);
+        if (GREEDY) for (int w = tid; w < gb * nchunks; w += kThreads) st_u64(rb + w, 0);
     }
     int holder = -1, last_weight = 0;
     {

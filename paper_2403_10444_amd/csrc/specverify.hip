@@ -10,6 +10,7 @@
 #include <stdint.h>
 #include <math.h>
 #include <atomic>
+#include <chrono>
 #include <mutex>
 
 #include "../../include/specverify.h"
@@ -138,39 +139,65 @@ sv_status_t launch_staged(int algo, const void *target_v, const void *draft_v, c
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
-// Probabilities as inputs: two or three launches, every element read once.  Scratch: the staged path's areas
+// A number for a call with probabilities, never 0: other than that of the 2^32 calls before, and where the first begins is
+// anyone's guess, so that what an unprepared workspace holds is not taken for this call's (see probs.hpp).
+unsigned probs_call_number()
+{
+    static std::atomic<unsigned> next{(unsigned)(((u64)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull) >> 32)};
+    unsigned n;
+    do n = next.fetch_add(1); while (n == 0);
+    return n;
+}
+
+// Probabilities as inputs: one to three launches, every element read once.  Scratch: the staged path's areas
 // (chunk partial sums where its row statistics go, the weights where its row constants go).
 template <typename T, bool ALIGNED>
 sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, const int32_t *tokens, const int32_t *draft_lens,
                          size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, const Layout &L,
                          char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
-    static_assert(sizeof(ProbWeight) <= sizeof(SeqCoef), "the weights reuse the staged path's row-constant area");
     const T *target = static_cast<const T *>(target_v);
     const T *draft = static_cast<const T *>(draft_v);
-    float2 *part = reinterpret_cast<float2 *>(ws + L.off_stats);
-    ProbWeight *weights = reinterpret_cast<ProbWeight *>(ws + L.off_coef);
+    ProbsParams P = {};
+    P.target = target; P.draft = draft; P.tstride = tstride; P.dstride = dstride;
+    P.tokens = tokens; P.draft_lens = draft_lens; P.uniforms = uniforms;
+    P.gamma = gamma; P.V = V; P.nchunks = L.nchunks; P.algo = algo;
+    // (the words where the staged path has its row statistics, one for every chunk of all rows)
+    P.part = reinterpret_cast<u64 *>(ws + L.off_stats);
+    P.rejected = P.part + (size_t)B * (gamma + 1) * L.nchunks;
+    static_assert(sizeof(ProbWeight) <= sizeof(SeqCoef), "the weights reuse the staged path's row-constant area");
+    ProbWeight *const weights = reinterpret_cast<ProbWeight *>(ws + L.off_coef);
+    P.weights = weights;
+    P.spin_limit = g_spin_limit.load();
+    P.call = probs_call_number();
+    P.accept_len = accept_len; P.next_token = next_token; P.debug_out = debug_out;
     const unsigned blocks = (unsigned)((size_t)B * (gamma + 1) * L.nchunks);
     // A position's weight: formed by each of its workgroups under its loads (B = 64, gamma = 8, V = 128256, bf16: 58 -> 51 us,
     // 1 sequence 18 -> 14; float32, B = 48 83 -> 69, 72 with the kernel in front), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
     // (Alg. 1 unless every sum is reported: 25 us against 48 there, unless the call runs at once anyway: kProbsAtOnce) and where there are many of them with less to read
     // than the weight takes to form (4096 sequences of 8 over 500 tokens: 150 us against 185, and 89 since short rows leave
     // out the vectors beyond them).
-    const int every_sum = debug_out ? 1 : 0;
+    const int every_sum = P.every_sum = debug_out ? 1 : 0;
     const bool many_short = V <= kChunk / 2 && (long long)B * (gamma + 1) > kProbsFormMax;
     const size_t row_bytes = (size_t)blocks * (V < kChunk ? V : kChunk) * sizeof(T);       // the target rows' (the last chunk counted whole)
     const bool in_front = (algo == kToken && !every_sum && (blocks > kProbsAtOnce || row_bytes > kProbsAtOnceBytes)) || many_short;
     if (in_front)
         probs_weights_kernel<T><<<B, 64, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, gamma, algo, weights, uniforms, every_sum);
-    void (*const residual)(const T *, const T *, size_t, size_t, const int32_t *, const int32_t *, const float *, int, int, int, int, int, float2 *, ProbWeight *) =
-        algo == kGreedy ? (in_front ? probs_residual_kernel<T, ALIGNED, true, false> : probs_residual_kernel<T, ALIGNED, true, true>)
-        : in_front ? probs_residual_kernel<T, ALIGNED, false, false> : probs_residual_kernel<T, ALIGNED, false, true>;
-    residual<<<blocks, kThreads, 0, stream>>>(target, draft, tstride, dstride, tokens, draft_lens, uniforms, gamma, V, L.nchunks, algo, every_sum, part, weights);
     const size_t kept_floats = (size_t)(gamma + 1) * L.nchunks * (algo == kGreedy ? 2 : 1);      // chunk sums (Alg. 4: and rejected masses)
-    const size_t keep = kept_floats <= (size_t)kProbsKeepMax ? kept_floats * sizeof(float) : 0;
-    probs_finalize_kernel<T, ALIGNED><<<B, kThreads, 2 * (gamma + 1) * sizeof(double) + keep, stream>>>(
-        target, draft, tstride, dstride, uniforms, draft_lens, gamma, V, L.nchunks, algo, part, weights,
-        accept_len, next_token, debug_out);
+    P.keep = kept_floats <= (size_t)kProbsKeepMax ? 1 : 0;
+    const size_t lds = probs_finish_doubles(gamma) * sizeof(double) + (P.keep ? kept_floats * sizeof(float) : 0);
+    static std::atomic<int> cap;
+    const int resident = resident_workgroups(probs_residual_kernel<T, ALIGNED, false, true, true>, cap);
+    if (resident < 1) return SV_ERR_HIP;
+    if (!in_front && blocks <= probs_at_once(resident, gamma)) {
+        (algo == kGreedy ? probs_residual_kernel<T, ALIGNED, true, true, true> : probs_residual_kernel<T, ALIGNED, false, true, true>)<<<blocks, kThreads, lds, stream>>>(P);
+        return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
+    }
+    void (*const residual)(const ProbsParams) =
+        algo == kGreedy ? (in_front ? probs_residual_kernel<T, ALIGNED, true, false, false> : probs_residual_kernel<T, ALIGNED, true, true, false>)
+        : in_front ? probs_residual_kernel<T, ALIGNED, false, false, false> : probs_residual_kernel<T, ALIGNED, false, true, false>;
+    residual<<<blocks, kThreads, 0, stream>>>(P);
+    (algo == kGreedy ? probs_finish_kernel<T, ALIGNED, true> : probs_finish_kernel<T, ALIGNED, false>)<<<B, kThreads, lds, stream>>>(P);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 

@@ -170,3 +170,46 @@ def test_token_verification_on_both_sides_of_what_runs_at_once(B, dtype):
     assert safe.mean() > 0.95
     tau, y = sv.spec_verify_probs("token", P, Q, inp["draft_tokens"], inp["uniforms"])
     assert np.array_equal(tau.cpu().numpy()[safe], ref["accept_len"][safe]) and np.array_equal(y.cpu().numpy()[safe], ref["next_token"][safe])
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", [(60, 1, 60000, "bf16"), (70, 1, 60000, "bf16"),      # 960 and 1120 workgroups: one launch and two (gamma < 4)
+                                             (50, 4, 60000, "f32"), (52, 4, 60000, "f32"),         # 2000 and 2080 (gamma >= 4)
+                                             (2, 64, 1100000, "bf16")])                            # 8775 sums a sequence: more than a workgroup keeps
+def test_probs_one_launch_on_whatever_the_workspace_holds(algo, B, gamma, V, dtype):
+    """Calls of one launch count on words of their own call only: the same results on a workspace that was never prepared and
+    holds other calls' words, ones or random bytes, call after call, and on a captured call replayed with other inputs."""
+    import paper_2403_10444_amd as sv
+    if V > 1000000 and algo != "greedy":
+        pytest.skip("one algorithm at this size")
+    cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=1.0, T=0.8)
+    P, Q, inp = _probs_inputs(cfg, seed=B + gamma)
+    want = _run_gpu(sv, algo, P, Q, inp)
+    if V <= 100000:
+        parity.compare(want, _run_oracle(algo, P, Q, inp), label=f"probs {B}x{gamma}x{V} {dtype} {algo}", greedy=(algo == "greedy"))
+    n = sv.spec_verify_workspace_bytes(B, gamma, V)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    ws = torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV, generator=gen)
+    for fill in (None, None, 255, 0, 1):
+        if fill is not None:
+            ws.fill_(fill)
+        got = _run_gpu(sv, algo, P, Q, inp, workspace=ws)
+        for key in want:
+            assert np.array_equal(got[key], want[key], equal_nan=True), (key, fill)
+    # the sums that matter only (no report), by a graph on the same workspace; the inputs change between its replays
+    tau, y = (torch.empty(B, dtype=torch.int32, device=DEV) for _ in range(2))
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"], workspace=ws, accept_len=tau, next_token=y)
+    first = inp["uniforms"].clone()
+    for turn in range(3):
+        inp["uniforms"].copy_(first if turn == 1 else (first + 0.3 * (turn + 1)).remainder(1.0).clamp(max=1 - 2.0 ** -24))
+        tau.fill_(-7), y.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"])
+        torch.cuda.synchronize()
+        assert torch.equal(tau, eager[0]) and torch.equal(y, eager[1]), turn
