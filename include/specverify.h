@@ -155,9 +155,10 @@ void spec_verify_debug_profile(void *device_buffer);
  *   tokens    [rows]     int32 out, device
  * Asynchronous on `stream`, allocates nothing.  SV_ERR_INVALID_ARG for null pointers, rows < 1,
  * V < 1, a temperature that is not positive and finite or an unknown dtype; SV_ERR_UNSUPPORTED
- * for more than 2^31 - 1 rows.  Rows too few to fill the device are spread over it in two launches where there
- * is scratch memory for them (64 rows of 128256 bf16 logits: 8.8 us against 13.4): on the null stream
- * (`stream` NULL) the library has 4 MiB of its own per GPU, on any other stream the next call takes the caller's.
+ * for more than 2^31 - 1 rows.  Rows too few to fill the device are spread over it where there is scratch
+ * memory for them (64 rows of 128256 bf16 logits: 7.3 us against 13.4, 1 row 5.3 against 12.7): on the null
+ * stream (`stream` NULL) the library has its own, 4 MiB per GPU, on any other stream the next call takes
+ * the caller's (and always has two launches: 8.1 and 7.8 us).
  */
 sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype,
                                float temperature, const float *uniforms, int32_t *tokens, void *stream);

@@ -57,6 +57,20 @@ struct SampleEntry {
 // library runs on has its own (a call's two launches must follow each other there: the host holds a lock over them).
 constexpr int kSampleOwnEntries = 1 << 18;                   // 4 MiB
 __device__ SampleEntry g_null_stream_entries[kSampleOwnEntries];
+// Calls on it of up to this many workgroups have one launch: their entries are words that announce themselves, two each (pack_entry),
+// zero between calls.  Two launches / one, us: 1 row of 128256 bf16 logits 7.8 / 5.3, 8 rows 8.3 / 5.7, 64 rows (1024 workgroups) 8.1 / 7.3,
+// float32 10.0 / 9.2; 64 rows of 202267, float32 (1600) 13.1 / 12.9; beyond, the workgroups that wait are in the way of others: 64 rows of 256000,
+// float32 (2048) 14.8 / 15.4, 200 rows of 128256 bf16 (3200) 13.2 / 15.4.
+constexpr int kSampleOneLaunch = 1536;
+constexpr int kSampleOneUnits = 4 * kWave;                   // ... of rows of up to this many units (V = 1000003: 2 rows 7.4 / 7.7 us)
+__device__ u64 g_null_stream_words[2 * kSampleOneLaunch * kWaves];
+// (never zero: the largest logit beside a one, the sum with -0 for 0)
+__device__ __forceinline__ void pack_entry(const SampleEntry &e, u64 &m, u64 &z)
+{
+    m = 1ull << 32 | __float_as_uint(e.m);
+    z = e.z > 0.0 ? (u64)__double_as_longlong(e.z) : 1ull << 63;
+}
+__device__ __forceinline__ SampleEntry unpack_entry(u64 m, u64 z) { return {__uint_as_float((unsigned)m), __longlong_as_double((long long)z)}; }
 
 // One unit of a row as loaded -> its entry (every lane gets it).  `left`: logits of the row from the unit's start on.
 template <typename T>
@@ -190,21 +204,92 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
     if (lane == 0) tokens[r] = y;
 }
 
-// The same in two launches, for rows too few to fill the device: every wave sweeps one unit and leaves its entry in
-// `entries` [rows, units] (NULL: the null stream's); then one wave per row scans them (up to kSampleSplitUnits units, a stretch of neighbours per
-// lane), finds the unit and walks it.
-template <typename T>
-__global__ __launch_bounds__(kThreads)
-void sample_units_kernel(const T *logits, int V, int units, float k, SampleEntry *entries)
+// For rows too few to fill the device: every wave sweeps one unit and leaves its entry; one wave per row then scans them (up
+// to kSampleSplitUnits units, a stretch of neighbours per lane), finds the unit and walks it: in a launch of its own, from `entries` [rows, units]
+// (NULL: the null stream's); or (ONE, calls on the null stream) as the first wave of the row's last workgroup, which waits for the words
+// of the others and clears them.
+template <typename T, int PER>
+__device__ __forceinline__ int draw_from_entries(const T *row, int V, int units, int per, float k, float u, const SampleEntry (&mine)[PER])
 {
-    const int unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+    const int lane = threadIdx.x & 63;
+    SampleEntry own = {-INFINITY, 0.0};
+#pragma unroll
+    for (int j = 0; j < PER; ++j) if (j < per) own.add(mine[j]);
+    const float M = wave_max(own.m);
+    const double z = own.relative_to(M), inc = wave_scan(z);
+    double t;
+    const int holder = locate_entry(z, inc, (double)u * read_lane_double(inc, kWave - 1), t);
+    // the unit among the holder's neighbours: the first whose running sum exceeds t, else its last with weight
+    int unit = 0;
+    double left = INFINITY, running = 0.0;
+    float m_unit = -INFINITY;
+    bool found = false;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j < per) {
+            const double zj = mine[j].relative_to(M);
+            if (!found && zj > 0.0) {
+                unit = lane * per + j;
+                m_unit = mine[j].m;
+                if (running + zj > t) { found = true; left = t - running; }
+            }
+            running += zj;
+        }
+    unit = __builtin_amdgcn_readlane(unit, holder);
+    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(m_unit), holder)));
+    left = ldexp(read_lane_double(left, holder), (int)(shift_of(M) - shift));
+    return walk_units(row, V, k, shift, left, unit, unit + 1);
+}
+
+template <typename T, bool ONE>
+__global__ __launch_bounds__(kThreads)
+void sample_units_kernel(const T *logits, int V, int units, float k, const float *uniforms, int32_t *tokens, SampleEntry *entries, int spin_limit)
+{
+    constexpr int kPer = kSampleOneUnits / kWave;
+    const int lane = threadIdx.x & 63, unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
     const size_t r = blockIdx.y;
     if (unit >= units) return;
     const int at = unit * kSampleUnit;
+    const T *const row = logits + r * (size_t)V;
     RawSlice<T, false, kLaneSmall> raw;
-    issue_loads<T, false, kLaneSmall>(logits + r * (size_t)V + at, 0, V - at, raw);
+    issue_loads<T, false, kLaneSmall>(row + at, 0, V - at, raw);
     const SampleEntry e = sweep_unit<T>(raw, V - at, k);
-    if ((threadIdx.x & 63) == 0) (entries ? entries : g_null_stream_entries)[r * units + unit] = e;
+    if constexpr (!ONE) {
+        if (lane == 0) (entries ? entries : g_null_stream_entries)[r * units + unit] = e;
+    } else {
+        u64 *const words = g_null_stream_words + 2 * r * units;
+        if (lane < 2) {
+            u64 m, z;
+            pack_entry(e, m, z);
+            st_u64(words + 2 * unit + lane, lane == 0 ? m : z);
+        }
+        if (blockIdx.x != gridDim.x - 1 || threadIdx.x >= kWave) return;
+        const float u = load_uniform(uniforms + r);
+        const int per = (units - 1) / kWave + 1;
+        bool gave_up = false;
+        // (lanes without an entry of their own look at the last one, which is waited for anyway)
+        u64 m[kPer], z[kPer];
+        for (int spins = 0;; ++spins) {
+            bool missing = false;
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if (j < per) {
+                    const u64 *const word = words + 2 * min(lane * per + j, units - 1);
+                    m[j] = ld_u64(word); z[j] = ld_u64(word + 1);
+                }
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) if (j < per) missing = missing || m[j] == 0 || z[j] == 0;
+            if (!__any(missing)) break;
+            if (spins >= spin_limit) { gave_up = true; break; }
+            __builtin_amdgcn_s_sleep(6);                 // (looks in quick succession hold up the writes to the lines they look at: 8 rows of 128256 logits 6.1 us with 1, 5.7 with 6)
+        }
+        SampleEntry mine[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) if (j < per) mine[j] = lane * per + j < units ? unpack_entry(m[j], z[j]) : SampleEntry{-INFINITY, 0.0};
+        for (int n = lane; n < 2 * units; n += kWave) st_u64(words + n, 0);
+        const int y = draw_from_entries(row, V, units, per, k, u, mine);
+        if (lane == 0) tokens[r] = gave_up ? -1 : y;
+    }
 }
 template <typename T>
 __global__ __launch_bounds__(kWave)
@@ -216,37 +301,13 @@ void sample_finish_kernel(const T *logits, int V, int units, float k, const floa
     const float u = load_uniform(uniforms + r);
     const int per = (units - 1) / kWave + 1;
     if (!entries) entries = g_null_stream_entries;
-    SampleEntry mine[kPer], own = {-INFINITY, 0.0};
+    SampleEntry mine[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         mine[j] = {-INFINITY, 0.0};
         if (j < per && lane * per + j < units) mine[j] = entries[r * units + lane * per + j];
     }
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) own.add(mine[j]);
-    const float M = wave_max(own.m);
-    const double z = own.relative_to(M), inc = wave_scan(z);
-    double t;
-    const int holder = locate_entry(z, inc, (double)u * read_lane_double(inc, kWave - 1), t);
-    // the unit among the holder's neighbours: the first whose running sum exceeds t, else its last with weight
-    int unit = 0;
-    double left = INFINITY, running = 0.0;
-    float m_unit = -INFINITY;
-    bool found = false;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const double zj = mine[j].relative_to(M);
-        if (!found && zj > 0.0) {
-            unit = lane * per + j;
-            m_unit = mine[j].m;
-            if (running + zj > t) { found = true; left = t - running; }
-        }
-        running += zj;
-    }
-    unit = __builtin_amdgcn_readlane(unit, holder);
-    const float shift = shift_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(m_unit), holder)));
-    left = ldexp(read_lane_double(left, holder), (int)(shift_of(M) - shift));
-    const int y = walk_units(logits + r * (size_t)V, V, k, shift, left, unit, unit + 1);
+    const int y = draw_from_entries(logits + r * (size_t)V, V, units, per, k, u, mine);
     if (lane == 0) tokens[r] = y;
 }
 

@@ -382,15 +382,24 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
-// The drafting step: how many waves share a row.
+std::mutex g_null_stream_mutex;          // over the two launches of a drafting call on the null stream
+
+// The drafting step: how many waves share a row.  (`split`: rows spread over the device, through `entries`, or NULL: the null stream's.)
 template <typename T>
-sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, bool two_launches, SampleEntry *entries, hipStream_t stream)
+sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, bool split, SampleEntry *entries, hipStream_t stream)
 {
     const T *logits = static_cast<const T *>(logits_v);
-    if (two_launches) {
+    if (split) {
         const int units = (V - 1) / kSampleUnit + 1;
-        sample_units_kernel<T><<<dim3((unsigned)((units - 1) / kWaves + 1), (unsigned)rows), kThreads, 0, stream>>>(logits, V, units, k, entries);
-        sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
+        const dim3 grid((unsigned)((units - 1) / kWaves + 1), (unsigned)rows);
+        if (!entries && units <= kSampleOneUnits && (long long)grid.x * rows <= kSampleOneLaunch) {
+            sample_units_kernel<T, true><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, nullptr, kDefaultSpinLimit);
+        } else {
+            std::unique_lock<std::mutex> lock(g_null_stream_mutex, std::defer_lock);
+            if (!entries) lock.lock();
+            sample_units_kernel<T, false><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, entries, 0);
+            sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
+        }
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }
     // (no kernel that takes more than kSampleManyRows rows has more than 256 threads for one)
@@ -526,7 +535,6 @@ struct StaticScratch {
 };
 std::mutex g_static_mutex;
 StaticScratch g_static[kMaxDevices];
-std::mutex g_null_stream_mutex;          // over the two launches of a drafting call on the null stream
 
 }  // namespace
 
@@ -667,14 +675,12 @@ sv_status_t spec_sample_tokens_ws(const void *logits, int64_t rows, int32_t V, s
     if (workspace && workspace_bytes < wanted) return SV_ERR_WORKSPACE_TOO_SMALL;
     SampleEntry *const entries = static_cast<SampleEntry *>(workspace);
     const bool null_stream = !workspace && !stream_v && wanted && wanted <= (size_t)kSampleOwnEntries * sizeof(SampleEntry);
-    const bool two_launches = wanted && (workspace || null_stream);
+    const bool split = wanted && (workspace || null_stream);
     const float k = (float)(1.4426950408889634074 / (double)temperature);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    std::unique_lock<std::mutex> lock(g_null_stream_mutex, std::defer_lock);
-    if (null_stream) lock.lock();
     return dtype == SV_DTYPE_F32
-        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, two_launches, entries, stream)
-        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, two_launches, entries, stream);
+        ? launch_sample<float>(logits, (int)rows, V, k, uniforms, tokens, split, entries, stream)
+        : launch_sample<bf16_t>(logits, (int)rows, V, k, uniforms, tokens, split, entries, stream);
 }
 
 sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype, float temperature,

@@ -204,3 +204,29 @@ def test_toy_loop_reproduces_the_ordering_of_the_ccdf():
     exact_token = (2 / 3) ** np.arange(gamma + 1)
     assert np.abs(out["token"] - exact_token).max() < 4 * 0.5 / np.sqrt(B * iters)
     assert np.all(out["block"][2:] > out["token"][2:])         # Pr(tau >= 1) = 2/3 for both
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(1, 24 * 2048 + 1),                                # the narrowest rows that are spread: 25 units
+                                    (3, 64 * 2048), (3, 64 * 2048 + 1), (2, 256 * 2048), (2, 256 * 2048 + 1),      # entries per lane; one launch and two
+                                    (96, 61 * 2048 + 7), (97, 61 * 2048 + 7)])          # 1536 workgroups, one launch; 1552, two
+def test_sample_tokens_on_the_null_stream(rows, V, dtype):
+    """One launch where the call is small enough, call after call on the library's own words: the tokens of the one-workgroup-per-row
+    kernel (another stream without scratch memory), which sums in another order: as the oracle says where the two differ."""
+    from tests.parity import in_cell
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    x = (torch.randn((rows, V), generator=g, device="cuda") * 3.0).to(dtype)
+    x[0, V // 3:] = -float("inf")                                     # (whole units without weight)
+    side = torch.cuda.Stream()
+    for turn in range(3):
+        u = torch.rand((rows,), generator=g, device="cuda")
+        if turn == 1:
+            u[0], u[-1] = 0.0, 1.0 - 2.0 ** -24
+        torch.cuda.synchronize()
+        got = sv.spec_sample_tokens(x, u, 0.9, stream=0)
+        want = sv.spec_sample_tokens(x, u, 0.9, tokens=torch.empty((rows,), dtype=torch.int32, device="cuda"), stream=side.cuda_stream)
+        torch.cuda.synchronize()
+        for r in (got != want).nonzero().flatten().tolist():
+            p = torch.softmax(x[r].double() / 0.9, -1).cpu().numpy()
+            assert in_cell(p, float(u[r]), int(got[r])), (turn, r)
+        assert int((got != want).sum()) <= 1
