@@ -53,3 +53,20 @@ def test_rows_at_any_address(V, dtype):
                                   dtype=oracle.F32 if dtype == "f32" else oracle.BF16)
         bad = (tau.cpu().numpy() != ref["accept_len"]) | (y.cpu().numpy() != ref["next_token"])
         assert not np.any(bad & (ref["margins"].min(axis=1) >= parity.MARGIN)), (V, dtype, offset, pad)
+
+
+# (the large kernel's draw takes a row's shares of the residual 64 at a time, and keeps the first 128: rows of 64 and 65, 128 and 129 wave
+# chunks - they come in fours - and of more, of 2048 logits and of 4096)
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("dtype,path,chunk", [("bf16", 3, 2048), ("f32", 3, 2048), ("bf16", 4, 4096)])
+@pytest.mark.parametrize("chunks", [64, 68, 128, 132, 196])
+def test_rows_of_many_shares(chunks, dtype, path, chunk, algo):
+    for less, seed in ((0, 1), (4 * chunk - 3, 2)):                          # a last workgroup that is full, and one of three logits
+        cfg = workloads.Config("shares", 3, 2, chunks * chunk - less, dtype, 2.0, 0.8 if seed == 1 else 3.0, 0.9, False, 1)
+        inp = workloads.generate(cfg, seed=chunks + seed, device=DEV)
+        sv.spec_verify_debug_config(path, -1)
+        try:
+            got = parity.run_gpu(algo, inp, cfg.temperature)
+        finally:
+            sv.spec_verify_debug_config(0, -1)
+        parity.compare(got, parity.run_oracle(algo, inp, cfg.temperature), label=f"{cfg.V}/{dtype}/{algo}", greedy=algo == "greedy")
