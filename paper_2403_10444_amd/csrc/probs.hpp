@@ -1,7 +1,7 @@
 // Verification with the distributions themselves as inputs (the ps / qs arrays of App. A): target rows
 // hold p_i(x), draft rows q_i(x), used as given - no temperature, no normalisation sweep.  The weight
 // w_i of Alg. 2 needs only the two gathered probabilities of each earlier drafted token, so every
-// element is read from HBM exactly once and no workgroup waits for another:
+// element is read from HBM exactly once and no workgroup waits for another on the way to its sums:
 //
 //   1. probs_residual_kernel  one workgroup per (sequence, position, chunk of kChunk tokens): the position's weight from
 //                             the ratios r_1 .. r_i of the drafted tokens and the recursion w_i = min(w_{i-1} r_i, 1) (in

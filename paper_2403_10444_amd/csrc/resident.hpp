@@ -1,4 +1,5 @@
-// Calls of few resident sets (all workgroups run at once, or nearly; rows of at most 32 workgroups).
+// Calls of few resident sets (rows of at most 32 workgroups).  Most of those whose workgroups all run at once, and most float32 ones, go to
+// the kernel in together.hpp, which has one trip less and holds more registers; this one has the others.
 //
 // Such a call is as long as its chain of dependent trips through device memory.  The large kernel (fused.hpp) hands a
 // row pair's results to ONE wave, the row's leader: it collects the row's partial sums of S_i, judges the position's
@@ -22,7 +23,8 @@ constexpr int kResidentMaxGroups = 32;        // workgroups per row: one poll of
 // Up to how many times the workgroups that the device keeps resident the library takes this kernel by itself.  Its
 // workgroups hold their registers until the row's S_i is there, which costs nothing while everything runs at once and
 // more and more as workgroups queue for the compute units; the large kernel has its row leaders read the logits once more
-// instead.  Measured, this kernel / the large one:
+// instead.  Measured, this kernel / the large one (before the calls of one set, and most float32 ones, had the kernel of together.hpp, which is faster
+// there: the line is the same for both):
 //   bf16, V = 128256: gamma = 2: 1.3 sets 18 / 22 us, 2.4 sets 27 / 26; gamma = 8: 1.2 sets 19 / 21, 2.4 sets 27 / 29,
 //   3.9 sets 40 / 37; gamma = 16: 2.3 sets 28 / 29, 3.8 sets 38 / 35
 //   bf16, V = 32000: gamma = 2: 2.4 sets 26 / 26; gamma = 8: 2.4 sets 28 / 31, 4.0 sets 40 / 40; gamma = 16: 4.0 sets 39 / 42
