@@ -36,7 +36,13 @@ constexpr size_t kProbsAtOnceBytes = 20u << 20;
 // 11.0 / 9.1; B = 1, gamma = 8, V = 50257 11.7 / 10.5; B = 4, gamma = 4, V = 256000 (640 workgroups) 13.5 / 11.7; B = 25, gamma = 1, V = 128256 (800) 12.3 / 12.0;
 // float32: B = 34, gamma = 4, V = 16000 16.1 / 13.8; B = 21, gamma = 4, V = 128256 (1680) 25.7 / 23.6.  Beyond: B = 64, gamma = 1, V = 128256,
 // float32 (2048) 25.7 / 31.0, bf16, gamma = 16, B = 11, V = 128256 (2992) 26.3 / 25.6, gamma = 8, B = 64, V = 128256 (9216) 51.0 / 53.5
-inline long long probs_at_once(long long resident, int gamma) { return gamma >= 4 ? 2 * resident : resident; }
+// Unaligned bf16 rows, whose loads straddle lines, with long drafts less far: V = 109165, gamma = 14, 1050 workgroups 19.2 / 17.2, 1260 20.2 / 19.8, 1470
+// 21.0 / 21.5; V = 30001, gamma = 8, 1296 21.1 / 20.4, 1512 21.6 / 22.4, 2016 24.7 / 24.8 (aligned, V = 109168, 1470 18.3 / 17.6; unaligned float32 26.9 / 26.1).
+inline long long probs_at_once(long long resident, int gamma, bool f32, bool aligned)
+{
+    if (gamma < 4) return resident;
+    return gamma >= 8 && !f32 && !aligned ? resident + resident / 4 : 2 * resident;
+}
 constexpr int kProbsKeepMax = 8192;      // chunk sums of one sequence that the workgroup that finishes it keeps in LDS (32 KB)
 
 struct ProbWeight {

@@ -189,7 +189,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     static std::atomic<int> cap;
     const int resident = resident_workgroups(probs_residual_kernel<T, ALIGNED, false, true, true>, cap);
     if (resident < 1) return SV_ERR_HIP;
-    if (!in_front && blocks <= probs_at_once(resident, gamma)) {
+    if (!in_front && blocks <= probs_at_once(resident, gamma, ElemTraits<T>::kVec == 4, ALIGNED)) {
         (algo == kGreedy ? probs_residual_kernel<T, ALIGNED, true, true, true> : probs_residual_kernel<T, ALIGNED, false, true, true>)<<<blocks, kThreads, lds, stream>>>(P);
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }

@@ -214,10 +214,13 @@ struct UnitSums {
 // V = 30001, 684 13.4 / 11.6; drafts of four and more up to an eighth beyond, where only last target rows are late: gamma = 4, V = 30001, 1100
 // 15.6 / 13.8, gamma = 8, V = 100277, 1053 15.6 / 14.4 (gamma = 2, V = 5000, 1101 12.7 / 13.1).  Beyond, the other kernel runs a fifth more workgroups at once:
 // gamma = 8, V = 64000, 1368 15.5 / 16.3, V = 100277, 1404 17.2 / 18.1; further on neither is ahead by much (gamma = 8, V = 64000, 1872 18.6 / 17.4, gamma = 16, V =
-// 100277, 2652 29.2 / 31.0), and with every S_i reported this one is behind.
+// 100277, 2652 29.2 / 31.0), and with every S_i reported this one is behind.  Long float32 drafts of wider rows that nearly fill the device or more (everybody reads
+// the words of thirteen rows and more) are the other kernel's too: gamma = 13, V = 89412, 924 workgroups 16.3 / 17.2, V = 130372, 896 15.5 / 16.1, gamma = 15, V =
+// 96256, 960 16.1 / 16.5, 1152 18.3 / 18.8; gamma = 16, V = 56644, 714 14.5 / 13.2, V = 130372, 816 14.8 / 14.5, gamma = 12, V = 66000, 936 16.5 / 15.9.
 inline bool runs_together(long long workgroups, long long resident, int groups, int gamma, bool f32)
 {
     if (groups > 16 && (gamma > 8 || (gamma > 4 && workgroups > resident))) return false;
+    if (f32 && groups > 4 && gamma > 12 && 5 * workgroups > 4 * resident) return false;
     return f32 || workgroups <= (gamma >= 4 ? resident + resident / 8 : resident);
 }
 
