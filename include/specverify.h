@@ -158,7 +158,8 @@ void spec_verify_debug_profile(void *device_buffer);
  * for more than 2^31 - 1 rows.  Rows too few to fill the device are spread over it where there is scratch
  * memory for them (64 rows of 128256 bf16 logits: 7.3 us against 13.4, 1 row 5.3 against 12.7): on the null
  * stream (`stream` NULL) the library has its own, 4 MiB per GPU, on any other stream the next call takes
- * the caller's (and always has two launches: 8.1 and 7.8 us).
+ * the caller's (and always has two launches: 8.1 and 7.8 us).  A token never depends on how long a wait takes: in the one
+ * launch on the null stream a row's last workgroup waits for the others, and forms what is missing itself where that wait runs out.
  */
 sv_status_t spec_sample_tokens(const void *logits, int64_t rows, int32_t V, sv_dtype_t dtype,
                                float temperature, const float *uniforms, int32_t *tokens, void *stream);

@@ -57,20 +57,25 @@ struct SampleEntry {
 // library runs on has its own (a call's two launches must follow each other there: the host holds a lock over them).
 constexpr int kSampleOwnEntries = 1 << 18;                   // 4 MiB
 __device__ SampleEntry g_null_stream_entries[kSampleOwnEntries];
-// Calls on it of up to this many workgroups have one launch: their entries are words that announce themselves, two each (pack_entry),
-// zero between calls.  Two launches / one, us: 1 row of 128256 bf16 logits 7.8 / 5.3, 8 rows 8.3 / 5.7, 64 rows (1024 workgroups) 8.1 / 7.3,
+// Calls on it of up to this many workgroups have one launch: their entries are words that announce themselves, three each (entry_word).
+// Two launches / one, us: 1 row of 128256 bf16 logits 7.8 / 5.3, 8 rows 8.3 / 5.7, 64 rows (1024 workgroups) 8.1 / 7.3,
 // float32 10.0 / 9.2; 64 rows of 202267, float32 (1600) 13.1 / 12.9; beyond, the workgroups that wait are in the way of others: 64 rows of 256000,
 // float32 (2048) 14.8 / 15.4, 200 rows of 128256 bf16 (3200) 13.2 / 15.4.
 constexpr int kSampleOneLaunch = 1536;
 constexpr int kSampleOneUnits = 4 * kWave;                   // ... of rows of up to this many units (V = 1000003: 2 rows 7.4 / 7.7 us)
-__device__ u64 g_null_stream_words[2 * kSampleOneLaunch * kWaves];
-// (never zero: the largest logit beside a one, the sum with -0 for 0)
-__device__ __forceinline__ void pack_entry(const SampleEntry &e, u64 &m, u64 &z)
+// A word is the call's number, never 0, above 32 bits of the entry (its largest logit; the two halves of its sum), and counts for the call
+// of that number only: what the waves of a call whose wait ran out left behind (below) is nobody's.  Otherwise zero between calls.
+constexpr int kEntryWords = 3;
+__device__ u64 g_null_stream_words[kEntryWords * kSampleOneLaunch * kWaves];
+__device__ __forceinline__ u64 entry_word(const SampleEntry &e, int n, unsigned call)
 {
-    m = 1ull << 32 | __float_as_uint(e.m);
-    z = e.z > 0.0 ? (u64)__double_as_longlong(e.z) : 1ull << 63;
+    const u64 z = (u64)__double_as_longlong(e.z);
+    return (u64)call << 32 | (n == 0 ? __float_as_uint(e.m) : (unsigned)(n == 1 ? z : z >> 32));
 }
-__device__ __forceinline__ SampleEntry unpack_entry(u64 m, u64 z) { return {__uint_as_float((unsigned)m), __longlong_as_double((long long)z)}; }
+__device__ __forceinline__ SampleEntry unpack_entry(u64 m, u64 lo, u64 hi)
+{
+    return {__uint_as_float((unsigned)m), __longlong_as_double((long long)(hi << 32 | (lo & 0xffffffffull)))};
+}
 
 // One unit of a row as loaded -> its entry (every lane gets it).  `left`: logits of the row from the unit's start on.
 template <typename T>
@@ -88,6 +93,35 @@ __device__ __forceinline__ SampleEntry sweep_unit(RawSlice<T, false, kLaneSmall>
     double acc[2] = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < LANE; ++j) acc[j & 1] += (double)fast_exp2(__builtin_fmaf(x[j], k, -shift));
+    double z0, z1;
+    halves_sum_f64(acc[0] + acc[1], z0, z1);
+    e.z = z0 + z1;
+    return e;
+}
+
+// The same entry, vector by vector from a second look at the unit: slow, and in few registers (`unit`: the unit's start).
+template <typename T>
+__device__ __forceinline__ SampleEntry sweep_unit_slowly(const T *unit, int left, float k)
+{
+    constexpr int LANE = kLaneSmall, kVec = ElemTraits<T>::kVec;
+    const int lane = threadIdx.x & 63;
+    SampleEntry e = {-INFINITY, 0.0};
+    double acc[2] = {0.0, 0.0};
+    float x[kVec], m = -INFINITY, shift = 0.f;
+#pragma unroll 1
+    for (int step = 0; step < 2 * (LANE / kVec); ++step) {
+        const int at = ((step & (LANE / kVec - 1)) * kWave + lane) * kVec;
+        const uint4 raw = load_raw<T, false, true>(unit, left, at);
+        unpack_raw<T, false>(raw, left, at, x);
+        if (step < LANE / kVec) {
+#pragma unroll
+            for (int j = 0; j < kVec; ++j) m = fmaxf(m, x[j]);
+            if (step == LANE / kVec - 1) { e.m = wave_max(m * k); shift = shift_of(e.m); }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kVec; ++j) acc[j & 1] += (double)fast_exp2(__builtin_fmaf(x[j], k, -shift));
+        }
+    }
     double z0, z1;
     halves_sum_f64(acc[0] + acc[1], z0, z1);
     e.z = z0 + z1;
@@ -207,7 +241,7 @@ void sample_rows_kernel(const T *logits, int V, float k, const float *uniforms, 
 // For rows too few to fill the device: every wave sweeps one unit and leaves its entry; one wave per row then scans them (up
 // to kSampleSplitUnits units, a stretch of neighbours per lane), finds the unit and walks it: in a launch of its own, from `entries` [rows, units]
 // (NULL: the null stream's); or (ONE, calls on the null stream) as the first wave of the row's last workgroup, which waits for the words
-// of the others and clears them.
+// of the others and clears them.  Where that wait runs out (another kernel holds the compute units for seconds), it forms the missing entries itself.
 template <typename T, int PER>
 __device__ __forceinline__ int draw_from_entries(const T *row, int V, int units, int per, float k, float u, const SampleEntry (&mine)[PER])
 {
@@ -243,52 +277,57 @@ __device__ __forceinline__ int draw_from_entries(const T *row, int V, int units,
 
 template <typename T, bool ONE>
 __global__ __launch_bounds__(kThreads)
-void sample_units_kernel(const T *logits, int V, int units, float k, const float *uniforms, int32_t *tokens, SampleEntry *entries, int spin_limit)
+void sample_units_kernel(const T *logits, int V, int units, float k, const float *uniforms, int32_t *tokens, SampleEntry *entries, unsigned call, int spin_limit)
 {
     constexpr int kPer = kSampleOneUnits / kWave;
     const int lane = threadIdx.x & 63, unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
     const size_t r = blockIdx.y;
     if (unit >= units) return;
-    const int at = unit * kSampleUnit;
     const T *const row = logits + r * (size_t)V;
+    const int at = unit * kSampleUnit;
     RawSlice<T, false, kLaneSmall> raw;
     issue_loads<T, false, kLaneSmall>(row + at, 0, V - at, raw);
     const SampleEntry e = sweep_unit<T>(raw, V - at, k);
     if constexpr (!ONE) {
         if (lane == 0) (entries ? entries : g_null_stream_entries)[r * units + unit] = e;
     } else {
-        u64 *const words = g_null_stream_words + 2 * r * units;
-        if (lane < 2) {
-            u64 m, z;
-            pack_entry(e, m, z);
-            st_u64(words + 2 * unit + lane, lane == 0 ? m : z);
-        }
+        u64 *const words = g_null_stream_words + kEntryWords * r * units;
+        if (lane < kEntryWords) st_u64(words + kEntryWords * unit + lane, entry_word(e, lane, call));
         if (blockIdx.x != gridDim.x - 1 || threadIdx.x >= kWave) return;
         const float u = load_uniform(uniforms + r);
         const int per = (units - 1) / kWave + 1;
-        bool gave_up = false;
         // (lanes without an entry of their own look at the last one, which is waited for anyway)
-        u64 m[kPer], z[kPer];
+        u64 m[kPer], lo[kPer], hi[kPer];
         for (int spins = 0;; ++spins) {
-            bool missing = false;
+            int missing = 0;                                 // bit j: the lane's entry j
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                m[j] = lo[j] = hi[j] = 0;
+                if (j < per) {
+                    const u64 *const word = words + kEntryWords * min(lane * per + j, units - 1);
+                    m[j] = ld_u64(word); lo[j] = ld_u64(word + 1); hi[j] = ld_u64(word + 2);
+                }
+            }
 #pragma unroll
             for (int j = 0; j < kPer; ++j)
-                if (j < per) {
-                    const u64 *const word = words + 2 * min(lane * per + j, units - 1);
-                    m[j] = ld_u64(word); z[j] = ld_u64(word + 1);
-                }
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) if (j < per) missing = missing || m[j] == 0 || z[j] == 0;
-            if (!__any(missing)) break;
-            if (spins >= spin_limit) { gave_up = true; break; }
+                if (j < per && ((unsigned)(m[j] >> 32) != call || (unsigned)(lo[j] >> 32) != call || (unsigned)(hi[j] >> 32) != call)) missing |= 1 << j;
+            if (!__any(missing != 0)) break;
             __builtin_amdgcn_s_sleep(6);                 // (looks in quick succession hold up the writes to the lines they look at: 8 rows of 128256 logits 6.1 us with 1, 5.7 with 6)
+            if (spins < spin_limit) continue;
+            // (the words that a late wave will write, the same; nothing of it is prepared in front of the wait)
+            for (int n = 0; n < units; ++n) {
+                asm volatile("" : "+s"(n));
+                if ((__builtin_amdgcn_readlane(missing, n / per) >> n % per & 1) == 0) continue;
+                const SampleEntry again = sweep_unit_slowly<T>(row + n * kSampleUnit, V - n * kSampleUnit, k);
+                if (lane < kEntryWords) st_u64(words + kEntryWords * n + lane, entry_word(again, lane, call));
+            }
         }
         SampleEntry mine[kPer];
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) if (j < per) mine[j] = lane * per + j < units ? unpack_entry(m[j], z[j]) : SampleEntry{-INFINITY, 0.0};
-        for (int n = lane; n < 2 * units; n += kWave) st_u64(words + n, 0);
+        for (int j = 0; j < kPer; ++j) mine[j] = j < per && lane * per + j < units ? unpack_entry(m[j], lo[j], hi[j]) : SampleEntry{-INFINITY, 0.0};
+        for (int n = lane; n < kEntryWords * units; n += kWave) st_u64(words + n, 0);
         const int y = draw_from_entries(row, V, units, per, k, u, mine);
-        if (lane == 0) tokens[r] = gave_up ? -1 : y;
+        if (lane == 0) tokens[r] = y;
     }
 }
 template <typename T>

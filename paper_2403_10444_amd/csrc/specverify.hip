@@ -384,6 +384,15 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
 
 std::mutex g_null_stream_mutex;          // over the two launches of a drafting call on the null stream
 
+// A number for a drafting call of one launch, never 0: other than that of the 2^32 calls before (see sample.hpp).
+unsigned sample_call_number()
+{
+    static std::atomic<unsigned> next{1};
+    unsigned n;
+    do n = next.fetch_add(1); while (n == 0);
+    return n;
+}
+
 // The drafting step: how many waves share a row.  (`split`: rows spread over the device, through `entries`, or NULL: the null stream's.)
 template <typename T>
 sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const float *uniforms, int32_t *tokens, bool split, SampleEntry *entries, hipStream_t stream)
@@ -393,11 +402,11 @@ sv_status_t launch_sample(const void *logits_v, int rows, int V, float k, const 
         const int units = (V - 1) / kSampleUnit + 1;
         const dim3 grid((unsigned)((units - 1) / kWaves + 1), (unsigned)rows);
         if (!entries && units <= kSampleOneUnits && (long long)grid.x * rows <= kSampleOneLaunch) {
-            sample_units_kernel<T, true><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, nullptr, kDefaultSpinLimit);
+            sample_units_kernel<T, true><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, nullptr, sample_call_number(), g_spin_limit.load());
         } else {
             std::unique_lock<std::mutex> lock(g_null_stream_mutex, std::defer_lock);
             if (!entries) lock.lock();
-            sample_units_kernel<T, false><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, entries, 0);
+            sample_units_kernel<T, false><<<grid, kThreads, 0, stream>>>(logits, V, units, k, uniforms, tokens, entries, 0, 0);
             sample_finish_kernel<T><<<(unsigned)rows, kWave, 0, stream>>>(logits, V, units, k, uniforms, entries, tokens);
         }
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;

@@ -230,3 +230,26 @@ def test_sample_tokens_on_the_null_stream(rows, V, dtype):
             p = torch.softmax(x[r].double() / 0.9, -1).cpu().numpy()
             assert in_cell(p, float(u[r]), int(got[r])), (turn, r)
         assert int((got != want).sum()) <= 1
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_sample_tokens_on_the_null_stream_after_waits_that_run_out(dtype):
+    """A wave that stops waiting for the other units of its row forms what is missing itself: the same tokens, call after call, and what the
+    others leave behind for it is nobody's: the calls that follow, of other rows, shapes and types, are right."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    calls = []
+    for rows, V in ((64, 128256), (96, 61 * 2048 + 7), (1, 24 * 2048 + 1), (2, 256 * 2048 - 1), (64, 100001)):
+        for dt in (dtype, torch.float32):
+            x = (torch.randn((rows, V), generator=g, device="cuda") * 3.0).to(dt)
+            u = torch.rand((rows,), generator=g, device="cuda")
+            calls.append((x, u, sv.spec_sample_tokens(x, u, 0.9, stream=0)))
+    for turn in range(3):
+        for limit in (0, -1, 0, 0, -1):
+            sv.spec_verify_debug_config(0, limit)
+            try:
+                for n in range(len(calls)):
+                    x, u, want = calls[(n * 3 + turn) % len(calls)]
+                    got = sv.spec_sample_tokens(x, u, 0.9, stream=0)
+                    assert torch.equal(got, want), (turn, limit, tuple(x.shape), int((got != want).sum()), int(got.min()))
+            finally:
+                sv.spec_verify_debug_config(0, -1)
