@@ -337,7 +337,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
     const float *eta = P.uniforms + (size_t)b * (gamma + 1);
     // the chunk sums stay in LDS for the draw when they fit (the host sizes the dynamic LDS to match: one float per
     // sum, a second one per chunk for Alg. 4's rejected mass)
-    const bool keep = P.keep != 0;
+    const bool keep = ONE || P.keep != 0;               // (calls of one launch have no more sums than that)
     float *kept = reinterpret_cast<float *>(smd + probs_finish_doubles(gamma));
     float *kept_rej = kept + (gamma + 1) * nchunks;
 
@@ -376,9 +376,8 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
                 acc += (double)kept[i * nchunks + c];
                 if (GREEDY) rej += (double)kept_rej[i * nchunks + c];
             } else {
-                const size_t w = (size_t)i * nchunks + c;
-                const float2 v = take_shares<GREEDY, ONE>(pb + w, i < gb ? rb + w : nullptr, P.call, P.spin_limit, gave_up);
-                acc += (double)v.x; rej += (double)v.y;
+                const u64 v = pb[(size_t)i * nchunks + c];
+                acc += (double)stat_shift(v); rej += (double)stat_sum(v);
             }
         }
         acc = group_sum<kWave>(acc);
@@ -467,7 +466,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
         double carry = 0.0, t_in = INFINITY;
         for (int c0 = 0; c0 < nchunks && chunk < 0; c0 += 64) {
             const int c = c0 + lane;
-            const double v = c < nchunks ? (double)(keep ? kept[tau * nchunks + c] : __uint_as_float((unsigned)(ONE ? ld_u64(pp + c) : pp[c]))) : 0.0;
+            const double v = c < nchunks ? (double)(keep ? kept[tau * nchunks + c] : stat_shift(pp[c])) : 0.0;
             const double inc = wave_scan(v) + carry;
             const unsigned long long nz = __ballot(v > 0.0), hit = __ballot(c < nchunks && inc > t);
             if (nz) last_nonzero = c0 + 63 - __clzll((long long)nz);
@@ -504,11 +503,6 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
         }
         t_in -= total;
         ++c;
-    }
-    // (sums too many to keep: zeros are left behind now that they have been read for the last time)
-    if (ONE && !keep) {
-        for (int w = tid; w < n_words; w += kThreads) st_u64(pb + w, 0);
-        if (GREEDY) for (int w = tid; w < gb * nchunks; w += kThreads) st_u64(rb + w, 0);
     }
     int holder = -1, last_weight = 0;
     {

@@ -189,7 +189,8 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     static std::atomic<int> cap;
     const int resident = resident_workgroups(probs_residual_kernel<T, ALIGNED, false, true, true>, cap);
     if (resident < 1) return SV_ERR_HIP;
-    if (!in_front && blocks <= probs_at_once(resident, gamma, ElemTraits<T>::kVec == 4, ALIGNED)) {
+    // (the workgroup that finishes a sequence keeps its sums: no call this small has too many)
+    if (!in_front && P.keep && blocks <= probs_at_once(resident, gamma, ElemTraits<T>::kVec == 4, ALIGNED)) {
         (algo == kGreedy ? probs_residual_kernel<T, ALIGNED, true, true, true> : probs_residual_kernel<T, ALIGNED, false, true, true>)<<<blocks, kThreads, lds, stream>>>(P);
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }

@@ -174,19 +174,15 @@ def test_token_verification_on_both_sides_of_what_runs_at_once(B, dtype):
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma,V,dtype", [(60, 1, 60000, "bf16"), (70, 1, 60000, "bf16"),      # 960 and 1120 workgroups: one launch and two (gamma < 4)
-                                             (50, 4, 60000, "f32"), (52, 4, 60000, "f32"),         # 2000 and 2080 (gamma >= 4)
-                                             (2, 64, 1100000, "bf16")])                            # 8775 sums a sequence: more than a workgroup keeps
+                                             (50, 4, 60000, "f32"), (52, 4, 60000, "f32")])        # 2000 and 2080 (gamma >= 4)
 def test_probs_one_launch_on_whatever_the_workspace_holds(algo, B, gamma, V, dtype):
     """Calls of one launch count on words of their own call only: the same results on a workspace that was never prepared and
     holds other calls' words, ones or random bytes, call after call, and on a captured call replayed with other inputs."""
     import paper_2403_10444_amd as sv
-    if V > 1000000 and algo != "greedy":
-        pytest.skip("one algorithm at this size")
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=1.0, T=0.8)
     P, Q, inp = _probs_inputs(cfg, seed=B + gamma)
     want = _run_gpu(sv, algo, P, Q, inp)
-    if V <= 100000:
-        parity.compare(want, _run_oracle(algo, P, Q, inp), label=f"probs {B}x{gamma}x{V} {dtype} {algo}", greedy=(algo == "greedy"))
+    parity.compare(want, _run_oracle(algo, P, Q, inp), label=f"probs {B}x{gamma}x{V} {dtype} {algo}", greedy=(algo == "greedy"))
     n = sv.spec_verify_workspace_bytes(B, gamma, V)
     gen = torch.Generator(device=DEV).manual_seed(1)
     ws = torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV, generator=gen)
@@ -213,3 +209,24 @@ def test_probs_one_launch_on_whatever_the_workspace_holds(algo, B, gamma, V, dty
         eager = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"])
         torch.cuda.synchronize()
         assert torch.equal(tau, eager[0]) and torch.equal(y, eager[1]), turn
+
+
+def test_probs_more_sums_than_a_workgroup_keeps():
+    """8775 sums a sequence (Alg. 4: and as many rejected masses): two launches, the second one reads them from memory again."""
+    import paper_2403_10444_amd as sv
+    B, gamma, V = 2, 64, 1100000
+    cfg = _custom(B, gamma, V, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8)
+    P, Q, inp = _probs_inputs(cfg, seed=3)
+    got = _run_gpu(sv, "greedy", P, Q, inp)
+    for b in range(B):
+        w = torch.as_tensor(got["dbg"][b, :gamma, 0]).double()
+        S = torch.stack([(float(w[i]) * P[b, i].double() - Q[b, i].double()).clamp_(min=0).sum() for i in range(gamma)]).cpu().numpy()
+        R = torch.stack([(Q[b, i].double() - float(w[i]) * P[b, i].double()).clamp_(min=0).sum() for i in range(gamma)]).cpu().numpy()
+        # (w is reported as a float, and the sums are of floats: 2^-24 each, and some 2^-22 for the float sums of a chunk)
+        tol = 5e-7 * np.maximum(got["dbg"][b, :gamma, 0], 1.0)
+        assert np.all(np.abs(got["dbg"][b, :gamma, 1] - S) <= tol)
+        h = np.where(R > 0, np.minimum(S / np.maximum(R, 1e-300), 1.0), 1.0)
+        assert np.all(np.abs(got["dbg"][b, 1:gamma, 2] - h[1:]) <= 1e-5)
+        tests = inp["uniforms"][b, :gamma].cpu().numpy() < got["dbg"][b, 1:, 2]
+        assert got["accept_len"][b] == (np.nonzero(tests)[0].max() + 1 if tests.any() else 0)
+        assert 0 <= got["next_token"][b] < V
