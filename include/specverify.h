@@ -296,8 +296,8 @@ sv_status_t spec_verify_ex_noalloc(sv_algo_t algo, const void *target_logits, co
  * token with p_{i-1}(X_i) = 0 has ratio 0 and is never accepted.  draft_lens, the row strides and all
  * other arguments as for spec_verify_ex; the workspace is the same one (its initialised state is
  * neither needed nor disturbed).  Every element is read from device memory once, in one launch where the
- * call's workgroups all run at once, else in two (three for token verification without debug_out and for
- * thousands of short rows).
+ * call's workgroups all run at once and the stream is not being captured, else in two (three for token verification
+ * without debug_out and for thousands of short rows).
  */
 sv_status_t spec_verify_probs(sv_algo_t algo, const void *target_probs, const void *draft_probs,
                               const int32_t *draft_tokens, const int32_t *draft_lens,

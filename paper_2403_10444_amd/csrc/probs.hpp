@@ -150,36 +150,53 @@ struct ProbsParams {
     const float *uniforms;
     int gamma, V, nchunks, algo, every_sum, keep;      // keep: whether a sequence's chunk sums fit the launch's LDS
     int spin_limit;
-    unsigned call;                // this call's number (never 0)
-    u64 *part, *rejected;         // [B, gamma + 1, nchunks], [B, gamma, nchunks]: a chunk's share of S_i, of the rejected mass (Alg. 4): a float
-                                  // below the call's number; calls of more launches: both in `part`
+    u64 call;                     // calls of one launch: this call's number (see ShareWords)
+    // a chunk's shares of S_i and of the rejected mass (Alg. 4).  Calls of more launches: `part`, [B, gamma + 1, nchunks], both in one word.
+    // Calls of one: `part`, [B, gamma, nchunks, 2], of the row pairs, `part_last` and `check_last`, [B, nchunks], of a sequence's last target row
+    u64 *part, *part_last;
+    unsigned *check_last;
     ProbWeight *weights;          // [B, gamma + 1], calls of more launches than one
     int32_t *accept_len, *next_token;
     float *debug_out;
 };
 
 // ------------------------------------------------------------------ calls of one launch: how the shares reach the workgroup that finishes a sequence
-// That is its last one, which waits for the words of the others (all of them started before it) and leaves zeros behind.  A word counts
-// once its upper half is the number of this call: the memory need not be prepared, whatever it held before - and a captured
-// call, which has the same number every time, finds the zeros of the time before.  (The last to arrive finishing it, found by a count per
-// sequence, was 7 times slower: read-modify-writes of one line by workgroups all over the device take 40 ns each, one after the other.)
-__device__ __forceinline__ void leave_share(u64 *word, unsigned call, float v) { st_u64(word, (u64)call << 32 | __float_as_uint(v)); }
-__device__ __forceinline__ float await_share(const u64 *word, unsigned call, int limit, bool &gave_up)
+// That is its last one, which waits for the words of the others (all of them started before it).  The memory is not prepared: it holds whatever
+// other kernels, other calls or other tensors left there.  So a chunk's shares count where 64 bits beside them are this call's number, which
+// no call before it had: two words of 32 bits of it and one share each, every half of the number combined with the OTHER word's share.  A pair
+// of one old word and a new one is then taken only where the old word's share is the new one; a pair of two old words where all 64 bits meet by chance.
+// (The last target row's chunks have one share: a word, and a check of 32 bits.)  Counted arrivals instead of a wait, found by a count per
+// sequence, were slower: read-modify-writes of one line by workgroups all over the device take 40 ns each, one after the other.
+__device__ __forceinline__ void leave_shares(u64 *words, u64 call, float acc, float rej)
 {
-    u64 v = ld_u64(word);
-    for (int spins = 0; (unsigned)(v >> 32) != call; v = ld_u64(word)) {
+    const unsigned a = __float_as_uint(acc), r = __float_as_uint(rej);
+    st_u64(words, (u64)((unsigned)(call >> 32) ^ r) << 32 | a);
+    st_u64(words + 1, (u64)((unsigned)call ^ a) << 32 | r);
+}
+__device__ __forceinline__ float2 await_shares(const u64 *words, u64 call, int limit, bool &gave_up)
+{
+    for (int spins = 0;;) {
+        const u64 v = ld_u64(words), w = ld_u64(words + 1);
+        const unsigned a = (unsigned)v, r = (unsigned)w;
+        if (((unsigned)(v >> 32) ^ r) == (unsigned)(call >> 32) && ((unsigned)(w >> 32) ^ a) == (unsigned)call) return make_float2(__uint_as_float(a), __uint_as_float(r));
+        if (++spins > limit) { gave_up = true; return make_float2(0.f, 0.f); }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+__device__ __forceinline__ void leave_last_share(u64 *word, unsigned *check, u64 call, float acc)
+{
+    st_u64(word, (call >> 32) << 32 | __float_as_uint(acc));
+    st_u32(check, (unsigned)call ^ __float_as_uint(acc));
+}
+__device__ __forceinline__ float await_last_share(const u64 *word, const unsigned *check, u64 call, int limit, bool &gave_up)
+{
+    for (int spins = 0;;) {
+        const u64 v = ld_u64(word);
+        const unsigned c = ld_u32(check);
+        if (v >> 32 == call >> 32 && (c ^ (unsigned)v) == (unsigned)call) return __uint_as_float((unsigned)v);
         if (++spins > limit) { gave_up = true; return 0.f; }
         __builtin_amdgcn_s_sleep(1);
     }
-    return __uint_as_float((unsigned)v);
-}
-// A chunk's share of S_i and, for Alg. 4 (`rej_word`: not at the last position), of the rejected mass, as the workgroup that finishes the
-// sequence takes them (ONE: calls of one launch; else both are in one word, plain memory between two launches).
-template <bool GREEDY, bool ONE>
-__device__ __forceinline__ float2 take_shares(const u64 *word, const u64 *rej_word, unsigned call, int limit, bool &gave_up)
-{
-    if constexpr (ONE) return make_float2(await_share(word, call, limit, gave_up), GREEDY && rej_word ? await_share(rej_word, call, limit, gave_up) : 0.f);
-    else { const u64 w = *word; return make_float2(stat_shift(w), stat_sum(w)); }
 }
 
 template <typename T, bool ALIGNED, bool GREEDY, bool ONE>
@@ -269,13 +286,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ONE ? 
         acc = block_sum(acc, lds);
         if constexpr (GREEDY) rej = block_sum(rej, lds);
         if (tid == 0) {
-            u64 *const word = P.part + (size_t)pr * nchunks + c;
-            if constexpr (ONE) {
-                leave_share(word, P.call, acc);
-                if (GREEDY && !last) leave_share(P.rejected + ((size_t)b * gamma + i) * nchunks + c, P.call, rej);
-            } else {
-                *word = pack_stat(acc, rej);
-            }
+            const size_t last_word = (size_t)b * nchunks + c;
+            if constexpr (!ONE) P.part[(size_t)pr * nchunks + c] = pack_stat(acc, rej);
+            else if (last) leave_last_share(P.part_last + last_word, P.check_last + last_word, P.call, acc);
+            else leave_shares(P.part + 2 * (((size_t)b * gamma + i) * nchunks + c), P.call, acc, rej);
         }
     }
     if constexpr (ONE) {
@@ -333,7 +347,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
     double *S = smd, *R = smd + (gamma + 1);
     ProbWeight *const wb = reinterpret_cast<ProbWeight *>(smd + 2 * (gamma + 1));          // the sequence's constants, read once
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    u64 *const pb = P.part + (size_t)b * (gamma + 1) * nchunks, *const rb = P.rejected + (size_t)b * gamma * nchunks;
+    const u64 *const pb = P.part + (size_t)b * (ONE ? 2 * gamma : gamma + 1) * nchunks;
     const float *eta = P.uniforms + (size_t)b * (gamma + 1);
     // the chunk sums stay in LDS for the draw when they fit (the host sizes the dynamic LDS to match: one float per
     // sum, a second one per chunk for Alg. 4's rejected mass)
@@ -357,11 +371,17 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
     if (keep) {
         for (int w = tid; w < n_words; w += kThreads) {
             const int i = w / nchunks;
-            const bool is = !ONE || wb[i].needed != 0;
-            const float2 v = is ? take_shares<GREEDY, ONE>(pb + w, i < gb ? rb + w : nullptr, P.call, P.spin_limit, gave_up) : make_float2(0.f, 0.f);
+            float2 v = make_float2(0.f, 0.f);
+            if constexpr (!ONE) {
+                const u64 word = pb[w];
+                v = make_float2(stat_shift(word), stat_sum(word));
+            } else if (wb[i].needed) {
+                const size_t last_word = (size_t)b * nchunks + (w - i * nchunks);
+                if (i == gb) v.x = await_last_share(P.part_last + last_word, P.check_last + last_word, P.call, P.spin_limit, gave_up);
+                else v = await_shares(pb + 2 * w, P.call, P.spin_limit, gave_up);
+            }
             kept[w] = v.x;
             if constexpr (GREEDY) kept_rej[w] = v.y;
-            if (ONE && is) { st_u64(pb + w, 0); if (GREEDY && i < gb) st_u64(rb + w, 0); }
         }
     }
     if (!ONE) constants();

@@ -139,14 +139,30 @@ sv_status_t launch_staged(int algo, const void *target_v, const void *draft_v, c
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
-// A number for a call with probabilities, never 0: other than that of the 2^32 calls before, and where the first begins is
-// anyone's guess, so that what an unprepared workspace holds is not taken for this call's (see probs.hpp).
-unsigned probs_call_number()
+// A number of 64 bits for a call with probabilities: no other call of this process has it, and which ones come is anyone's guess (a count
+// from a start that depends on the time and on where the process lies, through a bijection), so that what an unprepared workspace holds is not
+// taken for this call's (see probs.hpp).
+u64 probs_call_number()
 {
-    static std::atomic<unsigned> next{(unsigned)(((u64)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull) >> 32)};
-    unsigned n;
-    do n = next.fetch_add(1); while (n == 0);
+    auto mixed = [](u64 x) {                             // (splitmix64's finishing steps)
+        x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+        x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+        return x ^ (x >> 31);
+    };
+    static std::atomic<u64> next{mixed((u64)std::chrono::steady_clock::now().time_since_epoch().count()) ^ (u64)reinterpret_cast<uintptr_t>(&next)};
+    u64 n;
+    do n = mixed(next.fetch_add(1)); while (n == 0);     // (what zeros say is no call's)
     return n;
+}
+
+// Whether calls on the stream are being recorded (the null stream's never are).
+bool being_captured(hipStream_t stream)
+{
+    if (!stream) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                             // (what is wrong with the stream the launches will say)
+    return true;
 }
 
 // Probabilities as inputs: one to three launches, every element read once.  Scratch: the staged path's areas
@@ -162,9 +178,10 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     P.target = target; P.draft = draft; P.tstride = tstride; P.dstride = dstride;
     P.tokens = tokens; P.draft_lens = draft_lens; P.uniforms = uniforms;
     P.gamma = gamma; P.V = V; P.nchunks = L.nchunks; P.algo = algo;
-    // (the words where the staged path has its row statistics, one for every chunk of all rows)
+    // (the words where the staged path has its row statistics, one for every chunk of all rows, and its residual partial sums)
     P.part = reinterpret_cast<u64 *>(ws + L.off_stats);
-    P.rejected = P.part + (size_t)B * (gamma + 1) * L.nchunks;
+    P.part_last = P.part + 2 * (size_t)B * gamma * L.nchunks;
+    P.check_last = reinterpret_cast<unsigned *>(ws + L.off_sspart);
     static_assert(sizeof(ProbWeight) <= sizeof(SeqCoef), "the weights reuse the staged path's row-constant area");
     ProbWeight *const weights = reinterpret_cast<ProbWeight *>(ws + L.off_coef);
     P.weights = weights;
@@ -190,7 +207,8 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     const int resident = resident_workgroups(probs_residual_kernel<T, ALIGNED, false, true, true>, cap);
     if (resident < 1) return SV_ERR_HIP;
     // (the workgroup that finishes a sequence keeps its sums: no call this small has too many)
-    if (!in_front && P.keep && blocks <= probs_at_once(resident, gamma, ElemTraits<T>::kVec == 4, ALIGNED)) {
+    // A recorded call has the same number every time it is replayed, and would take the words of the time before for its own: it has two launches.
+    if (!in_front && P.keep && blocks <= probs_at_once(resident, gamma, ElemTraits<T>::kVec == 4, ALIGNED) && !being_captured(stream)) {
         (algo == kGreedy ? probs_residual_kernel<T, ALIGNED, true, true, true> : probs_residual_kernel<T, ALIGNED, false, true, true>)<<<blocks, kThreads, lds, stream>>>(P);
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }

@@ -230,3 +230,61 @@ def test_probs_more_sums_than_a_workgroup_keeps():
         tests = inp["uniforms"][b, :gamma].cpu().numpy() < got["dbg"][b, 1:, 2]
         assert got["accept_len"][b] == (np.nonzero(tests)[0].max() + 1 if tests.any() else 0)
         assert 0 <= got["next_token"][b] < V
+
+
+@pytest.mark.parametrize("algo", ["block", "greedy"])
+def test_probs_words_that_look_like_the_next_calls(algo):
+    """What an unprepared workspace holds is never taken for the call's own, also where it carries the numbers of other calls, counted on."""
+    import paper_2403_10444_amd as sv
+    B, gamma, V = 12, 4, 40000
+    P, Q, inp = _probs_inputs(_custom(B, gamma, V, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8), seed=17)
+    want = _run_gpu(sv, algo, P, Q, inp)
+    ws = torch.zeros(sv.spec_verify_workspace_bytes(B, gamma, V) // 8, dtype=torch.int64, device=DEV)
+    junk = int(np.float32(0.25).view(np.int32))
+    for step in (1, 2, 3):
+        # (waits that run out leave words of the call behind whatever a call clears)
+        sv.spec_verify_debug_config(0, 0)
+        try:
+            _run_gpu(sv, algo, P, Q, inp, workspace=ws.view(torch.uint8))
+        finally:
+            sv.spec_verify_debug_config(0, -1)
+        upper = (ws >> 32).cpu().numpy()
+        numbers, count = np.unique(upper[upper != 0], return_counts=True)
+        for _ in range(step - 1):
+            _run_gpu(sv, algo, P, Q, inp)
+        number = int(numbers[count.argmax()]) + step if len(numbers) else step
+        ws.fill_(number << 32 | junk)
+        got = _run_gpu(sv, algo, P, Q, inp, workspace=ws.view(torch.uint8))
+        for key in want:
+            assert np.array_equal(got[key], want[key], equal_nan=True), (key, step)
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+def test_probs_recorded_calls_replayed_after_waits_that_run_out(algo):
+    """A recorded call carries the same arguments every time: none of a replay's words may count for the next one, whose inputs differ."""
+    import paper_2403_10444_amd as sv
+    B, gamma, V = 12, 4, 40000
+    P, Q, inp = _probs_inputs(_custom(B, gamma, V, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8), seed=18)
+    P2, Q2, inp2 = _probs_inputs(_custom(B, gamma, V, "bf16", sigma_t=2.0, sigma_d=1.5, T=0.8), seed=19)
+    ws = torch.zeros(sv.spec_verify_workspace_bytes(B, gamma, V), dtype=torch.uint8, device=DEV)
+    p, q, tok, u = P.clone(), Q.clone(), inp["draft_tokens"].clone(), inp["uniforms"].clone()
+    tau, y = (torch.empty(B, dtype=torch.int32, device=DEV) for _ in range(2))
+    sv.spec_verify_probs(algo, p, q, tok, u, workspace=ws, accept_len=tau, next_token=y)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    sv.spec_verify_debug_config(0, 0)
+    try:
+        with torch.cuda.graph(graph, stream=side):
+            sv.spec_verify_probs(algo, p, q, tok, u, workspace=ws, accept_len=tau, next_token=y)
+    finally:
+        sv.spec_verify_debug_config(0, -1)
+    for turn in range(6):
+        a, b, c = (P, Q, inp) if turn % 2 else (P2, Q2, inp2)
+        p.copy_(a), q.copy_(b), tok.copy_(c["draft_tokens"]), u.copy_(c["uniforms"])
+        tau.fill_(-7), y.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = sv.spec_verify_probs(algo, p, q, tok, u)
+        torch.cuda.synchronize()
+        assert torch.equal(tau, eager[0]) and torch.equal(y, eager[1]), turn
