@@ -41,7 +41,7 @@
  * Graph capture: a call is kernel launches only, but the FIRST call of each kernel variant (logit type, alignment,
  * row width class) asks the runtime once how many of its workgroups the device holds at a time; make one call of the
  * shape outside the capture first.
- * If the verification kernel ever gives up one of its (bounded) waits - which needs a device that does not start
+ * If a kernel that verifies logits ever gives up one of its (bounded) waits - which needs a device that does not start
  * workgroups in index order, or another kernel that takes its compute units away for seconds - the sequences concerned
  * get accept_len = next_token = -1 instead of a result, and spec_verify_workspace_check reports SV_ERR_INTERNAL.
  */
@@ -297,7 +297,8 @@ sv_status_t spec_verify_ex_noalloc(sv_algo_t algo, const void *target_logits, co
  * other arguments as for spec_verify_ex; the workspace is the same one (its initialised state is
  * neither needed nor disturbed).  Every element is read from device memory once, in one launch where the
  * call's workgroups all run at once and the stream is not being captured, else in two (three for token verification
- * without debug_out and for thousands of short rows).
+ * without debug_out and for thousands of short rows).  Results never depend on how long a wait takes: in the one launch,
+ * where the workgroup that finishes a sequence stops waiting for the others, it forms what is missing itself.
  */
 sv_status_t spec_verify_probs(sv_algo_t algo, const void *target_probs, const void *draft_probs,
                               const int32_t *draft_tokens, const int32_t *draft_lens,

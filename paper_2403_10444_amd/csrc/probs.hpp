@@ -69,6 +69,23 @@ __device__ __forceinline__ float prob_residual(float p, float q, float w_hi, flo
     return __builtin_fmaf(w_lo, p, __builtin_fmaf(w_hi, p, -q));
 }
 
+// A vector's part of a chunk's share of S_i (`last`: a sequence's last target row, q == 0) and, for Alg. 4, of the rejected mass.
+template <bool GREEDY, int N>
+__device__ __forceinline__ void add_residuals(const float (&xp)[N], const float (&xq)[N], bool last, float w_hi, float w_lo, float &acc, float &rej)
+{
+    if (last) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) acc += xp[e];
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const float d = prob_residual(xp[e], xq[e], w_hi, w_lo);
+        acc += fmaxf(d, 0.f);
+        if constexpr (GREEDY) rej += fmaxf(-d, 0.f);
+    }
+}
+
 __device__ __forceinline__ int clamped_draft_len(const int32_t *draft_lens, int b, int gamma)
 {
     if (!draft_lens) return gamma;
@@ -161,7 +178,8 @@ struct ProbsParams {
 };
 
 // ------------------------------------------------------------------ calls of one launch: how the shares reach the workgroup that finishes a sequence
-// That is its last one, which waits for the words of the others (all of them started before it).  The memory is not prepared: it holds whatever
+// That is its last one, which waits for the words of the others (all of them started before it); where a wait runs out (another kernel holds the
+// compute units for seconds) it forms the missing shares itself, in the same order.  The memory is not prepared: it holds whatever
 // other kernels, other calls or other tensors left there.  So a chunk's shares count where 64 bits beside them are this call's number, which
 // no call before it had: two words of 32 bits of it and one share each, every half of the number combined with the OTHER word's share.  A pair
 // of one old word and a new one is then taken only where the old word's share is the new one; a pair of two old words where all 64 bits meet by chance.
@@ -173,13 +191,14 @@ __device__ __forceinline__ void leave_shares(u64 *words, u64 call, float acc, fl
     st_u64(words, (u64)((unsigned)(call >> 32) ^ r) << 32 | a);
     st_u64(words + 1, (u64)((unsigned)call ^ a) << 32 | r);
 }
+constexpr float kMissingShare = -1.f;                     // (shares are sums of what is not negative)
 __device__ __forceinline__ float2 await_shares(const u64 *words, u64 call, int limit, bool &gave_up)
 {
     for (int spins = 0;;) {
         const u64 v = ld_u64(words), w = ld_u64(words + 1);
         const unsigned a = (unsigned)v, r = (unsigned)w;
         if (((unsigned)(v >> 32) ^ r) == (unsigned)(call >> 32) && ((unsigned)(w >> 32) ^ a) == (unsigned)call) return make_float2(__uint_as_float(a), __uint_as_float(r));
-        if (++spins > limit) { gave_up = true; return make_float2(0.f, 0.f); }
+        if (++spins > limit) { gave_up = true; return make_float2(kMissingShare, 0.f); }
         __builtin_amdgcn_s_sleep(1);
     }
 }
@@ -194,7 +213,7 @@ __device__ __forceinline__ float await_last_share(const u64 *word, const unsigne
         const u64 v = ld_u64(word);
         const unsigned c = ld_u32(check);
         if (v >> 32 == call >> 32 && (c ^ (unsigned)v) == (unsigned)call) return __uint_as_float((unsigned)v);
-        if (++spins > limit) { gave_up = true; return 0.f; }
+        if (++spins > limit) { gave_up = true; return kMissingShare; }
         __builtin_amdgcn_s_sleep(1);
     }
 }
@@ -270,18 +289,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ONE ? 
             const int idx = c * kChunk + (u * kThreads + tid) * kVec;
             float xp[kVec], xq[kVec];
             unpack_probs<T, ALIGNED>(rp[u], V, idx, xp);
-            if (last) {
-#pragma unroll
-                for (int e = 0; e < kVec; ++e) acc += xp[e];
-            } else {
-                unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
-#pragma unroll
-                for (int e = 0; e < kVec; ++e) {
-                    const float d = prob_residual(xp[e], xq[e], w_hi, w_lo);
-                    acc += fmaxf(d, 0.f);
-                    if constexpr (GREEDY) rej += fmaxf(-d, 0.f);
-                }
-            }
+            if (!last) unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
+            add_residuals<GREEDY>(xp, xq, last, w_hi, w_lo, acc, rej);
         }
         acc = block_sum(acc, lds);
         if constexpr (GREEDY) rej = block_sum(rej, lds);
@@ -385,7 +394,30 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
         }
     }
     if (!ONE) constants();
+    if (ONE && gave_up) s_gave_up = 1;
     __syncthreads();
+    if (ONE && s_gave_up) {
+        constexpr int kVec = ElemTraits<T>::kVec;
+        __shared__ float sums[kWaves];
+        for (int w = 0; w < n_words; ++w) {
+            if (kept[w] != kMissingShare) continue;              // (the same for the whole workgroup)
+            const int i = w / nchunks, start = (w - i * nchunks) * kChunk;
+            const T *const prow = target + ((size_t)b * (gamma + 1) + i) * tstride, *const qrow = draft + ((size_t)b * gamma + (i < gb ? i : 0)) * dstride;
+            float acc = 0.f, rej = 0.f;
+#pragma unroll 1
+            for (int at = 0; at < kChunk && start + at < V; at += kThreads * kVec) {
+                const int idx = start + at + tid * kVec;
+                float xp[kVec], xq[kVec];
+                unpack_probs<T, ALIGNED>(load_raw<T, ALIGNED, true>(prow, V, idx), V, idx, xp);
+                unpack_probs<T, ALIGNED>(load_raw<T, ALIGNED, true>(qrow, V, idx), V, idx, xq);
+                add_residuals<GREEDY>(xp, xq, i == gb, wb[i].w_hi, wb[i].w_lo, acc, rej);
+            }
+            acc = block_sum(acc, sums);
+            if constexpr (GREEDY) rej = block_sum(rej, sums);
+            if (tid == 0) { kept[w] = acc; if constexpr (GREEDY) kept_rej[w] = rej; }
+        }
+        __syncthreads();
+    }
 
     // S_i = sum over the chunks: wave (i mod 4) takes position i, lanes stride over the chunks
     for (int i = wave; i <= gb; i += kWaves) {
@@ -404,12 +436,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
         if (GREEDY) rej = group_sum<kWave>(rej);
         if (lane == 0) { S[i] = acc; R[i] = rej; }
     }
-    if (ONE && gave_up) s_gave_up = 1;
     __syncthreads();
-    if (ONE && s_gave_up) {
-        if (tid == 0) { accept_len[b] = -1; next_token[b] = -1; }
-        return;
-    }
 
     if (wave == 0) {
         // accept tests eta_i < h_i: lane l judges position l + 1 (positions 1 .. gb <= 64)

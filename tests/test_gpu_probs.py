@@ -288,3 +288,27 @@ def test_probs_recorded_calls_replayed_after_waits_that_run_out(algo):
         eager = sv.spec_verify_probs(algo, p, q, tok, u)
         torch.cuda.synchronize()
         assert torch.equal(tau, eager[0]) and torch.equal(y, eager[1]), turn
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", [(12, 4, 40000, "bf16"), (9, 5, 12917, "f32"), (30, 3, 16389, "bf16"), (7, 8, 8192, "f32"), (40, 2, 300, "bf16"),
+                                             (3, 64, 20001, "bf16")])
+def test_probs_waits_that_run_out(algo, B, gamma, V, dtype):
+    """The workgroup that finishes a sequence forms the shares itself that it stops waiting for: the same results, bit for bit."""
+    import paper_2403_10444_amd as sv
+    P, Q, inp = _probs_inputs(_custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=1.0, T=0.8), seed=B + V)
+    lens = torch.tensor([1 + (3 * b) % gamma for b in range(B)], dtype=torch.int32, device=DEV)
+    ws = sv.alloc_workspace(B, gamma, V, DEV)
+    runs = []
+    for limit in (-1, 0, 0, -1):
+        sv.spec_verify_debug_config(0, limit)
+        try:
+            got = _run_gpu(sv, algo, P, Q, inp, workspace=ws)
+            tau, y = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"], draft_lens=lens, workspace=ws)
+            runs.append((got["accept_len"], got["next_token"], got["dbg"], tau.cpu().numpy(), y.cpu().numpy()))
+        finally:
+            sv.spec_verify_debug_config(0, -1)
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert np.array_equal(a, b, equal_nan=True)
+    assert sv.spec_verify_workspace_check(ws, B, gamma, V) == 0
