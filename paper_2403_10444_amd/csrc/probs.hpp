@@ -306,7 +306,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ONE ? 
     }
 }
 // One workgroup per sequence, after probs_residual_kernel.  Four waves per SIMD, so that 1024 sequences are finished at once instead of 768 (aligned float32, 1000
-// sequences of 12 over 10728 tokens, Alg. 1: 59.3 -> 56.7 us the whole call); unaligned float32 rows would spill (500 of 12 over 10727: 37.8 -> 39.5).
+// sequences of 12 over 10728 tokens, Alg. 1: 59.3 -> 56.7 us the whole call); unaligned float32 rows would spill (this kernel, sequences of 12 over 10727, three
+// waves / four: 1000 19.5 / 18.8 us, 500 11.9 / 12.9).
 template <typename T, bool ALIGNED, bool GREEDY>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ElemTraits<T>::kVec == 8 || ALIGNED ? 4 : 3))) void probs_finish_kernel(const ProbsParams P)
 {
@@ -325,10 +326,17 @@ __device__ __forceinline__ void prob_wave_weights(const T *prow, const T *qrow, 
     constexpr int kVec = ElemTraits<T>::kVec, kNV = kPerThread / kVec;
     const int first = start + (int)(threadIdx.x & 63) * kVec;
     uint4 rp[kNV], rq[kNV];
+    if (!ALIGNED && V < kVec) {
+        // (asked once instead of at each of the loads: unaligned float32 rows, 1000 sequences of 12 over 10727 tokens, this kernel 23.7 -> 19.4 us)
+        const uint4 p = load_short_row(prow, V), q = load_short_row(qrow, V);
 #pragma unroll
-    for (int v = 0; v < kNV; ++v) {
-        rp[v] = load_raw<T, ALIGNED, false>(prow, V, first + v * kWave * kVec);
-        if (residual) rq[v] = load_raw<T, ALIGNED, false>(qrow, V, first + v * kWave * kVec);
+        for (int v = 0; v < kNV; ++v) { rp[v] = p; rq[v] = q; }
+    } else {
+#pragma unroll
+        for (int v = 0; v < kNV; ++v) {
+            rp[v] = load_raw<T, ALIGNED, false>(prow, V, first + v * kWave * kVec);
+            if (residual) rq[v] = load_raw<T, ALIGNED, false>(qrow, V, first + v * kWave * kVec);
+        }
     }
 #pragma unroll
     for (int v = 0; v < kNV; ++v) {
@@ -355,7 +363,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
     float *const debug_out = P.debug_out;
     double *S = smd, *R = smd + (gamma + 1);
     ProbWeight *const wb = reinterpret_cast<ProbWeight *>(smd + 2 * (gamma + 1));          // the sequence's constants, read once
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u64 *const pb = P.part + (size_t)b * (ONE ? 2 * gamma : gamma + 1) * nchunks;
     const float *eta = P.uniforms + (size_t)b * (gamma + 1);
     // the chunk sums stay in LDS for the draw when they fit (the host sizes the dynamic LDS to match: one float per

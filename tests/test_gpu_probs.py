@@ -312,3 +312,18 @@ def test_probs_waits_that_run_out(algo, B, gamma, V, dtype):
         for a, b in zip(runs[0], other):
             assert np.array_equal(a, b, equal_nan=True)
     assert sv.spec_verify_workspace_check(ws, B, gamma, V) == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,gamma", [(30, 3), (60, 64), (700, 3)])               # one launch; the launch of its own for the finish; with the weights' in front
+def test_probs_rows_shorter_than_a_vector(B, gamma, dtype):
+    import paper_2403_10444_amd as sv
+    for V in (1, 2, 3, 5, 7, 9):
+        P, Q, inp = _probs_inputs(_custom(B, gamma, V, dtype, sigma_t=1.0, sigma_d=0.5, T=1.0), seed=V + B)
+        for algo in ("block", "token", "greedy"):
+            got, ref = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"]), _run_oracle(algo, P, Q, inp)
+            torch.cuda.synchronize()
+            tau, y = (t.cpu().numpy() for t in got)
+            safe = ref["margins"].min(axis=1) >= parity.MARGIN
+            assert np.array_equal(tau[safe], ref["accept_len"][safe]) and np.array_equal(y[safe], ref["next_token"][safe]), (V, algo)
+            assert np.all((y >= 0) & (y < V))
