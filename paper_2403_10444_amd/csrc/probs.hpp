@@ -289,8 +289,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ONE ? 
             const int idx = c * kChunk + (u * kThreads + tid) * kVec;
             float xp[kVec], xq[kVec];
             unpack_probs<T, ALIGNED>(rp[u], V, idx, xp);
-            if (!last) unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
-            add_residuals<GREEDY>(xp, xq, last, w_hi, w_lo, acc, rej);
+            // (one question per vector: float32, 34 sequences of 4 over 16000 tokens 14.0 -> 13.9 us)
+            if (last) {
+                add_residuals<GREEDY>(xp, xp, true, w_hi, w_lo, acc, rej);
+            } else {
+                unpack_probs<T, ALIGNED>(rq[u], V, idx, xq);
+                add_residuals<GREEDY>(xp, xq, false, w_hi, w_lo, acc, rej);
+            }
         }
         acc = block_sum(acc, lds);
         if constexpr (GREEDY) rej = block_sum(rej, lds);
@@ -404,7 +409,7 @@ __device__ __forceinline__ void probs_finish(const ProbsParams &P, int b, int gb
     if (!ONE) constants();
     if (ONE && gave_up) s_gave_up = 1;
     __syncthreads();
-    if (ONE && s_gave_up) {
+    if (ONE && __builtin_expect(s_gave_up != 0, 0)) {
         constexpr int kVec = ElemTraits<T>::kVec;
         __shared__ float sums[kWaves];
         for (int w = 0; w < n_words; ++w) {
