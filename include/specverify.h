@@ -98,11 +98,12 @@ sv_status_t spec_verify_workspace_check(const void *workspace, int32_t B, int32_
  * most 2048 logits, or whose 2 gamma + 1 rows fit into LDS together, (2 gamma + 1) V <= 14336: one workgroup
  * (or wave) per sequence; else, calls of at most a few times the workgroups that the device keeps resident
  * (1.8 to 4.3 times, by type, row width, draft length and whether sequences bring their own) and rows of at
- * most 32 * 8192 logits: the kernel for calls of few resident sets;
+ * most 32 * 8192 logits: one of the two kernels for calls of few resident sets;
  * else the fused kernel where it takes the shape, else the staged kernels.  5 = the kernels of one workgroup
  * per sequence, as far as the sequence fits LDS; 7 = the
- * kernel for calls of few resident sets, up to three times or the library's own line where that is more
- * (calls beyond the limits of 5 and 7 are then refused), 1 = the
+ * kernels for calls of few resident sets, up to three times or the library's own line where that is more, whichever of the two
+ * the library takes for the call; 8 = of these the one whose workgroups form the ratios of all earlier positions themselves, 9 = the other one
+ * (calls beyond the limits of 5 and of 7, 8, 9 are then refused), 1 = the
  * four-launch staged kernels, 2 = the
  * single-launch fused kernel (takes V <= 128 * 8192 and a device that keeps four rows'
  * workgroups resident; other shapes are then refused), 3 / 4 = the fused kernel with its
@@ -121,7 +122,7 @@ enum {
     SV_KERNEL_STAGED = 1,     /* the four staged kernels                                   */
     SV_KERNEL_FUSED = 2,      /* the single-launch fused kernel                            */
     SV_KERNEL_TINY = 5,       /* one workgroup per sequence                                */
-    SV_KERNEL_RESIDENT = 7,   /* the kernel for calls of few resident sets                 */
+    SV_KERNEL_RESIDENT = 7,   /* a kernel for calls of few resident sets                   */
     SV_KERNEL_PROBS = 8       /* the kernels that take probabilities                       */
 };
 int32_t spec_verify_debug_last_kernel(void);
@@ -129,6 +130,10 @@ int32_t spec_verify_debug_last_kernel(void);
 /* Testing hook: how positions learned w_i in the last call of this process that took the fused kernel: 1 = as one published
  * word that travels from position to position, 0 = from the ratios of the earlier ones (-1 before the first such call).  */
 int32_t spec_verify_debug_last_chain(void);
+
+/* Testing hook: which of the two kernels the last call of few resident sets (SV_KERNEL_RESIDENT) of this process took: 1 = the one whose
+ * workgroups form the ratios of all earlier positions themselves, 0 = the other one (-1 before the first such call).  */
+int32_t spec_verify_debug_last_together(void);
 
 #ifdef SPECVERIFY_PROFILE_BUILD
 /* Tuning builds of the library only (compiled with -DSV_PROFILE; the product library exports no such symbol and

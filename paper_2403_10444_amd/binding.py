@@ -35,6 +35,7 @@ EXPORTED = (
     "spec_verify_debug_config",
     "spec_verify_debug_last_kernel",
     "spec_verify_debug_last_chain",
+    "spec_verify_debug_last_together",
     "spec_verify_debug_copy",
     "spec_verify_debug_stream_probe",
     "spec_sample_tokens",
@@ -113,6 +114,8 @@ def load() -> ctypes.CDLL:
         lib.spec_verify_debug_last_kernel.argtypes = []
         lib.spec_verify_debug_last_chain.restype = ctypes.c_int32
         lib.spec_verify_debug_last_chain.argtypes = []
+        lib.spec_verify_debug_last_together.restype = ctypes.c_int32
+        lib.spec_verify_debug_last_together.argtypes = []
         lib.spec_verify_debug_config.restype = None
         lib.spec_verify_debug_config.argtypes = [ctypes.c_int32, ctypes.c_int32]
         if hasattr(lib, "spec_verify_debug_profile"):          # tuning builds only
@@ -175,6 +178,11 @@ def spec_verify_debug_last_kernel() -> int:
 def spec_verify_debug_last_chain() -> int:
     """Testing hook: whether the last call on the fused kernel handed w_i on in a chain (see the header)."""
     return int(load().spec_verify_debug_last_chain())
+
+
+def spec_verify_debug_last_together() -> int:
+    """Testing hook: which kernel the last call of few resident sets took: 1 the one of together.hpp, 0 that of resident.hpp."""
+    return int(load().spec_verify_debug_last_together())
 
 
 def spec_verify_debug_profile(buffer) -> None:

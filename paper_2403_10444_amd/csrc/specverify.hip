@@ -33,10 +33,11 @@ constexpr int kDefaultSpinLimit = 1 << 20;
 // launches of whole sequences or rows (2^24 + 3 rows of 2049 logits to draw from, 256 threads each: three rows were drawn).
 constexpr unsigned long long kMaxLaunchThreads = 0xffffffffull;
 
-std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernel for calls of few resident sets (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
+std::atomic<int> g_path{0};                       // 0 auto, 1 staged, 2 fused, 5 one workgroup per sequence, 7 the kernels for calls of few resident sets, 8 / 9 that of together.hpp / of resident.hpp (testing hook; 3 / 4 / 6: fused with small / large units / small ones without the chain)
 std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
 std::atomic<int> g_last_chain{-1};                  // whether the last call on the fused kernel had the chain
+std::atomic<int> g_last_together{-1};               // whether the last call of few resident sets had the kernel of together.hpp
 std::atomic<int> g_lane{0};                        // 0 auto, 32 or 64: logits per lane of the fused kernel's units (testing hook)
 std::atomic<int> g_chain{-1};                      // -1 auto, 0 / 1: whether the fused kernel's leaders hand w_i on in a chain (testing hook)
 #ifdef SV_PROFILE
@@ -312,7 +313,7 @@ FusedParams word_params(int algo, const void *target, const void *draft, const i
     return P;
 }
 
-// The kernel for calls of few resident sets; SV_ERR_UNSUPPORTED for the calls it does not take (more workgroups than
+// The kernels for calls of few resident sets; SV_ERR_UNSUPPORTED for the calls they do not take (more workgroups than
 // resident_sets() times what the device keeps resident - kResidentSetsForced where the testing hook asks for it and that is more -,
 // rows of more than kResidentMaxGroups workgroups).
 template <typename T, bool ALIGNED>
@@ -327,14 +328,18 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     const int capacity = resident_workgroups(kernel, cap);
     if (capacity < 1) return SV_ERR_HIP;
     double sets = resident_sets(gamma, nwg, ElemTraits<T>::kVec == 4, draft_lens != nullptr, ALIGNED);
-    if (g_path.load() == 7 && sets < kResidentSetsForced) sets = kResidentSetsForced;
+    const int path = g_path.load();
+    if (path >= 7 && sets < kResidentSetsForced) sets = kResidentSetsForced;
     if ((double)((long long)nwg * B * (gamma + 1)) > sets * capacity) return SV_ERR_UNSUPPORTED;
     // (a rule without the report, which changes no decision)
-    if (runs_together((long long)nwg * B * (gamma + 1), resident_workgroups(together_verify_kernel<T, ALIGNED, 1>, cap_together), nwg, gamma, ElemTraits<T>::kVec == 4))
+    const bool together = path >= 8 ? path == 8
+        : runs_together((long long)nwg * B * (gamma + 1), resident_workgroups(together_verify_kernel<T, ALIGNED, 1>, cap_together), nwg, gamma, ElemTraits<T>::kVec == 4);
+    if (together)
         kernel = nwg <= 4 ? together_verify_kernel<T, ALIGNED, 0> : nwg <= 16 ? together_verify_kernel<T, ALIGNED, 1> : together_verify_kernel<T, ALIGNED, 2>;
     const FusedParams P = word_params(algo, target, draft, tokens, draft_lens, tstride, dstride, uniforms, B, gamma, V, k, kd, L,
                                       ws, accept_len, next_token, debug_out);
     kernel<<<dim3((unsigned)nwg, (unsigned)B, (unsigned)(gamma + 1)), kThreads, 0, stream>>>(P);
+    g_last_together.store(together ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
@@ -526,12 +531,12 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
 #define SV_DISPATCH(FN)                                                                   \
     (dtype == SV_DTYPE_F32 ? (aligned ? FN<float, true>(SV_ARGS) : FN<float, false>(SV_ARGS)) \
                            : (aligned ? FN<bf16_t, true>(SV_ARGS) : FN<bf16_t, false>(SV_ARGS)))
-    // calls of few resident sets: the kernel without a row leader's second look at the logits
-    if ((path == 7 || path == 0) && L.fused_ok) {
+    // calls of few resident sets: the kernels without a row leader's second look at the logits
+    if ((path >= 7 || path == 0) && L.fused_ok) {
         const sv_status_t st = SV_DISPATCH(launch_resident);
         if (st == SV_OK) g_last_kernel.store(SV_KERNEL_RESIDENT);
-        if (st != SV_ERR_UNSUPPORTED || path == 7) return st;
-    } else if (path == 7) {
+        if (st != SV_ERR_UNSUPPORTED || path >= 7) return st;
+    } else if (path >= 7) {
         return SV_ERR_UNSUPPORTED;
     }
     // the fused kernel (every logit read once) is the default; the staged kernels (every logit read twice)
@@ -604,10 +609,12 @@ int32_t spec_verify_debug_last_kernel(void) { return g_last_kernel.load(); }
 
 int32_t spec_verify_debug_last_chain(void) { return g_last_chain.load(); }
 
+int32_t spec_verify_debug_last_together(void) { return g_last_together.load(); }
+
 void spec_verify_debug_config(int32_t path, int32_t spin_limit)
 {
     const bool fused_form = path == 3 || path == 4 || path == 6;
-    g_path.store((path >= 0 && path <= 2) || path == 5 || path == 7 ? path : fused_form ? 2 : 0);
+    g_path.store((path >= 0 && path <= 2) || path == 5 || (path >= 7 && path <= 9) ? path : fused_form ? 2 : 0);
     g_lane.store(path == 4 ? kLaneLarge : fused_form ? kLaneSmall : 0);
     g_chain.store(fused_form ? path != 6 : -1);
     g_spin_limit.store(spin_limit >= 0 ? spin_limit : kDefaultSpinLimit);

@@ -32,7 +32,7 @@ def test_verification(T, to_target, to_draft, dtype):
         inp["draft_tokens"] = torch.multinomial(q.view(-1, V), 1).view(cfg.B, cfg.gamma).to(torch.int32)
         for algo in ("block", "token", "greedy"):
             ref = parity.run_oracle(algo, inp, T)
-            for path in (0, 1, 3, 4, 6, 7):
+            for path in (0, 1, 3, 4, 6, 8, 9):
                 sv.spec_verify_debug_config(path, -1)
                 try:
                     parity.compare(parity.run_gpu(algo, inp, T), ref, label=f"{to_target}/{to_draft}/T{T}/V{V}/{algo}/path{path}", greedy=algo == "greedy")
@@ -70,7 +70,7 @@ def test_tokens_stay_inside_the_vocabulary_beyond_the_range_of_logits(dtype):
         inp["target_logits"][::2, :, 3] = 1e10
         inp["draft_logits"][::3, :, 5] = 1e10
         for algo in ("block", "token", "greedy"):
-            for path in (0, 1, 3, 4, 6, 7):
+            for path in (0, 1, 3, 4, 6, 8, 9):
                 sv.spec_verify_debug_config(path, -1)
                 try:
                     tau, y = parity.ALGOS[algo][1](inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 1.0)

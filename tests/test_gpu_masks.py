@@ -35,7 +35,7 @@ def test_verification(T, value, dtype):
         inp["draft_tokens"] = torch.multinomial(q.view(-1, V), 1).view(cfg.B, cfg.gamma).to(torch.int32)
         for algo in ("block", "token", "greedy"):
             ref = parity.run_oracle(algo, inp, T)
-            for path in (0, 1, 3, 4, 6, 7):
+            for path in (0, 1, 3, 4, 6, 8, 9):
                 sv.spec_verify_debug_config(path, -1)
                 try:
                     parity.compare(parity.run_gpu(algo, inp, T), ref, label=f"{value}/T{T}/V{V}/{algo}/path{path}", greedy=algo == "greedy")

@@ -1,6 +1,6 @@
-"""The kernel for calls whose workgroups all run at once (every workgroup of a row forms the row's S_i, the one that
-holds the token draws it from its registers) against the CPU oracle: forced through the testing hook, as the library's
-own choice for such calls, and in turns with the large kernel on one workspace."""
+"""The kernels for calls of few resident sets against the CPU oracle, each forced through the testing hook: that of resident.hpp (every
+workgroup of a row forms the row's S_i, the one that holds the token draws it from its registers) and that of together.hpp (every workgroup forms
+the ratios of all earlier positions too); the library's own choice between them, and in turns with the large kernel on one workspace."""
 from __future__ import annotations
 
 import numpy as np
@@ -15,15 +15,20 @@ from tests import parity
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
-RESIDENT = 7                 # spec_verify_debug_config path
+TOGETHER, RESIDENT = 8, 9    # spec_verify_debug_config path
 FUSED = 3                    # the large kernel, small units
 
 
-@pytest.fixture(autouse=True)
-def forced():
-    sv.spec_verify_debug_config(RESIDENT, -1)
-    yield
+@pytest.fixture(autouse=True, params=[RESIDENT, TOGETHER], ids=["resident", "together"])
+def forced(request):
+    sv.spec_verify_debug_config(request.param, -1)
+    yield request.param
     sv.spec_verify_debug_config(0, -1)
+
+
+def _ran(path):
+    """Whether the last call took the kernel that `path` forces."""
+    return sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT and sv.spec_verify_debug_last_together() == (path == TOGETHER)
 
 
 def _custom(B, gamma, V, dtype="bf16", sigma_t=3.0, sigma_d=1.0, T=1.0, zipf=False):
@@ -56,37 +61,38 @@ SHAPES = [
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma,V,dtype", SHAPES)
-def test_shapes(B, gamma, V, dtype, algo):
+def test_shapes(B, gamma, V, dtype, algo, forced):
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=0.8, T=0.9)
     for seed in (41, 42):
         inp = workloads.generate(cfg, seed=seed + B + gamma, device=DEV)
         rep = parity.compare(parity.run_gpu(algo, inp, cfg.temperature), parity.run_oracle(algo, inp, cfg.temperature),
-                             label=f"{cfg.name}/{algo}/resident", greedy=algo == "greedy")
+                             label=f"{cfg.name}/{algo}/path{forced}", greedy=algo == "greedy")
+        assert _ran(forced)
         parity.record(rep)
 
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
-def test_configuration_2_two_seeds(algo):
+def test_configuration_2_two_seeds(algo, forced):
     cfg = workloads.CONFIGS[2]
     for seed in (2000, 2001):
         inp = workloads.generate(cfg, seed=seed, device=DEV)
         rep = parity.compare(parity.run_gpu(algo, inp, cfg.temperature), parity.run_oracle(algo, inp, cfg.temperature),
-                             label=f"cfg2/seed{seed}/{algo}/resident", greedy=algo == "greedy")
+                             label=f"cfg2/seed{seed}/{algo}/path{forced}", greedy=algo == "greedy")
         parity.record(rep)
 
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
-def test_the_librarys_own_choice_for_calls_of_one_resident_set_is_this_kernel(algo):
-    """Without the hook the library takes this kernel where the call's workgroups all run at once: same outputs, bit for
-    bit, debug block included; the large kernel forced on the same inputs agrees with both on tau and Y (its residual
-    masses are sums in another order)."""
-    cfg = _custom(12, 6, 20000, "bf16", sigma_t=3.0, sigma_d=1.0, T=0.8)
+def test_the_librarys_own_choice_is_this_kernel(algo, forced):
+    """Without the hook the library takes the kernel of together.hpp where the call's workgroups all run at once (252 here), that of
+    resident.hpp beyond (1440): same outputs, bit for bit, debug block included; the large kernel forced on the same inputs agrees with both on
+    tau and Y (its residual masses are sums in another order)."""
+    cfg = _custom(*((12, 6, 20000) if forced == TOGETHER else (40, 8, 32000)), "bf16", sigma_t=3.0, sigma_d=1.0, T=0.8)
     inp = workloads.generate(cfg, seed=78, device=DEV)
     a = parity.run_gpu(algo, inp, cfg.temperature)
-    assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT
+    assert _ran(forced)
     sv.spec_verify_debug_config(0, -1)
     b = parity.run_gpu(algo, inp, cfg.temperature)
-    assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT
+    assert _ran(forced)
     sv.spec_verify_debug_config(FUSED, -1)
     c = parity.run_gpu(algo, inp, cfg.temperature)
     assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_FUSED
@@ -99,12 +105,13 @@ def test_the_librarys_own_choice_for_calls_of_one_resident_set_is_this_kernel(al
 
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
-def test_in_turns_with_the_large_kernel_on_one_workspace(algo):
-    """The two kernels share the control words and the call count of a workspace: calls of either may follow each
+def test_in_turns_with_the_large_kernel_on_one_workspace(algo, forced):
+    """The kernels share the control words and the call count of a workspace: calls of any may follow each
     other, in any order, and every call gives what it gives on a fresh workspace."""
     cfg = _custom(9, 5, 12000, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8)
     ws = sv.alloc_workspace(cfg.B, cfg.gamma, cfg.V, DEV)
-    order = [RESIDENT, FUSED, FUSED, RESIDENT, RESIDENT, FUSED, RESIDENT, 4, RESIDENT, FUSED]          # (4: the large kernel with its large units)
+    # (4: the large kernel with its large units.  The kernel of together.hpp leaves copies of its words where the others have none of their own)
+    order = [forced, FUSED, FUSED, forced, forced, FUSED, forced, 4, forced, FUSED, TOGETHER, RESIDENT, TOGETHER, TOGETHER, RESIDENT, RESIDENT, TOGETHER, 6, TOGETHER]
     for n, path in enumerate(order):
         inp = workloads.generate(cfg, seed=900 + n, device=DEV)
         sv.spec_verify_debug_config(path, -1)
@@ -113,7 +120,7 @@ def test_in_turns_with_the_large_kernel_on_one_workspace(algo):
         parity.compare(got, parity.run_oracle(algo, inp, cfg.temperature), label=f"turn{n}/path{path}", greedy=algo == "greedy")
 
 
-def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_kernel_otherwise():
+def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_kernel_otherwise(forced):
     for B, gamma, V in ((400, 8, 32000), (1, 1, 270000)):       # more workgroups than run at once; rows of 33 workgroups
         cfg = workloads.Config("not_resident", B, gamma, V, "bf16", 2.0, 1.0, 1.0, False, 1)
         inp = workloads.generate(cfg, seed=1, device=DEV)
@@ -123,21 +130,22 @@ def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_ker
         sv.spec_verify_debug_config(0, -1)
         parity.compare(parity.run_gpu("block", inp, 1.0), parity.run_oracle("block", inp, 1.0))
         assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_FUSED
-        sv.spec_verify_debug_config(RESIDENT, -1)
+        sv.spec_verify_debug_config(forced, -1)
 
 
 @pytest.mark.parametrize("B,gamma,V,dtype,lens", [(560, 8, 5000, "bf16", True), (270, 8, 9000, "bf16", True), (440, 8, 3000, "bf16", False),
                                                   (340, 8, 5000, "f32", True)])
-def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype, lens):
-    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths)."""
+def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype, lens, forced):
+    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths): the same decisions (here, where no uniform
+    is next to an edge, from both kernels)."""
     cfg = workloads.Config(f"forced_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 1.0, 0.8, False, 1)
     inp = workloads.generate(cfg, seed=B, device=DEV)
     dl = torch.tensor([1 + (b * 5) % gamma for b in range(B)], dtype=torch.int32, device=DEV) if lens else None
     out = []
-    for path in (0, RESIDENT):
+    for path in (0, forced):
         sv.spec_verify_debug_config(path, -1)
         tau, y = sv.spec_verify_ex("block", inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 0.8, draft_lens=dl)
-        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT
+        assert _ran(path or (TOGETHER if dtype == "f32" else RESIDENT))
         out.append((tau.cpu().numpy(), y.cpu().numpy()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
@@ -150,7 +158,9 @@ def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype
     (169, 8, 9001, "f32", False, "RESIDENT"), (158, 8, 9000, "f32", False, "RESIDENT"),       # two: 3.0, aligned 2.8
     (162, 8, 9000, "f32", False, "FUSED"), (73, 8, 25000, "f32", False, "RESIDENT"), (75, 8, 25000, "f32", False, "FUSED"),
     (52, 8, 65536, "bf16", True, "RESIDENT"), (56, 8, 65536, "bf16", True, "FUSED")])         # own lengths, eight: 3.0
-def test_the_line_to_the_large_kernel(B, gamma, V, dtype, lens, kernel):
+def test_the_line_to_the_large_kernel(B, gamma, V, dtype, lens, kernel, forced):
+    if forced == TOGETHER:
+        pytest.skip("the library's own choice: once is enough")
     from tests.test_gpu_random_shapes import _check
     cfg = workloads.Config(f"line_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 0.7, 0.9, False, 1)
     _check(dict(cfg=cfg, algo="block", path="default", top_k=0, use_lens=lens, pad_t=0, pad_d=0, lens_seed=B), B + V, False)
@@ -204,7 +214,7 @@ def test_masked_logits_top_k(algo, kt, kd):
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma,V,dtype", [(24, 8, 8400, "bf16"), (9, 5, 12917, "f32"), (40, 16, 3000, "bf16"), (50, 8, 30000, "bf16")])
-def test_ragged_draft_lengths(algo, B, gamma, V, dtype):
+def test_ragged_draft_lengths(algo, B, gamma, V, dtype, forced):
     """Sequence b must come out exactly as a call with gamma = draft_lens[b] on its leading rows does; the rows beyond
     a sequence's length are poisoned with NaN to show that they are never read."""
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=1.0, T=0.8)
@@ -224,6 +234,7 @@ def test_ragged_draft_lengths(algo, B, gamma, V, dtype):
         tau, y = sv.spec_verify_ex(algo, tl, dl, inp["draft_tokens"], inp["uniforms"], cfg.temperature,
                                    draft_lens=torch.as_tensor(lens, device=DEV), workspace=ws)
         torch.cuda.synchronize()
+        assert _ran(forced)
         tau, y = tau.cpu().numpy(), y.cpu().numpy()
         n_safe = 0
         for g in np.unique(lens):
@@ -239,7 +250,7 @@ def test_ragged_draft_lengths(algo, B, gamma, V, dtype):
         assert n_safe >= 0.8 * B
         sv.spec_verify_debug_config(FUSED, -1)
         sv.spec_verify_ex(algo, inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], cfg.temperature, workspace=ws)
-        sv.spec_verify_debug_config(RESIDENT, -1)
+        sv.spec_verify_debug_config(forced, -1)
 
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
@@ -273,20 +284,21 @@ def test_workspace_must_be_initialised_for_the_shape():
     assert bool((tau == -1).all()) and bool((y == -1).all())
 
 
-def test_waits_that_run_out_give_minus_one_and_the_workspace_says_so():
+def test_waits_that_run_out_give_minus_one_and_the_workspace_says_so(forced):
     """A spin limit of zero polls makes every wait that finds its word missing give up at once; the kernel still ends,
     every sequence either has its correct result or -1, and the workspace reports the error where any gave up."""
     cfg = _custom(40, 6, 16000, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8)
     inp = workloads.generate(cfg, seed=11, device=DEV)
     ws = sv.alloc_workspace(cfg.B, cfg.gamma, cfg.V, DEV)
-    sv.spec_verify_debug_config(RESIDENT, 0)
+    sv.spec_verify_debug_config(forced, 0)
     try:
         tau, y = sv.spec_verify_block(inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"],
                                       cfg.temperature, workspace=ws)
         torch.cuda.synchronize()
         status = binding.spec_verify_workspace_check(ws, cfg.B, cfg.gamma, cfg.V)
     finally:
-        sv.spec_verify_debug_config(RESIDENT, -1)
+        sv.spec_verify_debug_config(forced, -1)
+    assert _ran(forced)
     assert status in (0, 5)                      # 5 = SV_ERR_INTERNAL when some wave really had to wait
     tau, y = tau.cpu().numpy(), y.cpu().numpy()
     ref = parity.run_oracle("block", inp, cfg.temperature)
@@ -299,3 +311,17 @@ def test_waits_that_run_out_give_minus_one_and_the_workspace_says_so():
     sv.spec_verify_workspace_init(ws, cfg.B, cfg.gamma, cfg.V)
     parity.compare(parity.run_gpu("block", inp, cfg.temperature, workspace=ws), ref)
     assert binding.spec_verify_workspace_check(ws, cfg.B, cfg.gamma, cfg.V) == 0
+
+
+# (shapes where the library takes that kernel: long float32 drafts of wide rows, and a resident set's worth and more of them)
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype", [(1, 10, 140000, "f32"), (9, 16, 40964, "f32"), (9, 16, 40961, "f32")])
+def test_float32_rows_on_the_kernel_that_the_library_takes(B, gamma, V, dtype, algo, forced):
+    cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=0.5, T=0.9)
+    inp = workloads.generate(cfg, seed=V + B, device=DEV)
+    ref = parity.run_oracle(algo, inp, cfg.temperature)
+    parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}/path{forced}", greedy=algo == "greedy")
+    assert _ran(forced)
+    sv.spec_verify_debug_config(0, -1)
+    parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}", greedy=algo == "greedy")
+    assert _ran(RESIDENT)

@@ -38,7 +38,7 @@ def test_rows_at_any_address(V, dtype):
         ref = parity.run_oracle(algo, inp, T)
         dbg = torch.full((cfg.B, cfg.gamma + 1, 3), float("nan"), dtype=torch.float32, device=DEV)
         t, d = _placed(inp["target_logits"], offset, pad), _placed(inp["draft_logits"], offset, pad)
-        for path in (0, 1, 3, 7):
+        for path in (0, 1, 3, 8, 9):
             sv.spec_verify_debug_config(path, -1)
             try:
                 tau, y = sv.spec_verify_ex(algo, t, d, inp["draft_tokens"], inp["uniforms"], T, debug_out=dbg)

@@ -35,7 +35,7 @@ def test_forms(B, gamma, V, dtype, algo):
     for seed, sigma_d in ((1, 0.8), (2, 0.05)):                              # (close models: most tokens are accepted)
         inp = workloads.generate(workloads.with_overrides(cfg, sigma_draft=sigma_d), seed=seed + gamma + V, device=DEV)
         got = parity.run_gpu(algo, inp, cfg.temperature)
-        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT
+        assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT and sv.spec_verify_debug_last_together() == 1
         parity.compare(got, parity.run_oracle(algo, inp, cfg.temperature), label=f"{cfg.name}/{algo}", greedy=algo == "greedy")
 
 
@@ -60,7 +60,7 @@ def test_in_turns_with_the_other_kernels_on_one_workspace():
     workspace, drafts of the sequences' own lengths among them."""
     B, gamma, V = 24, 7, 30001                                               # (768 workgroups)
     ws = sv.alloc_workspace(B, gamma, V, DEV)
-    for n, path in enumerate([0, 0, 3, 0, 4, 0, 6, 4, 0, 0, 3, 4, 0]):
+    for n, path in enumerate([0, 0, 3, 0, 4, 0, 6, 4, 0, 0, 3, 4, 0, 9, 0, 9, 9, 3, 0, 9]):
         cfg = _cfg(B, gamma, V, "f32" if n % 3 == 2 else "bf16")
         inp = workloads.generate(cfg, seed=100 + n, device=DEV)
         sv.spec_verify_debug_config(path, -1)
@@ -77,3 +77,20 @@ def test_in_turns_with_the_other_kernels_on_one_workspace():
         parity.compare(got, ref, label=f"turn{n}/path{path}")
         assert (np.array([int((a != b).sum()) for a, b in zip(own, fresh)]) <= (0 if path == 0 else 1)).all()
         assert binding.spec_verify_workspace_check(ws, B, gamma, V) == binding.SV_OK
+
+
+# Both sides of the lines between this kernel and the other one for calls of few resident sets (runs_together): what calls of 1024 resident workgroups
+# are, by type, draft length and row width.
+@pytest.mark.parametrize("B,gamma,V,dtype,together", [
+    (1, 8, 140000, "bf16", 1), (1, 9, 140000, "bf16", 0), (1, 8, 140000, "f32", 1), (1, 9, 140000, "f32", 0),        # 18 workgroups a row: drafts of up to 8
+    (8, 6, 140000, "bf16", 1), (9, 6, 140000, "bf16", 0), (11, 4, 140000, "bf16", 1), (13, 4, 140000, "bf16", 0),    # 1008, 1134; 990, 1170
+    (8, 16, 40961, "f32", 1), (9, 16, 40961, "f32", 0), (11, 12, 40961, "f32", 1),                                    # 816, 918; drafts of up to 12: 858
+    (32, 8, 30001, "bf16", 1), (33, 8, 30001, "bf16", 0), (64, 3, 30001, "bf16", 1), (65, 3, 30001, "bf16", 0),      # 1152, 1188; drafts of three 1024, 1040
+    (70, 8, 16000, "f32", 1)])                                                                                        # 1260: float32 has no such line
+def test_both_sides_of_its_lines(B, gamma, V, dtype, together):
+    cfg = _cfg(B, gamma, V, dtype)
+    inp = workloads.generate(cfg, seed=B + gamma, device=DEV)
+    algo = ("block", "token", "greedy")[(B + gamma) % 3]
+    got = parity.run_gpu(algo, inp, cfg.temperature)
+    assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_RESIDENT and sv.spec_verify_debug_last_together() == together
+    parity.compare(got, parity.run_oracle(algo, inp, cfg.temperature), label=f"{cfg.name}/{algo}", greedy=algo == "greedy")
