@@ -1527,4 +1527,12 @@ __global__ void workspace_init_kernel(int *words, size_t n, int magic)
         words[idx] = idx == kHdrMagic ? magic : 0;
 }
 
+// After a call with the larger units (testing hook), whose words lie closer together than the workspace is laid out for: clears the copy that
+// the next call uses as that layout has it (`P.nu`: its units per row), one wave per row slot.  (The call itself has cleared what its own layout reaches.)
+__global__ __launch_bounds__(kWave) void clear_next_words_kernel(const FusedParams P)
+{
+    if (P.header[kHdrMagic] != P.magic) return;
+    clear_row_words(P, words_of(P, (unsigned)P.gen[blockIdx.x] & 1u), blockIdx.x, blockIdx.y, true);
+}
+
 }  // namespace sv

@@ -402,6 +402,10 @@ sv_status_t launch_fused(int algo, const void *target, const void *draft, const 
     const int forced_chain = g_chain.load();
     const bool in_chain = large || (P.prune && (forced_chain >= 0 ? forced_chain != 0 : sets > (draft_lens ? 0.9 : 0.45) * gamma));
     (in_chain ? chain : ratios)<<<grid, kThreads, 0, stream>>>(P);
+    if (nu != L.nu) {
+        P.nu = L.nu;
+        clear_next_words_kernel<<<dim3((unsigned)B, (unsigned)(gamma + 1)), kWave, 0, stream>>>(P);
+    }
     g_last_chain.store(in_chain ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }

@@ -325,3 +325,33 @@ def test_float32_rows_on_the_kernel_that_the_library_takes(B, gamma, V, dtype, a
     sv.spec_verify_debug_config(0, -1)
     parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}", greedy=algo == "greedy")
     assert _ran(RESIDENT)
+
+
+def test_every_kernel_leaves_the_words_of_the_next_call_clear(forced):
+    """Whatever follows whatever on a workspace: the copy of the words that the next call uses is zero, all of it (the kernel of the larger
+    units has its words closer together than the others)."""
+    if forced == TOGETHER:
+        pytest.skip("forces every kernel itself")
+    B, gamma, V = 9, 5, 40000
+    cfg = _custom(B, gamma, V, "bf16", sigma_t=2.5, sigma_d=1.0, T=0.8)
+    inp = workloads.generate(cfg, seed=3, device=DEV)
+    lens = torch.tensor([1 + b % gamma for b in range(B)], dtype=torch.int32, device=DEV)
+    ws = sv.alloc_workspace(B, gamma, V, DEV)
+    # the control words: header, call counts, two copies (see the library's layout)
+    rows, nwg = B * gamma, -(-V // 8192)
+    first = 256 + -(-4 * B // 256) * 256
+    n = 8 * (3 * rows + 4 * rows * nwg + 4 * B * nwg)
+    n = -(-n // 16) * 16 + 8 * 2 * rows * nwg + 4 * 4 * rows * nwg
+    n = -(-n // 8) * 8 + 8 * B * nwg
+    copies = (first, first + -(-n // 256) * 256)
+    for path in (3, 4, 4, RESIDENT, 4, TOGETHER, 4, 6, TOGETHER, RESIDENT, 4, 3):
+        for dl in (None, lens):
+            sv.spec_verify_debug_config(path, -1)
+            sv.spec_verify_ex("block", inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 0.8, draft_lens=dl, workspace=ws)
+            torch.cuda.synchronize()
+            counts = ws[256:256 + 4 * B].view(torch.int32) & 1
+            assert bool((counts == counts[0]).all())
+            at = copies[int(counts[0])]
+            assert int(ws[at:at + n].count_nonzero()) == 0, (path, dl is not None)
+            other = copies[1 - int(counts[0])]
+            assert int(ws[other:other + n].count_nonzero()) > 0
