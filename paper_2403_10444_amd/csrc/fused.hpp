@@ -80,8 +80,9 @@ __host__ __device__ inline int workspace_magic(int B, int gamma, int V)
     return (int)(0x53564b34u ^ ((unsigned)B * 2654435761u + (unsigned)gamma * 40503u + (unsigned)V * 2246822519u));
 }
 
-// (kHdrRowWords: non-zero once a kernel that publishes the per-wave words of target rows - the one of the larger units -
-// has worked on the workspace: only then do the other kernels' leaders clear those words with the rest of a row's)
+// (kHdrRowWords: non-zero once a kernel has worked on the workspace that fills in Words::pstat - the one of the larger units, with the
+// per-wave words of target rows, or that of together.hpp, with copies of a row's words: only then do the other kernels' leaders clear that
+// area with the rest of a row's words.  It stays set until the workspace is prepared again)
 enum HeaderWord : int { kHdrMagic = 0, kHdrError = 1, kHdrRowWords = 2, kHdrWords = 64 };
 
 typedef unsigned long long u64;
@@ -96,7 +97,8 @@ struct Words {
                           //                          passes (Alg. 2 / 4: eta_i < h_i; Alg. 1: the test of X_{i+1}) and the token drawn from
                           //                          row pair i's residual where tau can still be i; by the leader of row pair i
     u64 *pstat;           // [B, gamma, nu]           (largest scaled logit, sum) per wave chunk of a row pair's target row: filled in
-                          //                          only by a wave that has to draw from that row itself (draw_from_target_row)
+                          //                          only by a wave that has to draw from that row itself (draw_from_target_row).  The
+                          //                          kernel of together.hpp has two more copies of the row's pgrp / qgrp words there
     u64 *plast;           // [B, nu]                  the same of the sequence's last target row (row draft_lens[b])
     u64 *pgrp, *qgrp;     // [B, gamma, nu / 4, 2]    packed (shift, sum) per workgroup chunk of a row pair's target / draft row, side by
                           //                          side (qgrp = pgrp + 1; entry e of a row's words lies 2 e words on): a workgroup's two
@@ -790,7 +792,7 @@ __device__ __forceinline__ int draw_from_row(const FusedParams &P, const Words &
     // (the first kHeld shares of the residual per lane - the whole row up to kHeld * 64 chunks - are asked for in one go, the row's constants
     // formed under them, and kept for the second pass.  Asked for again in each pass, the draw took two or three trips through memory one after
     // the other at the end of every row that can become tau: 1097 ragged sequences of up to 6 drafted tokens and 14230 entries bf16 92.5 ->
-    // 87.9 us, 427 of 8 48.3 -> 46.8, 64 of 8 and 128256 full 49.2 -> 48.8)
+    // 87.9 us, 427 of 8 48.3 -> 46.8; 64 of 8 and 128256, whose positions rarely become tau, the same within the spread)
     constexpr int kHeld = 2;
     unsigned held[kHeld];
     float Mrow = 0.f;
@@ -963,7 +965,7 @@ __device__ __forceinline__ int draw_from_target_row(const FusedParams &P, const 
 
 // ------------------------------------------------------------------ whole sequences
 // Whether a row's per-wave words of the target row may hold anything: always for the kernel that publishes them, else
-// only if such a kernel has worked on this workspace since it was prepared.
+// only if such a kernel, or that of together.hpp, has worked on this workspace since it was prepared.
 template <int LANE> __device__ __forceinline__ bool row_words_used(const int *header)
 {
     if constexpr (!kLazyRowWords<LANE>) return true;

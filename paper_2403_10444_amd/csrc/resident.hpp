@@ -51,7 +51,7 @@ inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths, b
     if (own_lengths ? groups >= 5 : groups >= 3 && gamma < 8) line = line < 3.0 ? line : 3.0;
     return line;
 }
-constexpr double kResidentSetsForced = 3.0;   // at least this where the testing hook asks for this kernel
+constexpr double kResidentSetsForced = 3.0;   // at least this where the testing hook asks for this kernel or that of together.hpp
 
 // (largest scaled logit, sum) of four words, one per lane of a quad: every lane of the quad gets the combination
 // (fixed order, the sums through exact powers of two).

@@ -21,30 +21,7 @@
 namespace sv {
 
 // ------------------------------------------------------------------ segments of a wave
-// A wave works on several rows at once, four lanes for each or sixteen (WIDE): reductions over
-// such a segment that leave every lane of it with the result, in a fixed order.
-template <bool WIDE>
-__device__ __forceinline__ float seg_max(float v)
-{
-    v = fmaxf(v, __int_as_float(dpp_shift<0xB1>(__float_as_int(v))));             // quad_perm:[1,0,3,2]
-    v = fmaxf(v, __int_as_float(dpp_shift<0x4E>(__float_as_int(v))));             // quad_perm:[2,3,0,1]
-    if constexpr (WIDE) {
-        v = fmaxf(v, __int_as_float(dpp_shift<0x141>(__float_as_int(v))));        // row_half_mirror
-        v = fmaxf(v, __int_as_float(dpp_shift<0x140>(__float_as_int(v))));        // row_mirror
-    }
-    return v;
-}
-template <bool WIDE>
-__device__ __forceinline__ double seg_sum(double v)
-{
-    v += dpp_shift_double<0xB1>(v);
-    v += dpp_shift_double<0x4E>(v);
-    if constexpr (WIDE) {
-        v += dpp_shift_double<0x141>(v);
-        v += dpp_shift_double<0x140>(v);
-    }
-    return v;
-}
+// A wave works on several rows at once, four lanes for each or sixteen (reductions over a segment: group_max, group_sum).
 // Inclusive scans over the first n lanes (the others hold 0; up to 16 they lie in one DPP row: four steps instead of six).
 __device__ __forceinline__ double scan_of(double v, int n)
 {
@@ -116,7 +93,7 @@ template <typename T, int FORM>
 __device__ __forceinline__ void rows_normalisers(const FusedParams &P, size_t seq_d, size_t seq_u, const u64 *pairs, int pair_stride, int n, int own, int nwg,
                                                  int wave, uint32_t bits, RowsOut &out, bool &gave_up)
 {
-    constexpr bool kWide = FORM > 0, kTwo = FORM == 2;
+    constexpr bool kTwo = FORM == 2;
     const int lane = threadIdx.x & 63, e = lane & (kSegment<FORM> - 1), e2 = e + kSegment<FORM>;
     for (int r0 = wave * kWaveRows<FORM>; r0 < n; r0 += kWaves * kWaveRows<FORM>) {
         const int row = r0 + lane / kSegment<FORM>;
@@ -135,7 +112,7 @@ __device__ __forceinline__ void rows_normalisers(const FusedParams &P, size_t se
         // the lane's words against the segment's largest, through exact powers of two
         float mp = e < nwg ? stat_shift(p) : -INFINITY, mq = e < nwg ? stat_shift(q) : -INFINITY, Mp = mp, Mq = mq;
         if constexpr (kTwo) { Mp = e2 < nwg ? fmaxf(mp, stat_shift(p2)) : mp; Mq = e2 < nwg ? fmaxf(mq, stat_shift(q2)) : mq; }
-        Mp = seg_max<kWide>(Mp); Mq = seg_max<kWide>(Mq);
+        Mp = group_max<kSegment<FORM>>(Mp); Mq = group_max<kSegment<FORM>>(Mq);
         auto mass = [](bool is, u64 w, float M) {
             const float m = stat_shift(w);
             const double z = ldexp((double)stat_sum(w), (int)(shift_of(m) - shift_of(M)));
@@ -144,8 +121,8 @@ __device__ __forceinline__ void rows_normalisers(const FusedParams &P, size_t se
         double zp = mass(e < nwg, p, Mp);
         double zq = mass(e < nwg, q, Mq);
         if constexpr (kTwo) { zp += mass(e2 < nwg, p2, Mp); zq += mass(e2 < nwg, q2, Mq); }
-        zp = seg_sum<kWide>(zp);
-        zq = seg_sum<kWide>(zq);
+        zp = group_sum<kSegment<FORM>>(zp);
+        zq = group_sum<kSegment<FORM>>(zq);
         // even lanes go on with the target row, odd ones with the draft row
         const bool odd = (lane & 1) != 0;
         const float M = odd ? Mq : Mp;
