@@ -218,7 +218,7 @@ def main():
         binding.SV_KERNEL_STAGED: "whole call: the four staged kernels (row_stats, prefix_weights, residual, finalize)",
         binding.SV_KERNEL_FUSED: "whole call: fused_verify_kernel, the call's only kernel",
         binding.SV_KERNEL_TINY: "whole call: small_verify_kernel or tiny_verify_kernel (one workgroup or wave per sequence), the call's only kernel",
-        binding.SV_KERNEL_RESIDENT: "whole call: together_verify_kernel or resident_verify_kernel (calls of few resident sets), the call's only kernel",
+        binding.SV_KERNEL_RESIDENT: f"whole call: {'together' if sv.spec_verify_debug_last_together() else 'resident'}_verify_kernel (calls of few resident sets), the call's only kernel",
         binding.SV_KERNEL_PROBS: "whole call: probs_residual_kernel, in calls beyond what runs at once probs_finish_kernel (in some calls probs_weights_kernel in front)",
     }[sv.spec_verify_debug_last_kernel()]
 
