@@ -16,6 +16,7 @@ from tests import parity
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 TOGETHER, RESIDENT = 8, 9    # spec_verify_debug_config path
+NAMES = {TOGETHER: "together", RESIDENT: "resident"}
 FUSED = 3                    # the large kernel, small units
 
 
@@ -66,7 +67,7 @@ def test_shapes(B, gamma, V, dtype, algo, forced):
     for seed in (41, 42):
         inp = workloads.generate(cfg, seed=seed + B + gamma, device=DEV)
         rep = parity.compare(parity.run_gpu(algo, inp, cfg.temperature), parity.run_oracle(algo, inp, cfg.temperature),
-                             label=f"{cfg.name}/{algo}/path{forced}", greedy=algo == "greedy")
+                             label=f"{cfg.name}/{algo}/{NAMES[forced]}", greedy=algo == "greedy")
         assert _ran(forced)
         parity.record(rep)
 
@@ -77,7 +78,7 @@ def test_configuration_2_two_seeds(algo, forced):
     for seed in (2000, 2001):
         inp = workloads.generate(cfg, seed=seed, device=DEV)
         rep = parity.compare(parity.run_gpu(algo, inp, cfg.temperature), parity.run_oracle(algo, inp, cfg.temperature),
-                             label=f"cfg2/seed{seed}/{algo}/path{forced}", greedy=algo == "greedy")
+                             label=f"cfg2/seed{seed}/{algo}/{NAMES[forced]}", greedy=algo == "greedy")
         parity.record(rep)
 
 
@@ -320,7 +321,7 @@ def test_float32_rows_on_the_kernel_that_the_library_takes(B, gamma, V, dtype, a
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.5, sigma_d=0.5, T=0.9)
     inp = workloads.generate(cfg, seed=V + B, device=DEV)
     ref = parity.run_oracle(algo, inp, cfg.temperature)
-    parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}/path{forced}", greedy=algo == "greedy")
+    parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}/{NAMES[forced]}", greedy=algo == "greedy")
     assert _ran(forced)
     sv.spec_verify_debug_config(0, -1)
     parity.compare(parity.run_gpu(algo, inp, cfg.temperature), ref, label=f"{cfg.name}/{algo}", greedy=algo == "greedy")
