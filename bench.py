@@ -214,11 +214,12 @@ def main():
     healthy("timed region")
     mean_tau = float(tau.float().mean().item())
     # which kernels the timed calls were (the library chooses by the shape of the call)
+    one_per_row = sv.spec_verify_debug_last_form()[0] == binding.SV_FORM_ROW
     kernel_text = {
         binding.SV_KERNEL_STAGED: "whole call: the four staged kernels (row_stats, prefix_weights, residual, finalize)",
-        binding.SV_KERNEL_FUSED: "whole call: fused_verify_kernel, the call's only kernel",
-        binding.SV_KERNEL_TINY: "whole call: small_verify_kernel or tiny_verify_kernel (one workgroup or wave per sequence), the call's only kernel",
-        binding.SV_KERNEL_RESIDENT: f"whole call: {'together' if sv.spec_verify_debug_last_together() else 'resident'}_verify_kernel (calls of few resident sets), the call's only kernel",
+        binding.SV_KERNEL_FUSED: f"whole call: {'rows' if one_per_row else 'fused'}_verify_kernel, the call's only kernel",
+        binding.SV_KERNEL_TINY: "whole call: packed_verify_kernel, small_verify_kernel or tiny_verify_kernel (a workgroup for one sequence or several), the call's only kernel",
+        binding.SV_KERNEL_RESIDENT: f"whole call: {'rows' if one_per_row else 'together' if sv.spec_verify_debug_last_together() else 'resident'}_verify_kernel (calls of few resident sets), the call's only kernel",
         binding.SV_KERNEL_PROBS: "whole call: probs_residual_kernel, in calls beyond what runs at once probs_finish_kernel (in some calls probs_weights_kernel in front)",
     }[sv.spec_verify_debug_last_kernel()]
 

@@ -36,6 +36,7 @@ EXPORTED = (
     "spec_verify_debug_last_kernel",
     "spec_verify_debug_last_chain",
     "spec_verify_debug_last_together",
+    "spec_verify_debug_last_form",
     "spec_verify_debug_copy",
     "spec_verify_debug_stream_probe",
     "spec_sample_tokens",
@@ -116,6 +117,8 @@ def load() -> ctypes.CDLL:
         lib.spec_verify_debug_last_chain.argtypes = []
         lib.spec_verify_debug_last_together.restype = ctypes.c_int32
         lib.spec_verify_debug_last_together.argtypes = []
+        lib.spec_verify_debug_last_form.restype = ctypes.c_int32
+        lib.spec_verify_debug_last_form.argtypes = []
         lib.spec_verify_debug_config.restype = None
         lib.spec_verify_debug_config.argtypes = [ctypes.c_int32, ctypes.c_int32]
         if hasattr(lib, "spec_verify_debug_profile"):          # tuning builds only
@@ -183,6 +186,16 @@ def spec_verify_debug_last_chain() -> int:
 def spec_verify_debug_last_together() -> int:
     """Testing hook: which kernel the last call of few resident sets took: 1 the one of together.hpp, 0 that of resident.hpp."""
     return int(load().spec_verify_debug_last_together())
+
+
+SV_FORM_SEQUENCE_IN_LDS, SV_FORM_SEQUENCE, SV_FORM_SEQUENCES, SV_FORM_ROW = 1, 2, 3, 4
+
+
+def spec_verify_debug_last_form() -> tuple:
+    """Testing hook: the form of its kernel that the last verification call took: (SV_FORM_*, lanes that share a row (pair), logits of a
+    row per lane); zeros where the kernel has one form."""
+    form = int(load().spec_verify_debug_last_form())
+    return form // 1000000, form // 1000 % 1000, form % 1000
 
 
 def spec_verify_debug_profile(buffer) -> None:

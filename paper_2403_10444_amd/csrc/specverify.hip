@@ -39,6 +39,7 @@ std::atomic<int> g_spin_limit{kDefaultSpinLimit};
 std::atomic<int> g_last_kernel{0};                  // the kernels of the last verification call that was launched (SV_KERNEL_*)
 std::atomic<int> g_last_chain{-1};                  // whether the last call on the fused kernel had the chain
 std::atomic<int> g_last_together{-1};               // whether the last call of few resident sets had the kernel of together.hpp
+std::atomic<int> g_last_form{0};                    // which form of its kernel the last verification call had (SV_FORM_*)
 std::atomic<int> g_lane{0};                        // 0 auto, 32 or 64: logits per lane of the fused kernel's units (testing hook)
 std::atomic<int> g_chain{-1};                      // -1 auto, 0 / 1: whether the fused kernel's leaders hand w_i on in a chain (testing hook)
 #ifdef SV_PROFILE
@@ -113,6 +114,8 @@ int resident_workgroups(K kernel, std::atomic<int> &cache, int threads = kThread
     return cus * per_cu;
 }
 
+void report_form(int form, int lanes, int logits) { g_last_form.store(form * 1000000 + lanes * 1000 + logits); }
+
 template <typename T, bool ALIGNED>
 sv_status_t launch_staged(int algo, const void *target_v, const void *draft_v, const int32_t *tokens, const int32_t *draft_lens,
                           size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd, const Layout &L,
@@ -183,7 +186,7 @@ bool being_captured(hipStream_t stream)
 struct PackedLaunch {
     void (*kernel)(const FusedParams);
     unsigned blocks, threads;
-    int seqs;
+    int seqs, lanes, logits;             // sequences of a workgroup; lanes of a row pair, logits of a row per lane
 };
 template <typename T, bool PROBS, int G, int LANE>
 PackedLaunch packed_launch_of(int B, int gamma, int seqs)
@@ -192,8 +195,8 @@ PackedLaunch packed_launch_of(int B, int gamma, int seqs)
     void (*const kernel)(const FusedParams) = seg16 ? packed_verify_kernel<T, PROBS, G, LANE, 16> : packed_verify_kernel<T, PROBS, G, LANE, kWave>;
     const int seg = seg16 ? 16 : kWave, one = (gamma + 1) * G > seg ? (gamma + 1) * G : seg;      // lanes of one sequence
     const int threads = (seqs * one + kWave - 1) / kWave * kWave;
-    if (threads > (G == 1 ? 2 * kWave : kTinyThreads)) return {nullptr, 0, 0, 0};
-    return {kernel, (unsigned)((B - 1) / seqs + 1), (unsigned)threads, seqs};
+    if (threads > (G == 1 ? 2 * kWave : kTinyThreads)) return {};
+    return {kernel, (unsigned)((B - 1) / seqs + 1), (unsigned)threads, seqs, G, LANE};
 }
 template <typename T, bool PROBS>
 PackedLaunch packed_launch(int B, int gamma, int V)
@@ -216,7 +219,7 @@ PackedLaunch packed_launch(int B, int gamma, int V)
         if (V > 32 * 16 && V <= 32 * 32) return rows > 3072 || gamma >= 16 ? packed_launch_of<T, PROBS, 32, 32>(B, gamma, 1) : packed_launch_of<T, PROBS, 64, 16>(B, gamma, 1);
         if (V > 32 * 32 && V <= kSmallMaxRow && (gamma < 6 || rows <= 6000)) return packed_launch_of<T, PROBS, 64, 32>(B, gamma, 1);
     }
-    return {nullptr, 0, 0, 0};
+    return {};
 }
 
 // Probabilities as inputs: one to three launches, every element read once.  Scratch (rows of more than 2048 tokens): the staged path's areas
@@ -236,6 +239,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
         F.group_seqs = packed.seqs; F.inv_slots = (unsigned)(0x100000000ull / (unsigned)(gamma + 1)) + 1u;
         F.accept_len = accept_len; F.next_token = next_token; F.debug_out = debug_out;
         packed.kernel<<<packed.blocks, packed.threads, 0, stream>>>(F);
+        report_form(SV_FORM_SEQUENCES, packed.lanes, packed.logits);
         return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
     }
     ProbsParams P = {};
@@ -300,18 +304,19 @@ bool tiny_ok(int gamma, int V) { return (size_t)(2 * gamma + 1) * (size_t)V <= (
 struct SmallLaunch {
     void (*kernel)(const FusedParams);
     unsigned blocks, threads;
+    int lanes, logits;
 };
 template <typename T, int G, int LANE>
 SmallLaunch small_launch_of(int B, int gamma)
 {
     const int threads = ((gamma + 1) * G + kWave - 1) / kWave * kWave;           // a group per row pair and one for the last target row
     if constexpr (G != kWave || LANE != 8) {             // (those take no draft that fills the workgroup)
-        if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, true>, (unsigned)B, kTinyThreads};
+        if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, true>, (unsigned)B, kTinyThreads, G, LANE};
     }
     if constexpr (G == kWave) {                          // (shorter drafts over fewer lanes are packed_launch's)
-        if (threads <= kTinyThreads) return {small_verify_kernel<T, G, LANE, false>, (unsigned)B, (unsigned)threads};
+        if (threads <= kTinyThreads) return {small_verify_kernel<T, G, LANE, false>, (unsigned)B, (unsigned)threads, G, LANE};
     }
-    return {nullptr, 0, 0};
+    return {};
 }
 template <typename T>
 SmallLaunch small_launch(int B, int gamma, int V)
@@ -321,7 +326,7 @@ SmallLaunch small_launch(int B, int gamma, int V)
     if (V <= 64 * 16) return small_launch_of<T, 64, 16>(B, gamma);
     if (V <= 64 * 24 && (tiny_ok(gamma, V) || B > kSmallMinWide)) return small_launch_of<T, 64, 24>(B, gamma);
     if (V <= kSmallMaxRow && (tiny_ok(gamma, V) || B > kSmallMinWide)) return small_launch_of<T, 64, 32>(B, gamma);
-    return {nullptr, 0, 0};
+    return {};
 }
 
 // One workgroup per sequence (SV_ERR_UNSUPPORTED: the sequence does not fit one).
@@ -331,7 +336,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
                         int magic, char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
     const PackedLaunch packed = packed_launch<T, false>(B, gamma, V);
-    const SmallLaunch small = packed.kernel ? SmallLaunch{packed.kernel, packed.blocks, packed.threads} : small_launch<T>(B, gamma, V);
+    const SmallLaunch small = packed.kernel ? SmallLaunch{packed.kernel, packed.blocks, packed.threads, packed.lanes, packed.logits} : small_launch<T>(B, gamma, V);
     if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     FusedParams P = {};
     P.target = target; P.draft = draft; P.tokens = tokens; P.draft_lens = draft_lens; P.uniforms = uniforms;
@@ -345,6 +350,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
 #ifdef SV_PROFILE
     P.prof = g_prof.load();
 #endif
+    report_form(packed.kernel ? SV_FORM_SEQUENCES : small.kernel ? SV_FORM_SEQUENCE : SV_FORM_SEQUENCE_IN_LDS, small.lanes, small.logits);
     if (small.kernel) small.kernel<<<small.blocks, small.threads, 0, stream>>>(P);
     else tiny_verify_kernel<T><<<(unsigned)B, kTinyThreads, 0, stream>>>(P);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
@@ -405,6 +411,7 @@ sv_status_t launch_rows(FusedParams P, bool in_chain, hipStream_t stream)
     P.inv_slots = (unsigned)(0x100000000ull / (unsigned)(P.gamma + 1)) + 1u;
     if ((size_t)n_groups * (P.gamma + 1) > 65535u) return SV_ERR_UNSUPPORTED;
     kernel<<<dim3((unsigned)P.group_seqs, (unsigned)(n_groups * (P.gamma + 1))), waves * kWave, 0, stream>>>(P);
+    report_form(SV_FORM_ROW, waves * kWave, lane_logits);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
@@ -596,6 +603,7 @@ sv_status_t verify_entry(int algo, bool probs, const void *target, const void *d
                          ((size_t)V * esize) % 16 == 0 && (tstride * esize) % 16 == 0 && (dstride * esize) % 16 == 0;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     char *ws = static_cast<char *>(workspace);
+    g_last_form.store(0);
     // Launches of `threads` threads per sequence along x, as many as kMaxLaunchThreads asks for (nearly always one), equally
     // large: `launch` gets the arguments of its sequences.  What they leave in the scratch areas is their own.
     auto in_slices = [&](unsigned long long threads, auto launch) {
@@ -722,6 +730,8 @@ int32_t spec_verify_debug_last_kernel(void) { return g_last_kernel.load(); }
 int32_t spec_verify_debug_last_chain(void) { return g_last_chain.load(); }
 
 int32_t spec_verify_debug_last_together(void) { return g_last_together.load(); }
+
+int32_t spec_verify_debug_last_form(void) { return g_last_form.load(); }
 
 void spec_verify_debug_config(int32_t path, int32_t spin_limit)
 {

@@ -40,6 +40,7 @@ def _host(t):
 
 
 def _check(case, it, probs):
+    """(False: not compared, the case is outside the contract.)"""
     cfg, algo = case["cfg"], case["algo"]
     B, gamma, V, T = cfg.B, cfg.gamma, cfg.V, cfg.temperature
     inp = workloads.generate(cfg, seed=1000 + it, device=DEV, top_k_target=case["top_k"], top_k_draft=3 * case["top_k"])
@@ -48,7 +49,7 @@ def _check(case, it, probs):
         rows_t = torch.softmax(rows_t.float() / T, -1).to(rows_t.dtype)
         rows_d = torch.softmax(rows_d.float() / T, -1).to(rows_d.dtype)
         if not bool((torch.gather(rows_d.float(), 2, inp["draft_tokens"].long().unsqueeze(-1)) > 0).all()):
-            return                                   # a drafted token's probability rounded to zero: outside the contract
+            return False                             # a drafted token's probability rounded to zero: outside the contract
     lens = (np.random.default_rng(case["lens_seed"]).integers(1, gamma + 1, size=B).astype(np.int32)
             if case["use_lens"] else np.full(B, gamma, np.int32))
     tb = torch.full((B, gamma + 1, V + case["pad_t"]), float("nan"), dtype=rows_t.dtype, device=DEV)
@@ -99,6 +100,7 @@ def _check(case, it, probs):
         S, w = ref["dbg"][:, :, 1], ref["dbg"][:, :, 0]
         tol = parity.S_RTOL * S + parity.S_FLOOR * np.maximum(w, 1e-30)
         assert np.all(np.abs(dbg[sel, :g + 1, 1].astype(np.float64) - S) <= tol), (case, int(g))
+    return True
 
 
 @pytest.mark.parametrize("probs", [False, True], ids=["logits", "probs"])
@@ -210,4 +212,4 @@ def test_more_than_one_set_leaves_out_what_the_next_position_rules_out(algo, B, 
     """The kernel for calls of few resident sets, 1.2 to 2.4 of them, close models: many weights of 1 and passed tests of Alg. 1."""
     cfg = workloads.Config(f"beyond_B{B}_g{gamma}_V{V}", B, gamma, V, "bf16", 3.0, sigma, 0.9, False, 1)
     _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens, pad_t=0, pad_d=0, lens_seed=B), 970 + B, False)
-    assert (sv.spec_verify_debug_last_kernel(), sv.spec_verify_debug_last_together()) == (7, 0)
+    assert (sv.spec_verify_debug_last_kernel(), sv.spec_verify_debug_last_together(), sv.spec_verify_debug_last_form()) == (7, 0, (0, 0, 0))

@@ -135,10 +135,10 @@ def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_ker
 
 
 @pytest.mark.parametrize("B,gamma,V,dtype,lens", [(560, 8, 5000, "bf16", True), (270, 8, 9000, "bf16", True), (440, 8, 3000, "bf16", False),
-                                                  (340, 8, 5000, "f32", True)])
+                                                  (340, 8, 5000, "f32", True), (140, 8, 25000, "bf16", True), (73, 8, 25000, "f32", False)])
 def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype, lens, forced):
-    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths): the same decisions (here, where no uniform
-    is next to an edge, from both kernels)."""
+    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths; the bf16 ones of those have a form with one workgroup per
+    row, which the library takes by itself): the same decisions (here, where no uniform is next to an edge, from all kernels)."""
     cfg = workloads.Config(f"forced_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 1.0, 0.8, False, 1)
     inp = workloads.generate(cfg, seed=B, device=DEV)
     dl = torch.tensor([1 + (b * 5) % gamma for b in range(B)], dtype=torch.int32, device=DEV) if lens else None
@@ -147,6 +147,7 @@ def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype
         sv.spec_verify_debug_config(path, -1)
         tau, y = sv.spec_verify_ex("block", inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 0.8, draft_lens=dl)
         assert _ran(path or (TOGETHER if dtype == "f32" else RESIDENT))
+        assert (sv.spec_verify_debug_last_form()[0] == binding.SV_FORM_ROW) == (path == 0 and V < 10000 and dtype == "bf16")
         out.append((tau.cpu().numpy(), y.cpu().numpy()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
@@ -158,7 +159,9 @@ def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype
     (1279, 2, 3000, "bf16", False, "RESIDENT"), (1282, 2, 3000, "bf16", False, "FUSED"),
     (169, 8, 9001, "f32", False, "RESIDENT"), (158, 8, 9000, "f32", False, "RESIDENT"),       # two: 3.0, aligned 2.8
     (162, 8, 9000, "f32", False, "FUSED"), (73, 8, 25000, "f32", False, "RESIDENT"), (75, 8, 25000, "f32", False, "FUSED"),
-    (52, 8, 65536, "bf16", True, "RESIDENT"), (56, 8, 65536, "bf16", True, "FUSED")])         # own lengths, eight: 3.0
+    (52, 8, 65536, "bf16", True, "RESIDENT"), (56, 8, 65536, "bf16", True, "FUSED"),          # own lengths, eight: 3.0
+    (90, 8, 40000, "bf16", False, "RESIDENT"), (91, 8, 40000, "bf16", False, "FUSED"),        # five: 3.2
+    (85, 8, 30001, "f32", False, "RESIDENT"), (86, 8, 30001, "f32", False, "FUSED")])         # four, not aligned: 3.0
 def test_the_line_to_the_large_kernel(B, gamma, V, dtype, lens, kernel, forced):
     if forced == TOGETHER:
         pytest.skip("the library's own choice: once is enough")
@@ -166,6 +169,8 @@ def test_the_line_to_the_large_kernel(B, gamma, V, dtype, lens, kernel, forced):
     cfg = workloads.Config(f"line_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 0.7, 0.9, False, 1)
     _check(dict(cfg=cfg, algo="block", path="default", top_k=0, use_lens=lens, pad_t=0, pad_d=0, lens_seed=B), B + V, False)
     assert sv.spec_verify_debug_last_kernel() == getattr(binding, "SV_KERNEL_" + kernel)
+    # (rows of up to 12288 logits have the form of one workgroup per row on both sides: the line only lets it hand w_i on in a chain)
+    assert (sv.spec_verify_debug_last_form()[0] == binding.SV_FORM_ROW) == (V <= 12288)
 
 
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])

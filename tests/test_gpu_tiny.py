@@ -202,6 +202,7 @@ def test_rows_of_24_logits_per_lane(B, gamma, V, dtype, algo):
     cfg = workloads.Config(f"lane24_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 0.8, 0.9, False, 1)
     for n, (lens, pad_t, pad_d, top_k) in enumerate([(False, 0, 0, 0), (True, 3, 8, 30)]):
         _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=n), 300 + n, False)
+        assert sv.spec_verify_debug_last_form() == (binding.SV_FORM_SEQUENCE, 64, 24 if V <= 1536 else 32)
 
 
 # ---- the kernel that keeps the rows in LDS, which rows of more than 2048 logits reach (shorter ones, above and below, stay in
@@ -217,6 +218,7 @@ def test_rows_in_lds(B, gamma, V, dtype, algo):
     for n, (lens, pad_t, pad_d, top_k) in enumerate([(False, 0, 0, 0), (True, 3, 8, 0), (True, 16, 5, 20), (False, 0, 0, 3)]):
         _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, False)
         assert sv.spec_verify_debug_last_kernel() == binding.SV_KERNEL_TINY
+        assert sv.spec_verify_debug_last_form() == (binding.SV_FORM_SEQUENCE_IN_LDS, 0, 0)
     sv.spec_verify_debug_config(TINY, -1)
     inp = workloads.generate(cfg, seed=V, device=DEV)
     for value in (0.0, 1.0 - 2.0 ** -24):
@@ -281,6 +283,16 @@ PACKED = [
     (5, 16, 257, "f32"), (3, 31, 512, "bf16"), (1639, 4, 300, "bf16"), (2, 63, 400, "f32"), (2, 64, 300, "bf16"),
     (4, 15, 511, "f32"), (4, 12, 513, "bf16"), (240, 12, 1024, "f32"), (2, 31, 700, "bf16"), (5, 15, 1025, "bf16"), (66, 5, 2048, "f32"), (3, 16, 1500, "f32"),
 ]
+# the forms that logits and probabilities of these calls take: (several sequences to a workgroup or one,) lanes of a row pair, logits of each (None: another kernel's)
+_ONE, _SEVERAL = binding.SV_FORM_SEQUENCE, binding.SV_FORM_SEQUENCES
+FORMS = dict(zip(PACKED, [
+    ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)),
+    ((_SEVERAL, 4, 8), (4, 8)), ((_SEVERAL, 4, 8), (4, 8)), ((_SEVERAL, 4, 8), (4, 8)),
+    ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 4, 32), (4, 32)),
+    ((_SEVERAL, 16, 16), (16, 16)), ((_SEVERAL, 16, 16), (16, 16)), ((_SEVERAL, 32, 8), (32, 8)), ((_SEVERAL, 16, 16), (16, 16)),
+    ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 16, 32), (16, 32)), ((_ONE, 16, 32), None),
+    ((_ONE, 64, 8), (64, 8)), ((_ONE, 64, 16), (64, 16)), ((_ONE, 64, 16), (32, 32)), (None, (32, 32)), (None, (64, 32)), ((_ONE, 64, 32), (64, 32)), (None, None),
+]))
 
 
 @pytest.mark.parametrize("probs", [False, True], ids=["logits", "probs"])
@@ -288,6 +300,9 @@ PACKED = [
 def test_sequences_that_share_a_workgroup(B, gamma, V, dtype, probs):
     from tests.test_gpu_random_shapes import _check
     cfg = workloads.Config(f"packed_B{B}_g{gamma}_V{V}_{dtype}", B, gamma, V, dtype, 2.0, 0.5, 0.9, False, 1)
+    of_logits, of_probs = FORMS[B, gamma, V, dtype]
     for algo in ("block", "token", "greedy"):
         for n, (lens, pad_t, pad_d, top_k) in enumerate([(False, 0, 0, 0), (True, 3, 8, 0), (True, 16, 0, 3)]):
-            _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, probs)
+            ran = _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, probs)
+            form = (of_probs and (_SEVERAL, *of_probs)) if probs else of_logits
+            assert not ran or sv.spec_verify_debug_last_form() == (form or (0, 0, 0))
