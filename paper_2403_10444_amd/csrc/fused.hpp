@@ -258,13 +258,20 @@ template <bool FMA> __device__ __forceinline__ double series_step(double s, doub
 }
 
 // exp2 of a double of moderate size to a relative error below 1e-12: the integer part goes into the exponent,
-// the fraction f in [-0.5, 0.5] through the series of exp(f ln 2) (|f ln 2| <= 0.347: ten terms).
-template <bool FMA = false>
+// the fraction f in [-0.5, 0.5] through the series of exp(f ln 2) (|f ln 2| <= 0.347: ten terms).  FULL: thirteen terms,
+// to the last place or two.
+template <bool FMA = false, bool FULL = false>
 __device__ __forceinline__ double exp2_precise(double x)
 {
     const double n = rint(x);
-    const double t = (x - n) * 0.69314718055994530942;
+    double t = (x - n) * 0.69314718055994530942;
     double s = 1.0 / 3628800.0;
+    if constexpr (FULL) {
+        s = 1.0 / 6227020800.0;
+        s = series_step<FMA>(s, t, 1.0 / 479001600.0);
+        s = series_step<FMA>(s, t, 1.0 / 39916800.0);
+        s = series_step<FMA>(s, t, 1.0 / 3628800.0);
+    }
     s = series_step<FMA>(s, t, 1.0 / 362880.0);
     s = series_step<FMA>(s, t, 1.0 / 40320.0);
     s = series_step<FMA>(s, t, 1.0 / 5040.0);
@@ -279,12 +286,17 @@ __device__ __forceinline__ double exp2_precise(double x)
 }
 
 // 1 - 2^x for x <= 0 without the cancellation next to x = 0: the series of -expm1(x ln 2) where |x ln 2| < 0.35.
-template <bool FMA = false>
+template <bool FMA = false, bool FULL = false>
 __device__ __forceinline__ double one_minus_exp2(double x)
 {
     const double t = x * 0.69314718055994530942;
     if (t > -0.35) {
         double s = 1.0 / 39916800.0;
+        if constexpr (FULL) {
+            s = 1.0 / 6227020800.0;
+            s = series_step<FMA>(s, t, 1.0 / 479001600.0);
+            s = series_step<FMA>(s, t, 1.0 / 39916800.0);
+        }
         s = series_step<FMA>(s, t, 1.0 / 3628800.0);
         s = series_step<FMA>(s, t, 1.0 / 362880.0);
         s = series_step<FMA>(s, t, 1.0 / 40320.0);
@@ -297,18 +309,18 @@ __device__ __forceinline__ double one_minus_exp2(double x)
         s = series_step<FMA>(s, t, 1.0);
         return -(s * t);
     }
-    return 1.0 - exp2_precise<FMA>(x);
+    return 1.0 - exp2_precise<FMA, FULL>(x);
 }
 
 // log2 of a positive double to an absolute error below 1e-12: the hardware's float log2 as a first guess g (off by
-// about 1e-7), then log2 z = g + log2(z 2^-g) with z 2^-g - 1 of that size, where two terms of the series are enough.
-template <bool FMA = false>
+// about 1e-7), then log2 z = g + log2(z 2^-g) with z 2^-g - 1 of that size, where two terms of the series are enough.  FULL: to the power's last places.
+template <bool FMA = false, bool FULL = false>
 __device__ __forceinline__ double log2_precise(double z)
 {
     int e;
     const double m = frexp(z, &e);            // z = m * 2^e, m in [0.5, 1)
     const double g = (double)__builtin_amdgcn_logf((float)m);
-    const double d = m * exp2_precise<FMA>(-g) - 1.0;
+    const double d = FULL ? __builtin_fma(m, exp2_precise<FMA, FULL>(-g), -1.0) : m * exp2_precise<FMA, FULL>(-g) - 1.0;
     return (double)e + g + (d - 0.5 * d * d) * 1.4426950408889634074;
 }
 

@@ -142,13 +142,17 @@ void packed_verify_kernel(const FusedParams P)
     const u64 in_segment = SEG == kWave ? ~0ull : (1ull << (SEG & 63)) - 1ull;
     const int segment = lane & ~(SEG - 1);                   // its first lane
     auto ballot = [&](bool p) { return __ballot(p) >> segment & in_segment; };
+    // (of probabilities by the series' full length: see log2_ratio)
+    auto power = [&](double x) {
+        return exp2_precise<PROBS || kFma, PROBS>(x);
+    };
     u64 tests_passed = 0;                                    // Alg. 1: bit j, the test of X_{j+1}
     double lr = 0.0, lw = 0.0, lw_next = 0.0, scale = 1.0;   // log2 r_{j+1}, log2 w_j, log2 w_{j+1}, the unit of the residual terms
     if (scalar_wave) {
         double log2_zp = 0.0, log2_zq = 0.0;
         if constexpr (PROBS) {
             // (a drafted token that the draft row rules out, q = 0, is no draft: whatever comes of it, the sums below stay finite)
-            lr = fmin(fmax(log2((double)own.tok_p[at]) - log2((double)own.tok_q[at]), kLog2RatioFloor), -kLog2RatioFloor);
+            lr = fmin(log2_ratio(own.tok_p[at], own.tok_q[at]), -kLog2RatioFloor);
         } else {
             const float Mp = own.max_p[at], Mq = own.max_q[at], sp = shift_of(Mp), sq = shift_of(Mq);
             log2_zp = log2_precise<kFma>(own.sum_p[at]); log2_zq = log2_precise<kFma>(own.sum_q[at]);
@@ -157,14 +161,18 @@ void packed_verify_kernel(const FusedParams P)
             const double lq = (double)own.tok_q[at] * P.kd - ((double)sq + log2_zq + P.k_eps * (double)Mq);
             lr = fmax(lp - lq, kLog2RatioFloor);
         }
-        if (token_algo) tests_passed = ballot(here && (double)eta_next < exp2_precise<kFma>(fmin(lr, 0.0)));
-        const double sum = segment_scan<SEG>(here ? lr : 0.0);
-        lw_next = algo == kBlock ? sum - segment_scan_max0<SEG>(sum) : sum;
+        if (token_algo) tests_passed = ballot(here && (double)eta_next < power(fmin(lr, 0.0)));
+        if constexpr (PROBS) {
+            lw_next = algo == kBlock ? clamped_weights<SEG>(here ? lr : 0.0) : segment_scan<SEG>(here ? lr : 0.0);
+        } else {
+            const double sum = segment_scan<SEG>(here ? lr : 0.0);
+            lw_next = algo == kBlock ? sum - segment_scan_max0<SEG>(sum) : sum;
+        }
         lw = __shfl_up(lw_next, 1, kWave);
         // (the residual of token verification is p - q; Alg. 4 on logits: w stays finite)
         if (j == 0 || token_algo) lw = 0.0;
         if constexpr (PROBS) {
-            const double w = exp2_precise<kFma>(lw);
+            const double w = power(lw);
             const float hi = (float)w;
             if (here) { own.factor[at] = hi; own.w_lo[at] = (float)(w - (double)hi); }
         } else {
@@ -224,7 +232,7 @@ void packed_verify_kernel(const FusedParams P)
         // Alg. 2 / 4, lane j judges position j >= 1: eta_j < h_j = S_j / (S_j + 1 - w_j), 1 where w_j >= 1 (see AcceptTest),
         // without the division; the last position, by lane gb - 1: eta_gb < w_gb.  Alg. 1: the tests came with the ratios.  (Alg. 4 on
         // probabilities, whose rows need not sum to one: S_j over the rejected mass)
-        const double one_minus_w = one_minus_exp2<kFma>(fmin(lw, 0.0));
+        const double one_minus_w = one_minus_exp2<PROBS || kFma, PROBS>(fmin(lw, 0.0));
         const double R = PROBS && greedy_algo ? own.sum_q[at] : S + one_minus_w;
         const bool sure = PROBS && greedy_algo ? !(R > 0.0) : lw >= 0.0;                // h_j = 1
         const u64 tests = token_algo ? tests_passed : ballot(here && j > 0 && (sure || (double)eta * R < S));
@@ -233,19 +241,19 @@ void packed_verify_kernel(const FusedParams P)
             tau = min(__ffsll((long long)~tests) - 1, gbj);                              // leading run of passes
             if (tau < 0) tau = gbj;
         } else {
-            const bool last = here && j == gbj - 1 && (lw_next >= 0.0 || (double)eta_next < exp2_precise<kFma>(lw_next));
+            const bool last = here && j == gbj - 1 && (lw_next >= 0.0 || (double)eta_next < power(lw_next));
             tau = ballot(last) ? gbj : tests ? 63 - __clzll((long long)tests) : 0;       // last passing sub-block
         }
         if (P.debug_out && here) {
-            const double next_h = exp2_precise<kFma>(fmin(token_algo ? lr : lw_next, 0.0));
+            const double next_h = power(fmin(token_algo ? lr : lw_next, 0.0));
             const double h = j == 0 || sure ? 1.0 : fmin(S / R, 1.0);
             float *d = P.debug_out + (seq_uj + j) * 3;
-            d[0] = (float)exp2_precise<kFma>(lw); d[1] = (float)S;
+            d[0] = (float)power(lw); d[1] = (float)S;
             if (!token_algo || j == 0) d[2] = (float)h;
             // (Alg. 1 has no w; its h_i = min(r_i, 1).  q_gamma == 0: S_gamma = w_gamma, times what the last target row sums to)
             if (token_algo) d[5] = (float)next_h;
             if (j == gbj - 1) {
-                const double w_last = token_algo ? 1.0 : exp2_precise<kFma>(lw_next);
+                const double w_last = token_algo ? 1.0 : power(lw_next);
                 d[3] = (float)w_last; d[4] = (float)(PROBS && algo != kBlock ? w_last * own.mass[at + 1] : w_last);
                 d[5] = (float)next_h;
             }

@@ -103,23 +103,47 @@ __host__ __device__ inline int probs_finish_doubles(int gamma) { return (2 + (in
 
 constexpr ProbWeight kFirstWeight = {1.0, 0.0, 1.0, 1.f, 0.f, 1};      // position 0: w_0 = 1; tau = 0 draws from the residual of rows 0
 
-// log2 r_i = log2 p - log2 q of a drafted token's two probabilities, kept finite downwards (a token outside the target's support: r = 0); infinite
-// where only the draft rules the token out.
+// log2 r_i of a drafted token's two probabilities, and the powers below, by the series of double's full length: what is kept of a weight is 48 bits (prob_residual), of which the
+// short ones that logits use would leave 41.  Error of the logarithm 1.8e-15 (most of it the last place of the result), of a power 1.2e-16 of it; the library's, which they are as
+// exact as (logarithms of p and q apart: 3.1e-15), take a tenth of a microsecond more on the chain.  Kept finite downwards (a token outside the target's support: r = 0); infinite where only the draft rules the token out.
 __device__ __forceinline__ double log2_ratio(float p, float q)
 {
     const bool is_ratio = p > 0.f && p < INFINITY && q > 0.f && q < INFINITY;
-    const double l = log2_precise<true>(is_ratio ? (double)p / (double)q : 1.0);
-    return is_ratio ? fmax(l, kLog2RatioFloor) : p > 0.f && q == 0.f ? (double)INFINITY : kLog2RatioFloor;
+    const double l = log2_precise<true, true>(is_ratio ? (double)p / (double)q : 1.0);
+    return is_ratio ? fmax(l, kLog2RatioFloor) : p > 0.f && q >= 0.f && q < INFINITY ? (double)INFINITY : kLog2RatioFloor;
+}
+
+// Lane j of a segment of SEG = 16 or 64 lanes gets log2 w_{j+1} of w_i = min(w_{i-1} r_i, 1), w_0 = 1, from log2 r_{j+1}.  A stretch of positions takes w to min(a w, c): two
+// neighbouring ones to min(a' a w, min(a c', c)), logarithms here.  As against a difference of prefix sums, what a large ratio added is gone where the min is taken, so that a
+// weight behind it is as exact as any (a ratio of infinity leaves no infinity: it is c = 1).  Lanes without a source get the zeros of a stretch that does nothing to a weight of at most 1.
+template <int CTRL, int ROW_MASK = 0xf> __device__ __forceinline__ void join_stretches(double &a, double &c)
+{
+    const double a_before = dpp_shift_double<CTRL, ROW_MASK>(a), c_before = dpp_shift_double<CTRL, ROW_MASK>(c);
+    c = fmin(c_before + a, c);
+    a += a_before;
+}
+template <int SEG> __device__ __forceinline__ double clamped_weights(double log2r)
+{
+    double a = log2r, c = 0.0;
+    join_stretches<0x111>(a, c);
+    join_stretches<0x112>(a, c);
+    join_stretches<0x114>(a, c);
+    join_stretches<0x118>(a, c);
+    if constexpr (SEG == kWave) {
+        join_stretches<0x142, 0xa>(a, c);
+        join_stretches<0x143, 0xc>(a, c);
+    }
+    return fmin(a, c);
 }
 
 // w_0 = 1, w_i = min(w_{i-1} r_i, 1) (Alg. 2; Alg. 4 omits the min), r_i = p_{i-1}(X_i) / q_{i-1}(X_i), for positions
 // 1 .. n of a sequence of draft length gb, by one wave: lane j comes with drafted token j + 1 (and its uniform), gathers its
-// two probabilities, and gets position j + 1's constants from the prefix sums of the log2 r (products of ratios neither overflow nor lose
-// 1 - w_i next to 1; see weights_from_ratios).  `for_tests`: whether one_minus_w and h_token are wanted, which only the workgroup that finishes the sequence reads.
-// What bounds it: one wave's chain of operations in double, which every workgroup of a position waits for: with one logarithm of the ratio instead of two, scans
-// over the lanes instead of a loop over the positions, and one power, calls that do not fill the device for long are 5 to 10 % faster (us a call, before / now, with
-// the changes of the finish: bf16: 204 of 10 over 8718 30.7 / 28.0, 117 ragged of 13 over 11200 19.5 / 17.6, 400 of 8 over 50257 118 / 111; float32: 143 ragged of 15
-// over 16146 42.3 / 39.5, 6 of 15 over 18438 14.3 / 12.8).
+// two probabilities, and gets position j + 1's constants by a scan over the log2 r (products of ratios neither overflow nor lose
+// 1 - w_i next to 1).  `for_tests`: whether one_minus_w and h_token are wanted, which only the workgroup that finishes the sequence reads.
+// What bounds it: one wave's chain of operations in double, which every workgroup of a position waits for: one logarithm of the ratio instead of two, a scan
+// over the lanes instead of a loop over the positions, and one power: calls that do not fill the device for long are 5 to 10 % faster (us a call, before / now, with
+// the changes of the finish: bf16: 204 of 10 over 8718 30.3 / 27.8, 117 ragged of 13 over 11200 18.8 / 17.3, 400 of 8 over 50257 118 / 111.7; float32: 143 ragged of 15
+// over 16146 42.4 / 39.6, 6 of 15 over 18438 14.0 / 12.5; with short series 27.7, 17.1, 111.5, 39.6, 12.5).
 template <typename T>
 __device__ __forceinline__ ProbWeight form_weights(const T *target_seq, const T *draft_seq, size_t tstride, size_t dstride, int tok, float eta,
                                                    int n, int gb, int algo, bool every_sum, bool for_tests)
@@ -127,22 +151,15 @@ __device__ __forceinline__ ProbWeight form_weights(const T *target_seq, const T 
     const int lane = threadIdx.x & 63, i = lane + 1;
     double log2r = 0.0;
     if (lane < n) log2r = log2_ratio(logit_as_float(target_seq + (size_t)lane * tstride + tok), logit_as_float(draft_seq + (size_t)lane * dstride + tok));
-    double log2w = 0.0;
-    if (algo == kBlock) {
-        // (a ratio of infinity ends at a weight of 1 like any other large one)
-        const double sum = wave_scan(fmin(log2r, -kLog2RatioFloor));
-        log2w = sum - wave_scan_max0(sum);
-    } else if (algo == kGreedy) {
-        log2w = wave_scan(log2r);
-    }
+    const double log2w = algo == kBlock ? clamped_weights<kWave>(log2r) : algo == kGreedy ? wave_scan(log2r) : 0.0;
     ProbWeight pw;
-    pw.w = log2w < 2000.0 ? exp2_precise<true>(log2w) : (double)INFINITY;
+    pw.w = log2w < 2000.0 ? exp2_precise<true, true>(log2w) : (double)INFINITY;
     pw.w_hi = (float)pw.w;
     pw.w_lo = (float)(pw.w - (double)pw.w_hi);
     pw.one_minus_w = 0.0;
     pw.h_token = 1.0;
-    if (algo == kToken) pw.h_token = exp2_precise<true>(fmin(log2r, 0.0));
-    else if (for_tests && algo == kBlock) pw.one_minus_w = one_minus_exp2<true>(log2w);
+    if (algo == kToken) pw.h_token = exp2_precise<true, true>(fmin(log2r, 0.0));
+    else if (for_tests && algo == kBlock) pw.one_minus_w = one_minus_exp2<true, true>(log2w);
     // Which sums can matter (exact, whatever the rows sum to).  Alg. 1 stops at the first failed test, so only a
     // position that every earlier test let through can become tau; the last target row is summed (and drawn
     // from) only if tau = gamma: every test passed (Alg. 1), or the last one did (Alg. 2 / 4: eta < w_gamma).
