@@ -195,11 +195,11 @@ void packed_verify_kernel(const FusedParams P)
     {
         double acc = 0.0, rej = 0.0;
         if constexpr (PROBS) {
-            // (a lane's terms in float, as in the kernels for wider rows)
-            float mine = 0.f, against = 0.f;
+            // (a vector's terms in float, of vectors in double: no chain of more than eight, as in the kernels for wider rows)
 #pragma unroll
             for (int v = 0; v < kNV; ++v)
                 if (v < nv) {
+                    float mine = 0.f, against = 0.f;
 #pragma unroll
                     for (int e = 0; e < kVec; ++e) {
                         const int n = v * kVec + e;
@@ -207,8 +207,8 @@ void packed_verify_kernel(const FusedParams P)
                         mine += pair ? fmaxf(d, 0.f) : xa[n];
                         against += fmaxf(-d, 0.f);
                     }
+                    acc += (double)mine; rej += (double)against;
                 }
-            acc = (double)mine; rej = (double)against;
         } else {
 #pragma unroll
             for (int v = 0; v < kNV; ++v)

@@ -61,3 +61,26 @@ def test_a_residual_far_below_its_row(B, gamma, V, algo, large_ratio):
     sv.spec_verify_probs(algo, P.to(DEV), Q.to(DEV), tok.to(DEV), torch.full((B, gamma + 1), 0.5, device=DEV), debug_out=dbg)
     got = dbg[:, at, 1].double().cpu().numpy()
     assert np.all(np.abs(got - want) <= 2.0 ** -10 * want), float(np.max(np.abs(got - want) / want))
+
+
+# (32 probabilities of a row per lane, 16, 8)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("B,gamma,V", [(3, 4, 2048), (800, 3, 1024), (2, 40, 500), (2, 64, 128), (4, 12, 1000), (3, 20, 500), (4, 2, 500)])
+def test_sums_of_short_rows(B, gamma, V, dtype):
+    """One large probability in front of every lane's share of a row, all others half a unit of its last place: a float chain loses each of them, sums of at most
+    eight terms at most seven.  Bound: seven roundings of 2^-24, one of the reported float."""
+    vec = 4 if dtype == torch.float32 else 8
+    P = torch.full((B, gamma + 1, V), 2.0 ** -24, dtype=dtype)
+    lanes = V // 32 if V > 128 else 4
+    P[..., :lanes * vec:vec] = 1.0
+    Q = torch.zeros((B, gamma, V), dtype=dtype)
+    Q[..., 0] = 1.0
+    P[..., 0] = 1.0
+    want = P[:, :gamma].double().sum(-1) - 1.0                      # (w = 1; token 0 is in both rows)
+    args = P.to(DEV), Q.to(DEV), torch.zeros((B, gamma), dtype=torch.int32, device=DEV), torch.full((B, gamma + 1), 0.5, device=DEV)
+    for algo in ("block", "token", "greedy"):
+        dbg = torch.zeros((B, gamma + 1, 3), device=DEV)
+        sv.spec_verify_probs(algo, *args, debug_out=dbg)
+        assert sv.spec_verify_debug_last_form()[0] == sv.binding.SV_FORM_SEQUENCES
+        got = dbg[:, :gamma, 1].double().cpu()
+        assert bool(((got - want).abs() <= 8 * 2.0 ** -24 * want).all()), float(((got - want).abs() / want).max())
