@@ -142,17 +142,14 @@ void packed_verify_kernel(const FusedParams P)
     const u64 in_segment = SEG == kWave ? ~0ull : (1ull << (SEG & 63)) - 1ull;
     const int segment = lane & ~(SEG - 1);                   // its first lane
     auto ballot = [&](bool p) { return __ballot(p) >> segment & in_segment; };
-    // (of probabilities by the series' full length: see log2_ratio)
-    auto power = [&](double x) {
-        return exp2_precise<PROBS || kFma, PROBS>(x);
-    };
+    // (of probabilities by the series' full length: see log2_ratio; Alg. 4's w is infinite from a token on that only the draft rules out, as in the kernels for wider rows)
+    auto power = [&](double x) { return PROBS && !(x < 2000.0) ? (double)INFINITY : exp2_precise<PROBS || kFma, PROBS>(x); };
     u64 tests_passed = 0;                                    // Alg. 1: bit j, the test of X_{j+1}
     double lr = 0.0, lw = 0.0, lw_next = 0.0, scale = 1.0;   // log2 r_{j+1}, log2 w_j, log2 w_{j+1}, the unit of the residual terms
     if (scalar_wave) {
         double log2_zp = 0.0, log2_zq = 0.0;
         if constexpr (PROBS) {
-            // (a drafted token that the draft row rules out, q = 0, is no draft: whatever comes of it, the sums below stay finite)
-            lr = fmin(log2_ratio(own.tok_p[at], own.tok_q[at]), -kLog2RatioFloor);
+            lr = log2_ratio(own.tok_p[at], own.tok_q[at]);
         } else {
             const float Mp = own.max_p[at], Mq = own.max_q[at], sp = shift_of(Mp), sq = shift_of(Mq);
             log2_zp = log2_precise<kFma>(own.sum_p[at]); log2_zq = log2_precise<kFma>(own.sum_q[at]);

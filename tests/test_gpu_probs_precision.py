@@ -84,3 +84,33 @@ def test_sums_of_short_rows(B, gamma, V, dtype):
         assert sv.spec_verify_debug_last_form()[0] == sv.binding.SV_FORM_SEQUENCES
         got = dbg[:, :gamma, 1].double().cpu()
         assert bool(((got - want).abs() <= 8 * 2.0 ** -24 * want).all()), float(((got - want).abs() / want).max())
+
+
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V", [(6, 5, 8), (6, 17, 8), (6, 5, 30), (6, 5, 100), (6, 5, 200), (6, 20, 300), (6, 5, 500), (6, 5, 900), (6, 5, 2000)])
+def test_tokens_that_one_row_rules_out(B, gamma, V, algo):
+    """Drafted tokens with q = 0 (no draft has them: r is infinite, a weight of 1 in Alg. 2, an infinite one in Alg. 4), with p = 0 behind them, and both: the same whatever
+    the row's width is - the rows with as many tokens of probability 0 behind them as the kernels for wider rows want."""
+    gen = torch.Generator().manual_seed(V + gamma)
+    P, Q = (torch.softmax(2.0 * torch.randn((B, n, V), generator=gen), -1) for n in (gamma + 1, gamma))
+    tok = torch.multinomial(Q.view(-1, V), 1, generator=gen).view(B, gamma).to(torch.int32)
+    uni = torch.randint(0, 1 << 24, (B, gamma + 1), generator=gen) * 2.0 ** -24
+    for b, (no_q, no_p) in enumerate([((0,), ()), ((0,), (1,)), ((1,), (2,)), ((1, 2), (0, 3)), ((), (2,)), ((2,), (2,))]):
+        for i in no_q:
+            Q[b, i, tok[b, i]] = 0.0
+        for i in no_p:
+            P[b, i, tok[b, i]] = 0.0
+    out = []
+    for width in (V, 2500):
+        p, q = torch.zeros((B, gamma + 1, width)), torch.zeros((B, gamma, width))
+        p[..., :V], q[..., :V] = P, Q
+        dbg = torch.zeros((B, gamma + 1, 3), device=DEV)
+        tau, y = sv.spec_verify_probs(algo, p.to(DEV), q.to(DEV), tok.to(DEV), uni.to(DEV), debug_out=dbg)
+        assert (sv.spec_verify_debug_last_form()[0] == sv.binding.SV_FORM_SEQUENCES) == (width == V)
+        out.append((tau.cpu().numpy(), y.cpu().numpy(), dbg.cpu().numpy()))
+    (tau, y, dbg), (tau_wide, y_wide, dbg_wide) = out
+    assert np.array_equal(tau, tau_wide) and np.array_equal(y, y_wide)
+    # (float sums of other chunks: some 2^-21 each; a difference of infinities is one in both)
+    assert np.allclose(dbg, dbg_wide, rtol=1e-6, atol=1e-9, equal_nan=True)
+    if algo == "greedy":
+        assert np.all(np.isinf(dbg[1, 1:, 0]))                     # an infinite ratio in front of one of 0
