@@ -314,7 +314,10 @@ void small_verify_kernel(const FusedParams P)
         float max_p[kPositions], max_q[kPositions], tok_p[kPositions], tok_q[kPositions], factor[kPositions];
         int tau, residual;                          // whether the draw is from the residual of row tau
     } own;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = lane & (G - 1);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = lane & (G - 1);
+    // (put together from the two, not kept beside them: bf16 rows of sixteen logits per lane take 64 registers that way, else 65, and seven waves share a SIMD instead of
+    // eight: 6153 sequences of 8 over 960 92 / 76 us, 774 over 946 17.7 / 14.8, 6067 of 14 over 640 151 / 121)
+    const int tid = wave * kWave + lane;
     const int b = blockIdx.x;
     const int gamma = P.gamma, V = P.V, algo = P.algo;
     const float k = P.k;
