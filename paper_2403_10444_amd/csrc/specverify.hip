@@ -173,9 +173,13 @@ bool being_captured(hipStream_t stream)
 // The kernel that holds several short sequences, or one, in the registers of a workgroup, and its launch (none: the rows or their groups are
 // too many).  Lanes per row pair and sequences per workgroup by the row's length, the rows in the call and the draft's length, us a call on the
 // device (dense calls, another one / the one taken):
-//   up to 8 tokens a lane per row pair, four sequences per wave: 8192 of 10 over 2, float32: four lanes each, one sequence per wave 11.8 / 5.9;
+//   up to 8 tokens a lane per row pair, four sequences per wave: 8192 of 10 over 2, float32: four lanes each, one sequence per wave 11.8 / 5.9 (not float32 rows a line
+//   apart in long drafts, of which every lane of a wave reads another line: 3914 of 50 over 5, 69 apart 16.3 / 22.3, 1952 of 60 over 6 9.5 / 10.4, dense 4756 of 53 over 4 13.2 / 7.2);
 //   up to 32 four lanes: 8192 of 10 over 30, bf16, one sequence per workgroup / four 14.0 / 10.5, 64 of them the same;
-//   up to 128 sixteen: four sequences where drafts are short (8192 of 4 over 60 17.9 / 13.8; of 10 over 128 29.0 / 25.9 with one);
+//   up to 128 sixteen: four sequences where drafts are short: 8192 of 4 over 60 17.9 / 13.8; bf16 2385 of 7 over 82 9.3 / 8.8;
+//   one sequence gets no more from this kernel than from small_verify_kernel, which has 56 registers instead of 68 (eight waves per SIMD, not seven; that one / this one:
+//   bf16, 5430 of 16 over 101 25.4 / 29.7, 4308 of 15 over 128 15.5 / 16.9, 7465 of 8 over 64 21.1 / 22.1, 3289 of 63 over 27 13.4 / 14.8; float32, 6711 of 12 over 78 24.0 /
+//   26.5, 7613 of 15 over 116 28.7 / 30.5, 7620 of 7 over 67 18.6 / 18.8);
 //   up to 256 32, in calls of many rows sixteen with twice the logits each: 512 of 8 over 192, bf16, a wave per row pair / 32 lanes / 16
 //   8.5 / 7.0 / 7.6, 8192 of them 73.3 / 45.3 / 38.6; float32, 1024 of 12 over 256 16.8 / 12.5 / 11.5; 2048 of 6 over 250 17.3 / 11.7 / 11.8, 10.8 with four sequences;
 //   up to 512 a wave per row pair (small_verify_kernel; probabilities: here), bf16 rows in bulk and drafts that a workgroup's sixteen waves do not hold 32
@@ -199,13 +203,21 @@ PackedLaunch packed_launch_of(int B, int gamma, int seqs)
     return {kernel, (unsigned)((B - 1) / seqs + 1), (unsigned)threads, seqs, G, LANE};
 }
 template <typename T, bool PROBS>
-PackedLaunch packed_launch(int B, int gamma, int V)
+PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
 {
     const long long rows = (long long)B * (gamma + 1);
     const bool bf16 = ElemTraits<T>::kVec == 8;
+    if (!PROBS && !bf16 && V <= 8 && gamma > 16 && tstride >= 32) return {};
     if (V <= 8) return packed_launch_of<T, PROBS, 1, 8>(B, gamma, gamma < 16 ? 4 : gamma == 16 ? 3 : 1);
-    if (V <= 4 * 8) return packed_launch_of<T, PROBS, 4, 8>(B, gamma, gamma <= 16 && B >= 512 ? 4 : 1);
-    if (V <= 16 * 8) return gamma < 64 ? packed_launch_of<T, PROBS, 16, 8>(B, gamma, gamma < 8 && B >= 1024 ? 4 : 1) : packed_launch_of<T, PROBS, 4, 32>(B, gamma, 1);
+    if (V <= 4 * 8) {
+        if (!PROBS && gamma > 16) return {};
+        return packed_launch_of<T, PROBS, 4, 8>(B, gamma, gamma <= 16 && B >= 512 ? 4 : 1);
+    }
+    if (V <= 16 * 8) {
+        const bool several = gamma == 7 ? B >= (PROBS ? 1024 : 2048) && (PROBS || bf16) : gamma < 7 && B >= 1024;
+        if (!PROBS && !several) return {};
+        return gamma < 64 ? packed_launch_of<T, PROBS, 16, 8>(B, gamma, several ? 4 : 1) : packed_launch_of<T, PROBS, 4, 32>(B, gamma, 1);
+    }
     if (V <= 16 * 16) {
         if (rows > 12288 || gamma >= 32) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
         return packed_launch_of<T, PROBS, 32, 8>(B, gamma, 1);
@@ -231,7 +243,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
 {
     const T *target = static_cast<const T *>(target_v);
     const T *draft = static_cast<const T *>(draft_v);
-    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V);
+    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V, tstride);
     if (packed.kernel) {
         FusedParams F = {};
         F.target = target; F.draft = draft; F.tokens = tokens; F.draft_lens = draft_lens; F.uniforms = uniforms;
@@ -310,10 +322,10 @@ template <typename T, int G, int LANE>
 SmallLaunch small_launch_of(int B, int gamma)
 {
     const int threads = ((gamma + 1) * G + kWave - 1) / kWave * kWave;           // a group per row pair and one for the last target row
-    if constexpr (G != kWave || LANE != 8) {             // (those take no draft that fills the workgroup)
+    if constexpr (G * (SV_MAX_GAMMA + 1) > kTinyThreads && (G != kWave || LANE != 8)) {             // (those take no draft that fills the workgroup)
         if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, true>, (unsigned)B, kTinyThreads, G, LANE};
     }
-    if constexpr (G == kWave) {                          // (shorter drafts over fewer lanes are packed_launch's)
+    if constexpr (G * LANE <= 16 * 8 || G == kWave) {    // (shorter drafts over sixteen lanes of 32 are packed_launch's)
         if (threads <= kTinyThreads) return {small_verify_kernel<T, G, LANE, false>, (unsigned)B, (unsigned)threads, G, LANE};
     }
     return {};
@@ -321,6 +333,8 @@ SmallLaunch small_launch_of(int B, int gamma)
 template <typename T>
 SmallLaunch small_launch(int B, int gamma, int V)
 {
+    if (V <= 4 * 8) return small_launch_of<T, 4, 8>(B, gamma);
+    if (V <= 16 * 8) return small_launch_of<T, 16, 8>(B, gamma);
     if (V <= 64 * 8 && gamma < kTinyWaves) return small_launch_of<T, 64, 8>(B, gamma);
     if (V <= 16 * 32) return small_launch_of<T, 16, 32>(B, gamma);
     if (V <= 64 * 16) return small_launch_of<T, 64, 16>(B, gamma);
@@ -335,7 +349,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
                         size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd,
                         int magic, char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
-    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V);
+    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V, tstride);
     const SmallLaunch small = packed.kernel ? SmallLaunch{packed.kernel, packed.blocks, packed.threads, packed.lanes, packed.logits} : small_launch<T>(B, gamma, V);
     if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     FusedParams P = {};

@@ -287,8 +287,8 @@ PACKED = [
 _ONE, _SEVERAL = binding.SV_FORM_SEQUENCE, binding.SV_FORM_SEQUENCES
 FORMS = dict(zip(PACKED, [
     ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)), ((_SEVERAL, 1, 8), (1, 8)),
-    ((_SEVERAL, 4, 8), (4, 8)), ((_SEVERAL, 4, 8), (4, 8)), ((_SEVERAL, 4, 8), (4, 8)),
-    ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 16, 8), (16, 8)), ((_SEVERAL, 4, 32), (4, 32)),
+    ((_SEVERAL, 4, 8), (4, 8)), ((_SEVERAL, 4, 8), (4, 8)), ((_ONE, 4, 8), (4, 8)),
+    ((_ONE, 16, 8), (16, 8)), ((_SEVERAL, 16, 8), (16, 8)), ((_ONE, 16, 8), (16, 8)), ((_ONE, 16, 8), (4, 32)),
     ((_SEVERAL, 16, 16), (16, 16)), ((_SEVERAL, 16, 16), (16, 16)), ((_SEVERAL, 32, 8), (32, 8)), ((_SEVERAL, 16, 16), (16, 16)),
     ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 32, 16), (32, 16)), ((_SEVERAL, 16, 32), (16, 32)), ((_ONE, 16, 32), None),
     ((_ONE, 64, 8), (64, 8)), ((_ONE, 64, 16), (64, 16)), ((_ONE, 64, 16), (32, 32)), (None, (32, 32)), (None, (64, 32)), ((_ONE, 64, 32), (64, 32)), (None, None),
@@ -306,3 +306,26 @@ def test_sequences_that_share_a_workgroup(B, gamma, V, dtype, probs):
             ran = _check(dict(cfg=cfg, algo=algo, path="default", top_k=top_k, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 10 * V + n, probs)
             form = (of_probs and (_SEVERAL, *of_probs)) if probs else of_logits
             assert not ran or sv.spec_verify_debug_last_form() == (form or (0, 0, 0))
+
+
+# ---- both sides of the lines between the forms of short rows (logits)
+@pytest.mark.parametrize("B,gamma,V,dtype,form", [
+    (600, 16, 32, "f32", (_SEVERAL, 4, 8)), (600, 17, 32, "f32", (_ONE, 4, 8)), (5, 64, 9, "bf16", (_ONE, 4, 8)),
+    (1024, 6, 128, "f32", (_SEVERAL, 16, 8)), (1023, 6, 128, "f32", (_ONE, 16, 8)), (2048, 7, 33, "f32", (_ONE, 16, 8)),
+    (2048, 7, 33, "bf16", (_SEVERAL, 16, 8)), (2047, 7, 33, "bf16", (_ONE, 16, 8)), (1024, 8, 128, "bf16", (_ONE, 16, 8)), (3, 63, 128, "bf16", (_ONE, 16, 8)), (3, 64, 128, "f32", (_ONE, 16, 8)),
+])
+def test_both_sides_of_the_lines_between_short_rows(B, gamma, V, dtype, form):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"lines_B{B}_g{gamma}_V{V}_{dtype}", B, gamma, V, dtype, 2.0, 0.5, 0.9, False, 1)
+    for n, (algo, lens, pad_t, pad_d) in enumerate([("block", False, 0, 0), ("token", True, 3, 8), ("greedy", False, 0, 5)]):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 7 * V + n, False)
+        assert sv.spec_verify_debug_last_form() == form
+
+
+@pytest.mark.parametrize("gamma,pad_t,dtype,form", [(17, 23, "f32", (_SEVERAL, 1, 8)), (17, 24, "f32", (_ONE, 4, 8)), (16, 24, "f32", (_SEVERAL, 1, 8)), (17, 24, "bf16", (_SEVERAL, 1, 8))])
+def test_very_short_rows_that_lie_apart(gamma, pad_t, dtype, form):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"apart_g{gamma}_{dtype}", 70, gamma, 8, dtype, 2.0, 0.5, 0.9, False, 1)
+    for n, algo in enumerate(("block", "token", "greedy")):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=n == 1, pad_t=pad_t, pad_d=7, lens_seed=n), 40 + n, False)
+        assert sv.spec_verify_debug_last_form() == form
