@@ -182,21 +182,27 @@ bool being_captured(hipStream_t stream)
 //   26.5, 7613 of 15 over 116 28.7 / 30.5, 7620 of 7 over 67 18.6 / 18.8);
 //   up to 256 32, in calls of many rows sixteen with twice the logits each: 512 of 8 over 192, bf16, a wave per row pair / 32 lanes / 16
 //   8.5 / 7.0 / 7.6, 8192 of them 73.3 / 45.3 / 38.6; float32, 1024 of 12 over 256 16.8 / 12.5 / 11.5; 2048 of 6 over 250 17.3 / 11.7 / 11.8, 10.8 with four sequences;
-//   up to 512 a wave per row pair (small_verify_kernel; probabilities: here), bf16 rows in bulk and drafts that a workgroup's sixteen waves do not hold 32
-//   lanes: 2048 of 14 over 500 32.7 / 26.1, 1024 of 4 over 300 9.1 / 9.6; float32 2048 of 10 over 400 28.5 / 30.7; 64 of 16 over 400 9.5 / 8.2.
+//   up to 512 a wave per row pair (small_verify_kernel; probabilities: here), or 32 lanes: bf16 rows in bulk (that one / this one: 2048 of 14 over 500 32.7 / 26.1,
+//   7206 of 5 over 461 41.0 / 35.0, 2859 over 320 18.8 / 17.3; of 4 7946 over 284 40.2 / 38.7, 4339 over 512 21.0 / 22.4; of 2 3375 over 512 12.4 / 15.0; float32 2048 of 10 over
+//   400 28.5 / 30.7), and drafts that a workgroup's sixteen waves do not hold, else sixteen lanes of 32 (small_verify_kernel): up to drafts of 23 (two
+//   workgroups to a compute unit: 772 of 21 over 512, bf16 21.2 / 17.5, 864 of 20 over 448, float32 22.9 / 20.4, 2966 of 16 over 512 63.7 / 57.5; not bf16 rows of three vectors of sixteen lanes, in
+//   bulk: 1820 of 16 over 384 30.5 / 32.1, 2057 over 347 36.9 / 38.4, 1160 over 320 22.8 / 22.2), of 31 while each workgroup has its compute unit alone (144 of 26 over 512, float32
+//   10.9 / 9.5; 452 over 259 12.3 / 15.1; bf16 3090 of 27 over 384 52.6 / 77.3); from 32 on both are the same.
 // Probabilities, against the kernels for wider rows: 6000 of 10 over 2 163 / 5.8; 6000 of 10 over 256, float32 132.6 / 32.1; 1000 of 12 over 768, bf16 30.4 / 17.7 (a
 // wave per row pair 21.8; 200 of 12 7.3 either way); over 1025 ... 2048 tokens with longer drafts only while the workgroups are few: 512 of 10 over 2000, bf16 20.7 /
 // 16.6, 1000 28.8 / 30.5, 2048 50.4 / 58.0; 2048 of 4 35.1 / 32.4.
+constexpr int kComputeUnits = 256;
 struct PackedLaunch {
     void (*kernel)(const FusedParams);
     unsigned blocks, threads;
     int seqs, lanes, logits;             // sequences of a workgroup; lanes of a row pair, logits of a row per lane
 };
-template <typename T, bool PROBS, int G, int LANE>
+// (SEG: the only one of the two that calls of this form have; 0: by the draft's length)
+template <typename T, bool PROBS, int G, int LANE, int SEG = 0>
 PackedLaunch packed_launch_of(int B, int gamma, int seqs)
 {
-    const bool seg16 = gamma <= 16;
-    void (*const kernel)(const FusedParams) = seg16 ? packed_verify_kernel<T, PROBS, G, LANE, 16> : packed_verify_kernel<T, PROBS, G, LANE, kWave>;
+    const bool seg16 = SEG ? SEG == 16 : gamma <= 16;
+    void (*const kernel)(const FusedParams) = seg16 ? packed_verify_kernel<T, PROBS, G, LANE, SEG ? SEG : 16> : packed_verify_kernel<T, PROBS, G, LANE, SEG ? SEG : kWave>;
     const int seg = seg16 ? 16 : kWave, one = (gamma + 1) * G > seg ? (gamma + 1) * G : seg;      // lanes of one sequence
     const int threads = (seqs * one + kWave - 1) / kWave * kWave;
     if (threads > (G == 1 ? 2 * kWave : kTinyThreads)) return {};
@@ -223,9 +229,15 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
         return packed_launch_of<T, PROBS, 32, 8>(B, gamma, 1);
     }
     if (V <= 32 * 16) {
-        if (gamma >= 32) return packed_launch_of<T, PROBS, 16, 32>(B, gamma, 1);
-        if (gamma >= 16 || (rows > 8192 && (PROBS || bf16))) return packed_launch_of<T, PROBS, 32, 16>(B, gamma, 1);
-        if constexpr (PROBS) return packed_launch_of<T, PROBS, 64, 8>(B, gamma, 1);
+        if constexpr (PROBS) {
+            if (gamma >= 32) return packed_launch_of<T, PROBS, 16, 32>(B, gamma, 1);
+            if (gamma >= 16 || rows > 8192) return packed_launch_of<T, PROBS, 32, 16>(B, gamma, 1);
+            return packed_launch_of<T, PROBS, 64, 8>(B, gamma, 1);
+        } else {
+            const bool here = gamma < 16 ? bf16 && (gamma >= 5 ? rows > 8192 : gamma == 4 && rows > 24576)
+                            : gamma < 24 ? !(bf16 && V <= 384 && B > 1200) : gamma < 32 && B <= kComputeUnits;
+            if (here) return packed_launch_of<T, PROBS, 32, 16, ElemTraits<T>::kVec == 8 ? 0 : kWave>(B, gamma, 1);
+        }
     }
     if constexpr (PROBS) {
         if (V > 32 * 16 && V <= 32 * 32) return rows > 3072 || gamma >= 16 ? packed_launch_of<T, PROBS, 32, 32>(B, gamma, 1) : packed_launch_of<T, PROBS, 64, 16>(B, gamma, 1);
@@ -325,9 +337,7 @@ SmallLaunch small_launch_of(int B, int gamma)
     if constexpr (G * (SV_MAX_GAMMA + 1) > kTinyThreads && (G != kWave || LANE != 8)) {             // (those take no draft that fills the workgroup)
         if (threads > kTinyThreads && gamma * G <= kTinyThreads) return {small_verify_kernel<T, G, LANE, true>, (unsigned)B, kTinyThreads, G, LANE};
     }
-    if constexpr (G * LANE <= 16 * 8 || G == kWave) {    // (shorter drafts over sixteen lanes of 32 are packed_launch's)
-        if (threads <= kTinyThreads) return {small_verify_kernel<T, G, LANE, false>, (unsigned)B, (unsigned)threads, G, LANE};
-    }
+    if (threads <= kTinyThreads) return {small_verify_kernel<T, G, LANE, false>, (unsigned)B, (unsigned)threads, G, LANE};
     return {};
 }
 template <typename T>
