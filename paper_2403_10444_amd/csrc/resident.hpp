@@ -592,22 +592,44 @@ void resident_verify_kernel(const FusedParams P)
 constexpr int kRowsMaxRow = 2 * kThreads * 40;
 constexpr int kRowsMaxRowFew = kThreads * 48;   // in calls of few resident sets rows beyond, up to 16384 logits, do not come here
 // Calls of few resident sets that take it (`workgroups` of 8192 logits, `resident` of together.hpp's at once; `together`: whether that kernel has
-// the call else).  All that the first kernel of this file would have, and of the others (that kernel / this one, us): up to 4096 logits, bf16: 39 of 8
-// over 2100 10.4 / 9.4, 102 12.2 / 10.1; float32 68 of 8 over 4000 11.2 / 10.6, 853 of 2 over 2049 26.5 / 14.3; up to 8192, long drafts: 21 of 16 over 6000, float32
-// 10.9 / 10.1; others from about one set on: float32 230 of 3 over 5000 13.5 / 12.7, 153 11.8 / 11.8, 327 of 4 over 8001 25.5 / 21.6, 184 16.4 / 16.3; beyond, where two
-// workgroups become one, later: float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9; 102 of 5 over 11000 (1.2 sets) 15.5 / 16.5, 136 20.3 / 18.9; 60 of 8 over 18000 (1.6 sets)
-// 19.5 / 18.8.
+// the call else), from how many sixteenths of a resident set on (the kernel else / this one, us; the report of every S_i, which favours this one, decides nothing):
+//   up to 4096 logits four, bf16: 39 of 8 over 2100 10.4 / 9.4, 102 12.2 / 10.1; float32 68 of 8 over 4000 11.2 / 10.6, 853 of 2 over 2049 26.5 / 14.3;
+//   up to 6144 drafts of twelve and more too (54 of 12 over 4529, bf16 12.5 / 10.2, 31 of 14 over 4480 10.0 / 9.1), others from nearly a set on: float32 230 of 3 over 5000 13.5 /
+//   12.7, 153 11.8 / 11.8; up to 8192 all from a set on (327 of 4 over 8001 25.5 / 21.6, 184 16.4 / 16.3), such drafts before that while half of the places are
+//   free (20 of 15 over 7232 10.0 / 9.4, 24 of 16 over 7744 10.1 / 9.7), with Alg. 1, whose tests ask for no S_i, always (75 of 12 over 6900 12.0 / 11.5; Alg. 2 and 4, bf16 59 of 13 over
+//   7680 11.3 / 12.4, 57 of 16 over 7168, ragged 10.8 / 11.4, float32 54 of 16 over 7168 14.6 / 15.7);
+//   beyond, where two workgroups become one, later: up to 10240 float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9;
+//   up to 12288, 48 logits per lane, from one and a half sets on (bf16 34 of 16 over 10688 12.5 / 13.4, 43 of 13 over 11072 12.3 / 13.8, 86 of 8 over 12004 18.1 / 14.9; float32
+//   102 of 5 over 11000 15.5 / 16.5, 136 20.3 / 18.9; Alg. 1 58 of 12 over 11456, bf16 13.7 / 12.0, 107 of 5 over 10912 13.7 / 13.3), where sequences bring their own draft lengths, half of whose workgroups have
+//   nothing to do, from two (bf16 74 of 9 over 11712 11.9 / 13.1, 76 of 8 over 11503 14.2 / 15.4, 72 of 14 over 10944 16.5 / 12.8; float32 97 of 8 over 11328 15.1 / 16.2, 149 of 6 over
+//   10888 18.4 / 17.1); up to 17920 float32 60 of 8 over 18000 (1.6 sets) 19.5 / 18.8;
+//   beyond, where the eighth wave has logits too, bf16 from about one and a half on (35 of 10 over 18785 15.2 / 17.4, 31 of 13 over 20031 16.1 / 17.2, 34 of 14 over 19136 17.0 / 14.5), own
+//   lengths from two and a quarter (73 of 8 over 19633 15.2 / 18.0, 55 of 10 over 19116 13.3 / 15.1, 69 over 20096 20.6 / 17.2), not in float32 (79 of 6 over 19712, ragged 14.4 / 17.6, 54 of
+//   12 over 20142 25.5 / 27.6, 59 of 14 over 19779 31.1 / 33.4); Alg. 1 with drafts of eight and more again sooner (28 of 16 over 19108 14.6 / 12.1, 32 of 12 over 19456 13.1 / 11.8; float32 55
+//   of 14 over 18368 28.0 / 25.8; own lengths, bf16 43 of 16 over 18048 14.6 / 12.2, 39 of 9 over 19456 11.4 / 12.1).
 // (float32 drafts of their own lengths over 4097 ... 8192 logits would gain too - 341 of 8 over 5000 22.4 / 17.5 - but a test holds them to that kernel.)
-inline bool rows_alone(long long workgroups, long long resident, int gamma, int V, bool f32, bool own_lengths, bool together)
+inline bool rows_alone(long long workgroups, long long resident, int gamma, int V, bool f32, bool own_lengths, bool together, bool token_algo)
 {
     if (V > kRowsMaxRow || (V > kRowsMaxRowFew && V <= kThreads * 64)) return false;
-    if (!together) return true;
-    if (V <= kThreads * 16) return 4 * workgroups > resident;
-    if (V <= kThreads * 32) {
-        if (f32 && own_lengths) return false;
-        return gamma >= 12 ? 4 * workgroups > resident : workgroups > (V <= kThreads * 24 ? resident - resident / 8 : resident);
+    int sixteenths = 0;
+    if (V <= kThreads * 40) {
+        if (f32 && own_lengths && V > kThreads * 16 && V <= kThreads * 32) return false;
+        if (!together) return true;
+        if (V <= kThreads * 16) sixteenths = 4;
+        else if (V <= kThreads * 24) sixteenths = gamma >= 12 ? 4 : 14;
+        else if (V <= kThreads * 32) sixteenths = gamma >= 12 && (token_algo || 2 * workgroups <= resident) ? 4 : 16;
+        else sixteenths = 18;
+    } else if (V <= kThreads * 48) {
+        sixteenths = own_lengths ? 32 : token_algo ? 20 : 24;
+    } else if (V <= 7 * kWave * 40) {
+        sixteenths = together ? 24 : 0;
+    } else if (token_algo && gamma >= 8) {
+        sixteenths = own_lengths ? 34 : 20;
+    } else {
+        if (f32) return false;
+        sixteenths = own_lengths ? 36 : 23;
     }
-    return workgroups > resident + (V <= kThreads * 40 ? resident / 8 : resident / 2);
+    return 16 * workgroups > sixteenths * resident;
 }
 // waves per SIMD of a form: by what it has to keep in registers, 2 LANE floats per lane and some thirty more
 template <int LANE> constexpr int kRowsWavesPerSimd = LANE == 24 ? 6 : LANE == 32 ? 5 : LANE <= 48 ? 4 : 3;

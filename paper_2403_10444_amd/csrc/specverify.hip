@@ -467,7 +467,7 @@ sv_status_t launch_resident(int algo, const void *target, const void *draft, con
     // (where the row pairs are more than run at once: what leaves early makes room)
     P.prune = (long long)nwg * B * gamma > capacity ? 1 : 0;
     if (path == 0 && rows_alone((long long)nwg * B * (gamma + 1), resident_workgroups(together_verify_kernel<T, ALIGNED, 1>, cap_together), gamma, V,
-                                ElemTraits<T>::kVec == 4, draft_lens != nullptr, together)) {
+                                ElemTraits<T>::kVec == 4, draft_lens != nullptr, together, algo == kToken)) {
         const sv_status_t st = launch_rows<T, ALIGNED>(P, false, stream);
         if (st == SV_OK) g_last_together.store(0);
         if (st != SV_ERR_UNSUPPORTED) return st;
