@@ -597,7 +597,8 @@ constexpr int kRowsMaxRowFew = kThreads * 48;   // in calls of few resident sets
 //   up to 6144 drafts of twelve and more too (54 of 12 over 4529, bf16 12.5 / 10.2, 31 of 14 over 4480 10.0 / 9.1), others from nearly a set on: float32 230 of 3 over 5000 13.5 /
 //   12.7, 153 11.8 / 11.8; up to 8192 all from a set on (327 of 4 over 8001 25.5 / 21.6, 184 16.4 / 16.3), such drafts before that while half of the places are
 //   free (20 of 15 over 7232 10.0 / 9.4, 24 of 16 over 7744 10.1 / 9.7), with Alg. 1, whose tests ask for no S_i, always (75 of 12 over 6900 12.0 / 11.5; Alg. 2 and 4, bf16 59 of 13 over
-//   7680 11.3 / 12.4, 57 of 16 over 7168, ragged 10.8 / 11.4, float32 54 of 16 over 7168 14.6 / 15.7);
+//   7680 11.3 / 12.4, 57 of 16 over 7168, ragged 10.8 / 11.4, float32 54 of 16 over 7168 14.6 / 15.7), float32 drafts of their own lengths from 1.75 (94 of 12 over 7018 14.5 / 15.8, 127 of 9 over 8064 13.9 / 15.1, 138 of 12 over 7488 17.1 / 17.1, 304
+//   of 6 over 6882 21.0 / 18.4; up to 6144 like the others: 139 of 7 over 4736 12.2 / 11.7, 312 of 6 over 4864 18.1 / 14.9, 341 of 8 over 5000 22.4 / 17.5);
 //   beyond, where two workgroups become one, later: up to 10240 float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9;
 //   up to 12288, 48 logits per lane, from one and a half sets on (bf16 34 of 16 over 10688 12.5 / 13.4, 43 of 13 over 11072 12.3 / 13.8, 86 of 8 over 12004 18.1 / 14.9; float32
 //   102 of 5 over 11000 15.5 / 16.5, 136 20.3 / 18.9; Alg. 1 58 of 12 over 11456, bf16 13.7 / 12.0, 107 of 5 over 10912 13.7 / 13.3), where sequences bring their own draft lengths, half of whose workgroups have
@@ -607,17 +608,15 @@ constexpr int kRowsMaxRowFew = kThreads * 48;   // in calls of few resident sets
 //   lengths from two and a quarter (73 of 8 over 19633 15.2 / 18.0, 55 of 10 over 19116 13.3 / 15.1, 69 over 20096 20.6 / 17.2), not in float32 (79 of 6 over 19712, ragged 14.4 / 17.6, 54 of
 //   12 over 20142 25.5 / 27.6, 59 of 14 over 19779 31.1 / 33.4); Alg. 1 with drafts of eight and more again sooner (28 of 16 over 19108 14.6 / 12.1, 32 of 12 over 19456 13.1 / 11.8; float32 55
 //   of 14 over 18368 28.0 / 25.8; own lengths, bf16 43 of 16 over 18048 14.6 / 12.2, 39 of 9 over 19456 11.4 / 12.1).
-// (float32 drafts of their own lengths over 4097 ... 8192 logits would gain too - 341 of 8 over 5000 22.4 / 17.5 - but a test holds them to that kernel.)
 inline bool rows_alone(long long workgroups, long long resident, int gamma, int V, bool f32, bool own_lengths, bool together, bool token_algo)
 {
     if (V > kRowsMaxRow || (V > kRowsMaxRowFew && V <= kThreads * 64)) return false;
     int sixteenths = 0;
     if (V <= kThreads * 40) {
-        if (f32 && own_lengths && V > kThreads * 16 && V <= kThreads * 32) return false;
         if (!together) return true;
         if (V <= kThreads * 16) sixteenths = 4;
         else if (V <= kThreads * 24) sixteenths = gamma >= 12 ? 4 : 14;
-        else if (V <= kThreads * 32) sixteenths = gamma >= 12 && (token_algo || 2 * workgroups <= resident) ? 4 : 16;
+        else if (V <= kThreads * 32) sixteenths = f32 && own_lengths ? 28 : gamma >= 12 && (token_algo || 2 * workgroups <= resident) ? 4 : 16;
         else sixteenths = 18;
     } else if (V <= kThreads * 48) {
         sixteenths = own_lengths ? 32 : token_algo ? 20 : 24;

@@ -137,7 +137,7 @@ def test_calls_beyond_its_limits_are_refused_when_forced_and_go_to_the_large_ker
 @pytest.mark.parametrize("B,gamma,V,dtype,lens", [(560, 8, 5000, "bf16", True), (270, 8, 9000, "bf16", True), (440, 8, 3000, "bf16", False),
                                                   (340, 8, 5000, "f32", True), (140, 8, 25000, "bf16", True), (73, 8, 25000, "f32", False)])
 def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype, lens, forced):
-    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths; the bf16 ones of those have a form with one workgroup per
+    """... however many resident sets that is (4.3 for short rows and drafts of their own lengths; those of up to 20480 logits have a form with one workgroup per
     row, which the library takes by itself): the same decisions (here, where no uniform is next to an edge, from all kernels)."""
     cfg = workloads.Config(f"forced_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 1.0, 0.8, False, 1)
     inp = workloads.generate(cfg, seed=B, device=DEV)
@@ -146,8 +146,9 @@ def test_forced_it_takes_every_call_that_the_library_gives_it(B, gamma, V, dtype
     for path in (0, forced):
         sv.spec_verify_debug_config(path, -1)
         tau, y = sv.spec_verify_ex("block", inp["target_logits"], inp["draft_logits"], inp["draft_tokens"], inp["uniforms"], 0.8, draft_lens=dl)
-        assert _ran(path or (TOGETHER if dtype == "f32" else RESIDENT))
-        assert (sv.spec_verify_debug_last_form()[0] == binding.SV_FORM_ROW) == (path == 0 and V < 10000 and dtype == "bf16")
+        one_per_row = path == 0 and V < 10000
+        assert _ran(path or (RESIDENT if one_per_row or dtype == "bf16" else TOGETHER))
+        assert (sv.spec_verify_debug_last_form()[0] == binding.SV_FORM_ROW) == one_per_row
         out.append((tau.cpu().numpy(), y.cpu().numpy()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
