@@ -411,11 +411,14 @@ FusedParams word_params(int algo, const void *target, const void *draft, const i
     return P;
 }
 
-// Rows that one workgroup holds (rows_verify_kernel); `P`: the arguments of the call, `in_chain`: how a position learns w_i.
+// Rows that one workgroup holds (rows_verify_kernel); `P`: the arguments of the call, `in_chain`: how a position learns w_i (calls of few resident sets: from the
+// ratios; others by the large kernel's line, which holds here: 200 calls of 1.2 to 16 of its sets with the line / the ratios / the chain: 0.15 % over the faster of the two on
+// average, eleven more than 1 % over, the worst 1064 ragged of 4 over 2301, Alg. 1, 15.2 / 14.6 / 15.2 us; 104 ragged of 16 over 2163 11.2 / 11.2 / 18.5, 1912 of 8 over 4736 60.5 /
+// 64.7 / 60.4).
 template <typename T, bool ALIGNED>
 sv_status_t launch_rows(FusedParams P, bool in_chain, hipStream_t stream)
 {
-    static std::atomic<int> caps[3][65];
+    static std::atomic<int> caps[2][3][65];              // (of each kernel: with and without the chain, by waves, by logits per lane)
     void (*kernel)(const FusedParams) = nullptr;
     const int waves = P.V <= 4096 ? 2 : P.V <= kThreads * 64 ? 4 : 8;
     int lane_logits = (P.V + waves * kWave - 1) / (waves * kWave);
@@ -426,7 +429,7 @@ sv_status_t launch_rows(FusedParams P, bool in_chain, hipStream_t stream)
     SV_FORM(2, 24) SV_FORM(2, 32) SV_FORM(4, 24) SV_FORM(4, 32) SV_FORM(4, 40) SV_FORM(4, 48) SV_FORM(4, 64) SV_FORM(8, 40)
 #undef SV_FORM
     if (!kernel) return SV_ERR_UNSUPPORTED;
-    const int capacity = resident_workgroups(kernel, caps[waves / 4][lane_logits], waves * kWave);
+    const int capacity = resident_workgroups(kernel, caps[in_chain ? 1 : 0][waves / 4][lane_logits], waves * kWave);
     if (capacity < 1) return SV_ERR_HIP;
     // groups of sequences so large that one position of a group fills the device at least once
     const int groups = P.B / capacity > 1 ? P.B / capacity : 1;
