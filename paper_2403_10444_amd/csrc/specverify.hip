@@ -217,12 +217,12 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
     if (V <= 8) return packed_launch_of<T, PROBS, 1, 8>(B, gamma, gamma < 16 ? 4 : gamma == 16 ? 3 : 1);
     if (V <= 4 * 8) {
         if (!PROBS && gamma > 16) return {};
-        return packed_launch_of<T, PROBS, 4, 8>(B, gamma, gamma <= 16 && B >= 512 ? 4 : 1);
+        return packed_launch_of<T, PROBS, 4, 8, PROBS ? 0 : 16>(B, gamma, gamma <= 16 && B >= 512 ? 4 : 1);
     }
     if (V <= 16 * 8) {
         const bool several = gamma == 7 ? B >= (PROBS ? 1024 : 2048) && (PROBS || bf16) : gamma < 7 && B >= 1024;
-        if (!PROBS && !several) return {};
-        return gamma < 64 ? packed_launch_of<T, PROBS, 16, 8>(B, gamma, several ? 4 : 1) : packed_launch_of<T, PROBS, 4, 32>(B, gamma, 1);
+        if constexpr (PROBS) return gamma < 64 ? packed_launch_of<T, PROBS, 16, 8>(B, gamma, several ? 4 : 1) : packed_launch_of<T, PROBS, 4, 32, kWave>(B, gamma, 1);
+        else return several ? packed_launch_of<T, PROBS, 16, 8, 16>(B, gamma, 4) : PackedLaunch{};
     }
     if (V <= 16 * 16) {
         if (rows > 12288 || gamma >= 32) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
@@ -230,9 +230,9 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
     }
     if (V <= 32 * 16) {
         if constexpr (PROBS) {
-            if (gamma >= 32) return packed_launch_of<T, PROBS, 16, 32>(B, gamma, 1);
+            if (gamma >= 32) return packed_launch_of<T, PROBS, 16, 32, kWave>(B, gamma, 1);
             if (gamma >= 16 || rows > 8192) return packed_launch_of<T, PROBS, 32, 16>(B, gamma, 1);
-            return packed_launch_of<T, PROBS, 64, 8>(B, gamma, 1);
+            return packed_launch_of<T, PROBS, 64, 8, 16>(B, gamma, 1);
         } else {
             const bool here = gamma < 16 ? bf16 && (gamma >= 5 ? rows > 8192 : gamma == 4 && rows > 24576)
                             : gamma < 24 ? !(bf16 && V <= 384 && B > 1200) : gamma < 32 && B <= kComputeUnits;
@@ -240,8 +240,8 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
         }
     }
     if constexpr (PROBS) {
-        if (V > 32 * 16 && V <= 32 * 32) return rows > 3072 || gamma >= 16 ? packed_launch_of<T, PROBS, 32, 32>(B, gamma, 1) : packed_launch_of<T, PROBS, 64, 16>(B, gamma, 1);
-        if (V > 32 * 32 && V <= kSmallMaxRow && (gamma < 6 || rows <= 6000)) return packed_launch_of<T, PROBS, 64, 32>(B, gamma, 1);
+        if (V > 32 * 16 && V <= 32 * 32) return rows > 3072 || gamma >= 16 ? packed_launch_of<T, PROBS, 32, 32>(B, gamma, 1) : packed_launch_of<T, PROBS, 64, 16, 16>(B, gamma, 1);
+        if (V > 32 * 32 && V <= kSmallMaxRow && (gamma < 6 || rows <= 6000)) return packed_launch_of<T, PROBS, 64, 32, 16>(B, gamma, 1);
     }
     return {};
 }

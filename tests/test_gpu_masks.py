@@ -43,6 +43,30 @@ def test_verification(T, value, dtype):
                     sv.spec_verify_debug_config(0, -1)
 
 
+# Rows that share a workgroup with others, and rows that have one each (which take calls of more sequences): lanes, waves and half workgroups that hold
+# nothing but masked logits
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,value", MASKS)
+def test_short_rows_and_rows_of_one_workgroup(T, value, dtype):
+    low = _mask(dtype, value)
+    for B, gamma, V, form in [(9, 3, 7, sv.binding.SV_FORM_SEQUENCES), (600, 2, 30, sv.binding.SV_FORM_SEQUENCES), (1030, 2, 100, sv.binding.SV_FORM_SEQUENCES),
+                              (30, 3, 200, sv.binding.SV_FORM_SEQUENCES), (6, 17, 500, sv.binding.SV_FORM_SEQUENCES), (110, 2, 3000, sv.binding.SV_FORM_ROW),
+                              (210, 2, 9000, sv.binding.SV_FORM_ROW), (210, 2, 17000, sv.binding.SV_FORM_ROW)]:
+        cfg = workloads.Config(f"masked_short_V{V}", B, gamma, V, dtype, 2.5, 0.8, T, False, 1)
+        inp = workloads.generate(cfg, seed=V, device=DEV)
+        keep = torch.arange(V, device=DEV) % (V // 2) < V // 6 + 1
+        inp["draft_logits"][B // 2:, :, ~keep] = low                 # (the first sequences' drafts may come from what the target masks)
+        inp["target_logits"][..., ~keep] = low
+        q = torch.softmax(inp["draft_logits"].double() / T, -1)
+        gen = torch.Generator(device=DEV).manual_seed(V)
+        inp["draft_tokens"] = torch.multinomial(q.view(-1, V), 1, generator=gen).view(B, gamma).to(torch.int32)
+        some = sorted({0, B // 2 - 1, B // 2, B - 1, *range(0, B, B // 40 + 1)})
+        for algo in ("block", "token", "greedy"):
+            got = parity.run_gpu(algo, inp, T)
+            assert sv.spec_verify_debug_last_form()[0] == form
+            parity.compare(got, parity.run_oracle(algo, inp, T, rows=some), rows=some, label=f"{value}/T{T}/V{V}/{algo}", greedy=algo == "greedy")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,value", MASKS)
 def test_drafting(T, value, dtype):

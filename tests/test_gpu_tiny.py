@@ -273,6 +273,20 @@ def test_groups_of_lanes_at_their_edges(B, gamma, V, dtype, algo):
     parity.compare(got, parity.run_oracle(algo, inp, 0.9), label=f"{cfg.name}/{algo}/identical", greedy=algo == "greedy")
 
 
+# ---- rows of more than 2048 logits that fit LDS: both sides of the line from which they have workgroups of their own (600 target rows)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,gamma,V,in_lds", [(300, 1, 3000, True), (301, 1, 3000, False), (300, 1, 4778, True), (301, 1, 4778, False),
+                                              (200, 2, 2049, True), (201, 2, 2049, False), (200, 2, 2867, True), (201, 2, 2867, False)])
+def test_the_line_from_rows_in_lds(B, gamma, V, in_lds, dtype):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"lds_line_B{B}_g{gamma}_V{V}", B, gamma, V, dtype, 2.5, 0.8, 0.9, False, 1)
+    for n, (algo, lens, pad_t, pad_d) in enumerate([("block", False, 0, 0), ("token", True, 3, 8), ("greedy", True, 0, 5)]):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 50 + n, False)
+        form = sv.spec_verify_debug_last_form()
+        # (602 workgroups of rows of 4778: the kernel for calls that run at once)
+        assert form == ((binding.SV_FORM_SEQUENCE_IN_LDS, 0, 0) if in_lds else (binding.SV_FORM_ROW, 128, 24) if V <= 3072 else (0, 0, 0))
+
+
 # ---- several sequences to a workgroup, logits and probabilities: every number of lanes per row pair and of sequences per workgroup at the
 # edges of its range, a last workgroup that is partly empty, drafts of the most positions that a form holds
 PACKED = [
