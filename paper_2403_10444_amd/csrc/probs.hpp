@@ -27,7 +27,12 @@
 
 namespace sv {
 
-constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: up to how many each workgroup forms its position's weight
+// Target rows of at most half a chunk: up to how many each workgroup forms its position's weight (beyond: a kernel in front).  Each workgroup / in front, us, over 2049 ... 4096
+// tokens: bf16 309 sequences of 6 over 2086 17.1 / 18.2, 1031 of 3 over 3418 27.5 / 27.5, 876 of 5 over 2263 27.9 / 27.5, 1989 of 3 over 2828 42.0 / 39.7; float32 221 of 9 over 2547
+// 19.8 / 20.7, 824 of 4 over 3321 33.9 / 34.5, 561 of 8 over 2444 29.0 / 28.5, 1182 of 6 over 3163 51.4 / 50.2; own draft lengths 185 of 10 over 3158 15.1 / 16.4, 705 of 6 over 2353
+// 22.6 / 23.3, 1007 of 8 over 2252 28.1 / 28.0 (1642 calls of 1000 to 11000 rows: the line is 0.7 % over the faster of the two on average, one at 2000 2.3 %).  Shorter rows come here
+// from 6000 rows on only, where the kernel in front is the better one: float32 1064 of 10 over 1747 53.4 / 44.3, bf16 1105 of 8 over 1513 36.1 / 33.1.
+constexpr int kProbsFormMax = 5000;
 // Workgroups that run at once, or nearly, and what they read of the target rows: up to there forming the weights in every workgroup
 // costs no more than a launch in front (Alg. 1; every workgroup / in front, gamma = 8: V = 128256: bf16 864 workgroups 13.2 / 14.2 us, 1152
 // 14.4 / 14.3, 1440 15.3 / 14.9; float32 432 14.1 / 15.6, 576 15.1 / 14.7, 1152 20.1 / 16.6; V = 8192: bf16 1098 15.1 / 15.3, 1494 16.4 / 15.4; float32
@@ -35,9 +40,9 @@ constexpr int kProbsFormMax = 2000;      // row pairs of at most half a chunk: u
 constexpr unsigned kProbsAtOnce = 1280;
 constexpr size_t kProbsAtOnceBytes = 20u << 20;
 // Calls of up to this many workgroups have one launch (`resident`: how many of that launch's run at once).  Two / one, us: bf16: B = 10, gamma = 4, V = 16000
-// 11.0 / 9.1; B = 1, gamma = 8, V = 50257 11.7 / 10.5; B = 4, gamma = 4, V = 256000 (640 workgroups) 13.5 / 11.7; B = 25, gamma = 1, V = 128256 (800) 12.3 / 12.0;
-// float32: B = 34, gamma = 4, V = 16000 16.1 / 13.8; B = 21, gamma = 4, V = 128256 (1680) 25.7 / 23.6.  Beyond: B = 64, gamma = 1, V = 128256,
-// float32 (2048) 25.7 / 31.0, bf16, gamma = 16, B = 11, V = 128256 (2992) 26.3 / 25.6, gamma = 8, B = 64, V = 128256 (9216) 51.0 / 53.5
+// 10.9 / 9.5; B = 1, gamma = 8, V = 50257 11.4 / 10.3; B = 4, gamma = 4, V = 256000 (640 workgroups) 12.9 / 11.4; B = 25, gamma = 1, V = 128256 (800) 11.9 / 12.0;
+// float32: B = 34, gamma = 4, V = 16000 16.0 / 14.1; B = 21, gamma = 4, V = 128256 (1680) 25.4 / 23.7.  Beyond: B = 64, gamma = 1, V = 128256,
+// float32 (2048) 24.1 / 30.6, bf16, gamma = 16, B = 11, V = 128256 (2992) 23.9 / 22.9, gamma = 8, B = 64, V = 128256 (9216) 47.3 / 49.2.
 // Unaligned bf16 rows, whose loads straddle lines, with long drafts less far: V = 109165, gamma = 14, 1050 workgroups 19.2 / 17.2, 1260 20.2 / 19.8, 1470
 // 21.0 / 21.5; V = 30001, gamma = 8, 1296 21.1 / 20.4, 1512 21.6 / 22.4, 2016 24.7 / 24.8 (aligned, V = 109168, 1470 18.3 / 17.6; unaligned float32 26.9 / 26.1).
 inline long long probs_at_once(long long resident, int gamma, bool f32, bool aligned)

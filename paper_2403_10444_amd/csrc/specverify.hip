@@ -284,8 +284,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
     // A position's weight: formed by each of its workgroups under its loads (B = 64, gamma = 8, V = 128256, bf16: 58 -> 51 us,
     // 1 sequence 18 -> 14; float32, B = 48 83 -> 69, 72 with the kernel in front), or by a kernel in front.  That is the better way where most workgroups have nothing to sum
     // (Alg. 1 unless every sum is reported: 25 us against 48 there, unless the call runs at once anyway: kProbsAtOnce) and where there are many of them with less to read
-    // than the weight takes to form (4096 sequences of 8 over 500 tokens: 150 us against 185, and 89 since short rows leave
-    // out the vectors beyond them).
+    // than the weight takes to form (kProbsFormMax).
     const int every_sum = P.every_sum = debug_out ? 1 : 0;
     const bool many_short = V <= kChunk / 2 && (long long)B * (gamma + 1) > kProbsFormMax;
     const size_t row_bytes = (size_t)blocks * (V < kChunk ? V : kChunk) * sizeof(T);       // the target rows' (the last chunk counted whole)

@@ -130,10 +130,12 @@ def test_probs_unnormalised_rows_are_used_as_given():
 
 
 # (where the weights are formed - by every workgroup, or by a kernel in front - and how the finishing kernel walks: the last
-# positions of long drafts, rows at the edges of a wave's quarter of a chunk, thousands of short rows on both sides of the rule)
+# positions of long drafts, rows at the edges of a wave's quarter of a chunk, thousands of rows of up to half a chunk on both sides of the rule, 5000
+# of them; rows of 40 share a workgroup, packed.hpp)
 @pytest.mark.parametrize("algo", ["block", "token", "greedy"])
 @pytest.mark.parametrize("B,gamma,V,dtype", [(3, 64, 2049, "f32"), (4, 5, 2048, "bf16"), (5, 3, 4097, "bf16"), (3, 2, 8193, "f32"), (4, 1, 16383, "bf16"),
-                                             (499, 3, 40, "f32"), (501, 3, 40, "bf16"), (501, 3, 4100, "bf16")])
+                                             (499, 3, 40, "f32"), (501, 3, 40, "bf16"), (501, 3, 4100, "bf16"),
+                                             (1000, 4, 2100, "bf16"), (1001, 4, 2100, "f32"), (1001, 4, 4096, "bf16"), (1001, 4, 4097, "bf16"), (860, 6, 1030, "f32")])
 def test_weights_and_walk_at_their_edges(algo, B, gamma, V, dtype):
     import paper_2403_10444_amd as sv
     cfg = _custom(B, gamma, V, dtype, sigma_t=2.0, sigma_d=0.4, T=1.0)
@@ -340,7 +342,7 @@ def test_probs_waits_that_run_out(algo, B, gamma, V, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("B,gamma", [(30, 3), (60, 64), (700, 3)])               # one launch; the launch of its own for the finish; with the weights' in front
+@pytest.mark.parametrize("B,gamma", [(30, 3), (60, 64), (700, 3)])               # (packed.hpp: workgroups of several sequences, of one)
 def test_probs_rows_shorter_than_a_vector(B, gamma, dtype):
     import paper_2403_10444_amd as sv
     for V in (1, 2, 3, 5, 7, 9):

@@ -33,7 +33,7 @@ def _nearly_cancelling(rng):
 # (several sequences to a workgroup, one, the kernels for wider rows in one launch and in two, and with the weights from a kernel in front)
 @pytest.mark.parametrize("large_ratio", [False, True])
 @pytest.mark.parametrize("algo", ["block", "greedy"])
-@pytest.mark.parametrize("B,gamma,V", [(64, 3, 7), (64, 20, 31), (64, 3, 300), (64, 5, 2000), (64, 3, 2500), (500, 4, 2500), (300, 8, 9000)])
+@pytest.mark.parametrize("B,gamma,V", [(64, 3, 7), (64, 20, 31), (64, 3, 300), (64, 5, 2000), (64, 3, 2500), (500, 4, 2500), (1001, 4, 2500), (300, 8, 9000)])
 def test_a_residual_far_below_its_row(B, gamma, V, algo, large_ratio):
     """w = a / b, and at one token w c - d with a c - b d = k: S is k / b (in units of 2^-24).  `large_ratio`: ratios of 2^60 come before, whose
     weight is 1 (Alg. 2) - what they leave in sums of logarithms must not blur a / b.
