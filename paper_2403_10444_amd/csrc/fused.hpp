@@ -1083,8 +1083,8 @@ __device__ __forceinline__ void lead_row(int b, int i_own, int gb, unsigned par,
         last_passes = (double)eta_next < fmin(w_last, 1.0);
     }
     // without the chain, Alg. 2 / 4, every token accepted: tau and Y depend on nothing that an earlier position, or this row's residual, has to say, and in calls of few
-    // resident sets the earlier leaders may still be drawing (48 ragged of 6 over 100277, bf16: 26.4 -> 24.6 us; 60 ragged of 10 over 50000, float32, Alg. 4 38.0 -> 35.7;
-    // 24 of 8 over 128256 25.3 -> 25.0).  With the chain the earlier words are long there, and the kernel came out 0.4 to 0.8 % slower with it; so did, by 0.5 to 1.5 %,
+    // resident sets the earlier leaders may still be drawing (without / with it, us, bf16: 48 ragged of 6 over 100277 27.8 / 27.0, 60 over 128256 32.6 / 31.8, 100 over 50257 32.0 / 31.0;
+    // 24 of 8 over 128256 of close models 28.8 / 28.0, of others 24.8 / 25.0; float32, 60 ragged of 10 over 50000, Alg. 4 34.9 / 34.7).  With the chain the earlier words are long there, and the kernel came out 0.4 to 0.8 % slower with it; so did, by 0.5 to 1.5 %,
     // float32 calls with this rule for Alg. 1 or for the row's own shares.
     const bool all_accepted = !CHAIN && finisher && !token_algo && last_passes;
     constexpr bool kLeavesShares = ElemTraits<T>::kVec == 8;

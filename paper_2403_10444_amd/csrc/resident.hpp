@@ -41,10 +41,15 @@ inline double resident_sets(int gamma, int groups, bool f32, bool own_lengths, b
     const double sets = (f32 ? 1.8 : 2.5) * (own_lengths ? 1.25 : 1.0), few_positions = 1.0 + 0.5 * gamma;
     double line = (sets < few_positions ? sets : few_positions) * narrow;
     // What that line misses for rows of a few workgroups, where the large kernel has less to gain, above all where rows are not
-    // 16-byte aligned.  3.0 sets of rows of one workgroup: float32, V = 2500, gamma = 8 28.1 / 31.2, gamma = 2 26.6 / 27.9; V = 8192, gamma = 8
-    // 39.7 / 42.0; bf16, V = 2500, gamma = 2 27.9 / 30.8.  Not aligned: float32, gamma = 8, V = 9001, 2.9 sets 30.9 / 34.1, V = 30001 35.2 / 36.8; bf16,
-    // V = 9001, gamma = 2, 2.9 sets 30.1 / 31.6.  Aligned float32: gamma = 8, 2.7 sets, V = 16000 34.2 / 36.3, V = 32000 35.0 / 33.9, 2.6 sets 33.2 / 34.9,
-    // gamma = 4 33.2 / 32.6; own lengths, gamma = 8, V = 32000, 3.0 sets 26.4 / 27.5.
+    // 16-byte aligned: float32, gamma = 8, 2.9 sets, V = 30001 35.2 / 36.8; aligned float32: gamma = 8, V = 32000, 2.7 sets 35.0 / 33.9, 2.6 sets 33.2 / 34.9,
+    // gamma = 4 33.2 / 32.6; own lengths, gamma = 8, 3.0 sets 26.4 / 27.5.
+    // Rows of one and of two workgroups have the kernel of one workgroup per row (below, rows_verify_kernel) beyond this line, and up to 12288 logits before it too: there
+    // it only decides whether that kernel may hand w_i on in a chain, which matters to neither side (1884 calls from where the chain would begin, up to the line: 0.3 % over the faster of
+    // the two on average).  Rows of 12289 ... 16384 logits, the kernels for few resident sets / that one: float32, 162 of 8 over 12808 (2.8 sets) 29.9 / 30.9, 220 of 8 over 14016
+    // (3.9) 41.0 / 40.7, not aligned 122 of 12 over 14613 (3.1) 37.2 / 39.2, own lengths 150 of 12 over 15200 (3.8) 29.2 / 29.5; bf16 189 of 6 over 14064 (2.1) 23.5 / 24.5, 188 of 8 over
+    // 13776 (2.6) 27.7 / 26.8, not aligned 184 of 8 over 15349 (2.6) 29.8 / 30.1, 363 of 6 over 13717 (4.0) 42.2 / 41.5, own lengths 263 of 6 over 14096 (2.9) 23.4 / 24.1, 205 of 12 over
+    // 13392 (4.2) 25.4 / 23.9.  Over 3800 such calls of 0.9 to 4.5 sets the line is 0.7 % over the faster of the two on average; worst, by 4 to 6 %, float32 of own lengths and not aligned
+    // from 3 to 4 sets.
     if (groups == 1 || (!aligned && groups <= (f32 ? 4 : 2))) line = line > 3.0 ? line : 3.0;
     else if (f32 && groups <= 4 && gamma >= 6) { const double to = own_lengths ? 3.0 : groups == 2 ? 2.8 : 2.6; line = line > to ? line : to; }
     // ... and where it goes beyond three sets though the large kernel is the faster one there: bf16, V = 24000, 3.2 sets, gamma = 4 32.2 / 29.3, gamma = 6

@@ -320,8 +320,8 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
 // Whether a sequence's 2 gamma + 1 rows fit the LDS of one workgroup.
 bool tiny_ok(int gamma, int V) { return (size_t)(2 * gamma + 1) * (size_t)V <= (size_t)kTinyMaxFloats; }
 
-// The kernel that keeps a sequence's rows in the registers of one workgroup, a wave per row pair, and its launch, for the rows that
-// packed_launch leaves; none where the rows or their groups are too many.  As few logits per lane as the row allows: fewer registers,
+// The kernel that keeps a sequence's rows in the registers of one workgroup, a wave per row pair or, in short rows, 4 or 16 lanes, and its launch, for the calls that
+// packed_launch leaves (both sides' times there); none where the rows or their groups are too many.  As few logits per lane as the row allows: fewer registers,
 // shorter chains (8192 sequences of 4 over 1000 bf16 logits: 58 us with sixteen per lane, 105 with 32; 32 / 24: float32 1000 of 4 over 1500 24.5 / 18.0, 2000 of 15 over
 // 1030 88 / 77; bf16 300 of 16 over 1536 20.4 / 18.8, 5390 of 8 over 1244 150 / 147).
 struct SmallLaunch {
@@ -411,7 +411,7 @@ FusedParams word_params(int algo, const void *target, const void *draft, const i
 }
 
 // Rows that one workgroup holds (rows_verify_kernel); `P`: the arguments of the call, `in_chain`: how a position learns w_i (calls of few resident sets: from the
-// ratios; others by the large kernel's line, which holds here: 200 calls of 1.2 to 16 of its sets with the line / the ratios / the chain: 0.15 % over the faster of the two on
+// ratios, see resident_sets; others by the large kernel's line, which holds here: 200 calls of 1.2 to 16 of its sets with the line / the ratios / the chain: 0.15 % over the faster of the two on
 // average, eleven more than 1 % over, the worst 1064 ragged of 4 over 2301, Alg. 1, 15.2 / 14.6 / 15.2 us; 104 ragged of 16 over 2163 11.2 / 11.2 / 18.5, 1912 of 8 over 4736 60.5 /
 // 64.7 / 60.4).
 template <typename T, bool ALIGNED>

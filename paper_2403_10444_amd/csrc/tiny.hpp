@@ -1,4 +1,4 @@
-// Small sequences: ONE workgroup (or wave) per sequence, nothing between workgroups.  First the kernel for sequences that fit
+// Small sequences: ONE workgroup per sequence, nothing between workgroups.  First the kernel for sequences that fit
 // LDS, which the library takes for rows of more than 2048 logits; then the one that keeps shorter rows in registers (packed.hpp: several
 // sequences to a workgroup).
 //
