@@ -181,7 +181,9 @@ bool being_captured(hipStream_t stream)
 //   bf16, 5430 of 16 over 101 25.4 / 29.7, 4308 of 15 over 128 15.5 / 16.9, 7465 of 8 over 64 21.1 / 22.1, 3289 of 63 over 27 13.4 / 14.8; float32, 6711 of 12 over 78 24.0 /
 //   26.5, 7613 of 15 over 116 28.7 / 30.5, 7620 of 7 over 67 18.6 / 18.8);
 //   up to 256 32, in calls of many rows sixteen with twice the logits each: 512 of 8 over 192, bf16, a wave per row pair / 32 lanes / 16
-//   8.5 / 7.0 / 7.6, 8192 of them 73.3 / 45.3 / 38.6; float32, 1024 of 12 over 256 16.8 / 12.5 / 11.5; 2048 of 6 over 250 17.3 / 11.7 / 11.8, 10.8 with four sequences;
+//   8.5 / 7.0 / 7.6, 8192 of them 73.3 / 45.3 / 38.6; float32, 1024 of 12 over 256 16.8 / 12.5 / 11.5; 2048 of 6 over 250 17.3 / 11.7 / 11.8, 10.8 with four sequences; drafts of 24 and
+//   more, of whose workgroups a compute unit holds one, in calls of more sequences than units sixteen too (32 / 16: bf16 393 of 26 over 162 11.0 / 8.9, float32 264 of 26 over 255
+//   12.6 / 10.5; small_verify_kernel's sixteen of 32 9.2, 11.2);
 //   up to 512 a wave per row pair (small_verify_kernel; probabilities: here), or 32 lanes: bf16 rows in bulk (that one / this one: 2048 of 14 over 500 32.7 / 26.1,
 //   7206 of 5 over 461 41.0 / 35.0, 2859 over 320 18.8 / 17.3; of 4 7946 over 284 40.2 / 38.7, 4339 over 512 21.0 / 22.4; of 2 3375 over 512 12.4 / 15.0; float32 2048 of 10 over
 //   400 28.5 / 30.7), and drafts that a workgroup's sixteen waves do not hold, else sixteen lanes of 32 (small_verify_kernel): up to drafts of 23 (two
@@ -225,7 +227,7 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
         else return several ? packed_launch_of<T, PROBS, 16, 8, 16>(B, gamma, 4) : PackedLaunch{};
     }
     if (V <= 16 * 16) {
-        if (rows > 12288 || gamma >= 32) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
+        if (rows > 12288 || gamma >= 32 || (!PROBS && gamma >= 24 && B > kComputeUnits)) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
         return packed_launch_of<T, PROBS, 32, 8>(B, gamma, 1);
     }
     if (V <= 32 * 16) {

@@ -327,6 +327,7 @@ def test_sequences_that_share_a_workgroup(B, gamma, V, dtype, probs):
     (600, 16, 32, "f32", (_SEVERAL, 4, 8)), (600, 17, 32, "f32", (_ONE, 4, 8)), (5, 64, 9, "bf16", (_ONE, 4, 8)),
     (1024, 6, 128, "f32", (_SEVERAL, 16, 8)), (1023, 6, 128, "f32", (_ONE, 16, 8)), (2048, 7, 33, "f32", (_ONE, 16, 8)),
     (2048, 7, 33, "bf16", (_SEVERAL, 16, 8)), (2047, 7, 33, "bf16", (_ONE, 16, 8)), (1024, 8, 128, "bf16", (_ONE, 16, 8)), (3, 63, 128, "bf16", (_ONE, 16, 8)), (3, 64, 128, "f32", (_ONE, 16, 8)),
+    (257, 24, 256, "f32", (_SEVERAL, 16, 16)), (256, 31, 256, "bf16", (_SEVERAL, 32, 8)), (300, 31, 129, "bf16", (_SEVERAL, 16, 16)), (300, 23, 200, "f32", (_SEVERAL, 32, 8)),
     (1366, 5, 512, "bf16", (_SEVERAL, 32, 16)), (1365, 5, 512, "bf16", (_ONE, 64, 8)), (1366, 5, 300, "f32", (_ONE, 64, 8)),
     (4916, 4, 257, "bf16", (_SEVERAL, 32, 16)), (4915, 4, 257, "bf16", (_ONE, 64, 8)), (1201, 16, 384, "bf16", (_ONE, 16, 32)), (1200, 16, 384, "bf16", (_SEVERAL, 32, 16)),
     (1201, 16, 385, "bf16", (_SEVERAL, 32, 16)), (1201, 16, 384, "f32", (_SEVERAL, 32, 16)), (257, 23, 512, "bf16", (_SEVERAL, 32, 16)),
