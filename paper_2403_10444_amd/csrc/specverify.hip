@@ -193,6 +193,11 @@ bool being_captured(hipStream_t stream)
 // Probabilities, against the kernels for wider rows: 6000 of 10 over 2 163 / 5.8; 6000 of 10 over 256, float32 132.6 / 32.1; 1000 of 12 over 768, bf16 30.4 / 17.7 (a
 // wave per row pair 21.8; 200 of 12 7.3 either way); over 1025 ... 2048 tokens with longer drafts only while the workgroups are few: 512 of 10 over 2000, bf16 20.7 /
 // 16.6, 1000 28.8 / 30.5, 2048 50.4 / 58.0; 2048 of 4 35.1 / 32.4.
+// Alg. 1 without the report, long drafts: the kernels for wider rows do not read what lies behind the first failed test, which from this many bytes of target rows on saves
+// more than this kernel does (this one / those, drafts of 8 and more over 1025 ... 2048 tokens, of 16 over 513 ... 1024: float32 372 of 15 over 1864 26.9 / 22.4, 882 of 18 over 953 37.7 /
+// 32.3, 1503 of 27 over 814 75.3 / 52.4, 197 of 27 over 995 (20 MiB) 14.4 / 16.8, 412 of 12 over 1105 (22 MiB) 18.4 / 20.2; bf16 1383 of 19 over 810 41.0 / 38.3, 633 of 8 over 1620 20.2 / 19.5; poor drafts
+// more, up to 2.2 times), over 257 ... 512 with drafts of 32 and more from four times as many (float32 2172 of 53 over 367 108 / 94, 1467 of 52 over 266 (79 MiB) 60.9 / 61.0).
+constexpr size_t kPackedEarlyBytes = 32u << 20;
 constexpr int kComputeUnits = 256;
 struct PackedLaunch {
     void (*kernel)(const FusedParams);
@@ -210,8 +215,9 @@ PackedLaunch packed_launch_of(int B, int gamma, int seqs)
     if (threads > (G == 1 ? 2 * kWave : kTinyThreads)) return {};
     return {kernel, (unsigned)((B - 1) / seqs + 1), (unsigned)threads, seqs, G, LANE};
 }
+// (`stops_early`: Alg. 1 on probabilities without the report)
 template <typename T, bool PROBS>
-PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
+PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool stops_early)
 {
     const long long rows = (long long)B * (gamma + 1);
     const bool bf16 = ElemTraits<T>::kVec == 8;
@@ -229,6 +235,10 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride)
     if (V <= 16 * 16) {
         if (rows > 12288 || gamma >= 32 || (!PROBS && gamma >= 24 && B > kComputeUnits)) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
         return packed_launch_of<T, PROBS, 32, 8>(B, gamma, 1);
+    }
+    if constexpr (PROBS) {
+        const size_t bytes = (size_t)rows * V * sizeof(T);
+        if (stops_early && ((V > 32 * 16 && gamma >= (V > 32 * 32 ? 8 : 16) && bytes > kPackedEarlyBytes) || (V > 16 * 16 && gamma >= 32 && bytes > 4 * kPackedEarlyBytes))) return {};
     }
     if (V <= 32 * 16) {
         if constexpr (PROBS) {
@@ -257,7 +267,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
 {
     const T *target = static_cast<const T *>(target_v);
     const T *draft = static_cast<const T *>(draft_v);
-    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V, tstride);
+    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V, tstride, algo == kToken && !debug_out);
     if (packed.kernel) {
         FusedParams F = {};
         F.target = target; F.draft = draft; F.tokens = tokens; F.draft_lens = draft_lens; F.uniforms = uniforms;
@@ -360,7 +370,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
                         size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd,
                         int magic, char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
-    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V, tstride);
+    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V, tstride, false);
     const SmallLaunch small = packed.kernel ? SmallLaunch{packed.kernel, packed.blocks, packed.threads, packed.lanes, packed.logits} : small_launch<T>(B, gamma, V);
     if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     FusedParams P = {};

@@ -341,6 +341,22 @@ def test_probs_waits_that_run_out(algo, B, gamma, V, dtype):
     assert sv.spec_verify_workspace_check(ws, B, gamma, V) == 0
 
 
+# Alg. 1 without the report: both sides of the lines from which short rows go to the kernels that stop at the first failed test (32 MiB of target rows; 128)
+@pytest.mark.parametrize("B,gamma,V,dtype,lanes", [
+    (481, 16, 1024, "f32", 32), (482, 16, 1024, "f32", 0), (963, 16, 1024, "bf16", 32), (964, 16, 1024, "bf16", 0), (600, 15, 1024, "f32", 32),
+    (455, 8, 2048, "f32", 64), (456, 8, 2048, "f32", 0), (700, 7, 2048, "f32", 64), (1985, 32, 512, "f32", 16), (1986, 32, 512, "f32", 0)])
+def test_short_rows_of_which_few_are_needed(B, gamma, V, dtype, lanes):
+    import paper_2403_10444_amd as sv
+    P, Q, inp = _probs_inputs(_custom(B, gamma, V, dtype, sigma_t=2.0, sigma_d=1.0, T=1.0), seed=B + V)
+    tau, y = sv.spec_verify_probs("token", P, Q, inp["draft_tokens"], inp["uniforms"])
+    assert sv.spec_verify_debug_last_form()[:2] == ((sv.binding.SV_FORM_SEQUENCES, lanes) if lanes else (0, 0))
+    some = np.array(sorted({0, 1, B // 2, B - 1, *range(0, B, 16)}))
+    ref = _run_oracle("token", P[some], Q[some], {k: v[some] for k, v in inp.items()})
+    safe = ref["margins"].min(axis=1) >= parity.MARGIN
+    assert safe.mean() > 0.99
+    assert np.array_equal(tau.cpu().numpy()[some][safe], ref["accept_len"][safe]) and np.array_equal(y.cpu().numpy()[some][safe], ref["next_token"][safe])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,gamma", [(30, 3), (60, 64), (700, 3)])               # (packed.hpp: workgroups of several sequences, of one)
 def test_probs_rows_shorter_than_a_vector(B, gamma, dtype):
