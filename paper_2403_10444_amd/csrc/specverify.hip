@@ -192,7 +192,8 @@ bool being_captured(hipStream_t stream)
 //   10.9 / 9.5; 452 over 259 12.3 / 15.1; bf16 3090 of 27 over 384 52.6 / 77.3); from 32 on both are the same.
 // Probabilities, against the kernels for wider rows: 6000 of 10 over 2 163 / 5.8; 6000 of 10 over 256, float32 132.6 / 32.1; 1000 of 12 over 768, bf16 30.4 / 17.7 (a
 // wave per row pair 21.8; 200 of 12 7.3 either way); over 1025 ... 2048 tokens with longer drafts only while the workgroups are few: 512 of 10 over 2000, bf16 20.7 /
-// 16.6, 1000 28.8 / 30.5, 2048 50.4 / 58.0; 2048 of 4 35.1 / 32.4.
+// 16.6, 1000 28.8 / 30.5, 2048 50.4 / 58.0; 2048 of 4 35.1 / 32.4; and not few sequences of long drafts over more than 1536, whose rows those spread over the device (float32 1 of 13 over
+// 1875 9.5 / 11.2, 25 of 10 over 1740 9.4 / 10.0, 53 of 13 over 1600 10.9 / 10.8; bf16 29 of 14 over 2031 9.7 / 10.5, 6 of 10 over 1689 8.8 / 8.8, 59 of 14 over 2013 10.6 / 10.5).
 // Alg. 1 without the report, long drafts: the kernels for wider rows do not read what lies behind the first failed test, which from this many bytes of target rows on saves
 // more than this kernel does (this one / those, drafts of 8 and more over 1025 ... 2048 tokens, of 16 over 513 ... 1024: float32 372 of 15 over 1864 26.9 / 22.4, 882 of 18 over 953 37.7 /
 // 32.3, 1503 of 27 over 814 75.3 / 52.4, 197 of 27 over 995 (20 MiB) 14.4 / 16.8, 412 of 12 over 1105 (22 MiB) 18.4 / 20.2; bf16 1383 of 19 over 810 41.0 / 38.3, 633 of 8 over 1620 20.2 / 19.5; poor drafts
@@ -253,7 +254,8 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool stops_e
     }
     if constexpr (PROBS) {
         if (V > 32 * 16 && V <= 32 * 32) return rows > 3072 || gamma >= 16 ? packed_launch_of<T, PROBS, 32, 32>(B, gamma, 1) : packed_launch_of<T, PROBS, 64, 16, 16>(B, gamma, 1);
-        if (V > 32 * 32 && V <= kSmallMaxRow && (gamma < 6 || rows <= 6000)) return packed_launch_of<T, PROBS, 64, 32, 16>(B, gamma, 1);
+        const bool few_long = V > 64 * 24 && gamma >= (bf16 ? 12 : 10) && B <= (bf16 ? 32 : 64);
+        if (V > 32 * 32 && V <= kSmallMaxRow && (gamma < 6 || rows <= 6000) && !few_long) return packed_launch_of<T, PROBS, 64, 32, 16>(B, gamma, 1);
     }
     return {};
 }

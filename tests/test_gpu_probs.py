@@ -341,6 +341,24 @@ def test_probs_waits_that_run_out(algo, B, gamma, V, dtype):
     assert sv.spec_verify_workspace_check(ws, B, gamma, V) == 0
 
 
+# few sequences of long drafts over 1537 ... 2048 tokens: both sides of the lines to the kernels that spread a sequence's rows over the device
+@pytest.mark.parametrize("algo", ["block", "token", "greedy"])
+@pytest.mark.parametrize("B,gamma,V,dtype,packed", [
+    (32, 12, 1537, "bf16", False), (33, 12, 2048, "bf16", True), (32, 11, 2047, "bf16", True), (5, 15, 1536, "f32", True), (64, 10, 1537, "f32", False),
+    (65, 10, 2048, "f32", True), (64, 9, 2048, "f32", True), (1, 15, 2048, "f32", False)])
+def test_few_long_drafts_over_short_rows(B, gamma, V, dtype, packed, algo):
+    import paper_2403_10444_amd as sv
+    P, Q, inp = _probs_inputs(_custom(B, gamma, V, dtype, sigma_t=2.0, sigma_d=0.7, T=1.0), seed=B + V)
+    got, ref = _run_gpu(sv, algo, P, Q, inp), _run_oracle(algo, P, Q, inp)
+    assert sv.spec_verify_debug_last_form()[0] == (sv.binding.SV_FORM_SEQUENCES if packed else 0)
+    tau, y = sv.spec_verify_probs(algo, P, Q, inp["draft_tokens"], inp["uniforms"])
+    assert sv.spec_verify_debug_last_form()[0] == (sv.binding.SV_FORM_SEQUENCES if packed else 0)
+    safe = ref["margins"].min(axis=1) >= parity.MARGIN
+    assert safe.mean() >= 0.9 or B == 1
+    for key, plain in (("accept_len", tau), ("next_token", y)):
+        assert np.array_equal(got[key][safe], ref[key][safe]) and np.array_equal(plain.cpu().numpy()[safe], ref[key][safe]), key
+
+
 # Alg. 1 without the report: both sides of the lines from which short rows go to the kernels that stop at the first failed test (32 MiB of target rows; 128)
 @pytest.mark.parametrize("B,gamma,V,dtype,lanes", [
     (481, 16, 1024, "f32", 32), (482, 16, 1024, "f32", 0), (963, 16, 1024, "bf16", 32), (964, 16, 1024, "bf16", 0), (600, 15, 1024, "f32", 32),
