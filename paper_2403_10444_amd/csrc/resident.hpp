@@ -598,12 +598,15 @@ constexpr int kRowsMaxRow = 2 * kThreads * 40;
 constexpr int kRowsMaxRowFew = kThreads * 48;   // in calls of few resident sets rows beyond, up to 16384 logits, do not come here
 // Calls of few resident sets that take it (`workgroups` of 8192 logits, `resident` of together.hpp's at once; `together`: whether that kernel has
 // the call else), from how many sixteenths of a resident set on (the kernel else / this one, us; the report of every S_i, which favours this one, decides nothing):
-//   up to 4096 logits four, bf16: 39 of 8 over 2100 10.4 / 9.4, 102 12.2 / 10.1; float32 68 of 8 over 4000 11.2 / 10.6, 853 of 2 over 2049 26.5 / 14.3;
+//   up to 4096 logits four, bf16: 39 of 8 over 2100 10.4 / 9.4, 102 12.2 / 10.1; float32 68 of 8 over 4000 11.2 / 10.6, 853 of 2 over 2049 26.5 / 14.3; beyond 3072, drafts of up to eleven, six
+//   (bf16 53 of 6 over 3075, close models 11.2 / 11.6, 44 of 5 over 3678, others 10.2 / 9.9, float32 62 of 4 over 4073, close ones 11.5 / 12.2: 0.25 to 0.4 sets of close models 4 % slower);
 //   up to 6144 drafts of twelve and more too (54 of 12 over 4529, bf16 12.5 / 10.2, 31 of 14 over 4480 10.0 / 9.1), others from nearly a set on: float32 230 of 3 over 5000 13.5 /
-//   12.7, 153 11.8 / 11.8; up to 8192 all from a set on (327 of 4 over 8001 25.5 / 21.6, 184 16.4 / 16.3), such drafts before that while half of the places are
-//   free (20 of 15 over 7232 10.0 / 9.4, 24 of 16 over 7744 10.1 / 9.7), with Alg. 1, whose tests ask for no S_i, always (75 of 12 over 6900 12.0 / 11.5; Alg. 2 and 4, bf16 59 of 13 over
-//   7680 11.3 / 12.4, 57 of 16 over 7168, ragged 10.8 / 11.4, float32 54 of 16 over 7168 14.6 / 15.7), float32 drafts of their own lengths from 1.75 (94 of 12 over 7018 14.5 / 15.8, 127 of 9 over 8064 13.9 / 15.1, 138 of 12 over 7488 17.1 / 17.1, 304
-//   of 6 over 6882 21.0 / 18.4; up to 6144 like the others: 139 of 7 over 4736 12.2 / 11.7, 312 of 6 over 4864 18.1 / 14.9, 341 of 8 over 5000 22.4 / 17.5);
+//   12.7, 153 11.8 / 11.8; up to 8192 from a set on (327 of 4 over 8001 25.5 / 21.6, 184 16.4 / 16.3), drafts of
+//   twelve and more of Alg. 1, whose tests ask for no S_i, from four too (75 of 12 over 6900 12.0 / 11.5; Alg. 2 and 4 are faster here with poor drafts only, and slower by as much again with
+//   good ones: bf16 33 of 13 over 6484, poor 11.3 / 11.0, 21 of 15 over 6345, good 11.8 / 12.9, 59 of 13 over 7680 11.3 / 12.4, float32 22 of 12 over 6562, good 12.6 / 13.7, 54 of 16 over
+//   7168 14.6 / 15.7), own lengths from where that kernel's calls end (bf16 62 of 16 over 6853, good 13.6 / 14.3, 101 of 10 over 7896, poor 11.9 / 11.9), in float32 from 1.75 (94 of 12 over 7018 14.5 /
+//   15.8, 127 of 9 over 8064 13.9 / 15.1, 138 of 12 over 7488 17.1 / 17.1, 304 of 6 over 6882 21.0 / 18.4; up to 6144 like the others: 139 of 7 over 4736 12.2 / 11.7, 312 of 6 over
+//   4864 18.1 / 14.9, 341 of 8 over 5000 22.4 / 17.5);
 //   beyond, where two workgroups become one, later: up to 10240 float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9;
 //   up to 12288, 48 logits per lane, from one and a half sets on (bf16 34 of 16 over 10688 12.5 / 13.4, 43 of 13 over 11072 12.3 / 13.8, 86 of 8 over 12004 18.1 / 14.9; float32
 //   102 of 5 over 11000 15.5 / 16.5, 136 20.3 / 18.9; Alg. 1 58 of 12 over 11456, bf16 13.7 / 12.0, 107 of 5 over 10912 13.7 / 13.3), where sequences bring their own draft lengths, half of whose workgroups have
@@ -619,9 +622,9 @@ inline bool rows_alone(long long workgroups, long long resident, int gamma, int 
     int sixteenths = 0;
     if (V <= kThreads * 40) {
         if (!together) return true;
-        if (V <= kThreads * 16) sixteenths = 4;
+        if (V <= kThreads * 16) sixteenths = V > kThreads * 12 && gamma < 12 ? 6 : 4;
         else if (V <= kThreads * 24) sixteenths = gamma >= 12 ? 4 : 14;
-        else if (V <= kThreads * 32) sixteenths = f32 && own_lengths ? 28 : gamma >= 12 && (token_algo || 2 * workgroups <= resident) ? 4 : 16;
+        else if (V <= kThreads * 32) sixteenths = own_lengths ? (f32 ? 28 : 18) : gamma >= 12 && token_algo ? 4 : 16;
         else sixteenths = 18;
     } else if (V <= kThreads * 48) {
         sixteenths = own_lengths ? 32 : token_algo ? 20 : 24;
