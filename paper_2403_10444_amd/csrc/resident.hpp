@@ -607,7 +607,8 @@ constexpr int kRowsMaxRowFew = kThreads * 48;   // in calls of few resident sets
 //   7168 14.6 / 15.7), own lengths from where that kernel's calls end (bf16 62 of 16 over 6853, good 13.6 / 14.3, 101 of 10 over 7896, poor 11.9 / 11.9), in float32 from 1.75 (94 of 12 over 7018 14.5 /
 //   15.8, 127 of 9 over 8064 13.9 / 15.1, 138 of 12 over 7488 17.1 / 17.1, 304 of 6 over 6882 21.0 / 18.4; up to 6144 like the others: 139 of 7 over 4736 12.2 / 11.7, 312 of 6 over
 //   4864 18.1 / 14.9, 341 of 8 over 5000 22.4 / 17.5);
-//   beyond, where two workgroups become one, later: up to 10240 float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9;
+//   beyond, where two workgroups become one, later: up to 10240 float32 62 of 8 over 9000 14.8 / 13.9, 34 11.3 / 11.9, own lengths, float32, from 1.6 (42 of 14 over 9721 14.3 / 15.2,
+//   136 of 5 over 9369 15.9 / 16.6, 59 of 14 over 9938 16.6 / 16.6, 49 of 19 over 9668 16.2 / 15.5; bf16 ones gain from the first);
 //   up to 12288, 48 logits per lane, from one and a half sets on (bf16 34 of 16 over 10688 12.5 / 13.4, 43 of 13 over 11072 12.3 / 13.8, 86 of 8 over 12004 18.1 / 14.9; float32
 //   102 of 5 over 11000 15.5 / 16.5, 136 20.3 / 18.9; Alg. 1 58 of 12 over 11456, bf16 13.7 / 12.0, 107 of 5 over 10912 13.7 / 13.3), where sequences bring their own draft lengths, half of whose workgroups have
 //   nothing to do, from two (bf16 74 of 9 over 11712 11.9 / 13.1, 76 of 8 over 11503 14.2 / 15.4, 72 of 14 over 10944 16.5 / 12.8; float32 97 of 8 over 11328 15.1 / 16.2, 149 of 6 over
@@ -625,7 +626,7 @@ inline bool rows_alone(long long workgroups, long long resident, int gamma, int 
         if (V <= kThreads * 16) sixteenths = V > kThreads * 12 && gamma < 12 ? 6 : 4;
         else if (V <= kThreads * 24) sixteenths = gamma >= 12 ? 4 : 14;
         else if (V <= kThreads * 32) sixteenths = own_lengths ? (f32 ? 28 : 18) : gamma >= 12 && token_algo ? 4 : 16;
-        else sixteenths = 18;
+        else sixteenths = f32 && own_lengths ? 26 : 18;
     } else if (V <= kThreads * 48) {
         sixteenths = own_lengths ? 32 : token_algo ? 20 : 24;
     } else if (V <= 7 * kWave * 40) {
