@@ -176,7 +176,8 @@ bool being_captured(hipStream_t stream)
 //   up to 8 tokens a lane per row pair, four sequences per wave: 8192 of 10 over 2, float32: four lanes each, one sequence per wave 11.8 / 5.9 (not float32 rows a line
 //   apart in long drafts, of which every lane of a wave reads another line: 3914 of 50 over 5, 69 apart 16.3 / 22.3, 1952 of 60 over 6 9.5 / 10.4, dense 4756 of 53 over 4 13.2 / 7.2);
 //   up to 32 four lanes: 8192 of 10 over 30, bf16, one sequence per workgroup / four 14.0 / 10.5, 64 of them the same;
-//   up to 128 sixteen: four sequences where drafts are short: 8192 of 4 over 60 17.9 / 13.8; bf16 2385 of 7 over 82 9.3 / 8.8;
+//   up to 128 sixteen: four sequences where drafts are short: 8192 of 4 over 60 17.9 / 13.8; bf16 2385 of 7 over 82 9.3 / 8.8 (own lengths up to five drafted tokens, beyond in smaller calls
+//   only: float32 7744 of 5 over 59 15.7 / 15.1, 7197 of 6 over 52 15.5 / 16.4; bf16 4834 of 7 over 77 13.7 / 14.1);
 //   one sequence gets no more from this kernel than from small_verify_kernel, which has 56 registers instead of 68 (eight waves per SIMD, not seven; that one / this one:
 //   bf16, 5430 of 16 over 101 25.4 / 29.7, 4308 of 15 over 128 15.5 / 16.9, 7465 of 8 over 64 21.1 / 22.1, 3289 of 63 over 27 13.4 / 14.8; float32, 6711 of 12 over 78 24.0 /
 //   26.5, 7613 of 15 over 116 28.7 / 30.5, 7620 of 7 over 67 18.6 / 18.8);
@@ -185,7 +186,7 @@ bool being_captured(hipStream_t stream)
 //   more, of whose workgroups a compute unit holds one, in calls of more sequences than units sixteen too (32 / 16: bf16 393 of 26 over 162 11.0 / 8.9, float32 264 of 26 over 255
 //   12.6 / 10.5; small_verify_kernel's sixteen of 32 9.2, 11.2);
 //   up to 512 a wave per row pair (small_verify_kernel; probabilities: here), or 32 lanes: bf16 rows in bulk (that one / this one: 2048 of 14 over 500 32.7 / 26.1,
-//   7206 of 5 over 461 41.0 / 35.0, 2859 over 320 18.8 / 17.3; of 4 7946 over 284 40.2 / 38.7, 4339 over 512 21.0 / 22.4; of 2 3375 over 512 12.4 / 15.0; float32 2048 of 10 over
+//   7206 of 5 over 461 41.0 / 35.0, 2859 over 320 18.8 / 17.3; of 4 7946 over 284 40.2 / 38.7, 4339 over 512 21.0 / 22.4, of own lengths 5875 over 356 28.4 / 29.3, 16384 over 410 71.7 / 71.4; of 2 3375 over 512 12.4 / 15.0; float32 2048 of 10 over
 //   400 28.5 / 30.7), and drafts that a workgroup's sixteen waves do not hold, else sixteen lanes of 32 (small_verify_kernel): up to drafts of 23 (two
 //   workgroups to a compute unit: 772 of 21 over 512, bf16 21.2 / 17.5, 864 of 20 over 448, float32 22.9 / 20.4, 2966 of 16 over 512 63.7 / 57.5; not bf16 rows of three vectors of sixteen lanes, in
 //   bulk: 1820 of 16 over 384 30.5 / 32.1, 2057 over 347 36.9 / 38.4, 1160 over 320 22.8 / 22.2), of 31 while each workgroup has its compute unit alone (144 of 26 over 512, float32
@@ -218,7 +219,7 @@ PackedLaunch packed_launch_of(int B, int gamma, int seqs)
 }
 // (`stops_early`: Alg. 1 on probabilities without the report)
 template <typename T, bool PROBS>
-PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool stops_early)
+PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool own_lengths, bool stops_early)
 {
     const long long rows = (long long)B * (gamma + 1);
     const bool bf16 = ElemTraits<T>::kVec == 8;
@@ -230,8 +231,10 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool stops_e
     }
     if (V <= 16 * 8) {
         const bool several = gamma == 7 ? B >= (PROBS ? 1024 : 2048) && (PROBS || bf16) : gamma < 7 && B >= 1024;
+        // (own lengths: the waves of the sequences' last positions wait for nothing, so that long drafts gain less from sharing a workgroup)
+        const bool apart = !PROBS && own_lengths && gamma >= 6 && B >= (bf16 ? 4096 : 2048);
         if constexpr (PROBS) return gamma < 64 ? packed_launch_of<T, PROBS, 16, 8>(B, gamma, several ? 4 : 1) : packed_launch_of<T, PROBS, 4, 32, kWave>(B, gamma, 1);
-        else return several ? packed_launch_of<T, PROBS, 16, 8, 16>(B, gamma, 4) : PackedLaunch{};
+        else return several && !apart ? packed_launch_of<T, PROBS, 16, 8, 16>(B, gamma, 4) : PackedLaunch{};
     }
     if (V <= 16 * 16) {
         if (rows > 12288 || gamma >= 32 || (!PROBS && gamma >= 24 && B > kComputeUnits)) return packed_launch_of<T, PROBS, 16, 16>(B, gamma, gamma < 8 ? 4 : 1);
@@ -247,7 +250,7 @@ PackedLaunch packed_launch(int B, int gamma, int V, size_t tstride, bool stops_e
             if (gamma >= 16 || rows > 8192) return packed_launch_of<T, PROBS, 32, 16>(B, gamma, 1);
             return packed_launch_of<T, PROBS, 64, 8, 16>(B, gamma, 1);
         } else {
-            const bool here = gamma < 16 ? bf16 && (gamma >= 5 ? rows > 8192 : gamma == 4 && rows > 24576)
+            const bool here = gamma < 16 ? bf16 && (gamma >= 5 ? rows > 8192 : gamma == 4 && rows > (own_lengths ? 65536 : 24576))
                             : gamma < 24 ? !(bf16 && V <= 384 && B > 1200) : gamma < 32 && B <= kComputeUnits;
             if (here) return packed_launch_of<T, PROBS, 32, 16, ElemTraits<T>::kVec == 8 ? 0 : kWave>(B, gamma, 1);
         }
@@ -269,7 +272,7 @@ sv_status_t launch_probs(int algo, const void *target_v, const void *draft_v, co
 {
     const T *target = static_cast<const T *>(target_v);
     const T *draft = static_cast<const T *>(draft_v);
-    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V, tstride, algo == kToken && !debug_out);
+    const PackedLaunch packed = packed_launch<T, true>(B, gamma, V, tstride, draft_lens != nullptr, algo == kToken && !debug_out);
     if (packed.kernel) {
         FusedParams F = {};
         F.target = target; F.draft = draft; F.tokens = tokens; F.draft_lens = draft_lens; F.uniforms = uniforms;
@@ -372,7 +375,7 @@ sv_status_t launch_tiny(int algo, const void *target, const void *draft, const i
                         size_t tstride, size_t dstride, const float *uniforms, int B, int gamma, int V, float k, double kd,
                         int magic, char *ws, int32_t *accept_len, int32_t *next_token, float *debug_out, hipStream_t stream)
 {
-    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V, tstride, false);
+    const PackedLaunch packed = packed_launch<T, false>(B, gamma, V, tstride, draft_lens != nullptr, false);
     const SmallLaunch small = packed.kernel ? SmallLaunch{packed.kernel, packed.blocks, packed.threads, packed.lanes, packed.logits} : small_launch<T>(B, gamma, V);
     if (!small.kernel && !tiny_ok(gamma, V)) return SV_ERR_UNSUPPORTED;
     FusedParams P = {};

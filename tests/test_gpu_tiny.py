@@ -337,7 +337,19 @@ def test_both_sides_of_the_lines_between_short_rows(B, gamma, V, dtype, form):
     from tests.test_gpu_random_shapes import _check
     cfg = workloads.Config(f"lines_B{B}_g{gamma}_V{V}_{dtype}", B, gamma, V, dtype, 2.0, 0.5, 0.9, False, 1)
     for n, (algo, lens, pad_t, pad_d) in enumerate([("block", False, 0, 0), ("token", True, 3, 8), ("greedy", False, 0, 5)]):
-        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens, pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 7 * V + n, False)
+        # (drafts of four over 257 ... 512 and of their own lengths have another line, below)
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=lens and (gamma, V) != (4, 257), pad_t=pad_t, pad_d=pad_d, lens_seed=B + V), 7 * V + n, False)
+        assert sv.spec_verify_debug_last_form() == form
+
+
+@pytest.mark.parametrize("B,gamma,V,dtype,form", [
+    (2047, 6, 128, "f32", (_SEVERAL, 16, 8)), (2048, 6, 33, "f32", (_ONE, 16, 8)), (2048, 5, 33, "f32", (_SEVERAL, 16, 8)), (4095, 7, 40, "bf16", (_SEVERAL, 16, 8)), (4096, 7, 40, "bf16", (_ONE, 16, 8)),
+    (4096, 6, 33, "bf16", (_ONE, 16, 8)), (13107, 4, 257, "bf16", (_ONE, 64, 8)), (13108, 4, 257, "bf16", (_SEVERAL, 32, 16))])
+def test_both_sides_of_the_lines_between_short_rows_of_own_lengths(B, gamma, V, dtype, form):
+    from tests.test_gpu_random_shapes import _check
+    cfg = workloads.Config(f"own_lines_B{B}_g{gamma}_V{V}_{dtype}", B, gamma, V, dtype, 2.0, 0.5, 0.9, False, 1)
+    for n, algo in enumerate(("block", "token", "greedy")):
+        _check(dict(cfg=cfg, algo=algo, path="default", top_k=0, use_lens=True, pad_t=3 * n, pad_d=8 * n, lens_seed=B + V), 9 * V + n, False)
         assert sv.spec_verify_debug_last_form() == form
 
 
