@@ -5,7 +5,7 @@
 // are four), for many the vector instructions: a wave per row pair, or per sequence of a few tokens, spends most of them on reductions over
 // lanes and on scalars in double with most lanes idle.  8192 sequences of 10 over 2 tokens, float32: 11.8 -> 5.9 us; 8192 of 4 over 60 17.9 ->
 // 13.8; 3541 of 11 over 192, bf16 41.8 -> 21.2 (which lanes and how many sequences: packed_launch, with both sides' times).
-// Probabilities (PROBS) take this kernel up to 2048 tokens, in one launch and on no scratch memory: 2207 of 10 over 256, float32 55.7 -> 15;
+// Probabilities (PROBS) take this kernel up to 2048 tokens (but for the calls that packed_launch names), in one launch and on no scratch memory: 2207 of 10 over 256, float32 55.7 -> 15;
 // 6000 of 10 over 2 163 -> 5.8; 64 of 10 over 2 13.1 -> 4.9.
 #pragma once
 

@@ -13,7 +13,7 @@
 //   2. probs_finish           one workgroup per sequence: S_i, h_i, the accept tests of Alg. 1 / 2 / 4,
 //                             then the inverse-CDF draw of Y (pick the chunk from the partial sums,
 //                             re-read that one chunk)
-// (Rows of up to 2048 tokens have a kernel that keeps whole sequences in registers, packed.hpp.)
+// (Most calls over up to 2048 tokens have a kernel that keeps whole sequences in registers, packed.hpp; the others: packed_launch.)
 // Calls whose workgroups all run at once have one launch: a sequence's last workgroup goes on with step 2.  Larger ones have a launch for it
 // (probs_finish_kernel): there the waiting workgroups, and the registers of step 2 in all of them, cost more than the second launch
 // (probs_at_once).  (In some calls the weights come from a kernel in front, probs_weights_kernel, one wave per sequence.)
